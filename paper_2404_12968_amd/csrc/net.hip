@@ -37,96 +37,282 @@ __device__ __forceinline__ bf16x8 zero_bf16x8() {
     return z;
 }
 
+// A raw buffer resource over [base, base + bytes), bytes below 2^30: loads at an
+// offset past its end (an invalid lane passes kOut) return zero and touch no
+// memory.
+constexpr int kOut = 1 << 30;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_of(const void *base, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, bytes, 0x00020000);
+}
+
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+
+__device__ __forceinline__ bf16x8 load_bf16x8(__amdgpu_buffer_rsrc_t r, int off) {
+    return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+
+// A persistent grid's walk over row segments (n of them, spr to a row, H rows to
+// an image), PER at a time (this one the sub-th): each XCD takes one
+// contiguous run, which its workgroups walk side by side, so that the rows a
+// segment shares with those above and below it are in that XCD's L2 from
+// about the same time (k_conv_rows, 1024 x 1024 pixels: 34.8 us against 43.0 with a
+// contiguous run per workgroup, which re-reads the other two tap rows from
+// beyond L2).
+template <int PER>
+struct RowWalk {
+    long t, t1, row;   // segment, end of the run, image row over the batch
+    int sx, y;         // segment within the row, row within the image
+    int nl, drow, dsx;
+    __device__ __forceinline__ RowWalk(long n, int spr, int H, int sub) {
+        const int nb = (int)gridDim.x, nx = min(8, nb);
+        const int xcd = (int)blockIdx.x % nx, local = (int)blockIdx.x / nx;
+        nl = (nb - xcd + nx - 1) / nx * PER;
+        if (n < (1L << 30)) {   // 32-bit divisions: the 64-bit ones cost a small launch about 1 us
+            const unsigned len = (unsigned)n / (unsigned)nx, more = (unsigned)n % (unsigned)nx;
+            const unsigned t0 = len * (unsigned)xcd + min((unsigned)xcd, more);
+            const unsigned at = t0 + (unsigned)(local * PER + sub), r = at / (unsigned)spr;
+            t1 = t0 + len + ((unsigned)xcd < more ? 1u : 0u);
+            t = at;
+            row = r;
+            sx = (int)(at - r * (unsigned)spr);
+            y = (int)(r % (unsigned)H);
+        } else {
+            t = xcd * n / nx + local * PER + sub;
+            t1 = (xcd + 1) * n / nx;
+            row = t / spr;
+            sx = (int)(t - row * spr);
+            y = (int)(row % H);
+        }
+        drow = nl / spr;
+        dsx = nl - drow * spr;
+    }
+    __device__ __forceinline__ void next(int spr, int H) {
+        t += nl;
+        int dr = drow;
+        sx += dsx;
+        if (sx >= spr) {
+            sx -= spr;
+            ++dr;
+        }
+        row += dr;
+        y += dr;
+        while (y >= H) y -= H;
+    }
+};
+
+// Bias, activation and stores of one 32-pixel tile: this lane's pixel starts at
+// element o, its accumulators hold channels 8 i + 4 kh + j (4 i + j).
+template <int COUT>
+__device__ __forceinline__ void conv_store(const f32x16 &acc, const float *bl, int relu, int kh,
+                                           bool here, size_t o, __bf16 *__restrict__ yb,
+                                           float *__restrict__ yf) {
+            float v[COUT / 2];
+    #pragma unroll
+            for (int i = 0; i < COUT / 8; ++i)
+    #pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    float q = acc[4 * i + j] + bl[8 * i + 4 * kh + j];
+                    if (relu) q = q > 0.0f ? q : 0.0f;
+                    v[4 * i + j] = q;              // channel 8 i + 4 kh + j
+                }
+            if (yf && here) {
+    #pragma unroll
+                for (int i = 0; i < COUT / 8; ++i)
+                    *(float4 *)(yf + o + 8 * i + 4 * kh) =
+                        make_float4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
+            }
+            if (yb) {
+                // groups i < COUT / 16 to lanes 0..31, the rest to lanes 32..63:
+                // after the swap a lane holds channels 8 g .. 8 g + 7 of its pixel
+                // for g = i + kh COUT / 16
+                uint32_t q[COUT / 8][2];
+    #pragma unroll
+                for (int i = 0; i < COUT / 8; ++i) {
+                    bf16x4 pk;
+    #pragma unroll
+                    for (int j = 0; j < 4; ++j) pk[j] = (__bf16)v[4 * i + j];
+                    __builtin_memcpy(q[i], &pk, 8);
+                }
+    #pragma unroll
+                for (int i = 0; i < COUT / 16; ++i) {
+                    const auto s0 = __builtin_amdgcn_permlane32_swap(q[i][0], q[i + COUT / 16][0],
+                                                                     false, false);
+                    const auto s1 = __builtin_amdgcn_permlane32_swap(q[i][1], q[i + COUT / 16][1],
+                                                                     false, false);
+                    u32x4 out = {s0[0], s1[0], s0[1], s1[1]};
+                    if (here) *(u32x4 *)(yb + o + 8 * i + kh * (COUT / 2)) = out;
+                }
+            }
+}
+
 // --------------------------------------------------------------------------
 // Convolution, forward: y[p][co] = act(bias[co] + sum_{tap, ci}
 // w[co][tap][ci] x[p + dil * off(tap)][ci]), zero padding.  M = output
-// channel (32 weight rows), N = pixel, K = 9 * CIN.  The work-group stages
-// the weight matrix in LDS once (rows padded by 8 values to spread the LDS
-// banks); each wave then computes NP tiles of 32 consecutive pixels of a row
-// (tiles numbered over (image, row, column tile)), reusing each K step's
-// weight fragment for its NP tiles.  The epilogue adds the bias, applies the
-// activation and stores four consecutive channels per lane and row of the
-// accumulator.  The same kernel with flipped, transposed weights computes
-// the data gradient.
+// channel (32 weight rows), N = 32 consecutive pixels of a row, K = 9 * CIN in
+// steps of 16 in (tap, channel) order.  The same kernel with flipped,
+// transposed weights computes the data gradient.
+//
+// Every input pixel is read for nine taps: a wave keeps all weight fragments in
+// registers (no staging and no barrier per tile), issues the loads of all K
+// steps of a tile before its products, and walks tiles in RowWalk's order (x
+// shifts meet in L1, row shifts in L2).  Out-of-image taps are out-of-range
+// buffer loads (zero), tested once per column shift.  Lanes l and l + 32 hold
+// alternate groups of four channels of one pixel and trade them
+// (v_permlane32_swap) for 16-byte stores.  A 32 -> 32 layer of 1024 x 1024 pixels
+// takes 45.5 us (84 with the weights staged per 256 pixels, tiles in launch
+// order and 8-byte stores; 27 us at the copy rate), bound by the vector memory
+// path, whose loads take 32 of each pixel's 64 bytes at a time: k_conv_rows
+// takes the large layers.  A 2 x 61 x 93 layer takes 5 us (11.7).
+//   kConvWaves: the launch's resident workgroups per CU.
 // --------------------------------------------------------------------------
-template <int CIN, int COUT, int NP>
-__global__ __launch_bounds__(256) void k_conv_fwd(const __bf16 *__restrict__ x,
-                                                  const __bf16 *__restrict__ w,
-                                                  const float *__restrict__ bias, int B, int H,
-                                                  int W, int dil, int relu,
-                                                  __bf16 *__restrict__ yb,
-                                                  float *__restrict__ yf) {
-    constexpr int K = 9 * CIN;
-    constexpr int KP = K + 8;
-    __shared__ __bf16 wl[32 * KP];
-    for (int e = (int)threadIdx.x; e < 32 * (K / 8); e += 256) {
-        const int row = e / (K / 8), c8 = e % (K / 8);
-        *(bf16x8 *)(wl + row * KP + c8 * 8) = *(const bf16x8 *)(w + (size_t)row * K + c8 * 8);
-    }
+constexpr int kConvWaves = 2;
+
+template <int CIN, int COUT>
+__global__ __launch_bounds__(256, kConvWaves) void k_conv_fwd(
+    const __bf16 *__restrict__ x, const __bf16 *__restrict__ w, const float *__restrict__ bias,
+    int H, int W, int dilx, int dily, int relu, long nseg, int spr, __bf16 *__restrict__ yb,
+    float *__restrict__ yf) {
+    constexpr int K = 9 * CIN, NS = K / 16, PB = CIN * 2;   // PB: bytes per pixel
+    __shared__ float bl[32];
+    if (threadIdx.x < 32)
+        bl[threadIdx.x] = bias && (int)threadIdx.x < COUT ? bias[threadIdx.x] : 0.0f;
     __syncthreads();
-    const int tpr = (W + 31) / 32;
-    const long ntiles = (long)B * H * tpr;
-    const long t0 = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * NP;
     const int lane = (int)(threadIdx.x & 63u);
     const int n = lane & 31, kh = lane >> 5;
-    int tb[NP], ty[NP], tx[NP];
-    bool tv[NP];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    RowWalk<4> q(nseg, spr, H, wave);          // segments of one tile
+    if (q.t >= q.t1) return;
+    bf16x8 a[NS];
 #pragma unroll
-    for (int q = 0; q < NP; ++q) {
-        const long t = t0 + q;
-        tv[q] = t < ntiles;
-        const long tt = tv[q] ? t : 0;
-        tb[q] = (int)(tt / ((long)H * tpr));
-        const int rem = (int)(tt % ((long)H * tpr));
-        ty[q] = rem / tpr;
-        tx[q] = (rem % tpr) * 32 + n;
-    }
-    f32x16 acc[NP];
+    for (int s = 0; s < NS; ++s)
+        a[s] = *(const bf16x8 *)(w + (size_t)n * K + s * 16 + kh * 8);
+    const int lo = n * PB + kh * 16;
+    for (; q.t < q.t1; q.next(spr, H)) {
+        const unsigned x0 = (unsigned)q.sx * 32u;
+        f32x16 acc;
 #pragma unroll
-    for (int q = 0; q < NP; ++q)
+        for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+        int off[3];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[q][v] = 0.0f;
-#pragma unroll 3
-    for (int s = 0; s < K / 16; ++s) {
-        const int k = s * 16 + kh * 8;
-        const int tap = k / CIN, ci0 = k % CIN;
-        const int oy = (tap / 3 - 1) * dil, ox = (tap % 3 - 1) * dil;
-        const bf16x8 a = *(const bf16x8 *)(wl + n * KP + k);
-        bf16x8 bv[NP];
+        for (int c = 0; c < 3; ++c)
+            off[c] = x0 + (unsigned)n + (unsigned)((c - 1) * dilx) < (unsigned)W ? lo : kOut;
+        bf16x8 bv[NS];
 #pragma unroll
-        for (int q = 0; q < NP; ++q) {
-            const int yy = ty[q] + oy, xx = tx[q] + ox;
-            bv[q] = zero_bf16x8();
-            if (tv[q] && tx[q] < W && yy >= 0 && yy < H && xx >= 0 && xx < W)
-                bv[q] = *(const bf16x8 *)(x + (((size_t)tb[q] * H + yy) * W + xx) * CIN + ci0);
-        }
+        for (int r = 0; r < 3; ++r) {
+            const int yy = q.y + (r - 1) * dily;
+            const int bytes = (unsigned)yy < (unsigned)H ? 32 * PB : 0;
+            const char *src = (const char *)x +
+                              ((q.row + (long)(r - 1) * dily) * W + (long)x0) * PB;
 #pragma unroll
-        for (int q = 0; q < NP; ++q)
-            acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bv[q], acc[q], 0, 0, 0);
-    }
-#pragma unroll
-    for (int q = 0; q < NP; ++q) {
-        if (!tv[q] || tx[q] >= W) continue;
-        const size_t o = (((size_t)tb[q] * H + ty[q]) * W + tx[q]) * COUT;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int c0 = 8 * i + 4 * kh;    // channels c0 .. c0 + 3 of this lane
-            if (c0 >= COUT) continue;
-            float v[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                v[j] = acc[q][4 * i + j] + (bias ? bias[c0 + j] : 0.0f);
-                if (relu) v[j] = v[j] > 0.0f ? v[j] : 0.0f;
+            for (int c = 0; c < 3; ++c) {
+                const __amdgpu_buffer_rsrc_t rs = buf_of(src + (long)(c - 1) * dilx * PB, bytes);
+                if (CIN == 16) {
+                    bv[3 * r + c] = load_bf16x8(rs, off[c]);
+                } else {
+                    const int s = 2 * (3 * r + c);
+                    bv[s] = load_bf16x8(rs, off[c]);
+                    bv[(s + 1) % NS] = load_bf16x8(rs, off[c] + 32);
+                }
             }
-            if (yb) {
-                typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-                bf16x4 pk;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) pk[j] = (__bf16)v[j];
-                *(bf16x4 *)(yb + o + c0) = pk;
-            }
-            if (yf) *(float4 *)(yf + o + c0) = make_float4(v[0], v[1], v[2], v[3]);
         }
+        __builtin_amdgcn_sched_barrier(0);     // every load is on its way before the products
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s], bv[s], acc, 0, 0, 0);
+        conv_store<COUT>(acc, bl, relu, kh, x0 + (unsigned)n < (unsigned)W,
+                         ((size_t)q.row * W + x0 + n) * COUT, yb, yf);
+    }
+}
+
+// --------------------------------------------------------------------------
+// The same convolution for dilations up to 32, with the input staged in LDS:
+// bitwise what k_conv_fwd gives.  k_conv_fwd's nine reads of a pixel are bound
+// by the vector memory path (its loads take 32 of each pixel's 64 bytes).
+// Here a workgroup takes 128 pixels of a row, loads the three tap rows' runs
+// of 128 + 2 dil pixels once, as they lie in memory (the next segment's while
+// this one is computed), and its four waves read their 32-pixel tiles' taps
+// from LDS.  1024 x 1024 pixels, 32 -> 32: 34.8 us at dilations 1 to 9 and 40.7 at 27
+// (3.9 and 3.3 TB/s of activations read and written once; matrix products
+// 8 us, LDS reads about 15), 41 and 52 us with FP32 output.  Three workgroups
+// per CU (156 VGPRs): two take 41.8 us, and four spill.
+// --------------------------------------------------------------------------
+constexpr int kRowTile = 128, kRowSpan = kRowTile + 64, kRowsWaves = 3;
+
+template <int CIN, int COUT>
+__global__ __launch_bounds__(256, kRowsWaves) void k_conv_rows(
+    const __bf16 *__restrict__ x, const __bf16 *__restrict__ w, const float *__restrict__ bias,
+    int H, int W, int dil, int dily, int relu, long nseg, int spr, __bf16 *__restrict__ yb,
+    float *__restrict__ yf) {
+    constexpr int K = 9 * CIN, NS = K / 16, PB = CIN * 2;   // PB: bytes per pixel
+    constexpr int QPP = CIN / 8, PPL = 64 / QPP;            // 16-byte parts per pixel, pixels per load
+    constexpr int NL = (kRowSpan / PPL + 3) / 4;            // loads per wave and row
+    __shared__ __align__(16) char xs[3 * kRowSpan * PB];
+    __shared__ float bl[32];
+    if (threadIdx.x < 32)
+        bl[threadIdx.x] = bias && (int)threadIdx.x < COUT ? bias[threadIdx.x] : 0.0f;
+    const int lane = (int)(threadIdx.x & 63u);
+    const int n = lane & 31, kh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    RowWalk<1> q(nseg, spr, H, 0);
+    bf16x8 a[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+        a[s] = *(const bf16x8 *)(w + (size_t)n * K + s * 16 + kh * 8);
+    const int nstage = kRowTile + 2 * dil;
+    // LDS position of the 16-byte part q of staged pixel p: parts are permuted
+    // within a pixel so that eight neighbouring pixels' parts q lie in
+    // different banks
+    auto part_at = [](int p, int q) { return (p * QPP + (q ^ ((p * QPP >> 3) & (QPP - 1)))) * 16; };
+    int rd[3];                                 // this lane's reads, one per column shift
+#pragma unroll
+    for (int c = 0; c < 3; ++c) rd[c] = part_at(32 * wave + n + c * dil, kh);
+    bf16x8 st[3][NL];
+    auto load_seg = [&]() {
+        const int x0 = q.sx * kRowTile;
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const int yy = q.y + (r - 1) * dily;
+            const int bytes = (unsigned)yy < (unsigned)H ? 1024 : 0;
+            const char *src = (const char *)x + ((q.row + (long)(r - 1) * dily) * W + x0 - dil) * PB;
+#pragma unroll
+            for (int k = 0; k < NL; ++k) {
+                const int p0 = (wave + 4 * k) * PPL;
+                if (p0 >= nstage) continue;    // uniform
+                const int xx = x0 - dil + p0 + lane / QPP;
+                st[r][k] = load_bf16x8(buf_of(src + (long)p0 * PB, bytes),
+                                       (unsigned)xx < (unsigned)W ? lane * 16 : kOut);
+            }
+        }
+    };
+    if (q.t < q.t1) load_seg();
+    while (q.t < q.t1) {
+        __syncthreads();                       // the segment before has been read
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+            for (int k = 0; k < NL; ++k) {
+                const int p0 = (wave + 4 * k) * PPL;
+                if (p0 >= nstage) continue;
+                *(bf16x8 *)(xs + r * kRowSpan * PB + part_at(p0 + lane / QPP, lane % QPP)) = st[r][k];
+            }
+        __syncthreads();
+        const int x0 = q.sx * kRowTile + 32 * wave;
+        const size_t o = ((size_t)q.row * W + x0 + n) * COUT;
+        q.next(spr, H);
+        if (q.t < q.t1) load_seg();
+        if (x0 >= W) continue;                 // uniform: past the row's end
+        f32x16 acc;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int tap = s * 16 / CIN, odd = CIN == 32 ? s % 2 : 0;
+            const bf16x8 bv = *(const bf16x8 *)(xs + (tap / 3) * kRowSpan * PB +
+                                                (rd[tap % 3] ^ (odd * 32)));
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s], bv, acc, 0, 0, 0);
+        }
+        conv_store<COUT>(acc, bl, relu, kh, x0 + n < W, o, yb, yf);
     }
 }
 
@@ -619,24 +805,63 @@ bool chan_ok(int c) { return c == 16 || c == 32; }
             return nfail(GABP_E_DEVICE, std::string(#call) + ": " + hipGetErrorString(e_)); \
     } while (0)
 
-constexpr int kConvNP = 2;   // 32-pixel tiles per wave of the convolution
+int cu_count() {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus <= 0)
+        return 256;
+    return cus;
+}
+
+// A dilation beyond the image's side reaches nothing on that axis, whatever
+// it is: clamped there so that a column's position plus it stays in 32 bits.
+int clamp_dil(int dil, int side) { return dil < side ? dil : side; }
+
+// Whether k_conv_rows takes a convolution: its staged runs hold dilations up
+// to 32; below 65536 pixels its two barriers and staging cost more than the
+// strided loads they save (128 x 256: 5.2 against 4.7 us, 2 x 128 x 256: 7.0 against
+// 7.2, 8 x 256 x 256: 21.4 against 26.0, 1024 x 1024: 34.8 against 45.5), and so
+// do segments less than three quarters full (8 x 600 x 64: 20.4 against 18.5).
+bool conv_by_rows(int B, int H, int W, int dil) {
+    const long seg = gabp::kRowTile, spr = (W + seg - 1) / seg;
+    return dil <= 32 && (long)B * H * W >= 65536 && 4L * W >= 3 * seg * spr;
+}
 
 hipError_t conv_dispatch(const void *x, int B, int H, int W, int cin, const void *w,
                          const float *bias, int cout, int dil, int relu, void *yb, float *yf,
                          hipStream_t s) {
-    const long tiles = (long)B * H * ((W + 31) / 32);
-    const long waves = (tiles + kConvNP - 1) / kConvNP;
-    dim3 grid((unsigned)((waves + 3) / 4)), block(256);
     const __bf16 *xx = (const __bf16 *)x, *ww = (const __bf16 *)w;
     __bf16 *ybb = (__bf16 *)yb;
+    const int dx = clamp_dil(dil, W), dy = clamp_dil(dil, H);
+    // one round of resident workgroups over segments of 128 pixels (one per
+    // workgroup) or 32 (one per wave), so that weights are loaded once per wave
+    // and there is no tail
+    const bool rows = conv_by_rows(B, H, W, dil);
+    const int seg = rows ? gabp::kRowTile : 32, per = rows ? 1 : 4;
+    const int spr = W / seg + (W % seg != 0);
+    const long segs = (long)B * H * spr, want = (segs + per - 1) / per;
+    const long resident = (long)cu_count() * (rows ? gabp::kRowsWaves : gabp::kConvWaves);
+    dim3 grid((unsigned)(want < resident ? want : resident)), block(256);
+    if (rows) {
+        if (cin == 16 && cout == 16)
+            hipLaunchKernelGGL((gabp::k_conv_rows<16, 16>), grid, block, 0, s, xx, ww, bias, H, W, dx, dy, relu, segs, spr, ybb, yf);
+        else if (cin == 16)
+            hipLaunchKernelGGL((gabp::k_conv_rows<16, 32>), grid, block, 0, s, xx, ww, bias, H, W, dx, dy, relu, segs, spr, ybb, yf);
+        else if (cout == 16)
+            hipLaunchKernelGGL((gabp::k_conv_rows<32, 16>), grid, block, 0, s, xx, ww, bias, H, W, dx, dy, relu, segs, spr, ybb, yf);
+        else
+            hipLaunchKernelGGL((gabp::k_conv_rows<32, 32>), grid, block, 0, s, xx, ww, bias, H, W, dx, dy, relu, segs, spr, ybb, yf);
+        return hipGetLastError();
+    }
     if (cin == 16 && cout == 16)
-        hipLaunchKernelGGL((gabp::k_conv_fwd<16, 16, kConvNP>), grid, block, 0, s, xx, ww, bias, B, H, W, dil, relu, ybb, yf);
+        hipLaunchKernelGGL((gabp::k_conv_fwd<16, 16>), grid, block, 0, s, xx, ww, bias, H, W, dx, dy, relu, segs, spr, ybb, yf);
     else if (cin == 16)
-        hipLaunchKernelGGL((gabp::k_conv_fwd<16, 32, kConvNP>), grid, block, 0, s, xx, ww, bias, B, H, W, dil, relu, ybb, yf);
+        hipLaunchKernelGGL((gabp::k_conv_fwd<16, 32>), grid, block, 0, s, xx, ww, bias, H, W, dx, dy, relu, segs, spr, ybb, yf);
     else if (cout == 16)
-        hipLaunchKernelGGL((gabp::k_conv_fwd<32, 16, kConvNP>), grid, block, 0, s, xx, ww, bias, B, H, W, dil, relu, ybb, yf);
+        hipLaunchKernelGGL((gabp::k_conv_fwd<32, 16>), grid, block, 0, s, xx, ww, bias, H, W, dx, dy, relu, segs, spr, ybb, yf);
     else
-        hipLaunchKernelGGL((gabp::k_conv_fwd<32, 32, kConvNP>), grid, block, 0, s, xx, ww, bias, B, H, W, dil, relu, ybb, yf);
+        hipLaunchKernelGGL((gabp::k_conv_fwd<32, 32>), grid, block, 0, s, xx, ww, bias, H, W, dx, dy, relu, segs, spr, ybb, yf);
     return hipGetLastError();
 }
 
