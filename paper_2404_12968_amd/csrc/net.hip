@@ -316,12 +316,72 @@ __global__ __launch_bounds__(256, kRowsWaves) void k_conv_rows(
     }
 }
 
+// --------------------------------------------------------------------------
+// Backward of one layer, y = act(conv(x, w) + bias).  With dZ = dY * relu'(y)
+// (BF16):
+//   data gradient    dX = conv(dZ, flipped w)          (k_conv_fwd)
+//   weight gradient  dW[co][tap][ci] = sum_p dZ[p][co] x[p + dil off(tap)][ci]
+//   bias gradient    db[co] = sum_p dZ[p][co]
+//
+// k_wgrad forms dZ (written out for the data gradient, NULL when that is not
+// wanted), the weight and bias gradients' partial sums and, in the blocks
+// past nchunks, the flipped weights.  The weight gradient is an implicit GEMM on
+// the matrix cores with the pixels as the reduction dimension (M = 32 output
+// channels, N = 32 input channels of one tap, K = 16 pixels), whose operand
+// fragments are eight consecutive pixels of one channel.  A workgroup takes a
+// chunk of 1024 consecutive pixels (numbered over the whole batch) in units of
+// 64.  Its last wave forms the next unit's dZ while the three others, one per
+// tap row, stage the current unit's input pixels in LDS as they lie in memory
+// (64 bytes per pixel; the unit after it is loaded meanwhile) and read both
+// through the transposing LDS load (ds_read_b64_tr_b16).  To that load a
+// pixel is a row address of its own: a tap's shift is another row, and a tap
+// that leaves the image, or a pixel past the batch, reads a row of zeros (one
+// ballot per unit and tap says which).  So any width and dilation takes one
+// path and nothing is transposed in memory.  k_sum_partials adds the chunks'
+// partials; the order of every sum (16-pixel steps within a chunk, then 16
+// runs of chunks) is fixed.
+//
+// Bound by HBM on large inputs (dY, y and x read, dZ written: 34 us for
+// 8 x 256 x 256 pixels of a 32 -> 32 layer at the copy rate), by the latency of
+// a chunk's 16 units on small ones.
+// --------------------------------------------------------------------------
+constexpr int kUnit = 64;       // pixels per unit
+constexpr int kChunk = 1024;    // pixels per workgroup and partial sum
+constexpr int kSumRuns = 16;    // runs of chunks that k_sum_partials forms first
+constexpr int kSpan = 192;      // staged pixels per tap row: 64 + 2 dil where that is at
+                                // most 128, else 64 for each of the three taps
+
+// Eight pixels of 32 channels, transposed: lane l gets pixels 8 (l / 32) + j
+// (j < 8) of channel l % 32 from LDS rows of 64 bytes per pixel.  `at` and `at4`
+// are the lane's parts of the rows it passes to the two loads, pixels
+// 8 (l / 32) + (l % 16) / 4 and four on (tr_lane_offset past the fragment's pixel 0
+// where the pixels lie in a row).
+__device__ __forceinline__ int tr_lane_offset(int lane) {
+    return (8 * (lane >> 5) + ((lane & 15) >> 2)) * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+}
+__device__ __forceinline__ bf16x8 tr_frag(const char *at, const char *at4) {
+    typedef __attribute__((ext_vector_type(4))) short s16x4;
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    union {
+        s16x4 h[2];
+        bf16x8 v;
+    } f;
+    f.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)at);
+    f.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)at4);
+    return f.v;
+}
+// Orders a wave's LDS writes before its own later LDS reads of other lanes'
+// data and the reverse (the LDS serves a wave's accesses in order, so only
+// the compiler has to keep it).
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Flipped, transposed weights for the data gradient:
-// wt[ci][tap'][co] = w[co][8 - tap'][ci] (rows ci >= CIN and columns co >=
-// COUT are zero).
-__global__ __launch_bounds__(256) void k_flip_weights(const __bf16 *__restrict__ w, int cin,
-                                                      int cout, __bf16 *__restrict__ wt) {
-    const int idx = (int)(blockIdx.x * 256 + threadIdx.x);
+// wt[ci][tap'][co] = w[co][8 - tap'][ci] (rows ci >= CIN are zero).
+__device__ __forceinline__ void flip_weight(const __bf16 *__restrict__ w, int cin, int cout,
+                                            int idx, __bf16 *__restrict__ wt) {
     const int K2 = 9 * cout;               // row length of wt
     if (idx >= 32 * K2) return;
     const int ci = idx / K2, r = idx % K2;
@@ -331,207 +391,185 @@ __global__ __launch_bounds__(256) void k_flip_weights(const __bf16 *__restrict__
     wt[idx] = v;
 }
 
-// Backward of one layer, y = act(conv(x, w) + bias).  dZ = dY * relu'(y)
-// (BF16), then three products:
-//   data gradient    dX = conv(dZ, flipped w)          (k_conv_fwd)
-//   weight gradient  dW[co][tap][ci] = sum_p dZ[p][co] x[p + dil off(tap)][ci]
-//   bias gradient    db[co] = sum_p dZ[p][co]
-// The weight gradient is an implicit GEMM on the matrix cores with the pixels
-// as the reduction dimension (M = 32 output channels, N = 9 cin taps x
-// channels, K = pixels): no im2col is formed; each operand fragment is eight
-// consecutive pixels of one channel, read from channel-major copies of dZ
-// and x (dZT, xT: [channel][pixel], made by LDS-tiled transposes) at the
-// tap's pixel shift.  Work-groups take fixed pixel chunks (split-K) and the
-// partial sums are reduced in a fixed order, so the result is deterministic.
-
-constexpr int kTP = 64;   // pixels per transpose tile
-
-// dZ = dY * relu'(y): dz [P][C] BF16 (NHWC) and dzt [32][Ppad] (channel-major;
-// rows c >= C and columns p >= P zero), through a 32 x 64 LDS tile.
-__global__ __launch_bounds__(256) void k_relu_bwd_t(const float *__restrict__ dy,
-                                                    const __bf16 *__restrict__ y, long P, int C,
-                                                    int relu, __bf16 *__restrict__ dz,
-                                                    __bf16 *__restrict__ dzt, long Ppad) {
-    __shared__ __bf16 tile[32][kTP + 2];
-    const long p0 = (long)blockIdx.x * kTP;
-    for (int e = (int)threadIdx.x; e < kTP * 32; e += 256) {
-        const int p = e >> 5, c = e & 31;
-        float v = 0.0f;
-        if (c < C && p0 + p < P) {
-            const long o = (p0 + p) * C + c;
-            v = dy[o];
-            if (relu && !((float)y[o] > 0.0f)) v = 0.0f;
-            dz[o] = (__bf16)v;
-        }
-        tile[c][p] = (__bf16)v;
-    }
-    __syncthreads();
-    for (int e = (int)threadIdx.x; e < 32 * kTP; e += 256) {
-        const int c = e / kTP, p = e % kTP;
-        dzt[(size_t)c * Ppad + p0 + p] = tile[c][p];
-    }
-}
-
-// x [P][C] BF16 -> xt [C][Ppad] (columns p >= P zero), through an LDS tile.
-__global__ __launch_bounds__(256) void k_to_cmajor(const __bf16 *__restrict__ x, long P, int C,
-                                                   __bf16 *__restrict__ xt, long Ppad) {
-    __shared__ __bf16 tile[32][kTP + 2];
-    const long p0 = (long)blockIdx.x * kTP;
-    for (int e = (int)threadIdx.x; e < kTP * 32; e += 256) {
-        const int p = e >> 5, c = e & 31;
-        __bf16 v = (__bf16)0.0f;
-        if (c < C && p0 + p < P) v = x[(p0 + p) * C + c];
-        tile[c][p] = v;
-    }
-    __syncthreads();
-    for (int e = (int)threadIdx.x; e < C * kTP; e += 256) {
-        const int c = e / kTP, p = e % kTP;
-        xt[(size_t)c * Ppad + p0 + p] = tile[c][p];
-    }
-}
-
-// Weight and bias gradients of one layer.  One work-group per chunk of
-// `chunk` pixels (a multiple of 16); its waves split the N tiles, TPW tiles
-// each, and every wave walks all 16-pixel steps of the chunk.  For each step
-// a lane loads its A fragment (dZT row co = lane % 32, pixels p .. p + 7 with
-// p = step + 8 (lane / 32)) and one B fragment per tile of the wave (xT row
-// ci at the tap's shift, eight consecutive pixels: one 16-byte load when
-// they stay in one image row, masked element loads at the image edges), then
-// runs one MFMA per tile; the next step's loads are issued before this
-// step's MFMAs.  Each wave writes its tiles of the chunk's partial dW
-// [32][9 CIN], wave 0 also the partial db [32]; k_sum_rows sums the chunks
-// in order.
-template <int CIN, int TPW>
-__global__ __launch_bounds__(64 * (((9 * CIN + 31) / 32 + TPW - 1) / TPW)) void k_wgrad(
-    const __bf16 *__restrict__ dzt, const __bf16 *__restrict__ xt, int H, int W, int dil, long P,
-    long Ppad, int chunk, float *__restrict__ part, float *__restrict__ dbpart) {
+template <int CIN, int COUT>
+__global__ __launch_bounds__(256) void k_wgrad(
+    const float *__restrict__ dy, const __bf16 *__restrict__ y, int relu,
+    const __bf16 *__restrict__ x, int H, int W, int dilx, int dily, int P, int nchunks,
+    __bf16 *__restrict__ dz, float *__restrict__ part, float *__restrict__ dbpart,
+    const __bf16 *__restrict__ w, __bf16 *__restrict__ wt) {
     constexpr int NN = 9 * CIN;
-    constexpr int NT = (NN + 31) / 32;     // N tiles of 32 (tap, channel) columns
-    const int lane = (int)(threadIdx.x & 63u), w = (int)(threadIdx.x >> 6);
-    const int r = lane & 31, h = lane >> 5;
-    const long HW = (long)H * W;
-    f32x16 acc[TPW];
+    // three waves' staged pixels, each followed by a pixel of zeros; dZ, twice
+    constexpr int XB = (kSpan + 1) * 64, ZB = kUnit * 64;
+    __shared__ __align__(16) char lds[3 * XB + 2 * ZB];
+    if ((int)blockIdx.x >= nchunks) {
+        flip_weight(w, CIN, COUT, ((int)blockIdx.x - nchunks) * 256 + (int)threadIdx.x, wt);
+        return;
+    }
+    // channels that the layer does not have, and the pixels of zeros, stay zero
+    for (int e = (int)threadIdx.x; e < (3 * XB + 2 * ZB) / 16; e += 256)
+        *(u32x4 *)(lds + e * 16) = u32x4{0, 0, 0, 0};
+    __syncthreads();
+    const int lane = (int)(threadIdx.x & 63u);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    char *zs = lds + 3 * XB;
+    const int g = xcd_remap((int)blockIdx.x, nchunks);
+    const int c0 = g * kChunk, c1 = min(P, c0 + kChunk);
+    const int nu = (c1 - c0 + kUnit - 1) / kUnit;
+    if (wave == 3) {
+        // dZ of each unit, eight channels per lane
+        constexpr int LPP = COUT / 8, PPL = 64 / LPP, NC = kUnit / PPL;   // lanes per pixel, pixels per load
+        for (int i = 0; i <= nu; ++i) {
+            if (i < nu) {
+                float f[NC][8];
+                bf16x8 yv[NC];
 #pragma unroll
-    for (int k = 0; k < TPW; ++k)
+                for (int c = 0; c < NC; ++c) {
+                    const int p = c0 + i * kUnit + c * PPL + lane / LPP;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) f[c][j] = 0.0f;
+                    yv[c] = zero_bf16x8();
+                    if (p < c1) {
+                        const size_t e = (size_t)p * COUT + (lane % LPP) * 8;
+                        __builtin_memcpy(f[c], dy + e, 32);
+                        if (relu) __builtin_memcpy(&yv[c], y + e, 16);
+                    }
+                }
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    const int pu = c * PPL + lane / LPP, p = c0 + i * kUnit + pu;
+                    bf16x8 z;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        float v = f[c][j];
+                        if (relu && !((float)yv[c][j] > 0.0f)) v = 0.0f;
+                        z[j] = (__bf16)v;
+                    }
+                    *(bf16x8 *)(zs + (i & 1) * ZB + pu * 64 + (lane % LPP) * 16) = z;
+                    if (dz && p < c1) *(bf16x8 *)(dz + (size_t)p * COUT + (lane % LPP) * 8) = z;
+                }
+            }
+            __syncthreads();
+        }
+        return;
+    }
+    f32x16 acc[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[k][v] = 0.0f;
     float bsum = 0.0f;
-    // this lane's (tap, channel) in each of the wave's tiles
-    int tdy[TPW], tdx[TPW], tci[TPW];
+    char *xs = lds + wave * XB;
+    const int oy = (wave - 1) * dily;
+    const bool span = dilx <= 32;              // one staged run serves the three column shifts
+    const int pitch = span ? dilx : kUnit;     // staged pixels between two column shifts
+    const int nstage = span ? kUnit + 2 * dilx : 3 * kUnit;
+    constexpr int LPP = CIN / 8, PPL = 64 / LPP, NS = kSpan / PPL;
+    bf16x8 st[NS];
+    // loads of unit i: staged pixel p is pixel (unit's first) + oy W - dil + p, or
+    // + oy W + (c - 1) dil + p % 64 for the run c = p / 64 of a column shift
+    // (pixels outside the batch are not read)
+    auto load_unit = [&](int i) {
+        const long base = (long)c0 + i * kUnit + (long)oy * W;
 #pragma unroll
-    for (int k = 0; k < TPW; ++k) {
-        const int n = 32 * (w * TPW + k) + r;
-        const int tap = n / CIN;
-        tci[k] = n % CIN;
-        const bool real = tap < 9 && w * TPW + k < NT;
-        tdy[k] = real ? (tap / 3 - 1) * dil : 1 << 28;   // huge: never inside
-        tdx[k] = real ? (tap % 3 - 1) * dil : 0;
-        if (!real) tci[k] = 0;
-    }
-    const int c0 = (int)((long)blockIdx.x * chunk);
-    const int c1 = (int)(c0 + chunk < Ppad ? c0 + chunk : Ppad);
-    const int Pi = (int)P, HWi = (int)HW;
-    // eight aligned pixels stay in one image row (and a 16-pixel step moves
-    // at most one row on)
-    const bool rows8 = (W & 7) == 0 && W >= 16;
-    // image, row and column of this lane's first pixel of the next step to
-    // load, advanced by 16 pixels per step (no division in the loop)
-    int pb = (c0 + 8 * h) / HWi, prem = (c0 + 8 * h) - pb * HWi;
-    int py = prem / W, px = prem - py * W;
-    // operands of the 16-pixel step at s (zero past the chunk)
-    auto load_step = [&](int s, bf16x8 &a, bf16x8 *bv) {
-        a = zero_bf16x8();
-#pragma unroll
-        for (int k = 0; k < TPW; ++k) bv[k] = zero_bf16x8();
-        const int p = s + 8 * h;
-        const int b = pb, y = py, x = px;
-        px += 16;
-        if (px >= W) {
-            px -= W;
-            if (++py == H) {
-                py = 0;
-                ++pb;
-            }
-        }
-        if (s >= c1) return;
-        a = *(const bf16x8 *)(dzt + (size_t)r * Ppad + p);
-#pragma unroll
-        for (int k = 0; k < TPW; ++k) {
-            const __bf16 *src = xt + (size_t)tci[k] * Ppad;
-            if (rows8 && p + 8 <= Pi) {
-                const int yy = y + tdy[k];
-                if (yy >= 0 && yy < H) {
-                    const int xs = x + tdx[k];
-                    const int q = (b * H + yy) * W + xs;
-                    if (xs >= 0 && xs + 8 <= W) {
-                        __builtin_memcpy(&bv[k], src + q, 16);
-                    } else {
-#pragma unroll
-                        for (int j = 0; j < 8; ++j)
-                            if (xs + j >= 0 && xs + j < W) bv[k][j] = src[q + j];
-                    }
-                }
-            } else {
-                // general position: each pixel on its own (rows of any width,
-                // the last pixels of the batch)
-#pragma unroll 1
-                for (int j = 0; j < 8; ++j) {
-                    const int pj = p + j;
-                    if (pj >= Pi) break;
-                    const int bj = pj / HWi, rj = pj - bj * HWi;
-                    const int yj = rj / W + tdy[k], xj = rj % W + tdx[k];
-                    if (yj >= 0 && yj < H && xj >= 0 && xj < W)
-                        bv[k][j] = src[(bj * H + yj) * W + xj];
-                }
-            }
+        for (int c = 0; c < NS; ++c) {
+            if (c * PPL >= nstage) continue;   // uniform
+            const long q = base + (span ? (long)c * PPL - dilx
+                                        : (long)(c * PPL / kUnit - 1) * dilx + c * PPL % kUnit);
+            const int first = (int)min(max(-q, 0L), 64L), last = (int)min(max((long)P - q, 0L), 64L);
+            const int p = lane / LPP;
+            const bool ok = p >= first && p < last && c * PPL + p < nstage;
+            st[c] = load_bf16x8(buf_of(x + q * CIN, 1024), ok ? lane * 16 : kOut);
         }
     };
-    auto mma_step = [&](const bf16x8 &a, const bf16x8 *bv) {
+    const int lo = tr_lane_offset(lane);
+    const int lp = lo >> 6;                    // this lane's pixel of a fragment's first read
+    load_unit(0);
+    for (int i = 0; i < nu; ++i) {
+        wave_lds_order();                      // the reads of the unit before are done
 #pragma unroll
-        for (int j = 0; j < 8; ++j) bsum += (float)a[j];
+        for (int c = 0; c < NS; ++c) {
+            if (c * PPL >= nstage) continue;
+            *(bf16x8 *)(xs + (c * PPL + lane / LPP) * 64 + (lane % LPP) * 16) = st[c];
+        }
+        if (i + 1 < nu) load_unit(i + 1);
+        // which taps of the unit's pixels stay in the image
+        const unsigned p = (unsigned)(c0 + i * kUnit + lane);
+        const unsigned row = p / (unsigned)W;
+        const unsigned px = p - row * (unsigned)W;
+        const bool row_in = p < (unsigned)P && (row % (unsigned)H) + (unsigned)oy < (unsigned)H;
+        uint64_t in[3];
 #pragma unroll
-        for (int k = 0; k < TPW; ++k)
-            acc[k] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bv[k], acc[k], 0, 0, 0);
-    };
-    bf16x8 a0, a1, b0[TPW], b1[TPW];
-    int s = c0;
-    load_step(s, a0, b0);
-#pragma unroll 1
-    for (; s < c1; s += 32) {
-        load_step(s + 16, a1, b1);
-        mma_step(a0, b0);
-        if (s + 16 >= c1) break;
-        load_step(s + 32, a0, b0);
-        mma_step(a1, b1);
+        for (int c = 0; c < 3; ++c)
+            in[c] = __ballot(row_in && px + (unsigned)((c - 1) * dilx) < (unsigned)W);
+        __syncthreads();                       // the unit's dZ is there
+        wave_lds_order();
+        bf16x8 af[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const char *at = zs + (i & 1) * ZB + lo + k * 16 * 64;
+            af[k] = tr_frag(at, at + 4 * 64);
+            if (wave == 0) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) bsum += (float)af[k][j];
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                int o0 = lo + (c * pitch + k * 16) * 64, o1 = o0 + 4 * 64;
+                if (in[c] != ~0ull) {          // uniform
+                    const uint32_t m = (uint32_t)(in[c] >> (32 * (k / 2))) >> (16 * (k % 2));
+                    const int zero = kSpan * 64 + (lo & 63);
+                    if (!((m >> lp) & 1u)) o0 = zero;
+                    if (!((m >> (lp + 4)) & 1u)) o1 = zero;
+                }
+                acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[k], tr_frag(xs + o0, xs + o1),
+                                                                 acc[c], 0, 0, 0);
+            }
+        }
     }
-    // this wave's tiles of the partial: D[co][n] with co = 8 i + 4 h + j in
-    // accumulator 4 i + j, n = 32 tile + lane % 32
-    float *out = part + (size_t)blockIdx.x * 32 * NN;
+    __syncthreads();                           // the dZ wave's last
+    // D[co][ci] with co = 8 i + 4 h + j in accumulator 4 i + j, ci = lane % 32
+    const int r = lane & 31, h = lane >> 5;
+    float *out = part + (size_t)g * 32 * NN;
 #pragma unroll
-    for (int k = 0; k < TPW; ++k) {
-        const int n = 32 * (w * TPW + k) + r;
-        if (n >= NN) continue;
+    for (int c = 0; c < 3; ++c)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) out[(size_t)(8 * i + 4 * h + j) * NN + n] = acc[k][4 * i + j];
-    }
-    bsum += __shfl_xor(bsum, 32, 64);   // lanes r and r + 32 hold the same channel
-    if (w == 0 && h == 0) dbpart[(size_t)blockIdx.x * 32 + r] = bsum;
+        for (int v = 0; v < 16; ++v)
+            if (r < CIN)
+                out[(size_t)(8 * (v / 4) + 4 * h + v % 4) * NN + (3 * wave + c) * CIN + r] = acc[c][v];
+    bsum += __shfl_xor(bsum, 32, 64);          // lanes r and r + 32 hold the same channel
+    if (wave == 0 && h == 0) dbpart[(size_t)g * 32 + r] = bsum;
 }
 
-// out[g][i] = sum of in[r][i] over rows r in [g rpg, (g + 1) rpg) of nrows,
-// in order: the split-K partials of the weight and bias gradients are summed
-// in two such passes (groups, then the groups), a fixed order.
-__global__ __launch_bounds__(256) void k_sum_rows(const float *__restrict__ in, int nrows,
-                                                  int rpg, int ncols, float *__restrict__ out) {
-    const int i = (int)(blockIdx.x * 256 + threadIdx.x);
-    const int g = (int)blockIdx.y;
-    if (i >= ncols) return;
-    const int r0 = g * rpg, r1 = min(nrows, r0 + rpg);
+// dW and db from the chunks' partials: 32 columns per block (dW's ndw
+// columns, then db's 32), kSumRuns runs of rows summed in order, then the
+// runs in order.  Bound by the latency of a run's chain of loads (32 rows on
+// 512 chunks).
+__global__ __launch_bounds__(32 * kSumRuns) void k_sum_partials(const float *__restrict__ part,
+                                                                const float *__restrict__ dbpart,
+                                                                int nrows, int ndw,
+                                                                float *__restrict__ dw,
+                                                                float *__restrict__ db) {
+    __shared__ float sh[kSumRuns][32];
+    const int c = (int)(threadIdx.x & 31u), run = (int)(threadIdx.x >> 5);
+    const bool bias = (int)blockIdx.x * 32 >= ndw;
+    const int i = bias ? c : (int)blockIdx.x * 32 + c, pitch = bias ? 32 : ndw;
+    const float *in = bias ? dbpart : part;
+    const int per = (nrows + kSumRuns - 1) / kSumRuns;
+    const int r0 = run * per, r1 = min(nrows, r0 + per);
     float acc = 0.0f;
-    for (int r = r0; r < r1; ++r) acc += in[(size_t)r * ncols + i];
-    out[(size_t)g * ncols + i] = acc;
+#pragma unroll 8
+    for (int r = r0; r < r1; ++r) acc += in[(size_t)r * pitch + i];
+    sh[run][c] = acc;
+    __syncthreads();
+    if (run != 0) return;
+    float v = 0.0f;
+#pragma unroll
+    for (int k = 0; k < kSumRuns; ++k) v += sh[k][c];
+    if (bias) db[i] = v;
+    else dw[i] = v;
 }
 
 // Adam step on FP32 master weights (bias-corrected moments); refreshes the
@@ -865,12 +903,26 @@ hipError_t conv_dispatch(const void *x, int B, int H, int W, int cin, const void
     return hipGetLastError();
 }
 
-long pad64(long p) { return (p + 63) / 64 * 64; }
-// pixels per work-group of the weight gradient (split-K chunk), and the
-// groups of chunks its first summation pass forms
-constexpr long kWgradChunk = 1024;
-constexpr int kWgradTPW = 3;     // N tiles per wave
-constexpr int kSumGroups = 16;
+hipError_t wgrad_dispatch(const float *dy, const void *y, int relu, const void *x, int H, int W,
+                          int cin, int cout, int dil, int P, int nchunks, void *dz, float *part,
+                          float *dbpart, const void *w, void *wt, hipStream_t s) {
+    const int dx = clamp_dil(dil, W), dyl = clamp_dil(dil, H);
+    const int nflip = dz ? (32 * 9 * cout + 255) / 256 : 0;
+    dim3 grid((unsigned)(nchunks + nflip)), block(256);
+    const __bf16 *yy = (const __bf16 *)y, *xx = (const __bf16 *)x, *ww = (const __bf16 *)w;
+    __bf16 *z = (__bf16 *)dz, *t = (__bf16 *)wt;
+    if (cin == 16 && cout == 16)
+        hipLaunchKernelGGL((gabp::k_wgrad<16, 16>), grid, block, 0, s, dy, yy, relu, xx, H, W, dx, dyl, P, nchunks, z, part, dbpart, ww, t);
+    else if (cin == 16)
+        hipLaunchKernelGGL((gabp::k_wgrad<16, 32>), grid, block, 0, s, dy, yy, relu, xx, H, W, dx, dyl, P, nchunks, z, part, dbpart, ww, t);
+    else if (cout == 16)
+        hipLaunchKernelGGL((gabp::k_wgrad<32, 16>), grid, block, 0, s, dy, yy, relu, xx, H, W, dx, dyl, P, nchunks, z, part, dbpart, ww, t);
+    else
+        hipLaunchKernelGGL((gabp::k_wgrad<32, 32>), grid, block, 0, s, dy, yy, relu, xx, H, W, dx, dyl, P, nchunks, z, part, dbpart, ww, t);
+    return hipGetLastError();
+}
+
+long wgrad_chunks(long P) { return (P + gabp::kChunk - 1) / gabp::kChunk; }
 }  // namespace
 
 extern "C" {
@@ -888,16 +940,13 @@ gabp_status gabp_conv3x3_fwd(const void *x, int32_t B, int32_t H, int32_t W, int
 }
 
 size_t gabp_conv3x3_bwd_workspace(int32_t B, int32_t H, int32_t W, int32_t cin, int32_t cout) {
-    const long P = (long)B * H * W, Pp = pad64(P);
-    const long nchunks = (Pp + kWgradChunk - 1) / kWgradChunk;
+    const long P = (long)B * H * W;
+    const long nchunks = wgrad_chunks(P);
     size_t bytes = 0;
     bytes += (size_t)32 * 9 * 32 * 2 + 256;                  // flipped weights
     bytes += (size_t)P * cout * 2 + 256;                     // dz (NHWC)
-    bytes += (size_t)32 * Pp * 2 + 256;                      // dz channel-major
-    bytes += (size_t)cin * Pp * 2 + 256;                     // x channel-major
-    bytes += (size_t)nchunks * 32 * 9 * cin * 4 + 256;       // split-K partials of dw
+    bytes += (size_t)nchunks * 32 * 9 * cin * 4 + 256;       // the chunks' partials of dw
     bytes += (size_t)nchunks * 32 * 4 + 256;                 // and of db
-    bytes += (size_t)kSumGroups * 32 * (9 * cin + 1) * 4 + 512;   // group sums
     return bytes;
 }
 
@@ -917,8 +966,8 @@ gabp_status gabp_conv3x3_bwd(const void *x, const void *y, const float *dy, int3
     if (workspace_bytes < gabp_conv3x3_bwd_workspace(B, H, W, cin, cout))
         return nfail(GABP_E_NOMEM, "conv3x3_bwd: workspace too small");
     hipStream_t s = (hipStream_t)stream;
-    const long P = (long)B * H * W, Pp = pad64(P);
-    const int nchunks = (int)((Pp + kWgradChunk - 1) / kWgradChunk);
+    const long P = (long)B * H * W;
+    const int nchunks = (int)wgrad_chunks(P), ndw = 32 * 9 * cin;
     char *ws = (char *)workspace;
     auto take = [&](size_t bytes) {
         char *p = ws;
@@ -927,44 +976,14 @@ gabp_status gabp_conv3x3_bwd(const void *x, const void *y, const float *dy, int3
     };
     __bf16 *wt = (__bf16 *)take((size_t)32 * 9 * 32 * 2);
     __bf16 *dz = (__bf16 *)take((size_t)P * cout * 2);
-    __bf16 *dzt = (__bf16 *)take((size_t)32 * Pp * 2);
-    __bf16 *xt = (__bf16 *)take((size_t)cin * Pp * 2);
-    float *part = (float *)take((size_t)nchunks * 32 * 9 * cin * 4);
+    float *part = (float *)take((size_t)nchunks * ndw * 4);
     float *dbpart = (float *)take((size_t)nchunks * 32 * 4);
-    float *gpart = (float *)take((size_t)kSumGroups * 32 * 9 * cin * 4);
-    float *gdb = (float *)take((size_t)kSumGroups * 32 * 4);
-    const unsigned tiles = (unsigned)(Pp / gabp::kTP);
-    hipLaunchKernelGGL(gabp::k_relu_bwd_t, dim3(tiles), dim3(256), 0, s, dy, (const __bf16 *)y, P,
-                       cout, relu, dz, dzt, Pp);
-    hipLaunchKernelGGL(gabp::k_to_cmajor, dim3(tiles), dim3(256), 0, s, (const __bf16 *)x, P, cin,
-                       xt, Pp);
-    // waves per work-group: the N tiles (5 for 16 input channels, 9 for 32)
-    // in groups of kWgradTPW
-    if (cin == 16)
-        hipLaunchKernelGGL((gabp::k_wgrad<16, kWgradTPW>), dim3(nchunks),
-                           dim3(64 * ((5 + kWgradTPW - 1) / kWgradTPW)), 0, s,
-                           (const __bf16 *)dzt, (const __bf16 *)xt, H, W, dil, P, Pp,
-                           (int)kWgradChunk, part, dbpart);
-    else
-        hipLaunchKernelGGL((gabp::k_wgrad<32, kWgradTPW>), dim3(nchunks),
-                           dim3(64 * ((9 + kWgradTPW - 1) / kWgradTPW)), 0, s,
-                           (const __bf16 *)dzt, (const __bf16 *)xt, H, W, dil, P, Pp,
-                           (int)kWgradChunk, part, dbpart);
-    const int nn = 32 * 9 * cin;
-    const int rpg = (nchunks + kSumGroups - 1) / kSumGroups;
-    hipLaunchKernelGGL(gabp::k_sum_rows, dim3((nn + 255) / 256, kSumGroups), dim3(256), 0, s,
-                       (const float *)part, nchunks, rpg, nn, gpart);
-    hipLaunchKernelGGL(gabp::k_sum_rows, dim3((nn + 255) / 256, 1), dim3(256), 0, s,
-                       (const float *)gpart, kSumGroups, kSumGroups, nn, dw);
-    hipLaunchKernelGGL(gabp::k_sum_rows, dim3(1, kSumGroups), dim3(256), 0, s,
-                       (const float *)dbpart, nchunks, rpg, 32, gdb);
-    hipLaunchKernelGGL(gabp::k_sum_rows, dim3(1, 1), dim3(256), 0, s, (const float *)gdb,
-                       kSumGroups, kSumGroups, 32, db);
-    if (dx) {
-        hipLaunchKernelGGL(gabp::k_flip_weights, dim3((32 * 9 * cout + 255) / 256), dim3(256), 0, s,
-                           (const __bf16 *)w, cin, cout, wt);
-        NHIP(conv_dispatch(dz, B, H, W, cout, wt, nullptr, cin, dil, 0, nullptr, dx, s));
-    }
+    NHIP(wgrad_dispatch(dy, y, relu, x, H, W, cin, cout, dil, (int)P, nchunks, dx ? dz : nullptr,
+                        part, dbpart, w, wt, s));
+    if (dx) NHIP(conv_dispatch(dz, B, H, W, cout, wt, nullptr, cin, dil, 0, nullptr, dx, s));
+    hipLaunchKernelGGL(gabp::k_sum_partials, dim3((unsigned)(ndw / 32 + 1)),
+                       dim3(32 * gabp::kSumRuns), 0, s, (const float *)part, (const float *)dbpart,
+                       nchunks, ndw, dw, db);
     NHIP(hipGetLastError());
     return GABP_OK;
 }

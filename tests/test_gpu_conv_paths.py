@@ -69,3 +69,59 @@ def test_forward_at_tile_edges(G, B, H, W, dil, cin, cout):
     # FP32 sums of at most 288 exact products of BF16 values: 18 accumulations
     assert np.abs(yf.cpu().double().numpy() - ref).max() <= 2e-5 * (np.abs(ref).max() + 1.0)
     assert torch.equal(yb, yf.to(torch.bfloat16))
+
+
+# one pixel, units of 64 and chunks of 1024 pixels and their neighbours, rows
+# that straddle 16-pixel steps, dilations whose column shifts share a staged run
+# (up to 32) and those that do not
+BWD = [(1, 1, 1, 1), (1, 7, 9, 3), (1, 1, 65, 32), (1, 1025, 1, 9), (2, 16, 32, 33),
+       (1, 31, 33, 40), (3, 25, 93, 27), (1, 64, 97, 70)]
+
+
+@pytest.mark.parametrize("B,H,W,dil", BWD)
+@pytest.mark.parametrize("cin,cout,relu", [(16, 16, True), (16, 32, False), (32, 16, False),
+                                           (32, 32, True)])
+def test_backward_at_unit_edges(G, B, H, W, dil, cin, cout, relu):
+    rng = np.random.default_rng(H * W + dil)
+    x = _bf16(rng.normal(size=(B, H, W, cin)))
+    w = _weights(rng, cin, cout)
+    y = _bf16(rng.normal(size=(B, H, W, cout)))
+    dy = rng.normal(size=(B, H, W, cout)).astype(np.float32)
+    dw, db, dx, _ = G.gabp_conv3x3_bwd(x.cuda(), y.cuda(), torch.tensor(dy, device="cuda"),
+                                       w.cuda(), cout, dil, relu)
+    mask = (y.double().numpy() > 0) if relu else 1.0
+    dz = _bf16(dy * mask).double().numpy()
+    dxr, dwr, dbr = C.conv3x3_bwd(x.double().numpy(), np.ones_like(dz), dz,
+                                  w.double().numpy()[:cout].reshape(cout, 9, cin), dil, relu=False)
+    assert torch.all(dw[cout:] == 0) and torch.all(db[cout:] == 0)
+    # FP32 sums of exact products, at most 64 accumulations per chunk of 1024
+    # pixels and 32 more: their rounding is far below 2e-5 of the sum's scale
+    for got, ref in ((dw[:cout].reshape(cout, 9, cin), dwr), (db[:cout], dbr), (dx, dxr)):
+        np.testing.assert_allclose(got.cpu().double().numpy(), ref, rtol=0,
+                                   atol=2e-5 * (np.abs(ref).max() + 1.0))
+    # without the data gradient: the same weight and bias gradients
+    dw2, db2, none, _ = G.gabp_conv3x3_bwd(x.cuda(), y.cuda(), torch.tensor(dy, device="cuda"),
+                                           w.cuda(), cout, dil, relu, need_dx=False)
+    assert none is None and torch.equal(dw, dw2) and torch.equal(db, db2)
+
+
+@pytest.mark.parametrize("W,dil", [(93, 9), (64, 1), (70, 40)])
+def test_backward_infinite_input_reaches_only_its_taps(G, W, dil):
+    """An infinite input pixel at the end of a row enters the weight gradient
+    through the taps whose output pixel lies in the image and no others:
+    out-of-image taps and padding are no terms of the sums."""
+    B, H, cin, cout = 2, 12, 32, 32
+    rng = np.random.default_rng(W)
+    x = _bf16(rng.normal(size=(B, H, W, cin)))
+    yq, xq, ci = 5, W - 1, 7
+    x[1, yq, xq, ci] = float("inf")
+    dy = torch.tensor(np.abs(rng.normal(size=(B, H, W, cout))) + 0.1, dtype=torch.float32)
+    y = torch.ones((B, H, W, cout), dtype=torch.bfloat16)
+    dw, _, _, _ = G.gabp_conv3x3_bwd(x.cuda(), y.cuda(), dy.cuda(), _weights(rng, cin, cout).cuda(),
+                                     cout, dil, True)
+    want = torch.ones(cout, 9, cin, dtype=torch.bool)
+    for tap in range(9):
+        py, px = yq - (tap // 3 - 1) * dil, xq - (tap % 3 - 1) * dil
+        if 0 <= py < H and 0 <= px < W:
+            want[:, tap, ci] = False
+    assert torch.equal(torch.isfinite(dw[:cout].reshape(cout, 9, cin)).cpu(), want)
