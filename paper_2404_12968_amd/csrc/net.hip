@@ -37,6 +37,15 @@ __device__ __forceinline__ bf16x8 zero_bf16x8() {
     return z;
 }
 
+// A workgroup barrier that waits for the wave's LDS accesses but not for its
+// loads from memory (which __syncthreads would), so that loads issued ahead
+// stay in flight across it.  Orders LDS contents only.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // A raw buffer resource over [base, base + bytes), bytes below 2^30: loads at an
 // offset past its end (an invalid lane passes kOut) return zero and touch no
 // memory.
@@ -287,7 +296,7 @@ __global__ __launch_bounds__(256, kRowsWaves) void k_conv_rows(
     };
     if (q.t < q.t1) load_seg();
     while (q.t < q.t1) {
-        __syncthreads();                       // the segment before has been read
+        lds_barrier();                         // the segment before has been read
 #pragma unroll
         for (int r = 0; r < 3; ++r)
 #pragma unroll
@@ -296,7 +305,7 @@ __global__ __launch_bounds__(256, kRowsWaves) void k_conv_rows(
                 if (p0 >= nstage) continue;
                 *(bf16x8 *)(xs + r * kRowSpan * PB + part_at(p0 + lane / QPP, lane % QPP)) = st[r][k];
             }
-        __syncthreads();
+        lds_barrier();
         const int x0 = q.sx * kRowTile + 32 * wave;
         const size_t o = ((size_t)q.row * W + x0 + n) * COUT;
         q.next(spr, H);
@@ -341,9 +350,13 @@ __global__ __launch_bounds__(256, kRowsWaves) void k_conv_rows(
 // partials; the order of every sum (16-pixel steps within a chunk, then 16
 // runs of chunks) is fixed.
 //
-// Bound by HBM on large inputs (dY, y and x read, dZ written: 34 us for
-// 8 x 256 x 256 pixels of a 32 -> 32 layer at the copy rate), by the latency of
-// a chunk's 16 units on small ones.
+// Bound by HBM on large inputs (dY, y and x read, dZ written): 8 x 256 x 256 pixels
+// of a 32 -> 32 layer take 44 us, 3.8 TB/s (34 us at the copy rate; transposed
+// copies of dZ and x, then products and four sums, took 204).  Bound by the
+// latency of a chunk's 16 units on small ones: 36 us for 2 x 61 x 93 pixels
+// (544 with a per-pixel path for widths that are no multiple of 8).  The
+// barrier between the dZ wave and the others waits for LDS only, so that
+// loads stay in flight across it.
 // --------------------------------------------------------------------------
 constexpr int kUnit = 64;       // pixels per unit
 constexpr int kChunk = 1024;    // pixels per workgroup and partial sum
@@ -417,38 +430,43 @@ __global__ __launch_bounds__(256) void k_wgrad(
     const int nu = (c1 - c0 + kUnit - 1) / kUnit;
     if (wave == 3) {
         // dZ of each unit, eight channels per lane
+        // (loaded one unit ahead)
         constexpr int LPP = COUT / 8, PPL = 64 / LPP, NC = kUnit / PPL;   // lanes per pixel, pixels per load
-        for (int i = 0; i <= nu; ++i) {
-            if (i < nu) {
-                float f[NC][8];
-                bf16x8 yv[NC];
+        float f[NC][8];
+        bf16x8 yv[NC];
+        auto load_dy = [&](int i) {
 #pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    const int p = c0 + i * kUnit + c * PPL + lane / LPP;
+            for (int c = 0; c < NC; ++c) {
+                const int p = c0 + i * kUnit + c * PPL + lane / LPP;
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) f[c][j] = 0.0f;
-                    yv[c] = zero_bf16x8();
-                    if (p < c1) {
-                        const size_t e = (size_t)p * COUT + (lane % LPP) * 8;
-                        __builtin_memcpy(f[c], dy + e, 32);
-                        if (relu) __builtin_memcpy(&yv[c], y + e, 16);
-                    }
-                }
-#pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    const int pu = c * PPL + lane / LPP, p = c0 + i * kUnit + pu;
-                    bf16x8 z;
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        float v = f[c][j];
-                        if (relu && !((float)yv[c][j] > 0.0f)) v = 0.0f;
-                        z[j] = (__bf16)v;
-                    }
-                    *(bf16x8 *)(zs + (i & 1) * ZB + pu * 64 + (lane % LPP) * 16) = z;
-                    if (dz && p < c1) *(bf16x8 *)(dz + (size_t)p * COUT + (lane % LPP) * 8) = z;
+                for (int j = 0; j < 8; ++j) f[c][j] = 0.0f;
+                yv[c] = zero_bf16x8();
+                if (p < c1) {
+                    const size_t e = (size_t)p * COUT + (lane % LPP) * 8;
+                    __builtin_memcpy(f[c], dy + e, 32);
+                    if (relu) __builtin_memcpy(&yv[c], y + e, 16);
                 }
             }
-            __syncthreads();
+        };
+        load_dy(0);
+        for (int i = 0; i < nu; ++i) {
+            bf16x8 z[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    float v = f[c][j];
+                    if (relu && !((float)yv[c][j] > 0.0f)) v = 0.0f;
+                    z[c][j] = (__bf16)v;
+                }
+            if (i + 1 < nu) load_dy(i + 1);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const int pu = c * PPL + lane / LPP, p = c0 + i * kUnit + pu;
+                *(bf16x8 *)(zs + (i & 1) * ZB + pu * 64 + (lane % LPP) * 16) = z[c];
+                if (dz && p < c1) *(bf16x8 *)(dz + (size_t)p * COUT + (lane % LPP) * 8) = z[c];
+            }
+            lds_barrier();
         }
         return;
     }
@@ -501,8 +519,7 @@ __global__ __launch_bounds__(256) void k_wgrad(
 #pragma unroll
         for (int c = 0; c < 3; ++c)
             in[c] = __ballot(row_in && px + (unsigned)((c - 1) * dilx) < (unsigned)W);
-        __syncthreads();                       // the unit's dZ is there
-        wave_lds_order();
+        lds_barrier();                         // the unit's dZ is there
         bf16x8 af[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -513,23 +530,37 @@ __global__ __launch_bounds__(256) void k_wgrad(
                 for (int j = 0; j < 8; ++j) bsum += (float)af[k][j];
             }
         }
+        // LDS rows of the taps' fragments, selected apart from the products so
+        // that reads and products of the whole unit are one block
+        int o[3][4][2];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
+        for (int c = 0; c < 3; ++c)
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                int o0 = lo + (c * pitch + k * 16) * 64, o1 = o0 + 4 * 64;
-                if (in[c] != ~0ull) {          // uniform
-                    const uint32_t m = (uint32_t)(in[c] >> (32 * (k / 2))) >> (16 * (k % 2));
-                    const int zero = kSpan * 64 + (lo & 63);
-                    if (!((m >> lp) & 1u)) o0 = zero;
-                    if (!((m >> (lp + 4)) & 1u)) o1 = zero;
-                }
-                acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[k], tr_frag(xs + o0, xs + o1),
-                                                                 acc[c], 0, 0, 0);
+                o[c][k][0] = lo + (c * pitch + k * 16) * 64;
+                o[c][k][1] = o[c][k][0] + 4 * 64;
             }
+        if ((in[0] & in[1] & in[2]) != ~0ull) {   // uniform
+            const int zero = kSpan * 64 + (lo & 63);
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t m = (uint32_t)(in[c] >> (32 * (k / 2))) >> (16 * (k % 2));
+                    if (!((m >> lp) & 1u)) o[c][k][0] = zero;
+                    if (!((m >> (lp + 4)) & 1u)) o[c][k][1] = zero;
+                }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            bf16x8 bf[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) bf[c] = tr_frag(xs + o[c][k][0], xs + o[c][k][1]);
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[k], bf[c], acc[c], 0, 0, 0);
         }
     }
-    __syncthreads();                           // the dZ wave's last
     // D[co][ci] with co = 8 i + 4 h + j in accumulator 4 i + j, ci = lane % 32
     const int r = lane & 31, h = lane >> 5;
     float *out = part + (size_t)g * 32 * NN;
