@@ -247,7 +247,13 @@ gabp_status gabp_autotune(gabp_ctx *ctx, int32_t trials, double damping, int32_t
 gabp_status gabp_set_graph(gabp_ctx *ctx, int32_t enable);
 
 /* Tile configuration of a context's iteration kernels, a tuning knob that
- * never changes results.  rows_per_thread (1, 2, 4 or 8): rows each thread
+ * never changes results.  Until it is called, a context whose precision
+ * messages have frozen runs several information-only iterations per launch
+ * (how many, and on which tiles, follows from the lattice, the prior order and
+ * the dtype), and the last iteration of each gabp_iterate call singly; after a
+ * divergence inside such a launch the messages kept are those that
+ * two-iteration launches keep.  After it, launches are as set:
+ * rows_per_thread (1, 2, 4 or 8): rows each thread
  * of a 64-wide, 256-thread tile walks, for the single-iteration kernels.
  * pair_rows: once the precision messages have frozen, gabp_iterate runs
  * two information-only iterations per launch (one HBM pass per two

@@ -13,6 +13,7 @@
 #include <new>
 #include <string>
 
+#include "deep_tile.h"
 #include "gabp.h"
 #include "host_common.h"
 #include "internal.h"
@@ -37,6 +38,13 @@ std::string fmt(const char *f, double a = 0, double b = 0) {
 
 }  // namespace
 
+// Launches of one run of iterations (enqueue_iters), in this order.
+struct Launches {
+    int deeps = 0, deep_iters = 0, pairs = 0, singles = 0;
+    bool last_single = true;   // the last launch was a single iteration
+    bool ref = false;          // the t = 2 reference change was taken
+};
+
 struct gabp_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
@@ -60,15 +68,20 @@ struct gabp_ctx {
     HostMirror *host = nullptr;    // pinned
     int rpt = 4;                   // rows per thread of the iteration kernel's tile
     int pair = 0;                  // tile height of the two-iteration kernel, 0 = unused
+    bool deep = true;              // multi-iteration launches once frozen (until gabp_set_tile)
+    gabp::DeepPlan plan{0, 1};     // their region and iterations
     int cur = 0;                   // buffer holding the current messages m^iter
     // launches since the last flag read-back, one record per gabp_iterate
-    // call: it started at iteration `start` with buffer `buf`, ran `pairs`
+    // call: it started at iteration `start` with buffer `buf`, ran `deeps`
+    // launches of `deep_iters` iterations in all (deep_part), `pairs`
     // two-iteration launches, then `singles` one-iteration launches (each
     // launch writes the other buffer).  A divergence found at the next
     // read-back selects the buffer its launch wrote.
     struct LaunchRun {
         int64_t start;
-        int buf, pairs, singles;
+        int buf, deeps, deep_iters, pairs, singles;
+        bool tail_single;
+        double damping;
     };
     std::vector<LaunchRun> runs;
     // captured chunks: iterations are numbered from the device counter
@@ -79,11 +92,10 @@ struct gabp_ctx {
     hipStream_t side = nullptr;
     struct Chunk {
         int32_t k;
-        int cur, frozen, rpt, pair, tail;
+        int cur, frozen, rpt, pair, deep, tail;
         double eta;
         hipGraphExec_t exec;
-        int pairs, singles;
-        bool last_single;
+        Launches n;
     };
     std::vector<Chunk> chunks;
     // launches issued so far: one-iteration full and information-only
@@ -125,6 +137,35 @@ gabp_status ctx_ok(gabp_ctx *ctx) {
     return GABP_OK;
 }
 
+// Iterations before launch k of `launches` that share n iterations evenly.
+int deep_part(int n, int launches, int k) { return (int)((int64_t)n * k / launches); }
+
+// A multi-iteration launch met the divergence at iteration t.  Its input is
+// whole (it wrote the other buffer, and no later launch wrote), so the state
+// that two-iteration launches would have kept is made from it by single
+// iterations, recording into a spare flag word, which is cleared before each
+// of them.
+gabp_status hold_deep(gabp_ctx *ctx, const gabp_ctx::LaunchRun &r, int64_t t) {
+    const int total = r.deep_iters + 2 * r.pairs + r.singles;
+    const int pairs = held_pairs(total, r.tail_single);
+    const int64_t want = held_after_run(r.start, 0, pairs, t).iter;
+    int k = 0;
+    while (r.start + deep_part(r.deep_iters, r.deeps, k + 1) < t) ++k;
+    int64_t it = r.start + deep_part(r.deep_iters, r.deeps, k);
+    int buf = r.buf ^ (k & 1);
+    for (; it < want; ++it, buf ^= 1) {
+        GABP_HIP(ctx, gabp::launch_set_u32(ctx->flags + 7, 0u, ctx->stream));
+        GABP_HIP(ctx, gabp::launch_iter_theta(ctx->dtype == GABP_F32 ? 0 : 1, 1, ctx->L,
+                                              ctx->msg[buf], ctx->msg[buf ^ 1], ctx->gain,
+                                              ctx->b_w, r.damping, ctx->flags + 7, ctx->flags + 3,
+                                              (uint32_t)(it + 1 - ctx->tbase), ctx->stream));
+    }
+    GABP_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    ctx->iter = it;
+    ctx->cur = buf;
+    return GABP_OK;
+}
+
 // Copy the device flags (and reduction results) to the pinned mirror, wait,
 // and fold a recorded divergence into the host state.
 gabp_status sync_flags(gabp_ctx *ctx, bool with_red) {
@@ -144,8 +185,14 @@ gabp_status sync_flags(gabp_ctx *ctx, bool with_red) {
         // second iteration), in the buffer it wrote
         for (const auto &r : ctx->runs) {
             const int64_t rel = (int64_t)t - r.start;
-            if (rel < 1 || rel > 2 * (int64_t)r.pairs + r.singles) continue;
-            const HeldState h = held_after_run(r.start, r.buf, r.pairs, (int64_t)t);
+            if (rel < 1 || rel > r.deep_iters + 2 * (int64_t)r.pairs + r.singles) continue;
+            if (rel <= r.deep_iters) {
+                const gabp_status s1 = hold_deep(ctx, r, (int64_t)t);
+                if (s1 != GABP_OK) return s1;
+                break;
+            }
+            const HeldState h = held_after_run(r.start + r.deep_iters, r.buf ^ (r.deeps & 1),
+                                               r.pairs, (int64_t)t);
             ctx->iter = h.iter;
             ctx->cur = h.buf;
             break;
@@ -374,6 +421,10 @@ gabp_status gabp_create(const gabp_grid *grid, const gabp_stencil *stencil, cons
         return bail(GABP_E_INVALID);
     }
     ctx->iter = 0;
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess)
+        cus = 256;
+    ctx->plan = gabp::deep_plan(dtype == GABP_F32 ? 0 : 1, ctx->L.alpha, ctx->L.nx, ctx->L.ny, cus);
     {
         std::lock_guard<std::mutex> g(g_tune_mu);
         auto it = g_tune.find(tune_key(ctx));
@@ -403,27 +454,42 @@ namespace {
 
 // Issue n iterations on stream s, starting from iteration iter0 held in
 // buffer cur0, with iteration numbers relative to the device counter's value
-// tbase when they run.  Frozen contexts run two iterations per launch; with
-// tail_single the last one or two run singly, so that the two buffers end on
-// m^{t-1} and m^t (the message-change statistic and the freeze probe need
-// that), else pairs run while two iterations remain.  Touches no context
-// state; reports the launch counts, whether the last launch was single and
-// whether the t = 2 reference change was taken.
+// tbase when they run.  Frozen contexts run several iterations per launch:
+// all of them, or with tail_single all but the last, which runs singly, so that
+// the two buffers end on m^{t-1} and m^t (the message-change statistic and the
+// freeze probe need that).  With a tile set by gabp_set_tile they run two per
+// launch; with tail_single the last one or two singly, else while two remain.
+// Touches no context state; reports the launches.
 gabp_status enqueue_iters(gabp_ctx *ctx, int32_t n, double damping, hipStream_t s, int64_t iter0,
-                          int cur0, uint32_t tbase, bool tail_single, int &pairs, int &singles,
-                          bool &last_single, bool &ref) {
+                          int cur0, uint32_t tbase, bool tail_single, Launches &done) {
     const int dt = ctx->dtype == GABP_F32 ? 0 : 1;
     int64_t it = iter0;
     int cur = cur0;
-    pairs = singles = 0;
-    ref = false;
-    last_single = true;
+    done = Launches();
     const int32_t min_left = tail_single ? 3 : 2;
     int32_t k = 0;
     while (k < n) {
         const void *src = ctx->msg[cur];
         void *dst = ctx->msg[cur ^ 1];
-        if (ctx->frozen && ctx->pair != 0 && it >= 2 && n - k >= min_left) {
+        const int32_t many = n - k - (tail_single ? 1 : 0);
+        if (ctx->frozen && ctx->deep && it >= 2 && many >= 2 && done.deeps == 0) {
+            done.deeps = (many + ctx->plan.S - 1) / ctx->plan.S;
+            done.deep_iters = many;
+            for (int j = 0; j < done.deeps; ++j) {
+                const int i0 = deep_part(many, done.deeps, j);
+                const int len = deep_part(many, done.deeps, j + 1) - i0;
+                GABP_HIP(ctx, gabp::launch_iter_deep(dt, ctx->plan.region, len, ctx->L,
+                                                     ctx->msg[cur], ctx->msg[cur ^ 1], ctx->gain,
+                                                     ctx->b_w, damping, ctx->flags, ctx->flags + 3,
+                                                     (uint32_t)(it + i0 - tbase), s));
+                cur ^= 1;
+            }
+            it += many;
+            k += many;
+            done.last_single = false;
+            continue;
+        }
+        if (ctx->frozen && !ctx->deep && ctx->pair != 0 && it >= 2 && n - k >= min_left) {
             if (ctx->pair < 0)
                 GABP_HIP(ctx, gabp::launch_iter_theta2w(dt, -ctx->pair, ctx->L, src, dst,
                                                         ctx->gain, ctx->b_w, damping, ctx->flags,
@@ -434,8 +500,8 @@ gabp_status enqueue_iters(gabp_ctx *ctx, int32_t n, double damping, hipStream_t 
                                                        (uint32_t)(it - tbase), s));
             it += 2;
             k += 2;
-            ++pairs;
-            last_single = false;
+            ++done.pairs;
+            done.last_single = false;
         } else {
             const int64_t t = it + 1;
             if (ctx->frozen)
@@ -448,14 +514,14 @@ gabp_status enqueue_iters(gabp_ctx *ctx, int32_t n, double damping, hipStream_t 
                                                 (uint32_t)(t - tbase), s));
             it = t;
             ++k;
-            ++singles;
-            last_single = true;
+            ++done.singles;
+            done.last_single = true;
             if (t == 2) {
                 const int64_t m = (int64_t)(2 * ctx->L.deg) * ctx->L.plane;
                 GABP_HIP(ctx, gabp::launch_abs_change(dt, ctx->msg[0], ctx->msg[1], m,
                                                       ctx->partials, kNumPartials, ctx->red + 4,
                                                       s));
-                ref = true;
+                done.ref = true;
             }
         }
         cur ^= 1;
@@ -470,17 +536,19 @@ int64_t quantize_chunk(int64_t next, int64_t kmin) {
     return q;
 }
 
-// Context state after n iterations issued by enqueue_iters (runs of pairs
-// then singles; a chunk that ends on a pair leaves m^{t-2} in the other
-// buffer).
-void advance_state(gabp_ctx *ctx, int32_t n, int pairs, int singles, bool last_single, bool ref) {
-    ctx->runs.push_back({ctx->iter, ctx->cur, pairs, singles});
-    ctx->launches[ctx->frozen ? 1 : 0] += singles;
-    ctx->launches[ctx->pair > 0 ? 2 : 3] += pairs;
+// Context state after n iterations issued by enqueue_iters (a run that ends
+// on a launch of several iterations leaves an older state than m^{t-1} in the
+// other buffer).
+void advance_state(gabp_ctx *ctx, int32_t n, double damping, bool tail_single, const Launches &d) {
+    ctx->runs.push_back({ctx->iter, ctx->cur, d.deeps, d.deep_iters, d.pairs, d.singles,
+                         tail_single, damping});
+    ctx->launches[ctx->frozen ? 1 : 0] += d.singles;
+    ctx->launches[ctx->pair >= 0 ? 2 : 3] += d.pairs;
+    ctx->launches[2] += d.deeps;
     ctx->iter += n;
-    ctx->cur ^= (pairs + singles) & 1;
-    if (ref) ctx->have_ref = true;
-    if (n > 0) ctx->prev_valid = last_single;
+    ctx->cur ^= (d.deeps + d.pairs + d.singles) & 1;
+    if (d.ref) ctx->have_ref = true;
+    if (n > 0) ctx->prev_valid = d.last_single;
 }
 
 gabp_status check_iterate_args(gabp_ctx *ctx, int32_t n_iters, double damping) {
@@ -500,12 +568,11 @@ gabp_status run_chunk(gabp_ctx *ctx, int32_t k, double damping, bool tail_single
     gabp_status st = check_iterate_args(ctx, k, damping);
     if (st != GABP_OK) return st;
     if (!ctx->graphs || k < 2 || ctx->iter < 2) {
-        int pairs = 0, singles = 0;
-        bool last = true, ref = false;
+        Launches d;
         st = enqueue_iters(ctx, k, damping, ctx->stream, ctx->iter, ctx->cur, ctx->tbase,
-                           tail_single, pairs, singles, last, ref);
+                           tail_single, d);
         if (st != GABP_OK) return st;
-        advance_state(ctx, k, pairs, singles, last, ref);
+        advance_state(ctx, k, damping, tail_single, d);
         return GABP_OK;
     }
     if (ctx->tbase != (uint32_t)ctx->iter) {
@@ -515,7 +582,8 @@ gabp_status run_chunk(gabp_ctx *ctx, int32_t k, double damping, bool tail_single
     gabp_ctx::Chunk *c = nullptr;
     for (auto &e : ctx->chunks)
         if (e.k == k && e.cur == ctx->cur && e.frozen == (int)ctx->frozen && e.rpt == ctx->rpt &&
-            e.pair == ctx->pair && e.tail == (int)tail_single && e.eta == damping)
+            e.pair == ctx->pair && e.deep == (int)ctx->deep && e.tail == (int)tail_single &&
+            e.eta == damping)
             c = &e;
     if (!c) {
         if (ctx->chunks.size() >= 16) {
@@ -526,12 +594,11 @@ gabp_status run_chunk(gabp_ctx *ctx, int32_t k, double damping, bool tail_single
         if (!ctx->side)
             GABP_HIP(ctx, hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking));
         gabp_ctx::Chunk e{k,       ctx->cur, (int)ctx->frozen, ctx->rpt, ctx->pair,
-                          (int)tail_single, damping, nullptr, 0, 0, true};
-        bool ref = false;
+                          (int)ctx->deep, (int)tail_single, damping, nullptr, Launches()};
         GABP_HIP(ctx, hipStreamBeginCapture(ctx->side, hipStreamCaptureModeThreadLocal));
         // relative numbering: the counter holds the chunk's first iteration
         st = enqueue_iters(ctx, k, damping, ctx->side, ctx->iter, ctx->cur, (uint32_t)ctx->iter,
-                           tail_single, e.pairs, e.singles, e.last_single, ref);
+                           tail_single, e.n);
         if (st == GABP_OK && gabp::launch_add_u32(ctx->flags + 3, (uint32_t)k, ctx->side) != hipSuccess)
             st = fail(ctx, GABP_E_DEVICE, "capturing the counter advance failed");
         hipGraph_t g = nullptr;
@@ -549,7 +616,7 @@ gabp_status run_chunk(gabp_ctx *ctx, int32_t k, double damping, bool tail_single
     }
     GABP_HIP(ctx, hipGraphLaunch(c->exec, ctx->stream));
     ctx->tbase += (uint32_t)k;
-    advance_state(ctx, k, c->pairs, c->singles, c->last_single, false);
+    advance_state(ctx, k, damping, tail_single, c->n);
     return GABP_OK;
 }
 
@@ -560,12 +627,11 @@ gabp_status gabp_iterate(gabp_ctx *ctx, int32_t n_iters, double damping) {
     if (st != GABP_OK) return st;
     st = check_iterate_args(ctx, n_iters, damping);
     if (st != GABP_OK) return st;
-    int pairs = 0, singles = 0;
-    bool last = true, ref = false;
+    Launches d;
     st = enqueue_iters(ctx, n_iters, damping, ctx->stream, ctx->iter, ctx->cur, ctx->tbase, true,
-                       pairs, singles, last, ref);
+                       d);
     if (st != GABP_OK) return st;
-    advance_state(ctx, n_iters, pairs, singles, last, ref);
+    advance_state(ctx, n_iters, damping, true, d);
     return GABP_OK;
 }
 
@@ -806,7 +872,10 @@ gabp_status gabp_autotune(gabp_ctx *ctx, int32_t trials, double damping, int32_t
         return fail(ctx, GABP_E_DEVICE, "hipEventCreate failed");
     }
     const int saved_rpt = ctx->rpt, saved_pair = ctx->pair;
+    const bool saved_deep = ctx->deep;
+    ctx->deep = false;             // the timed calls run the shapes they set
     auto finish = [&](gabp_status s1) {
+        ctx->deep = saved_deep;
         (void)hipEventDestroy(ev[0]);
         (void)hipEventDestroy(ev[1]);
         return s1;
@@ -883,6 +952,7 @@ gabp_status gabp_set_tile(gabp_ctx *ctx, int32_t rows_per_thread, int32_t pair_r
                     "pair_rows must be 0, 4, -2 or (FP32 only) 8, 12, 16, 32, -4 or -8");
     ctx->rpt = rows_per_thread;
     ctx->pair = pair_rows;
+    ctx->deep = false;
     return GABP_OK;
 }
 

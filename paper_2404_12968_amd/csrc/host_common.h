@@ -70,6 +70,12 @@ inline HeldState held_after_run(int64_t start, int buf0, int64_t pairs, int64_t 
     return {t, buf0 ^ (int)(k & 1)};
 }
 
+// Two-iteration launches of a run of n frozen iterations: while three remain
+// when the last one or two run singly, else while two remain.
+inline int held_pairs(int n, bool tail_single) {
+    return tail_single ? (n >= 3 ? (n - 1) / 2 : 0) : n / 2;
+}
+
 // Batched runs: an instance at iteration t0 (its state in buffer t0 & 1)
 // runs `couples` couples of two-iteration launches if it is frozen (the
 // first reads buffer t0' & 1 and writes the other, the second writes back;

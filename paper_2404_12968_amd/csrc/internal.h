@@ -31,6 +31,12 @@ constexpr int kPairChoicesF32[] = {4, 8, 12, 16, 32};
 hipError_t launch_iter_theta2(int dtype, int th, const Lattice &L, const void *m_in, void *m_out,
                               const void *gain, const void *bw, double eta, uint32_t *flag,
                               const uint32_t *t_base, uint32_t t_off, hipStream_t s);
+// S information-only iterations per launch on the region'th region of the type
+// (deep_plan, deep_tile.h; S at most the region's `most`); m_in and m_out must
+// differ.  Bitwise equal to S launch_iter_theta calls.
+hipError_t launch_iter_deep(int dtype, int region, int S, const Lattice &L, const void *m_in,
+                            void *m_out, const void *gain, const void *bw, double eta,
+                            uint32_t *flag, const uint32_t *t_base, uint32_t t_off, hipStream_t s);
 // The same two iterations by the column-strip walker: persistent workgroups
 // of rb waves march down 64-column strips in bands of rb rows (rb = 2, 4 or
 // 8 for FP32, 2 for FP64).  Bitwise equal to two launch_iter_theta calls.
