@@ -252,7 +252,8 @@ gabp_status gabp_set_graph(gabp_ctx *ctx, int32_t enable);
  * (how many, and on which tiles, follows from the lattice, the prior order and
  * the dtype), and the last iteration of each gabp_iterate call singly; after a
  * divergence inside such a launch the messages kept are those that
- * two-iteration launches keep.  After it, launches are as set:
+ * two-iteration launches keep; single iterations take one row per thread
+ * unless the autotuner chose otherwise.  After it, launches are as set:
  * rows_per_thread (1, 2, 4 or 8): rows each thread
  * of a 64-wide, 256-thread tile walks, for the single-iteration kernels.
  * pair_rows: once the precision messages have frozen, gabp_iterate runs

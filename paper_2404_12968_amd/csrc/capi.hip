@@ -66,7 +66,8 @@ struct gabp_ctx {
                                    // messages changed by the last iteration (64-bit) and
                                    // [6] their largest relative change (float bits)
     HostMirror *host = nullptr;    // pinned
-    int rpt = 4;                   // rows per thread of the iteration kernel's tile
+    int rpt = 4;                   // rows per thread of the iteration kernel's tile, as set,
+    bool rpt_set = false;          // autotuned or default; launch_rpt() is what is launched
     int pair = 0;                  // tile height of the two-iteration kernel, 0 = unused
     bool deep = true;              // multi-iteration launches once frozen (until gabp_set_tile)
     gabp::DeepPlan plan{0, 1};     // their region and iterations
@@ -208,6 +209,14 @@ gabp_status sync_flags(gabp_ctx *ctx, bool with_red) {
 }
 
 const void *cur_msgs(const gabp_ctx *ctx) { return ctx->msg[ctx->cur]; }
+
+// Rows per thread of the one-iteration kernels: what gabp_set_tile or the
+// autotuner chose, else one, the fastest on every lattice measured: a thread's
+// rows are walked one after the other, each waiting for its loads, and only more
+// workgroups hide that.  One row against four (full iteration, us): FP64 5-point
+// 64^2 4.2 and 7.5, FP32 13-point 256^2 7.6 and 13.5, 1024^2 46.5 and 52.7, 8192 x
+// 4096 1273 and 1296; FP64 13-point 1024^2 84 and 90, 8192 x 4096 2671 and 2785.
+int launch_rpt(const gabp_ctx *ctx) { return ctx->rpt_set ? ctx->rpt : 1; }
 
 void drop_chunks(gabp_ctx *ctx) {
     for (auto &c : ctx->chunks) (void)hipGraphExecDestroy(c.exec);
@@ -430,6 +439,7 @@ gabp_status gabp_create(const gabp_grid *grid, const gabp_stencil *stencil, cons
         auto it = g_tune.find(tune_key(ctx));
         if (it != g_tune.end()) {
             ctx->rpt = it->second.first;
+            ctx->rpt_set = true;
             ctx->pair = it->second.second;
         } else {
             ctx->pair = dtype == GABP_F32 ? 8 : 4;
@@ -505,11 +515,11 @@ gabp_status enqueue_iters(gabp_ctx *ctx, int32_t n, double damping, hipStream_t 
         } else {
             const int64_t t = it + 1;
             if (ctx->frozen)
-                GABP_HIP(ctx, gabp::launch_iter_theta(dt, ctx->rpt, ctx->L, src, dst, ctx->gain,
+                GABP_HIP(ctx, gabp::launch_iter_theta(dt, launch_rpt(ctx), ctx->L, src, dst, ctx->gain,
                                                       ctx->b_w, damping, ctx->flags,
                                                       ctx->flags + 3, (uint32_t)(t - tbase), s));
             else
-                GABP_HIP(ctx, gabp::launch_iter(dt, ctx->rpt, ctx->L, src, dst, ctx->adiag_w,
+                GABP_HIP(ctx, gabp::launch_iter(dt, launch_rpt(ctx), ctx->L, src, dst, ctx->adiag_w,
                                                 ctx->b_w, damping, ctx->flags, ctx->flags + 3,
                                                 (uint32_t)(t - tbase), s));
             it = t;
@@ -581,7 +591,7 @@ gabp_status run_chunk(gabp_ctx *ctx, int32_t k, double damping, bool tail_single
     }
     gabp_ctx::Chunk *c = nullptr;
     for (auto &e : ctx->chunks)
-        if (e.k == k && e.cur == ctx->cur && e.frozen == (int)ctx->frozen && e.rpt == ctx->rpt &&
+        if (e.k == k && e.cur == ctx->cur && e.frozen == (int)ctx->frozen && e.rpt == launch_rpt(ctx) &&
             e.pair == ctx->pair && e.deep == (int)ctx->deep && e.tail == (int)tail_single &&
             e.eta == damping)
             c = &e;
@@ -593,7 +603,7 @@ gabp_status run_chunk(gabp_ctx *ctx, int32_t k, double damping, bool tail_single
         }
         if (!ctx->side)
             GABP_HIP(ctx, hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking));
-        gabp_ctx::Chunk e{k,       ctx->cur, (int)ctx->frozen, ctx->rpt, ctx->pair,
+        gabp_ctx::Chunk e{k,       ctx->cur, (int)ctx->frozen, launch_rpt(ctx), ctx->pair,
                           (int)ctx->deep, (int)tail_single, damping, nullptr, Launches()};
         GABP_HIP(ctx, hipStreamBeginCapture(ctx->side, hipStreamCaptureModeThreadLocal));
         // relative numbering: the counter holds the chunk's first iteration
@@ -872,10 +882,12 @@ gabp_status gabp_autotune(gabp_ctx *ctx, int32_t trials, double damping, int32_t
         return fail(ctx, GABP_E_DEVICE, "hipEventCreate failed");
     }
     const int saved_rpt = ctx->rpt, saved_pair = ctx->pair;
-    const bool saved_deep = ctx->deep;
+    const bool saved_deep = ctx->deep, saved_set = ctx->rpt_set;
     ctx->deep = false;             // the timed calls run the shapes they set
+    ctx->rpt_set = true;
     auto finish = [&](gabp_status s1) {
         ctx->deep = saved_deep;
+        if (s1 != GABP_OK) ctx->rpt_set = saved_set;
         (void)hipEventDestroy(ev[0]);
         (void)hipEventDestroy(ev[1]);
         return s1;
@@ -951,6 +963,7 @@ gabp_status gabp_set_tile(gabp_ctx *ctx, int32_t rows_per_thread, int32_t pair_r
         return fail(ctx, GABP_E_INVALID,
                     "pair_rows must be 0, 4, -2 or (FP32 only) 8, 12, 16, 32, -4 or -8");
     ctx->rpt = rows_per_thread;
+    ctx->rpt_set = true;
     ctx->pair = pair_rows;
     ctx->deep = false;
     return GABP_OK;
