@@ -32,6 +32,7 @@
 #include "internal.h"
 #include "iter_node.h"
 #include "pair_tile.h"
+#include "prec_change.h"
 #include "lattice.h"
 #include "numerics.h"
 
@@ -263,6 +264,25 @@ __global__ __launch_bounds__(256) void k_batch_reduce(const int *__restrict__ ac
         out[2 * I] = (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]);
         out[2 * I + 1] = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
     }
+}
+
+// The freeze test of every instance in a list of running ones: kProbeBlocks
+// blocks each, one launch (24 launches of up to 25 us each for 24 instances).
+constexpr int kProbeBlocks = 64;
+template <typename T>
+__global__ __launch_bounds__(256) void k_batch_prec_change(const BatchInst *__restrict__ inst,
+                                                           const int *__restrict__ act,
+                                                           const uint32_t *__restrict__ t_dev,
+                                                           uint64_t limit,
+                                                           unsigned long long *__restrict__ count,
+                                                           uint32_t *__restrict__ maxrel) {
+    const int I = __builtin_amdgcn_readfirstlane(act[blockIdx.y]);
+    const BatchInst &B = inst[I];
+    const uint32_t t = *t_dev;
+    prec_change_wave<T, LatticeRel>((const T *)B.msg[t & 1u], (const T *)B.msg[(t & 1u) ^ 1u],
+                                    (int64_t)B.L.deg * B.L.plane,
+                                    (int)(blockIdx.x * 4 + (threadIdx.x >> 6)), kProbeBlocks * 4,
+                                    limit, count + I, maxrel + I);
 }
 
 // Advances the device iteration counter after a chunk (a kernel node, so a
@@ -608,27 +628,26 @@ gabp_status launch_check(gabp_batch *b) {
 }
 
 // Precision-message change (count and largest relative change) of every
-// running, not yet frozen instance whose previous buffer is valid (outside
-// the captured graph).
+// running, not yet frozen instance (outside the captured graph): the list of
+// instances on single iterations, which with two-iteration launches in use
+// (always) is just them.  Before t = 2 there is no previous iteration to
+// compare with.
 gabp_status launch_probes(gabp_batch *b) {
-    bool any = false;
-    for (int i = 0; i < b->n; ++i) {
-        InstHost &H = b->h[i];
-        if (!(H.running && !H.frozen && H.prev_valid && H.iters >= 2)) continue;
-        any = true;
-        const int dt = b->dtype == GABP_F32 ? 0 : 1;
-        char *base = b->ws + H.base;
-        BHIP(b, gabp::launch_prec_change(dt, base + H.lay.msg[H.iters & 1],
-                                         base + H.lay.msg[(H.iters - 1) & 1],
-                                         (int64_t)H.L.deg * H.L.plane, b->d_cnt + i,
-                                         b->d_mrel + i, b->stream));
-    }
-    if (any) {
-        BHIP(b, hipMemcpyAsync(b->p_cnt, b->d_cnt, sizeof(unsigned long long) * (size_t)b->n,
-                               hipMemcpyDeviceToHost, b->stream));
-        BHIP(b, hipMemcpyAsync(b->p_mrel, b->d_mrel, sizeof(uint32_t) * (size_t)b->n,
-                               hipMemcpyDeviceToHost, b->stream));
-    }
+    if (b->nu == 0 || b->t < 2) return GABP_OK;
+    const dim3 grid(gabp::kProbeBlocks, (unsigned)b->nu);
+    if (b->dtype == GABP_F32)
+        hipLaunchKernelGGL((gabp::k_batch_prec_change<float>), grid, dim3(256), 0, b->stream,
+                           b->d_inst, b->d_actu, b->d_t, (uint64_t)b->freeze_slots, b->d_cnt,
+                           b->d_mrel);
+    else
+        hipLaunchKernelGGL((gabp::k_batch_prec_change<double>), grid, dim3(256), 0, b->stream,
+                           b->d_inst, b->d_actu, b->d_t, (uint64_t)b->freeze_slots, b->d_cnt,
+                           b->d_mrel);
+    BHIP(b, hipGetLastError());
+    BHIP(b, hipMemcpyAsync(b->p_cnt, b->d_cnt, sizeof(unsigned long long) * (size_t)b->n,
+                           hipMemcpyDeviceToHost, b->stream));
+    BHIP(b, hipMemcpyAsync(b->p_mrel, b->d_mrel, sizeof(uint32_t) * (size_t)b->n,
+                           hipMemcpyDeviceToHost, b->stream));
     return GABP_OK;
 }
 

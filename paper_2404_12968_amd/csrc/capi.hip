@@ -668,6 +668,7 @@ gabp_status gabp_residual(gabp_ctx *ctx, double *rel_residual, double *abs_resid
         GABP_HIP(ctx, hipMemsetAsync(ctx->flags + 4, 0, 3 * sizeof(uint32_t), ctx->stream));
         GABP_HIP(ctx, gabp::launch_prec_change(dt, ctx->msg[ctx->cur], ctx->msg[ctx->cur ^ 1],
                                                (int64_t)ctx->L.deg * ctx->L.plane,
+                                               (uint64_t)ctx->freeze_slots,
                                                (unsigned long long *)(ctx->flags + 4),
                                                ctx->flags + 6, ctx->stream));
     }

@@ -52,8 +52,9 @@ hipError_t launch_gain(int dtype, const Lattice &L, const void *m, const void *a
                        hipStream_t s);
 // Precision-message change between buffers a and b (n elements): adds the
 // number of bitwise differing elements to *count and raises *maxrel (float
-// bits) to their largest relative change.  The caller zeroes both first.
-hipError_t launch_prec_change(int dtype, const void *a, const void *b, int64_t n,
+// bits) to their largest relative change, or, past `limit` of them, leaves any
+// larger *count (prec_change.h).  The caller zeroes both first.
+hipError_t launch_prec_change(int dtype, const void *a, const void *b, int64_t n, uint64_t limit,
                               unsigned long long *count, uint32_t *maxrel, hipStream_t s);
 // Marginals: bel64 != NULL selects the frozen-precision variant that reads
 // the belief precisions from bel64; otherwise bel_out (may be NULL) receives

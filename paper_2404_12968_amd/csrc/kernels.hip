@@ -17,6 +17,7 @@
 #include "lattice.h"
 #include "numerics.h"
 #include "check_node.h"
+#include "prec_change.h"
 
 // Rounding is spelled out: no implicit multiply-add contraction in this file,
 // explicit fused multiply-adds where wanted.  The full iteration and the
@@ -302,41 +303,14 @@ __global__ __launch_bounds__(256) void k_msgs_set(Lattice L, T *__restrict__ m,
     }
 }
 
-// Change of the precision messages between two buffers: *count += the
-// number of the n elements whose bits differ (64-bit: n may exceed 2^32),
-// *maxrel = max of the relative
-// changes |a - b| / max(|a|, |b|) over them, as the bits of a non-negative
-// float (+inf for a non-finite element), so that unsigned comparison orders
-// them.  Both are independent of the order of the atomics.
 template <typename T>
 __global__ __launch_bounds__(256) void k_prec_change(const T *__restrict__ a,
                                                      const T *__restrict__ b, int64_t n,
+                                                     uint64_t limit,
                                                      unsigned long long *__restrict__ count,
                                                      uint32_t *__restrict__ maxrel) {
-    const int64_t stride = (int64_t)gridDim.x * 256;
-    uint32_t c = 0u;   // per thread: at most n / stride + 1 elements
-    float mr = 0.0f;
-    for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n; k += stride) {
-        const T x = a[k], y = b[k];
-        const bool diff = sizeof(T) == 4
-                              ? __float_as_uint((float)x) != __float_as_uint((float)y)
-                              : __double_as_longlong((double)x) != __double_as_longlong((double)y);
-        if (!diff) continue;
-        ++c;
-        const double dx = (double)x, dy = (double)y, d = fabs(dx - dy);
-        const double m = fmax(fabs(dx), fabs(dy));
-        const float rel = !isfinite(d) || !isfinite(m) ? INFINITY : d == 0.0 ? 0.0f : (float)(d / m);
-        mr = fmaxf(mr, rel);
-    }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        c += (uint32_t)__shfl_xor((int)c, o, 64);
-        mr = fmaxf(mr, __shfl_xor(mr, o, 64));
-    }
-    if ((threadIdx.x & 63u) == 0u && c != 0u) {
-        atomicAdd(count, (unsigned long long)c);
-        atomicMax(maxrel, __float_as_uint(mr));
-    }
+    prec_change_wave<T, LatticeRel>(a, b, n, (int)(blockIdx.x * 4 + (threadIdx.x >> 6)),
+                                    (int)gridDim.x * 4, limit, count, maxrel);
 }
 
 // Multigrid transfer: coarse node (i, j) sits on fine node (2i, 2j); every
@@ -444,16 +418,15 @@ static inline int tiles_of(const Lattice &L) {
     return L.tiles_x * ((L.ny + 3) / 4);
 }
 
-hipError_t launch_prec_change(int dtype, const void *a, const void *b, int64_t n,
+hipError_t launch_prec_change(int dtype, const void *a, const void *b, int64_t n, uint64_t limit,
                               unsigned long long *count, uint32_t *maxrel, hipStream_t s) {
-    int64_t want = (n + 255) / 256;
-    const int nb = (int)(want < 8192 ? (want > 0 ? want : 1) : 8192);
+    const int nb = prec_change_blocks(n, dtype == 0 ? 4 : 8);
     if (dtype == 0)
         hipLaunchKernelGGL((k_prec_change<float>), dim3(nb), dim3(256), 0, s, (const float *)a,
-                           (const float *)b, n, count, maxrel);
+                           (const float *)b, n, limit, count, maxrel);
     else
         hipLaunchKernelGGL((k_prec_change<double>), dim3(nb), dim3(256), 0, s, (const double *)a,
-                           (const double *)b, n, count, maxrel);
+                           (const double *)b, n, limit, count, maxrel);
     return hipGetLastError();
 }
 

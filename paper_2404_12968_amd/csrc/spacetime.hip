@@ -712,16 +712,17 @@ gabp_status gabp_st_residual(gabp_st_ctx *ctx, double *rel_residual, double *abs
         const int64_t n = (int64_t)gabp::st::kDeg * G.plane;
         hipLaunchKernelGGL(gabp::st::k_zero_u32, dim3(1), dim3(64), 0, ctx->stream,
                            ctx->flags + 4, 3);
-        const int pb = (int)std::min<int64_t>((n + 255) / 256, 4096);
+        const int pb = gabp::prec_change_blocks(n, ctx->dtype == GABP_F32 ? 4 : 8);
+        const uint64_t limit = (uint64_t)ctx->freeze_slots;
         if (ctx->dtype == GABP_F32)
             hipLaunchKernelGGL(gabp::st::k_prec_change<float>, dim3(pb), dim3(256), 0,
                                ctx->stream, (const float *)ctx->msg[ctx->cur],
-                               (const float *)ctx->msg[ctx->cur ^ 1], n,
+                               (const float *)ctx->msg[ctx->cur ^ 1], n, limit,
                                (unsigned long long *)(ctx->flags + 4), ctx->flags + 6);
         else
             hipLaunchKernelGGL(gabp::st::k_prec_change<double>, dim3(pb), dim3(256), 0,
                                ctx->stream, (const double *)ctx->msg[ctx->cur],
-                               (const double *)ctx->msg[ctx->cur ^ 1], n,
+                               (const double *)ctx->msg[ctx->cur ^ 1], n, limit,
                                (unsigned long long *)(ctx->flags + 4), ctx->flags + 6);
         ST_HIP(ctx, hipMemcpyAsync(ctx->host_flags, ctx->flags, 8 * sizeof(uint32_t),
                                    hipMemcpyDeviceToHost, ctx->stream));

@@ -37,10 +37,9 @@
 #include <math.h>
 #include <stdint.h>
 
-#include <type_traits>
-
 #include "lattice.h"
 #include "numerics.h"
+#include "prec_change.h"
 
 #pragma clang fp contract(off)
 
@@ -461,38 +460,24 @@ __global__ __launch_bounds__(256 * SL) void k_iter(Grid G, const T *__restrict__
     if (MODE != MODE_GAIN && bad) atomicCAS(diverged_at, 0u, it);
 }
 
-// Precision messages changed between two buffers: count of bitwise
-// differences (64-bit) and the largest relative change |a - b| / max(|a|,
-// |b|) as float bits (non-negative floats order like their bit patterns).
+// The freeze test (prec_change.h); a non-finite element counts as an infinite
+// change, and so does one whose two values are zeros of different sign.
+struct StRel {
+    __device__ __forceinline__ static float of(double u, double v) {
+        const double den = fmax(fabs(u), fabs(v));
+        const float r = den > 0.0 ? (float)(fabs(u - v) / den) : INFINITY;
+        return isnan(r) ? INFINITY : r;
+    }
+};
+
 template <typename T>
 __global__ __launch_bounds__(256) void k_prec_change(const T *__restrict__ a,
                                                      const T *__restrict__ b, int64_t n,
+                                                     uint64_t limit,
                                                      unsigned long long *__restrict__ count,
                                                      uint32_t *__restrict__ maxrel_bits) {
-    uint32_t cnt = 0;
-    float mx = 0.0f;
-    for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n;
-         k += (int64_t)gridDim.x * 256) {
-        const T u = a[k], v = b[k];
-        using U = typename std::conditional<sizeof(T) == 4, uint32_t, uint64_t>::type;
-        U ub, vb;
-        __builtin_memcpy(&ub, &u, sizeof(T));
-        __builtin_memcpy(&vb, &v, sizeof(T));
-        if (ub != vb) {
-            ++cnt;
-            const double den = fmax(fabs((double)u), fabs((double)v));
-            const float r = den > 0.0 ? (float)(fabs((double)u - (double)v) / den) : INFINITY;
-            mx = fmaxf(mx, isnan(r) ? INFINITY : r);
-        }
-    }
-    for (int o = 32; o >= 1; o >>= 1) {
-        cnt += __shfl_xor(cnt, o, 64);
-        mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-    }
-    if ((threadIdx.x & 63u) == 0u && cnt != 0u) {
-        atomicAdd(count, (unsigned long long)cnt);
-        atomicMax(maxrel_bits, __float_as_uint(mx));
-    }
+    prec_change_wave<T, StRel>(a, b, n, (int)(blockIdx.x * 4 + (threadIdx.x >> 6)),
+                               (int)gridDim.x * 4, limit, count, maxrel_bits);
 }
 
 }  // namespace st
