@@ -236,7 +236,7 @@ __global__ __launch_bounds__(256) void k_upsample(const double *__restrict__ coa
 // messages zero, information messages th_{i->j} = -(Q_ij/c) mu_i, so the
 // beliefs start at mu + (b - A mu) / diag(A) (the fixed point when mu is the
 // posterior mean).  The entries Q_ij/c are those the iteration uses.
-template <typename T, bool PX, bool PY>
+template <typename T>
 __global__ __launch_bounds__(256) void k_warm_init(Grid G, const double *__restrict__ mu,
                                                    T *__restrict__ m) {
     const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -248,13 +248,16 @@ __global__ __launch_bounds__(256) void k_warm_init(Grid G, const double *__restr
     const int kind = slice_kind(G, t);
     const T pq_same[3] = {(T)G.blk[kind][0], (T)G.blk[kind][1], (T)G.blk[kind][2]};
     const T pq_cross[3] = {(T)G.blk[3][0], (T)G.blk[3][1], (T)G.blk[3][2]};
-    const T gi = (T)g_at<PX, PY>(G, x, y);
+    const T gi = (T)(axis_g(x, G.nx, G.bcx) + axis_g(y, G.ny, G.bcy));
     const T mi = (T)mu[k];
     for (int d = 0; d < kDeg; ++d) {
         int xn, yn, tn;
-        const bool ok = nbr_at<PX, PY>(G, d, x, y, t, xn, yn, tn);
+        const bool ok = nbr(G, x, y, t, d, xn, yn, tn);
         T th = (T)0;
-        if (ok) th = -(q_dir<T, false, PX, PY>(G, d, x, y, t, gi, pq_same, pq_cross) * mi);
+        if (ok) {
+            const T gj = (T)(axis_g(xn, G.nx, G.bcx) + axis_g(yn, G.ny, G.bcy));
+            th = -(q_dir<T>(G, d, gi, gj, pq_same, pq_cross) * mi);
+        }
         (m + (size_t)d * G.plane)[i] = (T)0;
         (m + (size_t)(kDeg + d) * G.plane)[i] = th;
     }
@@ -426,43 +429,13 @@ gabp_status st_sync(gabp_st_ctx *ctx) {
     return GABP_OK;
 }
 
-// One iteration of a mode: the information-only iteration in one launch
-// over every tile; the others as the interior launch (tiles of the hole on
-// slices 1 .. nt - 2), then the boundary launch.
-template <typename T, int MODE, int SL, bool PX, bool PY>
-void launch_parts(const Grid &G, const void *in, void *out, void *gain, const void *aw,
-                  const void *bw, T eta, uint32_t *flags, uint32_t it, hipStream_t s) {
-    using namespace gabp::st;
-    if constexpr (MODE == MODE_THETA) {
-        const unsigned n = (unsigned)(G.tiles_x * G.tiles_y * ((G.nt + SL - 1) / SL));
-        hipLaunchKernelGGL((k_iter<T, MODE, PX, PY, SL, PART_ALL>), dim3(n), dim3(256 * SL), 0, s,
-                           G, (const T *)in, (T *)out, (T *)gain, (const T *)aw, (const T *)bw,
-                           eta, flags, it);
-        return;
-    } else {
-        const gabp::TileRange h = st_hole(G);
-        if (!h.empty() && G.nt >= 3) {
-            const unsigned n = (unsigned)(h.hole_count() * ((G.nt - 2 + SL - 1) / SL));
-            hipLaunchKernelGGL((k_iter<T, MODE, PX, PY, SL, PART_INTERIOR>), dim3(n), dim3(256 * SL),
-                               0, s, G, (const T *)in, (T *)out, (T *)gain, (const T *)aw,
-                               (const T *)bw, eta, flags, it);
-        }
-        const unsigned nb = (unsigned)st_boundary_count(G);
-        if (nb > 0)
-            hipLaunchKernelGGL((k_iter<T, MODE, PX, PY, 1, PART_BOUNDARY>), dim3(nb), dim3(256), 0, s,
-                               G, (const T *)in, (T *)out, (T *)gain, (const T *)aw, (const T *)bw,
-                               eta, flags, it);
-    }
-}
-
 template <typename T, int MODE, int SL>
 void launch_mode(const Grid &G, const void *in, void *out, void *gain, const void *aw,
                  const void *bw, T eta, uint32_t *flags, uint32_t it, hipStream_t s) {
-    const bool px = G.bcx == GABP_BC_PERIODIC, py = G.bcy == GABP_BC_PERIODIC;
-    if (px && py) launch_parts<T, MODE, SL, true, true>(G, in, out, gain, aw, bw, eta, flags, it, s);
-    else if (px) launch_parts<T, MODE, SL, true, false>(G, in, out, gain, aw, bw, eta, flags, it, s);
-    else if (py) launch_parts<T, MODE, SL, false, true>(G, in, out, gain, aw, bw, eta, flags, it, s);
-    else launch_parts<T, MODE, SL, false, false>(G, in, out, gain, aw, bw, eta, flags, it, s);
+    const unsigned n = (unsigned)(G.tiles_x * G.tiles_y * ((G.nt + SL - 1) / SL));
+    hipLaunchKernelGGL((gabp::st::k_iter<T, MODE, SL>), dim3(n), dim3(256 * SL), 0, s, G,
+                       (const T *)in, (T *)out, (T *)gain, (const T *)aw, (const T *)bw, eta,
+                       flags, it);
 }
 
 // mode's kernel; the information-only one covers theta_slices slices per
@@ -801,23 +774,16 @@ gabp_status gabp_st_warm_init(gabp_st_ctx *ctx, const double *mean) {
     if (!mean) return st_fail(ctx, GABP_E_INVALID, "mean is NULL");
     if (ctx->diverged_at != 0) return st_fail(ctx, GABP_E_DIVERGED, "the run has diverged");
     const Grid &G = ctx->G;
-    const bool px = G.bcx == GABP_BC_PERIODIC, py = G.bcy == GABP_BC_PERIODIC;
     const dim3 grid(node_blocks(G)), block(256);
     auto go = [&](auto kern, auto *buf) {
         hipLaunchKernelGGL(kern, grid, block, 0, ctx->stream, G, mean, buf);
     };
     if (ctx->dtype == GABP_F32) {
         float *m = (float *)ctx->msg[ctx->cur];
-        if (px && py) go(gabp::st::k_warm_init<float, true, true>, m);
-        else if (px) go(gabp::st::k_warm_init<float, true, false>, m);
-        else if (py) go(gabp::st::k_warm_init<float, false, true>, m);
-        else go(gabp::st::k_warm_init<float, false, false>, m);
+        go(gabp::st::k_warm_init<float>, m);
     } else {
         double *m = (double *)ctx->msg[ctx->cur];
-        if (px && py) go(gabp::st::k_warm_init<double, true, true>, m);
-        else if (px) go(gabp::st::k_warm_init<double, true, false>, m);
-        else if (py) go(gabp::st::k_warm_init<double, false, true>, m);
-        else go(gabp::st::k_warm_init<double, false, false>, m);
+        go(gabp::st::k_warm_init<double>, m);
     }
     ST_HIP(ctx, hipGetLastError());
     ctx->frozen = false;

@@ -28,9 +28,9 @@
 // plane index is n * slice + y * pitch + x with slice = pitch * ny.
 //
 // Launch shape.  A workgroup of 64 x 4 threads per slice owns one 64 x 4 tile
-// of one slice (or of SL consecutive slices); the workgroup order (wg_tile)
-// keeps the tiles that share halo rows and slices on one XCD at nearly the
-// same time.
+// of one slice (or of SL consecutive slices), a row to a wave; the workgroup
+// order (wg_tile) keeps the tiles that share halo rows and slices on one XCD at
+// nearly the same time.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -135,89 +135,57 @@ __device__ __forceinline__ T q_over_c(const Grid &G, int d, int kind, T gi, int 
 //   g = -(Q_ij/c)/Lam_c, new (g Q_ij/c, g th_c), damped with the previous
 //   outgoing message (Appendix "Re-weighted message updates"; Section
 //   "Update Damping").
-// INTERIOR: every neighbour exists (radius-2 spatial halo inside the grid, a
-// slice on either side) and needs no test.  Otherwise the code stays
-// branch-free: a missing neighbour's address is clamped to the node itself,
-// its message is read as zero, and its outgoing slot is written as zero.
+//
+// Boundaries cost no masks on the incoming messages: every coordinate wraps,
+// on any axis.  On a periodic axis that is the neighbour; on another one the
+// node reached lies at the far end, and its message in the opposite
+// direction leaves the grid there, a slot that is always zero.  A wave is one
+// row of one slice, so that the rows and slices reached are scalars and only
+// the five column offsets are per lane (Reach).  What remains of the boundary
+// is whether an outgoing edge exists and the neighbour counts in Q_ij; waves
+// whose edges all exist (`inner`, uniform) skip both.
 // --------------------------------------------------------------------------
-// v in [-2, n + 1] wrapped onto [0, n) without branches
-__device__ __forceinline__ int wrap(int v, int n) {
-    return v + n * ((int)(v < 0) - (int)(v >= n));
+__device__ __forceinline__ int wrap(int v, int n) {   // v in [-2, n + 1]
+    v = v < 0 ? v + n : (v >= n ? v - n : v);
+    return min(max(v, 0), n - 1);                     // n = 1: two steps wrap twice
 }
 
-// Boundary handling is compile-time: PX / PY say whether an axis is periodic.
-template <bool PX, bool PY>
-__device__ __forceinline__ bool nbr_at(const Grid &G, int d, int x, int y, int t, int &xn,
-                                       int &yn, int &tn) {
-    xn = x + sdx(d);
-    yn = y + sdy(d);
-    tn = t + sdt(d);
-    if (PX && sdx(d) != 0) xn = wrap(xn, G.nx);
-    if (PY && sdy(d) != 0) yn = wrap(yn, G.ny);
-    bool ok = (unsigned)tn < (unsigned)G.nt;
-    if (!PX) ok = ok && (unsigned)xn < (unsigned)G.nx;
-    if (!PY) ok = ok && (unsigned)yn < (unsigned)G.ny;
-    return ok;
+// What lies `bytes` behind a wave-uniform address.  With a 32-bit offset an
+// access takes the address from scalar registers and one register per lane, and
+// needs no 64-bit arithmetic.
+template <typename T>
+__device__ __forceinline__ T *behind(T *row, uint32_t bytes) {
+    return (T *)((char *)row + bytes);
+}
+template <typename T>
+__device__ __forceinline__ const T *behind(const T *row, uint32_t bytes) {
+    return (const T *)((const char *)row + bytes);
 }
 
-template <bool PX, bool PY>
-__device__ __forceinline__ int g_at(const Grid &G, int x, int y) {
-    return (PX ? 2 : (int)(x > 0) + (int)(x < G.nx - 1)) + (PY ? 2 : (int)(y > 0) + (int)(y < G.ny - 1));
-}
-
-// Plane index of neighbour d of (x, y, t) and whether it exists (a missing
-// neighbour's index is the node's own, so every load stays in bounds).
-template <bool INTERIOR, bool PX, bool PY>
-__device__ __forceinline__ uint32_t nbr_index(const Grid &G, int d, int x, int y, int t,
-                                              bool &ok) {
-    int xn, yn, tn;
-    if (INTERIOR) {
-        xn = x + sdx(d);
-        yn = y + sdy(d);
-        tn = t + sdt(d);
-        ok = true;
-    } else {
-        ok = nbr_at<PX, PY>(G, d, x, y, t, xn, yn, tn);
-        xn = ok ? xn : x;
-        yn = ok ? yn : y;
-        tn = ok ? tn : t;
-    }
-    return (uint32_t)tn * (uint32_t)G.slice + (uint32_t)(yn * G.pitch + xn);
-}
-
-// Incoming messages of one component (0: precisions, 1: information), zero
-// where the sender does not exist; bit d of okm says whether it does.
-template <typename T, bool INTERIOR, bool PX, bool PY>
-__device__ __forceinline__ void gather_in(const Grid &G, const T *__restrict__ m, int comp, int x,
-                                          int y, int t, T *v, uint64_t &okm) {
-    okm = 0;
+struct Reach {
+    uint32_t row[3][5];   // element offset of row y + dy of slice t + dt, wrapped
+    int col[5];           // column x + dx, wrapped (per lane)
+    uint32_t at[5];       // its byte offset in a row
+    __device__ __forceinline__ Reach(const Grid &G, int x, int y, int t, uint32_t esize) {
 #pragma unroll
-    for (int d = 0; d < kDeg; ++d) {
-        bool ok;
-        const uint32_t j = nbr_index<INTERIOR, PX, PY>(G, d, x, y, t, ok);
-        const T val = (m + (size_t)(comp * kDeg + (d ^ 1)) * G.plane)[j];
-        v[d] = ok ? val : (T)0;
-        okm |= (uint64_t)ok << d;
-    }
-}
-
-// Both components at once (the full iteration): same values as two
-// gather_in calls.
-template <typename T, bool INTERIOR, bool PX, bool PY>
-__device__ __forceinline__ void gather_both(const Grid &G, const T *__restrict__ m, int x, int y,
-                                            int t, T *lv, T *tv, uint64_t &okm) {
-    okm = 0;
+        for (int k = 0; k < 5; ++k) {
+            col[k] = wrap(x + k - 2, G.nx);
+            at[k] = (uint32_t)col[k] * esize;
+            asm volatile("" : "+v"(at[k]));   // not a 64-bit index to the compiler
+        }
 #pragma unroll
-    for (int d = 0; d < kDeg; ++d) {
-        bool ok;
-        const uint32_t j = nbr_index<INTERIOR, PX, PY>(G, d, x, y, t, ok);
-        const T l = (m + (size_t)(d ^ 1) * G.plane)[j];
-        const T th = (m + (size_t)(kDeg + (d ^ 1)) * G.plane)[j];
-        lv[d] = ok ? l : (T)0;
-        tv[d] = ok ? th : (T)0;
-        okm |= (uint64_t)ok << d;
+        for (int q = 0; q < 3; ++q) {
+            const uint32_t s = (uint32_t)wrap(t + q - 1, G.nt) * (uint32_t)G.slice;
+#pragma unroll
+            for (int k = 0; k < 5; ++k) row[q][k] = s + (uint32_t)(wrap(y + k - 2, G.ny) * G.pitch);
+        }
     }
-}
+    // incoming message of direction d, plane at m
+    template <typename T>
+    __device__ __forceinline__ T in(const T *__restrict__ m, int d) const {
+        return *behind(m + row[sdt(d) + 1][sdy(d) + 2], at[sdx(d) + 2]);
+    }
+};
 
 // Belief parameter: a + c * sum_d v[d], summed in direction order.
 template <typename T>
@@ -228,17 +196,12 @@ __device__ __forceinline__ T belief(T a, const T *v, T c) {
     return fmadd(c, s, a);
 }
 
-// Q_ij / c for direction d (closed forms at the top of this file); gi is
-// the node's neighbour count, pq_same / pq_cross the slice's blocks.
-template <typename T, bool INTERIOR, bool PX, bool PY>
-__device__ __forceinline__ T q_dir(const Grid &G, int d, int x, int y, int t, T gi,
-                                   const T *pq_same, const T *pq_cross) {
-    T gj = (T)4;
-    if (!INTERIOR && scls(d) == 1) {
-        int xn, yn, tn;
-        (void)nbr_at<PX, PY>(G, d, x, y, t, xn, yn, tn);
-        gj = (T)g_at<PX, PY>(G, xn, yn);
-    }
+// Q_ij / c for direction d (closed forms at the top of this file); gi and gj
+// are the two nodes' neighbour counts (gj for one step only), pq_same /
+// pq_cross the slice's blocks.
+template <typename T>
+__device__ __forceinline__ T q_dir(const Grid &G, int d, T gi, T gj, const T *pq_same,
+                                   const T *pq_cross) {
     const T *pqr = d < 12 ? pq_same : pq_cross;
     T q;
     if (scls(d) == 0) q = pqr[0] + pqr[1] * gi + pqr[2] * (gi * gi + gi);
@@ -255,7 +218,7 @@ __device__ __forceinline__ T q_dir(const Grid &G, int d, int x, int y, int t, T 
 // g = -(Q_ij/c)/Lam_c are then stored once (MODE_GAIN) and the iteration
 // updates only the information messages (MODE_THETA):
 //   th_i = b_i + c sum_d th_{k->i},  out_d = (1 - eta) out_d + eta g_d (th_i - th_{j->i}).
-// All three modes share gather_in, belief and q_dir, so the information-only
+// All three modes share Reach, belief and q_dir, so the information-only
 // iteration is bitwise the full one's.  New messages are written with
 // non-temporal stores (nothing reads them in the same launch; 4-5 % faster)
 // and the gains, read once per iteration, are loaded non-temporally (4 %
@@ -264,69 +227,76 @@ __device__ __forceinline__ T q_dir(const Grid &G, int d, int x, int y, int t, T 
 // --------------------------------------------------------------------------
 enum { MODE_FULL = 0, MODE_GAIN = 1, MODE_THETA = 2 };
 
-template <typename T, int MODE, bool INTERIOR, bool PX, bool PY>
-__device__ __forceinline__ void st_node(const Grid &G, const T *__restrict__ m_in,
-                                        T *__restrict__ m_out, T *__restrict__ gain,
-                                        const T *__restrict__ aw, const T *__restrict__ bw,
-                                        T eta, const T *pq_same, const T *pq_cross, bool &bad,
-                                        int x, int y, int t) {
-    const uint32_t i = (uint32_t)t * (uint32_t)G.slice + (uint32_t)(y * G.pitch + x);
-    const T c = (T)G.c, keep = (T)1 - eta;
-    const T gi = INTERIOR ? (T)4 : (T)g_at<PX, PY>(G, x, y);
-    uint64_t okm;
-    if constexpr (MODE == MODE_FULL) {
-        T lin[kDeg], tin[kDeg];
-        // the gather at a raised wave priority (as the lattice kernels):
-        // full iteration 2.78 -> 2.63 ms at 512 x 512 x 64; the
-        // information-only iteration does not gain from it
-        __builtin_amdgcn_s_setprio(2);
-        gather_both<T, INTERIOR, PX, PY>(G, m_in, x, y, t, lin, tin, okm);
-        __builtin_amdgcn_s_setprio(0);
-        const T bl = belief(aw[i], lin, c);
-        const T bt = belief(bw[i], tin, c);
+// Edges of a node: INNER, every neighbour exists and has four in its slice.
+template <typename T, bool INNER>
+struct Edges {
+    const Grid &G;
+    const T *pq_same, *pq_cross;
+    int x, y, t;
+    T gi, gs[4];   // neighbour counts of the node and of its four axis neighbours
+    __device__ __forceinline__ Edges(const Grid &g, const Reach &R, const T *same, const T *cross,
+                                     int x_, int y_, int t_)
+        : G(g), pq_same(same), pq_cross(cross), x(x_), y(y_), t(t_) {
+        gi = INNER ? (T)4 : count(x, y);
 #pragma unroll
-        for (int d = 0; d < kDeg; ++d) {
-            const T q = q_dir<T, INTERIOR, PX, PY>(G, d, x, y, t, gi, pq_same, pq_cross);
+        for (int k = 0; k < 4; ++k)
+            gs[k] = INNER ? (T)4 : count(R.col[dir_dx(k) + 2], wrap(y + dir_dy(k), G.ny));
+    }
+    __device__ __forceinline__ T count(int xn, int yn) const {
+        return (T)(axis_g(xn, G.nx, G.bcx) + axis_g(yn, G.ny, G.bcy));
+    }
+    __device__ __forceinline__ T q(int d) const {
+        const int step = sdx(d) == 1 ? 0 : sdx(d) == -1 ? 1 : sdy(d) == 1 ? 2 : 3;
+        return q_dir<T>(G, d, gi, scls(d) == 1 ? gs[step] : (T)0, pq_same, pq_cross);
+    }
+    __device__ __forceinline__ bool ok(int d) const {
+        if (INNER) return true;
+        const bool px = G.bcx == BC_PERIODIC, py = G.bcy == BC_PERIODIC;
+        return (bool)((int)((unsigned)(t + sdt(d)) < (unsigned)G.nt) &
+                      ((int)py | (int)((unsigned)(y + sdy(d)) < (unsigned)G.ny)) &
+                      ((int)px | (int)((unsigned)(x + sdx(d)) < (unsigned)G.nx)));
+    }
+};
+
+// New messages of a node from its gathered incoming ones and its beliefs (bl
+// unused in MODE_THETA, bt and tin in MODE_GAIN).  The planes' addresses are
+// made again (`plane` is a copy the compiler cannot tell from another value)
+// rather than kept from the gather: 76 pairs of scalar registers spill.
+template <typename T, int MODE, bool INNER>
+__device__ __forceinline__ void st_out(const Edges<T, INNER> &E, int64_t plane, uint32_t rc, uint32_t xb,
+                                       const T *__restrict__ m_in, T *__restrict__ m_out,
+                                       T *__restrict__ gain, T eta, const T *lin, const T *tin,
+                                       T bl, T bt, bool &bad) {
+    const T keep = (T)1 - eta;
+    T z = (T)0;   // MODE_THETA: stays zero exactly when every new message is finite
+#pragma unroll
+    for (int d = 0; d < kDeg; ++d) {
+        const bool ok = E.ok(d);
+        const size_t at = (size_t)d * plane + rc, at2 = (size_t)(kDeg + d) * plane + rc;
+        if constexpr (MODE == MODE_FULL) {
+            const T q = E.q(d);
             const T lc = bl - lin[d];
             const T tc = bt - tin[d];
             const T g = edge_gain(q, lc);
-            const T ol = (m_in + (size_t)d * G.plane)[i];
-            const T ot = (m_in + (size_t)(kDeg + d) * G.plane)[i];
-            T dl = fmadd(eta, g * q, keep * ol);
-            T dt = fmadd(eta, g * tc, keep * ot);
-            const bool ok = INTERIOR || ((okm >> d) & 1u);
+            T dl = fmadd(eta, g * q, keep * *behind(m_in + at, xb));
+            T dt = fmadd(eta, g * tc, keep * *behind(m_in + at2, xb));
             bad |= ok && (!(lc > (T)0) || !isfinite(dl) || !isfinite(dt));
             dl = ok ? dl : (T)0;
             dt = ok ? dt : (T)0;
-            __builtin_nontemporal_store(dl, &(m_out + (size_t)d * G.plane)[i]);
-            __builtin_nontemporal_store(dt, &(m_out + (size_t)(kDeg + d) * G.plane)[i]);
-        }
-    } else if constexpr (MODE == MODE_GAIN) {
-        T lin[kDeg];
-        gather_in<T, INTERIOR, PX, PY>(G, m_in, 0, x, y, t, lin, okm);
-        const T bl = belief(aw[i], lin, c);
-#pragma unroll
-        for (int d = 0; d < kDeg; ++d) {
-            const T q = q_dir<T, INTERIOR, PX, PY>(G, d, x, y, t, gi, pq_same, pq_cross);
-            const T g = edge_gain(q, bl - lin[d]);
-            const bool ok = INTERIOR || ((okm >> d) & 1u);
-            (gain + (size_t)d * G.plane)[i] = ok ? g : (T)0;
-        }
-    } else {
-        T tin[kDeg];
-        gather_in<T, INTERIOR, PX, PY>(G, m_in, 1, x, y, t, tin, okm);
-        const T bt = belief(bw[i], tin, c);
-#pragma unroll
-        for (int d = 0; d < kDeg; ++d) {
-            const T g = __builtin_nontemporal_load(&(gain + (size_t)d * G.plane)[i]);
-            const T ot = (m_in + (size_t)(kDeg + d) * G.plane)[i];
-            T dt = fmadd(eta, g * (bt - tin[d]), keep * ot);
-            const bool ok = INTERIOR || ((okm >> d) & 1u);
-            bad |= ok && !isfinite(dt);
-            dt = ok ? dt : (T)0;
-            __builtin_nontemporal_store(dt, &(m_out + (size_t)(kDeg + d) * G.plane)[i]);
+            __builtin_nontemporal_store(dl, behind(m_out + at, xb));
+            __builtin_nontemporal_store(dt, behind(m_out + at2, xb));
+        } else if constexpr (MODE == MODE_GAIN) {
+            const T g = edge_gain(E.q(d), bl - lin[d]);
+            *behind(gain + at, xb) = ok ? g : (T)0;
+        } else {
+            // edges that do not exist: gain and previous message are zero
+            const T g = __builtin_nontemporal_load(behind(gain + at, xb));
+            const T dt = fmadd(eta, g * (bt - tin[d]), keep * *behind(m_in + at2, xb));
+            z = fmadd(dt, (T)0, z);
+            __builtin_nontemporal_store(dt, behind(m_out + at2, xb));
         }
     }
+    if (MODE == MODE_THETA) bad = !(z == (T)0);
 }
 
 // Workgroup -> (tile x, tile y, first slice).  A workgroup covers one 64 x 4
@@ -362,101 +332,63 @@ __device__ __forceinline__ void wg_tile(int b, int tiles_x, int tiles_y, int nt,
     t0 = sg * SL;
 }
 
-// Interior tiles of a slice grid (a halo of 2 inside the slice: every
-// in-slice and cross-slice neighbour exists and none wraps); with the first
-// and last slice excluded they are the tiles the interior kernel runs.
-__host__ __device__ inline TileRange st_hole(const Grid &G) {
-    return interior_tiles(G.nx, G.ny, 1, 4);
-}
-
-// Boundary tiles: every tile of the first and last slice, then the ring of
-// each slice between (all tiles when the hole is empty or nt < 3).
-__host__ __device__ inline int64_t st_boundary_count(const Grid &G) {
-    const TileRange h = st_hole(G);
-    const int64_t all = (int64_t)G.tiles_x * G.tiles_y;
-    if (h.empty() || G.nt < 3) return all * G.nt;
-    return 2 * all + (int64_t)(G.nt - 2) * h.ring_count();
-}
-
-__device__ __forceinline__ void st_boundary_tile(const Grid &G, int b, int &tx, int &ty, int &t) {
-    const TileRange h = st_hole(G);
-    const int all = G.tiles_x * G.tiles_y;
-    int tile;
-    if (h.empty() || G.nt < 3) {
-        t = b / all;
-        tile = b - t * all;
-    } else if (b < 2 * all) {
-        t = b < all ? 0 : G.nt - 1;
-        tile = b < all ? b : b - all;
-    } else {
-        const int ring = (int)h.ring_count();
-        const int q = (b - 2 * all) / ring;
-        t = 1 + q;
-        h.ring(b - 2 * all - q * ring, tx, ty);
-        return;
-    }
-    ty = tile / G.tiles_x;
-    tx = tile - ty * G.tiles_x;
-}
-
-// One launch of a mode over the grid or part of it: PART_ALL every tile
-// (interior tiles through the interior path, in one kernel), PART_INTERIOR
-// the interior tiles of slices 1 .. nt - 2 (compiled without the boundary
-// paths: fewer registers, more waves per SIMD), PART_BOUNDARY the other tiles
-// (one slice per workgroup); an iteration is then the two launches.  The
-// full iteration runs split (3.07 -> 2.78 ms per iteration at 512 x 512 x 64:
-// 96 instead of 121 VGPRs); the information-only one, already streaming
-// near the copy rate, runs whole (split, its boundary sweep costs more than
-// the occupancy gains: 1.47 -> 1.53 ms).  diverged_at[0] records the first
-// iteration whose launches met an invalid value; launches of later
-// iterations return at once (the launches of the iteration that met it
-// complete, so its output buffer holds that iteration).  MODE_GAIN passes
+// One launch of a mode over the grid, SL slices per workgroup.  Bound by memory
+// on large grids: 512 x 512 x 64 in FP32, 2.38 ms per full iteration (10.3 GB read and
+// written once at least: 4.3 TB/s; 2.64 ms when boundary tiles took a masked
+// path in a second launch) and 1.42 ms per information-only one (7.6 GB, 5.4 TB/s,
+// above what a device copy streams).  Small ones wait for loads and, in the
+// full iteration, instruction issue: 100 x 75 x 12 takes 25 us (35) and 12.5 us
+// (13.7).  112 VGPRs in FP32 (four waves per SIMD; at five it spills) and 64.
+// diverged_at[0]
+// records the first iteration whose launch met an invalid value; launches of
+// later iterations return at once (the launch of the iteration that met it
+// completes, so its output buffer holds that iteration).  MODE_GAIN passes
 // it = 0.
-enum { PART_ALL = 0, PART_INTERIOR = 1, PART_BOUNDARY = 2 };
-
-template <typename T, int MODE, bool PX, bool PY, int SL, int PART>
-__global__ __launch_bounds__(256 * SL) void k_iter(Grid G, const T *__restrict__ m_in,
-                                                   T *__restrict__ m_out, T *__restrict__ gain,
-                                                   const T *__restrict__ aw,
-                                                   const T *__restrict__ bw, T eta,
-                                                   uint32_t *__restrict__ diverged_at,
-                                                   uint32_t it) {
+template <typename T, int MODE, int SL>
+__global__ __launch_bounds__(256 * SL, sizeof(T) == 8 ? 2 : MODE == MODE_THETA ? 8 : 4) void k_iter(
+    Grid G, const T *__restrict__ m_in, T *__restrict__ m_out, T *__restrict__ gain,
+    const T *__restrict__ aw, const T *__restrict__ bw, T eta, uint32_t *__restrict__ diverged_at,
+    uint32_t it) {
     const uint32_t seen = *diverged_at;
     if (MODE != MODE_GAIN && seen != 0u && seen < it) return;
-    const int b = xcd_remap((int)blockIdx.x, (int)gridDim.x);
-    int tx, ty, t;
-    if (PART == PART_ALL) {
-        int t0;
-        wg_tile<SL>(b, G.tiles_x, G.tiles_y, G.nt, tx, ty, t0);
-        t = t0 + (int)(threadIdx.x >> 8);          // one slice per four waves
-        if (t >= G.nt) return;
-    } else if (PART == PART_INTERIOR) {
-        const TileRange h = st_hole(G);
-        int t0;
-        wg_tile<SL>(b, h.txb - h.txa + 1, h.tyb - h.tya + 1, G.nt - 2, tx, ty, t0);
-        tx += h.txa;
-        ty += h.tya;
-        t = 1 + t0 + (int)(threadIdx.x >> 8);      // one slice per four waves
-        if (t > G.nt - 2) return;
-    } else {
-        st_boundary_tile(G, b, tx, ty, t);
-    }
+    int tx, ty, t0;
+    wg_tile<SL>(xcd_remap((int)blockIdx.x, (int)gridDim.x), G.tiles_x, G.tiles_y, G.nt, tx, ty, t0);
+    // one row of one slice per wave
+    const int t = __builtin_amdgcn_readfirstlane(t0 + (int)(threadIdx.x >> 8));
+    const int y = __builtin_amdgcn_readfirstlane(ty * 4 + (int)((threadIdx.x >> 6) & 3u));
     const int x = tx * 64 + (int)(threadIdx.x & 63u);
-    const int y = ty * 4 + (int)((threadIdx.x >> 6) & 3u);
+    if (t >= G.nt || y >= G.ny || x >= G.nx) return;
     // the slice's blocks (uniform over the wave) in message precision
     const int kind = slice_kind(G, t);
     const T pq_same[3] = {(T)G.blk[kind][0], (T)G.blk[kind][1], (T)G.blk[kind][2]};
     const T pq_cross[3] = {(T)G.blk[3][0], (T)G.blk[3][1], (T)G.blk[3][2]};
-    const bool inner = PART == PART_INTERIOR ||
-                       (PART == PART_ALL && tx * 64 >= 2 && tx * 64 + 66 <= G.nx && ty * 4 >= 2 &&
-                        ty * 4 + 6 <= G.ny && t > 0 && t < G.nt - 1);
+    const bool inner = (G.bcx == BC_PERIODIC || (tx * 64 >= 2 && tx * 64 + 66 <= G.nx)) &&
+                       (G.bcy == BC_PERIODIC || (y >= 2 && y + 2 < G.ny)) && t > 0 && t < G.nt - 1;
+    const Reach R(G, x, y, t, (uint32_t)sizeof(T));
+    const uint32_t rc = R.row[1][2], xb = R.at[2];   // the node's own row and column
+    const T c = (T)G.c;
+    T lin[kDeg], tin[kDeg], bl = 0, bt = 0;
+    // the full iteration's gather at a raised wave priority (as the lattice
+    // kernels); the information-only iteration does not gain from it
+    if (MODE == MODE_FULL) __builtin_amdgcn_s_setprio(2);
+#pragma unroll
+    for (int d = 0; d < kDeg; ++d) {
+        if (MODE != MODE_THETA) lin[d] = R.in(m_in + (size_t)(d ^ 1) * G.plane, d);
+        if (MODE != MODE_GAIN) tin[d] = R.in(m_in + (size_t)(kDeg + (d ^ 1)) * G.plane, d);
+    }
+    if (MODE == MODE_FULL) __builtin_amdgcn_s_setprio(0);
+    if (MODE != MODE_THETA) bl = belief(*behind(aw + rc, xb), lin, c);
+    if (MODE != MODE_GAIN) bt = belief(*behind(bw + rc, xb), tin, c);
+    uint32_t pl = (uint32_t)G.plane;      // below 2^31 + 512
+    asm volatile("" : "+s"(pl));
+    const int64_t plane = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)pl);
     bool bad = false;
-    if (inner)
-        st_node<T, MODE, true, PX, PY>(G, m_in, m_out, gain, aw, bw, eta, pq_same, pq_cross, bad,
-                                       x, y, t);
-    else if (x < G.nx && y < G.ny)
-        st_node<T, MODE, false, PX, PY>(G, m_in, m_out, gain, aw, bw, eta, pq_same, pq_cross,
-                                        bad, x, y, t);
+    if (MODE == MODE_THETA || inner)
+        st_out<T, MODE, true>(Edges<T, true>(G, R, pq_same, pq_cross, x, y, t), plane, rc, xb, m_in,
+                              m_out, gain, eta, lin, tin, bl, bt, bad);
+    else
+        st_out<T, MODE, false>(Edges<T, false>(G, R, pq_same, pq_cross, x, y, t), plane, rc, xb, m_in,
+                               m_out, gain, eta, lin, tin, bl, bt, bad);
     if (MODE != MODE_GAIN && bad) atomicCAS(diverged_at, 0u, it);
 }
 
