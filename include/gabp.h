@@ -247,13 +247,14 @@ gabp_status gabp_autotune(gabp_ctx *ctx, int32_t trials, double damping, int32_t
 gabp_status gabp_set_graph(gabp_ctx *ctx, int32_t enable);
 
 /* Tile configuration of a context's iteration kernels, a tuning knob that
- * never changes results.  Until it is called, a context whose precision
- * messages have frozen runs several information-only iterations per launch
- * (how many, and on which tiles, follows from the lattice, the prior order and
- * the dtype), and the last iteration of each gabp_iterate call singly; after a
- * divergence inside such a launch the messages kept are those that
- * two-iteration launches keep; single iterations take one row per thread
- * unless the autotuner chose otherwise.  After it, launches are as set:
+ * never changes results.  Until it is called, a context runs several
+ * iterations per launch (how many, and on which tiles, follows from the
+ * lattice, the prior order and the dtype; from iteration 2 on), and the last
+ * iteration of each gabp_iterate call singly; after a divergence inside such a
+ * launch the messages kept are those that single iterations (before the
+ * precision messages froze) or two-iteration launches (after) keep; single
+ * iterations take one row per thread unless the autotuner chose otherwise.
+ * After it, launches are as set:
  * rows_per_thread (1, 2, 4 or 8): rows each thread
  * of a 64-wide, 256-thread tile walks, for the single-iteration kernels.
  * pair_rows: once the precision messages have frozen, gabp_iterate runs
@@ -334,7 +335,7 @@ gabp_status gabp_copy_coarse_messages(gabp_ctx *coarse, gabp_ctx *fine);
 /* Iteration kernels launched by this context so far (graph replays
  * included): one-iteration launches of the full update (full) and of the
  * information-only update once the precision messages froze (theta), and
- * two-iteration launches on independent tiles (pair_tiles) and by the
+ * launches of two or more iterations on independent tiles (pair_tiles) and by the
  * column-strip walker (pair_walk); see gabp_set_tile.  Any pointer may be
  * NULL.  Does not synchronise; counts launches issued, not completed. */
 gabp_status gabp_launch_counts(const gabp_ctx *ctx, int64_t *full, int64_t *theta,

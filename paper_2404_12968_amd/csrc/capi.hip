@@ -13,6 +13,7 @@
 #include <new>
 #include <string>
 
+#include "deep_full.h"
 #include "deep_tile.h"
 #include "gabp.h"
 #include "host_common.h"
@@ -40,6 +41,7 @@ std::string fmt(const char *f, double a = 0, double b = 0) {
 
 // Launches of one run of iterations (enqueue_iters), in this order.
 struct Launches {
+    int lead = 0;              // one-iteration launches before the others
     int deeps = 0, deep_iters = 0, pairs = 0, singles = 0;
     bool last_single = true;   // the last launch was a single iteration
     bool ref = false;          // the t = 2 reference change was taken
@@ -69,19 +71,20 @@ struct gabp_ctx {
     int rpt = 4;                   // rows per thread of the iteration kernel's tile, as set,
     bool rpt_set = false;          // autotuned or default; launch_rpt() is what is launched
     int pair = 0;                  // tile height of the two-iteration kernel, 0 = unused
-    bool deep = true;              // multi-iteration launches once frozen (until gabp_set_tile)
-    gabp::DeepPlan plan{0, 1};     // their region and iterations
+    bool deep = true;              // multi-iteration launches (until gabp_set_tile): region and
+    gabp::DeepPlan plan{0, 1};     // iterations of the information-only and of the full
+    gabp::DeepPlan plan_full{0, 1};  // iteration
     int cur = 0;                   // buffer holding the current messages m^iter
     // launches since the last flag read-back, one record per gabp_iterate
-    // call: it started at iteration `start` with buffer `buf`, ran `deeps`
-    // launches of `deep_iters` iterations in all (deep_part), `pairs`
-    // two-iteration launches, then `singles` one-iteration launches (each
-    // launch writes the other buffer).  A divergence found at the next
-    // read-back selects the buffer its launch wrote.
+    // call: it started at iteration `start` with buffer `buf`, ran `lead`
+    // one-iteration launches, `deeps` launches of `deep_iters` iterations in all
+    // (deep_part), `pairs` two-iteration launches, then `singles` one-iteration
+    // launches (each launch writes the other buffer).  A divergence found at
+    // the next read-back selects the buffer its launch wrote.
     struct LaunchRun {
         int64_t start;
-        int buf, deeps, deep_iters, pairs, singles;
-        bool tail_single;
+        int buf, lead, deeps, deep_iters, pairs, singles;
+        bool frozen, tail_single;
         double damping;
     };
     std::vector<LaunchRun> runs;
@@ -143,23 +146,32 @@ int deep_part(int n, int launches, int k) { return (int)((int64_t)n * k / launch
 
 // A multi-iteration launch met the divergence at iteration t.  Its input is
 // whole (it wrote the other buffer, and no later launch wrote), so the state
-// that two-iteration launches would have kept is made from it by single
+// that single launches (full iterations) or two-iteration launches
+// (information-only ones) would have kept is made from it by single
 // iterations, recording into a spare flag word, which is cleared before each
 // of them.
 gabp_status hold_deep(gabp_ctx *ctx, const gabp_ctx::LaunchRun &r, int64_t t) {
+    const int dt = ctx->dtype == GABP_F32 ? 0 : 1;
+    const int64_t start = r.start + r.lead;
     const int total = r.deep_iters + 2 * r.pairs + r.singles;
-    const int pairs = held_pairs(total, r.tail_single);
-    const int64_t want = held_after_run(r.start, 0, pairs, t).iter;
+    const int pairs = r.frozen ? held_pairs(total, r.tail_single) : 0;
+    const int64_t want = held_after_run(start, 0, pairs, t).iter;
     int k = 0;
-    while (r.start + deep_part(r.deep_iters, r.deeps, k + 1) < t) ++k;
-    int64_t it = r.start + deep_part(r.deep_iters, r.deeps, k);
-    int buf = r.buf ^ (k & 1);
+    while (start + deep_part(r.deep_iters, r.deeps, k + 1) < t) ++k;
+    int64_t it = start + deep_part(r.deep_iters, r.deeps, k);
+    int buf = r.buf ^ ((r.lead + k) & 1);
     for (; it < want; ++it, buf ^= 1) {
+        const void *in = ctx->msg[buf];
+        void *out = ctx->msg[buf ^ 1];
+        const uint32_t off = (uint32_t)(it + 1 - ctx->tbase);
         GABP_HIP(ctx, gabp::launch_set_u32(ctx->flags + 7, 0u, ctx->stream));
-        GABP_HIP(ctx, gabp::launch_iter_theta(ctx->dtype == GABP_F32 ? 0 : 1, 1, ctx->L,
-                                              ctx->msg[buf], ctx->msg[buf ^ 1], ctx->gain,
-                                              ctx->b_w, r.damping, ctx->flags + 7, ctx->flags + 3,
-                                              (uint32_t)(it + 1 - ctx->tbase), ctx->stream));
+        GABP_HIP(ctx, r.frozen
+                          ? gabp::launch_iter_theta(dt, 1, ctx->L, in, out, ctx->gain, ctx->b_w,
+                                                    r.damping, ctx->flags + 7, ctx->flags + 3, off,
+                                                    ctx->stream)
+                          : gabp::launch_iter(dt, 1, ctx->L, in, out, ctx->adiag_w, ctx->b_w,
+                                              r.damping, ctx->flags + 7, ctx->flags + 3, off,
+                                              ctx->stream));
     }
     GABP_HIP(ctx, hipStreamSynchronize(ctx->stream));
     ctx->iter = it;
@@ -186,14 +198,19 @@ gabp_status sync_flags(gabp_ctx *ctx, bool with_red) {
         // second iteration), in the buffer it wrote
         for (const auto &r : ctx->runs) {
             const int64_t rel = (int64_t)t - r.start;
-            if (rel < 1 || rel > r.deep_iters + 2 * (int64_t)r.pairs + r.singles) continue;
-            if (rel <= r.deep_iters) {
+            if (rel < 1 || rel > r.lead + r.deep_iters + 2 * (int64_t)r.pairs + r.singles) continue;
+            if (rel <= r.lead) {
+                ctx->cur = r.buf ^ (int)(rel & 1);
+                break;
+            }
+            if (rel <= r.lead + r.deep_iters) {
                 const gabp_status s1 = hold_deep(ctx, r, (int64_t)t);
                 if (s1 != GABP_OK) return s1;
                 break;
             }
-            const HeldState h = held_after_run(r.start + r.deep_iters, r.buf ^ (r.deeps & 1),
-                                               r.pairs, (int64_t)t);
+            const HeldState h = held_after_run(r.start + r.lead + r.deep_iters,
+                                               r.buf ^ ((r.lead + r.deeps) & 1), r.pairs,
+                                               (int64_t)t);
             ctx->iter = h.iter;
             ctx->cur = h.buf;
             break;
@@ -434,6 +451,8 @@ gabp_status gabp_create(const gabp_grid *grid, const gabp_stencil *stencil, cons
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess)
         cus = 256;
     ctx->plan = gabp::deep_plan(dtype == GABP_F32 ? 0 : 1, ctx->L.alpha, ctx->L.nx, ctx->L.ny, cus);
+    ctx->plan_full = gabp::deep_full_plan(dtype == GABP_F32 ? 0 : 1, ctx->L.alpha, ctx->L.nx,
+                                          ctx->L.ny, cus);
     {
         std::lock_guard<std::mutex> g(g_tune_mu);
         auto it = g_tune.find(tune_key(ctx));
@@ -464,11 +483,13 @@ namespace {
 
 // Issue n iterations on stream s, starting from iteration iter0 held in
 // buffer cur0, with iteration numbers relative to the device counter's value
-// tbase when they run.  Frozen contexts run several iterations per launch:
-// all of them, or with tail_single all but the last, which runs singly, so that
-// the two buffers end on m^{t-1} and m^t (the message-change statistic and the
-// freeze probe need that).  With a tile set by gabp_set_tile they run two per
-// launch; with tail_single the last one or two singly, else while two remain.
+// tbase when they run.  Several iterations run per launch, in full (from t = 2
+// on, whose change the first iterations record) as information-only: all but the
+// last, which runs singly, so that the two buffers end on m^{t-1} and m^t (the
+// message-change statistic and the freeze probe need that); frozen contexts
+// need that with tail_single only, else they run all so.  With a tile set by
+// gabp_set_tile, full iterations run singly and frozen contexts two per launch;
+// with tail_single the last one or two singly, else while two remain.
 // Touches no context state; reports the launches.
 gabp_status enqueue_iters(gabp_ctx *ctx, int32_t n, double damping, hipStream_t s, int64_t iter0,
                           int cur0, uint32_t tbase, bool tail_single, Launches &done) {
@@ -481,17 +502,26 @@ gabp_status enqueue_iters(gabp_ctx *ctx, int32_t n, double damping, hipStream_t 
     while (k < n) {
         const void *src = ctx->msg[cur];
         void *dst = ctx->msg[cur ^ 1];
-        const int32_t many = n - k - (tail_single ? 1 : 0);
-        if (ctx->frozen && ctx->deep && it >= 2 && many >= 2 && done.deeps == 0) {
-            done.deeps = (many + ctx->plan.S - 1) / ctx->plan.S;
+        const int32_t many = n - k - (tail_single || !ctx->frozen ? 1 : 0);
+        if (ctx->deep && it >= 2 && many >= 2 && done.deeps == 0) {
+            const gabp::DeepPlan &p = ctx->frozen ? ctx->plan : ctx->plan_full;
+            done.lead = done.singles;
+            done.singles = 0;
+            done.deeps = (many + p.S - 1) / p.S;
             done.deep_iters = many;
             for (int j = 0; j < done.deeps; ++j) {
                 const int i0 = deep_part(many, done.deeps, j);
                 const int len = deep_part(many, done.deeps, j + 1) - i0;
-                GABP_HIP(ctx, gabp::launch_iter_deep(dt, ctx->plan.region, len, ctx->L,
-                                                     ctx->msg[cur], ctx->msg[cur ^ 1], ctx->gain,
-                                                     ctx->b_w, damping, ctx->flags, ctx->flags + 3,
-                                                     (uint32_t)(it + i0 - tbase), s));
+                const uint32_t off = (uint32_t)(it + i0 - tbase);
+                GABP_HIP(ctx, ctx->frozen
+                                  ? gabp::launch_iter_deep(dt, p.region, len, ctx->L, ctx->msg[cur],
+                                                           ctx->msg[cur ^ 1], ctx->gain, ctx->b_w,
+                                                           damping, ctx->flags, ctx->flags + 3, off,
+                                                           s)
+                                  : gabp::launch_iter_deep_full(
+                                        dt, p.region, len, ctx->L, ctx->msg[cur],
+                                        ctx->msg[cur ^ 1], ctx->adiag_w, ctx->b_w, damping,
+                                        ctx->flags, ctx->flags + 3, off, s));
                 cur ^= 1;
             }
             it += many;
@@ -550,13 +580,13 @@ int64_t quantize_chunk(int64_t next, int64_t kmin) {
 // on a launch of several iterations leaves an older state than m^{t-1} in the
 // other buffer).
 void advance_state(gabp_ctx *ctx, int32_t n, double damping, bool tail_single, const Launches &d) {
-    ctx->runs.push_back({ctx->iter, ctx->cur, d.deeps, d.deep_iters, d.pairs, d.singles,
-                         tail_single, damping});
-    ctx->launches[ctx->frozen ? 1 : 0] += d.singles;
+    ctx->runs.push_back({ctx->iter, ctx->cur, d.lead, d.deeps, d.deep_iters, d.pairs, d.singles,
+                         ctx->frozen, tail_single, damping});
+    ctx->launches[ctx->frozen ? 1 : 0] += d.lead + d.singles;
     ctx->launches[ctx->pair >= 0 ? 2 : 3] += d.pairs;
     ctx->launches[2] += d.deeps;
     ctx->iter += n;
-    ctx->cur ^= (d.deeps + d.pairs + d.singles) & 1;
+    ctx->cur ^= (d.lead + d.deeps + d.pairs + d.singles) & 1;
     if (d.ref) ctx->have_ref = true;
     if (n > 0) ctx->prev_valid = d.last_single;
 }

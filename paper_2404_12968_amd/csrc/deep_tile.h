@@ -89,13 +89,17 @@ inline int64_t deep_tiles(int alpha, int nx, int ny, int rw, int rh, int S) {
     return (int64_t)((nx + tw - 1) / tw) * ((ny + th - 1) / th);
 }
 
-inline DeepPlan deep_plan(int dtype, int alpha, int nx, int ny, int cus) {
-    int n;
-    const DeepChoice *c = deep_choices(dtype, alpha, n);
+inline DeepPlan deep_pick(const DeepChoice *c, int n, int alpha, int nx, int ny, int cus) {
     for (int k = 0; k < n; ++k)
         for (int S = c[k].most; S >= c[k].least; --S)
             if (deep_tiles(alpha, nx, ny, c[k].rw, c[k].rh, S) <= cus) return {k, S};
     return {n - 1, c[n - 1].bulk};
+}
+
+inline DeepPlan deep_plan(int dtype, int alpha, int nx, int ny, int cus) {
+    int n;
+    const DeepChoice *c = deep_choices(dtype, alpha, n);
+    return deep_pick(c, n, alpha, nx, ny, cus);
 }
 
 // First of the S iterations (1-based) in which this thread computed an

@@ -37,6 +37,11 @@ hipError_t launch_iter_theta2(int dtype, int th, const Lattice &L, const void *m
 hipError_t launch_iter_deep(int dtype, int region, int S, const Lattice &L, const void *m_in,
                             void *m_out, const void *gain, const void *bw, double eta,
                             uint32_t *flag, const uint32_t *t_base, uint32_t t_off, hipStream_t s);
+// The same for full iterations (deep_full_plan, deep_full.h).
+hipError_t launch_iter_deep_full(int dtype, int region, int S, const Lattice &L, const void *m_in,
+                                 void *m_out, const void *adiag, const void *bw, double eta,
+                                 uint32_t *flag, const uint32_t *t_base, uint32_t t_off,
+                                 hipStream_t s);
 // The same two iterations by the column-strip walker: persistent workgroups
 // of rb waves march down 64-column strips in bands of rb rows (rb = 2, 4 or
 // 8 for FP32, 2 for FP64).  Bitwise equal to two launch_iter_theta calls.

@@ -22,6 +22,7 @@
 #include "lattice.h"
 #include "numerics.h"
 #include "iter_node.h"
+#include "deep_full.h"
 #include "deep_tile.h"
 #include "pair_tile.h"
 #include "walk_strip.h"
@@ -187,6 +188,14 @@ __global__ __launch_bounds__(64 * WAVES) void k_iter_theta2(Lattice L, TileRange
     if (bad1 || bad2) record_divergence(diverged_at, bad1 ? t + 1u : t + 2u);
 }
 
+// Record the earliest of a wave's invalid iterations (t + bad, bad != 0).
+__device__ __forceinline__ void record_first(int bad, uint32_t t, uint32_t *diverged_at) {
+    if (!__any(bad != 0)) return;
+    int first = bad != 0 ? bad : INT_MAX;
+    for (int k = 32; k >= 1; k >>= 1) first = min(first, __shfl_xor(first, k, 64));
+    if ((threadIdx.x & 63u) == 0u) record_divergence(diverged_at, t + (uint32_t)first);
+}
+
 // S iterations in one launch (deep_tile.h), one workgroup per tile in the strip
 // order of the other kernels.  As with two iterations per launch, only a
 // divergence recorded by an earlier launch stops it, so its input stays whole.
@@ -214,11 +223,35 @@ __global__ __launch_bounds__(1024) void k_iter_deep(Lattice L, int S, int cols, 
     else
         bad = deep_tile<T, ALPHA, RW, RH, 1024, false>(L, m_in, m_out, gain, bw, eta, S, tx, ty,
                                                        stop, lds);
-    if (__any(bad != 0)) {
-        int first = bad != 0 ? bad : INT_MAX;
-        for (int k = 32; k >= 1; k >>= 1) first = min(first, __shfl_xor(first, k, 64));
-        if ((threadIdx.x & 63u) == 0u) record_divergence(diverged_at, t + (uint32_t)first);
-    }
+    record_first(bad, t, diverged_at);
+}
+
+// S full iterations in one launch (deep_full.h), launched and stopped alike.
+template <typename T, int ALPHA, int RW, int RH, int NT, bool SPLIT>
+__global__ __launch_bounds__(NT) void k_iter_deep_full(Lattice L, int S, int cols, int rows,
+                                                       const T *__restrict__ m_in,
+                                                       T *__restrict__ m_out,
+                                                       const T *__restrict__ adiag,
+                                                       const T *__restrict__ bw, T eta,
+                                                       uint32_t *__restrict__ diverged_at,
+                                                       const uint32_t *__restrict__ t_base,
+                                                       uint32_t t_off) {
+    using Rg = DeepRegion<ALPHA, RW, RH>;
+    __shared__ T lds[deep_full_lds<ALPHA, RW, RH, SPLIT>()];
+    const uint32_t t = *t_base + t_off;           // the iteration the launch starts from
+    const uint32_t seen = *diverged_at;
+    const bool stop = seen != 0u && seen <= t;
+    int tx, ty;
+    strip_order(xcd_remap((int)blockIdx.x, (int)gridDim.x), cols, rows, tx, ty);
+    const int x0 = tx * Rg::tw(S) - Rg::halo(S), y0 = ty * Rg::th(S) - Rg::halo(S);
+    int bad;
+    if (x0 >= Rg::R && x0 + RW + Rg::R <= L.nx && y0 >= Rg::R && y0 + RH + Rg::R <= L.ny)
+        bad = deep_full_tile<T, ALPHA, RW, RH, NT, SPLIT, true>(L, m_in, m_out, adiag, bw, eta, S,
+                                                                tx, ty, stop, lds);
+    else
+        bad = deep_full_tile<T, ALPHA, RW, RH, NT, SPLIT, false>(L, m_in, m_out, adiag, bw, eta,
+                                                                 S, tx, ty, stop, lds);
+    record_first(bad, t, diverged_at);
 }
 
 // Column-strip walker (walk_strip.h): one workgroup per (strip, segment)
@@ -392,6 +425,39 @@ hipError_t launch_iter_deep(int dtype, int region, int S, const Lattice &L, cons
         else launch_deep_k<double, 1, 64, 32>(L, S, m_in, m_out, gain, bw, eta, flag, t_base, t_off, s);
     } else {
         launch_deep_k<double, 2, 32, 32>(L, S, m_in, m_out, gain, bw, eta, flag, t_base, t_off, s);
+    }
+    return hipGetLastError();
+}
+
+template <typename T, int ALPHA, int RW, int RH, int NT, bool SPLIT>
+static void launch_full_k(const Lattice &L, int S, const void *m_in, void *m_out,
+                          const void *adiag, const void *bw, double eta, uint32_t *flag,
+                          const uint32_t *t_base, uint32_t t_off, hipStream_t s) {
+    using Rg = DeepRegion<ALPHA, RW, RH>;
+    const int cols = (L.nx + Rg::tw(S) - 1) / Rg::tw(S), rows = (L.ny + Rg::th(S) - 1) / Rg::th(S);
+    hipLaunchKernelGGL((k_iter_deep_full<T, ALPHA, RW, RH, NT, SPLIT>),
+                       dim3((unsigned)(cols * rows)), dim3(NT), 0, s, L, S, cols, rows,
+                       (const T *)m_in, (T *)m_out, (const T *)adiag, (const T *)bw, (T)eta, flag,
+                       t_base, t_off);
+}
+
+hipError_t launch_iter_deep_full(int dtype, int region, int S, const Lattice &L, const void *m_in,
+                                 void *m_out, const void *adiag, const void *bw, double eta,
+                                 uint32_t *flag, const uint32_t *t_base, uint32_t t_off,
+                                 hipStream_t s) {
+    if (dtype == 0 && L.alpha == 1) {
+        if (region == 0) launch_full_k<float, 1, 32, 32, 1024, false>(L, S, m_in, m_out, adiag, bw, eta, flag, t_base, t_off, s);
+        else launch_full_k<float, 1, 64, 16, 1024, false>(L, S, m_in, m_out, adiag, bw, eta, flag, t_base, t_off, s);
+    } else if (dtype == 0) {
+        if (region == 0) launch_full_k<float, 2, 32, 32, 1024, false>(L, S, m_in, m_out, adiag, bw, eta, flag, t_base, t_off, s);
+        else launch_full_k<float, 2, 64, 16, 1024, false>(L, S, m_in, m_out, adiag, bw, eta, flag, t_base, t_off, s);
+    } else if (L.alpha == 1) {
+        if (region == 0) launch_full_k<double, 1, 24, 24, 576, false>(L, S, m_in, m_out, adiag, bw, eta, flag, t_base, t_off, s);
+        else if (region == 1) launch_full_k<double, 1, 32, 32, 1024, false>(L, S, m_in, m_out, adiag, bw, eta, flag, t_base, t_off, s);
+        else launch_full_k<double, 1, 64, 32, 1024, false>(L, S, m_in, m_out, adiag, bw, eta, flag, t_base, t_off, s);
+    } else {
+        if (region == 0) launch_full_k<double, 2, 32, 16, 512, false>(L, S, m_in, m_out, adiag, bw, eta, flag, t_base, t_off, s);
+        else launch_full_k<double, 2, 32, 24, 768, true>(L, S, m_in, m_out, adiag, bw, eta, flag, t_base, t_off, s);
     }
     return hipGetLastError();
 }

@@ -53,21 +53,29 @@ __device__ __forceinline__ void node_nbrs(const Lattice &L, int x, int y, uint32
     }
 }
 
-// Off-diagonal prior precision divided by c for direction d of node (x, y)
-// with l_i = ell(x, y) precomputed (closed forms in lattice.h).
+// Off-diagonal prior precision divided by c for direction d of a node with
+// l_i = li whose neighbour there has l_j = lj (closed forms in lattice.h; only
+// d < 4 of the 13-point stencil depends on them).
 template <typename T, int ALPHA>
-__device__ __forceinline__ T q_over_c(const Lattice &L, int d, T li, int xn, int yn) {
+__device__ __forceinline__ T q_over_c_ell(const Lattice &L, int d, T li, T lj) {
     T q;
     if (ALPHA == 1) {
         q = -(T)L.tau * (d < 2 ? (T)L.ihx2 : (T)L.ihy2);
     } else if (d < 4) {
-        q = -(T)L.tau * (li + ell<T>(L, xn, yn)) * (d < 2 ? (T)L.ihx2 : (T)L.ihy2);
+        q = -(T)L.tau * (li + lj) * (d < 2 ? (T)L.ihx2 : (T)L.ihy2);
     } else if (d < 8) {
         q = d < 6 ? (T)(L.tau * L.ihx2 * L.ihx2) : (T)(L.tau * L.ihy2 * L.ihy2);
     } else {
         q = (T)(2.0 * L.tau * L.ihx2 * L.ihy2);
     }
     return q * (T)L.inv_c;
+}
+
+// The same for node (x, y) with l_i = ell(x, y) precomputed and its neighbour
+// (xn, yn).
+template <typename T, int ALPHA>
+__device__ __forceinline__ T q_over_c(const Lattice &L, int d, T li, int xn, int yn) {
+    return q_over_c_ell<T, ALPHA>(L, d, li, ALPHA == 2 && d < 4 ? ell<T>(L, xn, yn) : (T)0);
 }
 
 // Gain of edge i -> j: g = -(Q_ij/c) / Lam_c.  The new message is
