@@ -63,7 +63,8 @@ struct gabp_ctx {
     double *bel64 = nullptr;       // FP64 belief precisions once frozen
     void *adiag_w = nullptr, *b_w = nullptr;
     double *partials = nullptr, *red = nullptr;
-    uint32_t *flags = nullptr;     // [0] diverged-at iteration, [1] input error,
+    uint32_t *flags = nullptr;     // [0] diverged-at iteration, [1] input error, [2] workgroups
+                                   // of the residual done,
                                    // [3] iteration counter of the launches, [4, 5] precision
                                    // messages changed by the last iteration (64-bit) and
                                    // [6] their largest relative change (float bits)
@@ -179,14 +180,9 @@ gabp_status hold_deep(gabp_ctx *ctx, const gabp_ctx::LaunchRun &r, int64_t t) {
     return GABP_OK;
 }
 
-// Copy the device flags (and reduction results) to the pinned mirror, wait,
-// and fold a recorded divergence into the host state.
-gabp_status sync_flags(gabp_ctx *ctx, bool with_red) {
-    GABP_HIP(ctx, hipMemcpyAsync(ctx->host->flags, ctx->flags, 8 * sizeof(uint32_t),
-                                 hipMemcpyDeviceToHost, ctx->stream));
-    if (with_red)
-        GABP_HIP(ctx, hipMemcpyAsync(ctx->host->red, ctx->red, 8 * sizeof(double),
-                                     hipMemcpyDeviceToHost, ctx->stream));
+// Wait until the pinned mirror's flags are written and fold a recorded divergence
+// into the host state.
+gabp_status fold_flags(gabp_ctx *ctx) {
     GABP_HIP(ctx, hipStreamSynchronize(ctx->stream));
     const uint32_t t = ctx->host->flags[0];
     if (t != 0u && !ctx->diverged) {
@@ -223,6 +219,17 @@ gabp_status sync_flags(gabp_ctx *ctx, bool with_red) {
                         "message); messages kept at iteration %.0f",
                         (double)ctx->diverged_at, (double)ctx->iter));
     return GABP_OK;
+}
+
+// Copy the device flags (and reduction results) to the pinned mirror, then
+// fold_flags.
+gabp_status sync_flags(gabp_ctx *ctx, bool with_red) {
+    GABP_HIP(ctx, hipMemcpyAsync(ctx->host->flags, ctx->flags, 8 * sizeof(uint32_t),
+                                 hipMemcpyDeviceToHost, ctx->stream));
+    if (with_red)
+        GABP_HIP(ctx, hipMemcpyAsync(ctx->host->red, ctx->red, 8 * sizeof(double),
+                                     hipMemcpyDeviceToHost, ctx->stream));
+    return fold_flags(ctx);
 }
 
 const void *cur_msgs(const gabp_ctx *ctx) { return ctx->msg[ctx->cur]; }
@@ -694,20 +701,19 @@ gabp_status gabp_residual(gabp_ctx *ctx, double *rel_residual, double *abs_resid
     // How many precision messages did the last iteration change, and by how
     // much at most?
     const bool probe = !ctx->frozen && ctx->prev_valid && ctx->iter >= 2;
-    if (probe) {
-        GABP_HIP(ctx, hipMemsetAsync(ctx->flags + 4, 0, 3 * sizeof(uint32_t), ctx->stream));
-        GABP_HIP(ctx, gabp::launch_prec_change(dt, ctx->msg[ctx->cur], ctx->msg[ctx->cur ^ 1],
-                                               (int64_t)ctx->L.deg * ctx->L.plane,
-                                               (uint64_t)ctx->freeze_slots,
-                                               (unsigned long long *)(ctx->flags + 4),
-                                               ctx->flags + 6, ctx->stream));
-    }
-    GABP_HIP(ctx, gabp::launch_post(dt, ctx->L, cur_msgs(ctx), ctx->adiag64, ctx->b64,
-                                    ctx->frozen ? ctx->bel64 : nullptr, ctx->mu64, nullptr,
-                                    nullptr, probe ? ctx->bel64 : nullptr, ctx->stream));
+    if (probe)
+        GABP_HIP(ctx, gabp::launch_post_probe(dt, ctx->L, cur_msgs(ctx), ctx->msg[ctx->cur ^ 1],
+                                              (uint64_t)ctx->freeze_slots, ctx->flags,
+                                              ctx->adiag64, ctx->b64, ctx->mu64, ctx->bel64,
+                                              ctx->stream));
+    else
+        GABP_HIP(ctx, gabp::launch_post(dt, ctx->L, cur_msgs(ctx), ctx->adiag64, ctx->b64,
+                                        ctx->frozen ? ctx->bel64 : nullptr, ctx->mu64, nullptr,
+                                        nullptr, nullptr, ctx->stream));
     GABP_HIP(ctx, gabp::launch_resid(ctx->L, ctx->mu64, ctx->adiag64, ctx->b64, ctx->partials,
-                                     kNumPartials, ctx->red, ctx->stream));
-    st = sync_flags(ctx, true);
+                                     kNumPartials, ctx->flags, ctx->host->red, ctx->host->flags,
+                                     ctx->stream));
+    st = fold_flags(ctx);
     if (st != GABP_OK) return st;
     uint64_t changed = 0;
     std::memcpy(&changed, ctx->host->flags + 4, sizeof changed);

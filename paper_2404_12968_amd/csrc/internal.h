@@ -55,21 +55,26 @@ hipError_t launch_set_u32(uint32_t *p, uint32_t v, hipStream_t s);
 hipError_t launch_add_u32(uint32_t *p, uint32_t k, hipStream_t s);
 hipError_t launch_gain(int dtype, const Lattice &L, const void *m, const void *adiag, void *gain,
                        hipStream_t s);
-// Precision-message change between buffers a and b (n elements): adds the
-// number of bitwise differing elements to *count and raises *maxrel (float
-// bits) to their largest relative change, or, past `limit` of them, leaves any
-// larger *count (prec_change.h).  The caller zeroes both first.
-hipError_t launch_prec_change(int dtype, const void *a, const void *b, int64_t n, uint64_t limit,
-                              unsigned long long *count, uint32_t *maxrel, hipStream_t s);
 // Marginals: bel64 != NULL selects the frozen-precision variant that reads
 // the belief precisions from bel64; otherwise bel_out (may be NULL) receives
 // them.
 hipError_t launch_post(int dtype, const Lattice &L, const void *m, const double *adiag64,
                        const double *b64, const double *bel64, double *mu_plane, double *mean,
                        double *var, double *bel_out, hipStream_t s);
+// Marginals with bel_out, and in the same launch the freeze test of m against
+// the iteration before (prec_change.h): adds the number of bitwise differing
+// precision messages to flags[4, 5] (64-bit) and raises flags[6] (float bits) to
+// their largest relative change, or, past `limit` of them, leaves any larger
+// number.  The three words are zero before.
+hipError_t launch_post_probe(int dtype, const Lattice &L, const void *m, const void *prev,
+                             uint64_t limit, uint32_t *flags, const double *adiag64,
+                             const double *b64, double *mu_plane, double *bel_out, hipStream_t s);
+// FP64 residual sums |r|^2, |b|^2 into the host's pinned h_red[0, 1], and the
+// eight flag words into its h_flags; clears flags[4..6].  flags[2] counts the
+// workgroups done and is zero before and after.
 hipError_t launch_resid(const Lattice &L, const double *mu, const double *adiag64,
-                        const double *b64, double *partials, int npart, double *out,
-                        hipStream_t s);
+                        const double *b64, double *partials, int npart, uint32_t *flags,
+                        double *h_red, uint32_t *h_flags, hipStream_t s);
 hipError_t launch_abs_change(int dtype, const void *a, const void *b, int64_t n,
                              double *partials, int npart, double *out, hipStream_t s);
 // Deterministic fold of point observations into FP64 node terms (obs.hip):

@@ -34,9 +34,22 @@ namespace gabp {
 // when given, contiguous mean/var arrays.  Once the precision messages have
 // frozen, Lam_i is a constant read from bel64 (FROZEN) and only the
 // information messages are read; bel_out records Lam_i for that phase.
+// Workgroups past the ntiles of the marginals take the freeze test (prec_change.h)
+// of m against `prev`, in the same launch: neither needs the other, and a launch
+// of its own takes 3 to 4 us before the precision messages settle.
 // --------------------------------------------------------------------------
+struct FreezeTest {
+    const void *prev;            // messages of the iteration before
+    int64_t n;                   // precision slots
+    uint64_t limit;
+    unsigned long long *count;
+    uint32_t *maxrel;
+    int blocks;
+};
+
 template <typename T, int ALPHA, bool FROZEN>
-__global__ __launch_bounds__(256) void k_post(Lattice L, const T *__restrict__ m,
+__global__ __launch_bounds__(256) void k_post(Lattice L, int ntiles, FreezeTest ft,
+                                              const T *__restrict__ m,
                                               const double *__restrict__ adiag64,
                                               const double *__restrict__ b64,
                                               const double *__restrict__ bel64,
@@ -44,7 +57,13 @@ __global__ __launch_bounds__(256) void k_post(Lattice L, const T *__restrict__ m
                                               double *__restrict__ mean,
                                               double *__restrict__ var,
                                               double *__restrict__ bel_out) {
-    const int tile = xcd_remap((int)blockIdx.x, (int)gridDim.x);
+    if (!FROZEN && (int)blockIdx.x >= ntiles) {
+        prec_change_wave<T, LatticeRel>(m, (const T *)ft.prev, ft.n,
+                                        ((int)blockIdx.x - ntiles) * 4 + (int)(threadIdx.x >> 6),
+                                        ft.blocks * 4, ft.limit, ft.count, ft.maxrel);
+        return;
+    }
+    const int tile = xcd_remap((int)blockIdx.x, ntiles);
     const int x = (tile % L.tiles_x) * 64 + (int)(threadIdx.x & 63u);
     const int y = (tile / L.tiles_x) * 4 + (int)(threadIdx.x >> 6);
     if (x >= L.nx || y >= L.ny) return;
@@ -63,15 +82,27 @@ __global__ __launch_bounds__(256) void k_post(Lattice L, const T *__restrict__ m
 // node's arithmetic (resid_accum) and the order of the sums (tile by tile)
 // are those of resid_node, so the r^2 and b^2 partials (wave64 butterfly,
 // then LDS across the four waves, into partials[g]) are deterministic and do
-// not depend on the staging.
+// not depend on the staging.  The workgroup that finishes last adds the partials
+// up, in the order of k_reduce, and reports to the host's pinned mirror: the sums,
+// and the context's flag words, whose freeze-test words it clears for the next
+// check.  A check of a small lattice was seven operations (clear, freeze test,
+// marginals, residual, reduction, two copies), 19 us of device time on 64 x 64
+// nodes and a gap after each; it is two launches of 10 us together.
 // --------------------------------------------------------------------------
 constexpr int kResidUnroll = 4;
+
+__device__ __forceinline__ double load_shared(const double *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 template <int ALPHA>
 __global__ __launch_bounds__(256) void k_resid(Lattice L, const double *__restrict__ mu,
                                                const double *__restrict__ adiag64,
                                                const double *__restrict__ b64,
-                                               double *__restrict__ partials, int ntiles) {
+                                               double *__restrict__ partials, int ntiles,
+                                               uint32_t *__restrict__ flags,
+                                               double *__restrict__ h_red,
+                                               uint32_t *__restrict__ h_flags) {
     constexpr int DEG = ALPHA == 1 ? 4 : 12;
     constexpr int R = ALPHA == 1 ? 1 : 2;
     constexpr int WX = 64 + 2 * R, WY = 4 + 2 * R, WN = WX * WY;
@@ -180,9 +211,34 @@ __global__ __launch_bounds__(256) void k_resid(Lattice L, const double *__restri
         sh[1][w] = bb;
     }
     __syncthreads();
+    __shared__ bool last;
     if (threadIdx.x == 0) {
         partials[2 * g] = (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]);
         partials[2 * g + 1] = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
+        // releases this workgroup's partials, acquires everyone's before it
+        last = __hip_atomic_fetch_add(flags + 2, 1u, __ATOMIC_ACQ_REL,
+                                      __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)nb - 1u;
+    }
+    __syncthreads();
+    if (!last) return;
+    rr = bb = 0.0;
+    for (int k = (int)threadIdx.x; k < nb; k += 256) {
+        rr += load_shared(partials + 2 * k);
+        bb += load_shared(partials + 2 * k + 1);
+    }
+    rr = wave_sum(rr);
+    bb = wave_sum(bb);
+    if ((threadIdx.x & 63u) == 0u) {
+        sh[0][w] = rr;
+        sh[1][w] = bb;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        h_red[0] = (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]);
+        h_red[1] = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
+        for (int k = 0; k < 8; ++k) h_flags[k] = flags[k];
+        flags[2] = 0;
+        flags[4] = flags[5] = flags[6] = 0;
     }
 }
 
@@ -303,16 +359,6 @@ __global__ __launch_bounds__(256) void k_msgs_set(Lattice L, T *__restrict__ m,
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_prec_change(const T *__restrict__ a,
-                                                     const T *__restrict__ b, int64_t n,
-                                                     uint64_t limit,
-                                                     unsigned long long *__restrict__ count,
-                                                     uint32_t *__restrict__ maxrel) {
-    prec_change_wave<T, LatticeRel>(a, b, n, (int)(blockIdx.x * 4 + (threadIdx.x >> 6)),
-                                    (int)gridDim.x * 4, limit, count, maxrel);
-}
-
 // Multigrid transfer: coarse node (i, j) sits on fine node (2i, 2j); every
 // fine node takes the bilinear interpolation of the coarse mean (wrapping on
 // periodic axes, clamped at the end of others) into channel 0 of a
@@ -418,43 +464,55 @@ static inline int tiles_of(const Lattice &L) {
     return L.tiles_x * ((L.ny + 3) / 4);
 }
 
-hipError_t launch_prec_change(int dtype, const void *a, const void *b, int64_t n, uint64_t limit,
-                              unsigned long long *count, uint32_t *maxrel, hipStream_t s) {
-    const int nb = prec_change_blocks(n, dtype == 0 ? 4 : 8);
-    if (dtype == 0)
-        hipLaunchKernelGGL((k_prec_change<float>), dim3(nb), dim3(256), 0, s, (const float *)a,
-                           (const float *)b, n, limit, count, maxrel);
+template <typename T, int ALPHA>
+static void launch_post_a(bool frozen, const Lattice &L, const FreezeTest &ft, const void *m,
+                          const double *adiag64, const double *b64, const double *bel64,
+                          double *mu_plane, double *mean, double *var, double *bel_out,
+                          hipStream_t s) {
+    const int nt = tiles_of(L);
+    dim3 grid((unsigned)(nt + ft.blocks)), block(256);
+    if (frozen)
+        hipLaunchKernelGGL((k_post<T, ALPHA, true>), grid, block, 0, s, L, nt, ft, (const T *)m,
+                           adiag64, b64, bel64, mu_plane, mean, var, (double *)nullptr);
     else
-        hipLaunchKernelGGL((k_prec_change<double>), dim3(nb), dim3(256), 0, s, (const double *)a,
-                           (const double *)b, n, limit, count, maxrel);
-    return hipGetLastError();
+        hipLaunchKernelGGL((k_post<T, ALPHA, false>), grid, block, 0, s, L, nt, ft, (const T *)m,
+                           adiag64, b64, bel64, mu_plane, mean, var, bel_out);
 }
 
-template <typename T, int ALPHA>
-static void launch_post_a(bool frozen, const Lattice &L, const void *m, const double *adiag64,
-                          const double *b64, const double *bel64, double *mu_plane,
-                          double *mean, double *var, double *bel_out, hipStream_t s) {
-    dim3 grid(tiles_of(L)), block(256);
-    if (frozen)
-        hipLaunchKernelGGL((k_post<T, ALPHA, true>), grid, block, 0, s, L, (const T *)m, adiag64,
-                           b64, bel64, mu_plane, mean, var, (double *)nullptr);
-    else
-        hipLaunchKernelGGL((k_post<T, ALPHA, false>), grid, block, 0, s, L, (const T *)m, adiag64,
-                           b64, bel64, mu_plane, mean, var, bel_out);
+static hipError_t launch_post_ft(int dtype, const Lattice &L, const FreezeTest &ft, const void *m,
+                                 const double *adiag64, const double *b64, const double *bel64,
+                                 double *mu_plane, double *mean, double *var, double *bel_out,
+                                 hipStream_t s) {
+    const bool fr = bel64 != nullptr;
+    if (dtype == 0) {
+        if (L.alpha == 1) launch_post_a<float, 1>(fr, L, ft, m, adiag64, b64, bel64, mu_plane, mean, var, bel_out, s);
+        else launch_post_a<float, 2>(fr, L, ft, m, adiag64, b64, bel64, mu_plane, mean, var, bel_out, s);
+    } else {
+        if (L.alpha == 1) launch_post_a<double, 1>(fr, L, ft, m, adiag64, b64, bel64, mu_plane, mean, var, bel_out, s);
+        else launch_post_a<double, 2>(fr, L, ft, m, adiag64, b64, bel64, mu_plane, mean, var, bel_out, s);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_post(int dtype, const Lattice &L, const void *m, const double *adiag64,
                        const double *b64, const double *bel64, double *mu_plane, double *mean,
                        double *var, double *bel_out, hipStream_t s) {
-    const bool fr = bel64 != nullptr;
-    if (dtype == 0) {
-        if (L.alpha == 1) launch_post_a<float, 1>(fr, L, m, adiag64, b64, bel64, mu_plane, mean, var, bel_out, s);
-        else launch_post_a<float, 2>(fr, L, m, adiag64, b64, bel64, mu_plane, mean, var, bel_out, s);
-    } else {
-        if (L.alpha == 1) launch_post_a<double, 1>(fr, L, m, adiag64, b64, bel64, mu_plane, mean, var, bel_out, s);
-        else launch_post_a<double, 2>(fr, L, m, adiag64, b64, bel64, mu_plane, mean, var, bel_out, s);
-    }
-    return hipGetLastError();
+    return launch_post_ft(dtype, L, FreezeTest{}, m, adiag64, b64, bel64, mu_plane, mean, var,
+                          bel_out, s);
+}
+
+hipError_t launch_post_probe(int dtype, const Lattice &L, const void *m, const void *prev,
+                             uint64_t limit, uint32_t *flags, const double *adiag64,
+                             const double *b64, double *mu_plane, double *bel_out, hipStream_t s) {
+    FreezeTest ft{};
+    ft.prev = prev;
+    ft.n = (int64_t)L.deg * L.plane;
+    ft.limit = limit;
+    ft.count = (unsigned long long *)(flags + 4);
+    ft.maxrel = flags + 6;
+    ft.blocks = prec_change_blocks(ft.n, dtype == 0 ? 4 : 8);
+    return launch_post_ft(dtype, L, ft, m, adiag64, b64, nullptr, mu_plane, nullptr, nullptr,
+                          bel_out, s);
 }
 
 // Workgroups of the residual kernel that are resident at once on the current
@@ -479,19 +537,18 @@ static int resident_resid_blocks(int alpha) {
 }
 
 hipError_t launch_resid(const Lattice &L, const double *mu, const double *adiag64,
-                        const double *b64, double *partials, int npart, double *out,
-                        hipStream_t s) {
+                        const double *b64, double *partials, int npart, uint32_t *flags,
+                        double *h_red, uint32_t *h_flags, hipStream_t s) {
     const int nt = tiles_of(L);
     int nb = nt < npart ? nt : npart;
     const int resident = resident_resid_blocks(L.alpha);
     if (resident > 0 && resident < nb) nb = resident;
     if (L.alpha == 1)
         hipLaunchKernelGGL((k_resid<1>), dim3(nb), dim3(256), 0, s, L, mu, adiag64, b64, partials,
-                           nt);
+                           nt, flags, h_red, h_flags);
     else
         hipLaunchKernelGGL((k_resid<2>), dim3(nb), dim3(256), 0, s, L, mu, adiag64, b64, partials,
-                           nt);
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(256), 0, s, (const double *)partials, nb, out);
+                           nt, flags, h_red, h_flags);
     return hipGetLastError();
 }
 
