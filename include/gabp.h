@@ -149,9 +149,9 @@ gabp_status gabp_iterate(gabp_ctx *ctx, int32_t n_iters, double damping);
  * iterations until the precision messages froze, then after half the
  * iterations the observed geometric rate predicts to rel_tol (at least
  * |check_every|, at most 2000; with graphs on, rounded down to
- * |check_every| * 2^j).  Each chunk of iterations is recorded once as a
- * hipGraph (per chunk length, starting buffer, phase, tile shape and
- * damping) and replayed (see gabp_set_graph).  Once the precision messages
+ * |check_every| * 2^j).  With a tile set (gabp_set_tile) each chunk of
+ * iterations is recorded once as a hipGraph (per chunk length, starting buffer,
+ * phase, tile shape and damping) and replayed (see gabp_set_graph).  Once the precision messages
  * froze, a chunk may end on a two-iteration launch, so that afterwards the
  * two buffers need not hold consecutive iterations: gabp_message_change then
  * returns INVALID until gabp_iterate has run.  iters_done (total iterations
@@ -238,11 +238,13 @@ gabp_status gabp_autotune(gabp_ctx *ctx, int32_t trials, double damping, int32_t
 
 /* Chunk graphs of gabp_solve and gabp_solve_early_stop (Alg. 2, Iterate MP
  * Until Convergence: chunks of iterations between checks): enable != 0
- * (default) records each chunk of at least 2 iterations, once the context has
- * run 2 iterations, as a hipGraph on an internal stream and replays it on the
- * context's stream (iteration numbers come from a device counter the graph
- * advances); 0 launches every kernel directly and drops recorded graphs.
- * Results are bitwise identical either way.  gabp_iterate always launches
+ * (default) records, on a context with a tile set (gabp_set_tile), each chunk
+ * of at least 2 iterations, once the context has run 2 iterations, as a hipGraph
+ * on an internal stream and replays it on the context's stream (iteration
+ * numbers come from a device counter the graph advances); launches of several
+ * iterations, the default, are issued one by one.  0 launches every kernel
+ * directly and drops recorded graphs.  Results are bitwise identical either
+ * way; check intervals are rounded as gabp_solve says.  gabp_iterate always launches
  * directly. */
 gabp_status gabp_set_graph(gabp_ctx *ctx, int32_t enable);
 

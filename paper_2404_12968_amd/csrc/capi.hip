@@ -97,7 +97,7 @@ struct gabp_ctx {
     hipStream_t side = nullptr;
     struct Chunk {
         int32_t k;
-        int cur, frozen, rpt, pair, deep, tail;
+        int cur, frozen, rpt, pair, tail;
         double eta;
         hipGraphExec_t exec;
         Launches n;
@@ -611,10 +611,16 @@ gabp_status check_iterate_args(gabp_ctx *ctx, int32_t n_iters, double damping) {
 // k iterations as one captured graph (recorded once per chunk length,
 // starting buffer, phase, tile shape and damping; replayed after), else
 // eagerly.  The graph ends by advancing the device iteration counter.
+// Launches of several iterations are issued one by one: they take 8 us and
+// more, so the host stays ahead of the device, while a graph's launch starts 20 us
+// later than a kernel's and every new chunk length is recorded first.  Replayed
+// against issued, whole solves: 64 x 64 FP64 (56 chunks of two launches) 3.37
+// and 2.07 ms, 261 x 187 2.24 and 1.68 ms, 2048^2 22.4 and 21.7 ms.  With a tile
+// set, a launch is one or two iterations, 3 us and up, and a chunk is replayed.
 gabp_status run_chunk(gabp_ctx *ctx, int32_t k, double damping, bool tail_single) {
     gabp_status st = check_iterate_args(ctx, k, damping);
     if (st != GABP_OK) return st;
-    if (!ctx->graphs || k < 2 || ctx->iter < 2) {
+    if (!ctx->graphs || ctx->deep || k < 2 || ctx->iter < 2) {
         Launches d;
         st = enqueue_iters(ctx, k, damping, ctx->stream, ctx->iter, ctx->cur, ctx->tbase,
                            tail_single, d);
@@ -629,7 +635,7 @@ gabp_status run_chunk(gabp_ctx *ctx, int32_t k, double damping, bool tail_single
     gabp_ctx::Chunk *c = nullptr;
     for (auto &e : ctx->chunks)
         if (e.k == k && e.cur == ctx->cur && e.frozen == (int)ctx->frozen && e.rpt == launch_rpt(ctx) &&
-            e.pair == ctx->pair && e.deep == (int)ctx->deep && e.tail == (int)tail_single &&
+            e.pair == ctx->pair && e.tail == (int)tail_single &&
             e.eta == damping)
             c = &e;
     if (!c) {
@@ -641,7 +647,7 @@ gabp_status run_chunk(gabp_ctx *ctx, int32_t k, double damping, bool tail_single
         if (!ctx->side)
             GABP_HIP(ctx, hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking));
         gabp_ctx::Chunk e{k,       ctx->cur, (int)ctx->frozen, launch_rpt(ctx), ctx->pair,
-                          (int)ctx->deep, (int)tail_single, damping, nullptr, Launches()};
+                          (int)tail_single, damping, nullptr, Launches()};
         GABP_HIP(ctx, hipStreamBeginCapture(ctx->side, hipStreamCaptureModeThreadLocal));
         // relative numbering: the counter holds the chunk's first iteration
         st = enqueue_iters(ctx, k, damping, ctx->side, ctx->iter, ctx->cur, (uint32_t)ctx->iter,
