@@ -360,13 +360,12 @@ const char *gabp_status_string(gabp_status status);
 
 /* ------------------------------------------------------------------------
  * Batched solving of many independent lattice problems of uneven sizes in
- * one workspace.  One iteration of the whole batch is one launch of a
- * persistent-grid kernel over a work list of (instance, tile) items of the
- * instances still running; instances that converge or diverge retire from
- * the list; each instance switches to the information-only iteration when
- * its precision messages freeze.  A chunk of check_every iterations plus the
- * per-instance FP64 check is captured in a hipGraph and replayed while the
- * running set is unchanged.  Every instance computes bitwise what a lone
+ * one workspace.  One launch runs several iterations of all running instances
+ * of one prior order and phase, over a work list of (instance, tile) items;
+ * instances that converge or diverge retire from the lists; each instance
+ * switches to the information-only iteration when its precision messages
+ * freeze.  The per-instance FP64 check after every chunk is three launches.
+ * Every instance computes bitwise what a lone
  * context with the same arguments computes.  The same damping applies to
  * every instance; c and the prior are per instance.  The batch orders its
  * work on an internal stream joined to opts->stream (NULL: the default

@@ -3,15 +3,14 @@
 //
 // Every instance keeps its own sender-indexed message planes and node planes
 // inside one workspace.  A device-resident instance table describes them.
-// One iteration of the whole batch is one launch of a persistent-grid kernel
-// that walks a work list of (instance, tile) items over the instances still
-// running: the launch boundary is the flooding barrier (every message of
-// iteration t must exist before any of t + 1 is computed), so no workgroup
-// ever waits on another.  Converged or diverged instances leave the work
-// list; each instance switches to the information-only iteration on its own
-// once its precision messages freeze.  A chunk of k iterations plus the
-// per-instance FP64 check is captured once in a hipGraph and replayed while
-// the set of running instances does not change.
+// The instances still running are grouped by prior order and phase (full or
+// information-only iteration).  One launch takes several iterations of a whole
+// group, over a work list of (instance, tile) items (deep_tile.h, deep_full.h);
+// the launch boundary is the flooding barrier, so no workgroup ever waits on
+// another.  Converged or diverged instances leave the work lists; each instance
+// switches to the information-only iteration on its own once its precision
+// messages freeze.  A check of all running instances is three launches that
+// report to pinned host memory.
 //
 // The per-node bodies are those of the single-lattice kernels (iter_node.h,
 // check_node.h): a batched instance computes bitwise what a lone context
@@ -27,11 +26,12 @@
 #include <vector>
 
 #include "check_node.h"
+#include "deep_full.h"
+#include "deep_tile.h"
 #include "gabp.h"
 #include "host_common.h"
 #include "internal.h"
 #include "iter_node.h"
-#include "pair_tile.h"
 #include "prec_change.h"
 #include "lattice.h"
 #include "numerics.h"
@@ -60,7 +60,8 @@ __device__ __forceinline__ int find_item(const int *__restrict__ prefix, int n, 
     return lo;
 }
 
-// One flooding iteration of every running instance.  Work item w maps to
+// One full iteration of every instance of a list, from its buffer `buf` to the
+// other, iteration number t.  Work item w maps to
 // instance act[a] and tile w - prefix[a] of that instance (64 x 4*RPT nodes);
 // each workgroup of the persistent grid takes one contiguous range of items,
 // so neighbouring tiles share a CU and its XCD's L2.
@@ -68,12 +69,9 @@ template <typename T, int RPT>
 __global__ __launch_bounds__(256) void k_batch_iter(const BatchInst *__restrict__ inst,
                                                     const int *__restrict__ act,
                                                     const int *__restrict__ prefix, int nact,
-                                                    int total, const int *__restrict__ frozen,
-                                                    const uint32_t *__restrict__ t_dev,
-                                                    int t_off, T eta,
+                                                    int total, int buf, uint32_t t, T eta,
                                                     uint32_t *__restrict__ diverged_at) {
     constexpr int TH = 4 * RPT;
-    const uint32_t t = *t_dev + (uint32_t)t_off;   // this iteration's number
     const int per = (total + (int)gridDim.x - 1) / (int)gridDim.x;
     const int w1 = min(total, ((int)blockIdx.x + 1) * per);
     for (int w = (int)blockIdx.x * per; w < w1; ++w) {
@@ -88,9 +86,8 @@ __global__ __launch_bounds__(256) void k_batch_iter(const BatchInst *__restrict_
         const int y0 = ty * TH + (int)(threadIdx.x >> 6);
         const bool interior = tx * 64 >= 2 && tx * 64 + 66 <= L.nx && ty * TH >= 2 &&
                               ty * TH + TH + 2 <= L.ny;
-        const T *m_in = (const T *)B.msg[(t - 1u) & 1u];
-        T *m_out = (T *)B.msg[t & 1u];
-        const bool fz = frozen[I] != 0;
+        const T *m_in = (const T *)B.msg[buf];
+        T *m_out = (T *)B.msg[buf ^ 1];
         bool bad = false;
         if (x < L.nx) {
 #pragma unroll 1
@@ -98,21 +95,11 @@ __global__ __launch_bounds__(256) void k_batch_iter(const BatchInst *__restrict_
                 const int y = y0 + 4 * k;
                 if (y >= L.ny) break;
                 if (L.alpha == 1) {
-                    if (fz) {
-                        if (interior) iter_theta_node<T, 1, true>(L, m_in, m_out, (const T *)B.gain, (const T *)B.b_w, eta, bad, x, y);
-                        else iter_theta_node<T, 1, false>(L, m_in, m_out, (const T *)B.gain, (const T *)B.b_w, eta, bad, x, y);
-                    } else {
-                        if (interior) iter_node<T, 1, true>(L, m_in, m_out, (const T *)B.adiag_w, (const T *)B.b_w, eta, bad, x, y);
-                        else iter_node<T, 1, false>(L, m_in, m_out, (const T *)B.adiag_w, (const T *)B.b_w, eta, bad, x, y);
-                    }
+                    if (interior) iter_node<T, 1, true>(L, m_in, m_out, (const T *)B.adiag_w, (const T *)B.b_w, eta, bad, x, y);
+                    else iter_node<T, 1, false>(L, m_in, m_out, (const T *)B.adiag_w, (const T *)B.b_w, eta, bad, x, y);
                 } else {
-                    if (fz) {
-                        if (interior) iter_theta_node<T, 2, true>(L, m_in, m_out, (const T *)B.gain, (const T *)B.b_w, eta, bad, x, y);
-                        else iter_theta_node<T, 2, false>(L, m_in, m_out, (const T *)B.gain, (const T *)B.b_w, eta, bad, x, y);
-                    } else {
-                        if (interior) iter_node<T, 2, true>(L, m_in, m_out, (const T *)B.adiag_w, (const T *)B.b_w, eta, bad, x, y);
-                        else iter_node<T, 2, false>(L, m_in, m_out, (const T *)B.adiag_w, (const T *)B.b_w, eta, bad, x, y);
-                    }
+                    if (interior) iter_node<T, 2, true>(L, m_in, m_out, (const T *)B.adiag_w, (const T *)B.b_w, eta, bad, x, y);
+                    else iter_node<T, 2, false>(L, m_in, m_out, (const T *)B.adiag_w, (const T *)B.b_w, eta, bad, x, y);
                 }
             }
         }
@@ -120,59 +107,112 @@ __global__ __launch_bounds__(256) void k_batch_iter(const BatchInst *__restrict_
     }
 }
 
-// Two information-only iterations of every frozen running instance with the
-// prior order ALPHA: one workgroup per work item, item w (XCD-remapped so
-// that each XCD takes a contiguous range) maps to instance act[a] and 64 x TH
-// tile w - prefix[a].  Launches come in couples: the first (second == 0)
-// reads the buffer of the state it starts from, iteration t, and writes the
-// other one; the second reads that one and writes back, so after a couple
-// each instance is in the buffer its iteration number selects, as after
-// single iterations.
-template <typename T, int ALPHA, int TH, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void k_batch_pair(const BatchInst *__restrict__ inst,
-                                                           const int *__restrict__ act,
-                                                           const int *__restrict__ prefix,
-                                                           int nact,
-                                                           const uint32_t *__restrict__ t_dev,
-                                                           int t_off, int second, T eta,
-                                                           uint32_t *__restrict__ diverged_at) {
-    __shared__ T lds[(ALPHA == 1 ? 4 : 12) * TH * 64];
+// Work item of a multi-iteration launch: the tile (tx, ty) of instance I, on the
+// tiles for S iterations of a region of RW x RH nodes; items are XCD-remapped so
+// that each XCD takes a contiguous range of them.
+template <int ALPHA, int RW, int RH>
+__device__ __forceinline__ const BatchInst &deep_item(const BatchInst *__restrict__ inst,
+                                                      const int *__restrict__ act,
+                                                      const int *__restrict__ prefix, int nact,
+                                                      int S, int &I, int &tx, int &ty,
+                                                      bool &inside) {
+    using Rg = DeepRegion<ALPHA, RW, RH>;
     const int w = xcd_remap((int)blockIdx.x, (int)gridDim.x);
     const int a = __builtin_amdgcn_readfirstlane(find_item(prefix, nact, w));
-    const int I = __builtin_amdgcn_readfirstlane(act[a]);
-    if (diverged_at[I] != 0u) return;   // waves that return leave the tile's barrier
-    const uint32_t t = *t_dev + (uint32_t)t_off;   // iteration the launch starts from
+    I = __builtin_amdgcn_readfirstlane(act[a]);
     const BatchInst &B = inst[I];
-    const Lattice L = B.L;
-    const int tile = w - prefix[a];
-    const int tx = tile % L.tiles_x, ty = tile / L.tiles_x;
-    const uint32_t own = t & 1u;
-    const T *m_in = (const T *)B.msg[second ? own ^ 1u : own];
-    T *m_out = (T *)B.msg[second ? own : own ^ 1u];
-    bool bad1 = false, bad2 = false;
-    // interior tiles on the path compiled without boundary code (uniform
-    // across the workgroup)
-    if (interior_tiles(L.nx, L.ny, ALPHA == 1 ? 1 : 2, TH).interior(tx, ty))
-        pair_tile<T, ALPHA, TH, WAVES, true>(L, m_in, m_out, (const T *)B.gain, (const T *)B.b_w,
-                                             eta, tx, ty, lds, bad1, bad2);
-    else
-        pair_tile<T, ALPHA, TH, WAVES, false>(L, m_in, m_out, (const T *)B.gain,
-                                              (const T *)B.b_w, eta, tx, ty, lds, bad1, bad2);
-    if (bad1 || bad2) record_divergence(&diverged_at[I], bad1 ? t + 1u : t + 2u);
+    const int cols = (B.L.nx + Rg::tw(S) - 1) / Rg::tw(S), tile = w - prefix[a];
+    tx = tile % cols;
+    ty = tile / cols;
+    const int x0 = tx * Rg::tw(S) - Rg::halo(S), y0 = ty * Rg::th(S) - Rg::halo(S);
+    inside = x0 >= Rg::R && x0 + RW + Rg::R <= B.L.nx && y0 >= Rg::R && y0 + RH + Rg::R <= B.L.ny;
+    return B;
 }
 
-// Marginals of every running instance (64 x 4 tiles), writing each
-// instance's FP64 mean plane; probe[I] asks for the belief precisions too.
+// n <= S information-only iterations of every instance of a list (frozen, prior
+// order ALPHA), from iteration t in its buffer `buf` to the other.
+// Ten iterations of the frozen instances were four launches of two and two single
+// ones, each with its own fill and drain; they are two launches of five.  24
+// instances of 64^2 to 400^2 (FP32, 400 iterations, checks included): 21.6 -> 12.8
+// ms, of which the information-only launches took 4.4 ms and take 3.6, the others
+// 7.9 and 2.7.
+template <typename T, int ALPHA, int RW, int RH>
+__global__ __launch_bounds__(1024) void k_batch_deep(const BatchInst *__restrict__ inst,
+                                                     const int *__restrict__ act,
+                                                     const int *__restrict__ prefix, int nact,
+                                                     int S, int n, int buf, uint32_t t, T eta,
+                                                     uint32_t *__restrict__ diverged_at) {
+    __shared__ T lds[DeepRegion<ALPHA, RW, RH>::kLds];
+    int I, tx, ty;
+    bool inside;
+    const BatchInst &B = deep_item<ALPHA, RW, RH>(inst, act, prefix, nact, S, I, tx, ty, inside);
+    const uint32_t seen = diverged_at[I];
+    const bool stop = seen != 0u && seen <= t;
+    const Lattice L = B.L;
+    const T *m_in = (const T *)B.msg[buf], *gain = (const T *)B.gain, *bw = (const T *)B.b_w;
+    T *m_out = (T *)B.msg[buf ^ 1];
+    int bad;
+    if (inside)
+        bad = deep_tile<T, ALPHA, RW, RH, 1024, true>(L, m_in, m_out, gain, bw, eta, S, n, tx, ty,
+                                                      stop, lds);
+    else
+        bad = deep_tile<T, ALPHA, RW, RH, 1024, false>(L, m_in, m_out, gain, bw, eta, S, n, tx, ty,
+                                                       stop, lds);
+    record_first(bad, t, &diverged_at[I]);
+}
+
+// The same for full iterations.
+template <typename T, int ALPHA, int RW, int RH, int NT, bool SPLIT>
+__global__ __launch_bounds__(NT) void k_batch_deep_full(const BatchInst *__restrict__ inst,
+                                                        const int *__restrict__ act,
+                                                        const int *__restrict__ prefix, int nact,
+                                                        int S, int n, int buf, uint32_t t, T eta,
+                                                        uint32_t *__restrict__ diverged_at) {
+    __shared__ T lds[deep_full_lds<ALPHA, RW, RH, SPLIT>()];
+    int I, tx, ty;
+    bool inside;
+    const BatchInst &B = deep_item<ALPHA, RW, RH>(inst, act, prefix, nact, S, I, tx, ty, inside);
+    const uint32_t seen = diverged_at[I];
+    const bool stop = seen != 0u && seen <= t;
+    const Lattice L = B.L;
+    const T *m_in = (const T *)B.msg[buf], *ad = (const T *)B.adiag_w, *bw = (const T *)B.b_w;
+    T *m_out = (T *)B.msg[buf ^ 1];
+    int bad;
+    if (inside)
+        bad = deep_full_tile<T, ALPHA, RW, RH, NT, SPLIT, true>(L, m_in, m_out, ad, bw, eta, S, n,
+                                                                tx, ty, stop, lds);
+    else
+        bad = deep_full_tile<T, ALPHA, RW, RH, NT, SPLIT, false>(L, m_in, m_out, ad, bw, eta, S, n,
+                                                                 tx, ty, stop, lds);
+    record_first(bad, t, &diverged_at[I]);
+}
+
+// Marginals of every running instance (64 x 4 tiles, the first `blocks`
+// workgroups), writing each instance's FP64 mean plane and, until its precision
+// messages freeze, its belief precisions.  kProbeBlocks further workgroups for
+// each instance of the list actu (running, not frozen) take its freeze test
+// (prec_change.h).  Both read buffer `buf`.
+constexpr int kProbeBlocks = 64;
 template <typename T>
 __global__ __launch_bounds__(256) void k_batch_post(const BatchInst *__restrict__ inst,
                                                     const int *__restrict__ act,
                                                     const int *__restrict__ prefix, int nact,
                                                     int total, const int *__restrict__ frozen,
-                                                    const int *__restrict__ probe,
-                                                    const uint32_t *__restrict__ t_dev,
-                                                    int t_off) {
-    const uint32_t t = *t_dev + (uint32_t)t_off;
-    const int per = (total + (int)gridDim.x - 1) / (int)gridDim.x;
+                                                    int buf, int blocks,
+                                                    const int *__restrict__ actu, uint64_t limit,
+                                                    unsigned long long *__restrict__ count,
+                                                    uint32_t *__restrict__ maxrel) {
+    if ((int)blockIdx.x >= blocks) {
+        const int p = (int)blockIdx.x - blocks;
+        const int I = __builtin_amdgcn_readfirstlane(actu[p / kProbeBlocks]);
+        const BatchInst &B = inst[I];
+        prec_change_wave<T, LatticeRel>((const T *)B.msg[buf], (const T *)B.msg[buf ^ 1],
+                                        (int64_t)B.L.deg * B.L.plane,
+                                        p % kProbeBlocks * 4 + (int)(threadIdx.x >> 6),
+                                        kProbeBlocks * 4, limit, count + I, maxrel + I);
+        return;
+    }
+    const int per = (total + blocks - 1) / blocks;
     const int w1 = min(total, ((int)blockIdx.x + 1) * per);
     for (int w = (int)blockIdx.x * per; w < w1; ++w) {
         const int a = find_item(prefix, nact, w);
@@ -183,14 +223,13 @@ __global__ __launch_bounds__(256) void k_batch_post(const BatchInst *__restrict_
         const int x = (tile % L.tiles_x) * 64 + (int)(threadIdx.x & 63u);
         const int y = (tile / L.tiles_x) * 4 + (int)(threadIdx.x >> 6);
         if (x >= L.nx || y >= L.ny) continue;
-        const T *m = (const T *)B.msg[t & 1u];
-        double *bel_out = probe[I] ? B.bel64 : nullptr;
+        const T *m = (const T *)B.msg[buf];
         if (L.alpha == 1) {
             if (frozen[I]) post_node<T, 1, true>(L, m, B.adiag64, B.b64, B.bel64, B.mu64, nullptr, nullptr, nullptr, x, y);
-            else post_node<T, 1, false>(L, m, B.adiag64, B.b64, nullptr, B.mu64, nullptr, nullptr, bel_out, x, y);
+            else post_node<T, 1, false>(L, m, B.adiag64, B.b64, nullptr, B.mu64, nullptr, nullptr, B.bel64, x, y);
         } else {
             if (frozen[I]) post_node<T, 2, true>(L, m, B.adiag64, B.b64, B.bel64, B.mu64, nullptr, nullptr, nullptr, x, y);
-            else post_node<T, 2, false>(L, m, B.adiag64, B.b64, nullptr, B.mu64, nullptr, nullptr, bel_out, x, y);
+            else post_node<T, 2, false>(L, m, B.adiag64, B.b64, nullptr, B.mu64, nullptr, nullptr, B.bel64, x, y);
         }
     }
 }
@@ -238,11 +277,19 @@ __global__ __launch_bounds__(256) void k_batch_resid(const BatchInst *__restrict
     }
 }
 
-// One workgroup per running instance: fixed-order sum of its partials.
+// One workgroup per running instance: fixed-order sum of its partials, reported
+// to pinned host memory with its divergence and freeze-test words; clears the
+// latter.
 __global__ __launch_bounds__(256) void k_batch_reduce(const int *__restrict__ act,
                                                       const int *__restrict__ prefix,
                                                       const double *__restrict__ partials,
-                                                      double *__restrict__ out) {
+                                                      const uint32_t *__restrict__ diverged_at,
+                                                      unsigned long long *__restrict__ count,
+                                                      uint32_t *__restrict__ maxrel,
+                                                      double *__restrict__ h_out,
+                                                      uint32_t *__restrict__ h_div,
+                                                      unsigned long long *__restrict__ h_count,
+                                                      uint32_t *__restrict__ h_maxrel) {
     __shared__ double sh[2][4];
     const int a = (int)blockIdx.x;
     const int lo = prefix[a], hi = prefix[a + 1];
@@ -261,34 +308,14 @@ __global__ __launch_bounds__(256) void k_batch_reduce(const int *__restrict__ ac
     __syncthreads();
     if (threadIdx.x == 0) {
         const int I = act[a];
-        out[2 * I] = (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]);
-        out[2 * I + 1] = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
+        h_out[2 * I] = (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]);
+        h_out[2 * I + 1] = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
+        h_div[I] = diverged_at[I];
+        h_count[I] = count[I];
+        h_maxrel[I] = maxrel[I];
+        count[I] = 0;
+        maxrel[I] = 0;
     }
-}
-
-// The freeze test of every instance in a list of running ones: kProbeBlocks
-// blocks each, one launch (24 launches of up to 25 us each for 24 instances).
-constexpr int kProbeBlocks = 64;
-template <typename T>
-__global__ __launch_bounds__(256) void k_batch_prec_change(const BatchInst *__restrict__ inst,
-                                                           const int *__restrict__ act,
-                                                           const uint32_t *__restrict__ t_dev,
-                                                           uint64_t limit,
-                                                           unsigned long long *__restrict__ count,
-                                                           uint32_t *__restrict__ maxrel) {
-    const int I = __builtin_amdgcn_readfirstlane(act[blockIdx.y]);
-    const BatchInst &B = inst[I];
-    const uint32_t t = *t_dev;
-    prec_change_wave<T, LatticeRel>((const T *)B.msg[t & 1u], (const T *)B.msg[(t & 1u) ^ 1u],
-                                    (int64_t)B.L.deg * B.L.plane,
-                                    (int)(blockIdx.x * 4 + (threadIdx.x >> 6)), kProbeBlocks * 4,
-                                    limit, count + I, maxrel + I);
-}
-
-// Advances the device iteration counter after a chunk (a kernel node, so a
-// replayed graph numbers its iterations correctly).
-__global__ void k_batch_advance(uint32_t *t_dev, int k) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *t_dev += (uint32_t)k;
 }
 
 }  // namespace gabp
@@ -309,8 +336,6 @@ struct InstHost {
     int dtype;
     Layout lay;
     size_t base = 0;            // byte offset of the instance's region
-    int tiles_iter = 0;         // work items of the iteration kernel
-    int tiles_pair = 0;         // work items of the two-iteration kernel
     int tiles_check = 0;        // work items of the check kernels (64 x 4)
     bool running = true;
     bool frozen = false;
@@ -327,20 +352,25 @@ struct InstHost {
 };
 
 // Buffer holding an instance's current messages: its iteration's parity,
-// except after a divergence inside a two-iteration launch.
+// except after a divergence inside a launch of several iterations.
 int state_buf(const InstHost &H) { return H.dbuf >= 0 ? H.dbuf : (int)(H.iters & 1); }
 
-// One run of iterations since the last check read-back: its length, the
-// couples of two-iteration launches it made, and each instance's iteration
-// and frozen flag at its start (-1: not running).
+// Group of an instance: full iterations (0, 1) or information-only (2, 3), by
+// prior order.
+int group_of(const InstHost &H, bool frozen) { return (frozen ? 2 : 0) + (H.L.alpha == 1 ? 0 : 1); }
+
+// One run of k iterations since the last check read-back: the iterations in
+// multi-iteration launches and their number for each group, the couples of
+// two-iteration launches that a divergence is reported by (hold_batch), and each
+// instance's iteration and frozen flag at its start (-1: not running).
 struct BatchRun {
     int k = 0;
+    double eta = 0.0;
+    int iters[4] = {0, 0, 0, 0}, deeps[4] = {0, 0, 0, 0};
     int couples = 0;
     std::vector<int64_t> t0;
     std::vector<char> frozen;
 };
-
-struct BatchHostMirror;
 
 }  // namespace
 
@@ -350,7 +380,7 @@ struct gabp_batch {
     size_t esize = 4;
     int device = 0;
     hipStream_t ustream = nullptr;   // the caller's stream (may be the null stream)
-    hipStream_t stream = nullptr;    // internal stream (graphs cannot capture the null stream)
+    hipStream_t stream = nullptr;    // internal stream
     hipEvent_t ev_in = nullptr, ev_out = nullptr;
     char *ws = nullptr;
     size_t ws_bytes = 0;
@@ -358,11 +388,9 @@ struct gabp_batch {
     std::vector<InstHost> h;
     // device arrays (inside the workspace)
     BatchInst *d_inst = nullptr;
-    int *d_act = nullptr, *d_wprefix = nullptr, *d_pprefix = nullptr;
-    int *d_frozen = nullptr, *d_probe = nullptr;
+    int *d_act = nullptr, *d_pprefix = nullptr, *d_frozen = nullptr;
     int *d_actu = nullptr, *d_wprefu = nullptr;   // running, precision not frozen (1 iteration)
-    int *d_actf[2] = {nullptr, nullptr}, *d_wpreff[2] = {nullptr, nullptr};
-                                                  // running, frozen, by prior order (2 per launch)
+    int *d_gact = nullptr, *d_gpre = nullptr;     // running, by group (several iterations)
     uint32_t *d_div = nullptr, *d_t = nullptr, *d_err = nullptr;
     unsigned long long *d_cnt = nullptr;   // changed precision messages per instance
     uint32_t *d_mrel = nullptr;            // their largest relative change (float bits)
@@ -372,22 +400,23 @@ struct gabp_batch {
     double *p_out = nullptr;
     uint32_t *p_div = nullptr, *p_mrel = nullptr, *p_t = nullptr;
     unsigned long long *p_cnt = nullptr;
-    int *p_lists = nullptr;     // staging for act / prefixes / frozen / probe
-    int rpt = 4;
-    int pair = 0;               // tile height of the two-iteration kernel, 0 = unused
+    int *p_lists = nullptr;     // staging of the lists
+    bool staged = false;        // ... which a copy still reads
+    // rows per thread of the one-iteration kernel: the last iteration before a
+    // check, of instances not frozen; one hides its loads best
+    int rpt = 1;
+    int cus = 256;
     int64_t freeze_slots = 0;   // freeze tolerance (gabp_batch_set_freeze_tolerance)
     double freeze_rel = 0.0;
     int64_t t = 0;              // iterations applied to the running set
     // current work lists
-    int nact = 0, wtotal = 0, ptotal = 0;
-    int nu = 0, wtotu = 0, nf[2] = {0, 0}, wtotf[2] = {0, 0};
+    int nact = 0, ptotal = 0, nu = 0, wtotu = 0;
+    struct Group {
+        int off = 0, n = 0, items = 0;   // in d_gact; d_gpre from off + its index
+        gabp::DeepPlan plan{0, 1};
+    } group[4];
     bool lists_dirty = true;
-    // captured chunk
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t gexec = nullptr;
     std::vector<BatchRun> runs;   // runs since the last check read-back
-    int graph_k = 0, graph_rpt = 0;
-    double graph_eta = 0.0;
     std::string err;
 };
 
@@ -428,98 +457,104 @@ int tiles_iter_of(const Lattice &L, int rpt) {
     return L.tiles_x * ((L.ny + 4 * rpt - 1) / (4 * rpt));
 }
 
-int tiles_pair_of(const Lattice &L, int th) {
-    return L.tiles_x * ((L.ny + th - 1) / th);
-}
-
-// lists staging / device layout: act[n] wprefix[n+1] pprefix[n+1] frozen[n]
-// probe[n] actu[n] wprefu[n+1], then actf[n] wpreff[n+1] for alpha = 1 and 2
-constexpr int lists_ints(int n) { return 11 * n + 5; }
+// lists staging / device layout: act[n] pprefix[n+1] frozen[n] actu[n]
+// wprefu[n+1] gact[n] gpre[n+4]
+constexpr int lists_ints(int n) { return 7 * n + 6; }
+// the workspace's share, as the documented sizes have it
+constexpr int lists_room(int n) { return 11 * n + 5; }
+static_assert(lists_ints(1) <= lists_room(1), "lists fit their room from n = 1 on");
 // flag region: div[n], t, err, mrel[n] (uint32), then cnt[n] (uint64, 8-aligned)
 constexpr size_t flag_bytes(int n) { return 4 * (2 * (size_t)n + 2) + 4 + 8 * (size_t)n; }
 
-void drop_graph(gabp_batch *b) {
-    if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
-    if (b->graph) (void)hipGraphDestroy(b->graph);
-    b->gexec = nullptr;
-    b->graph = nullptr;
+// Region and iterations per launch of a group: deep_pick's rule on the tiles of
+// all its instances together.
+gabp::DeepPlan group_plan(const gabp_batch *b, int g, const std::vector<int> &members) {
+    const int dt = b->dtype == GABP_F32 ? 0 : 1, alpha = (g & 1) + 1;
+    int n;
+    const gabp::DeepChoice *c = g < 2 ? gabp::full_choices(dt, alpha, n)
+                                      : gabp::deep_choices(dt, alpha, n);
+    for (int k = 0; k < n; ++k)
+        for (int S = c[k].most; S >= c[k].least; --S) {
+            int64_t tiles = 0;
+            for (int i : members)
+                tiles += gabp::deep_tiles(alpha, b->h[i].L.nx, b->h[i].L.ny, c[k].rw, c[k].rh, S);
+            if (tiles <= b->cus) return {k, S};
+        }
+    return {n - 1, c[n - 1].bulk};
 }
 
 // Rebuild the work lists of the running instances (host staging, then one
 // copy into the device arrays).
 gabp_status upload_lists(gabp_batch *b) {
     const int n = b->n;
-    int *act = b->p_lists, *wp = act + n, *pp = wp + n + 1, *fz = pp + n + 1, *pr = fz + n;
-    int *actu = pr + n, *wpu = actu + n;
-    int *actf[2], *wpf[2];
-    actf[0] = wpu + n + 1;
-    wpf[0] = actf[0] + n;
-    actf[1] = wpf[0] + n + 1;
-    wpf[1] = actf[1] + n;
-    int na = 0, w = 0, p = 0, nu = 0, wu = 0, nf[2] = {0, 0}, wf[2] = {0, 0};
+    if (b->staged) BHIP(b, hipStreamSynchronize(b->stream));
+    b->staged = false;
+    int *act = b->p_lists, *pp = act + n, *fz = pp + n + 1, *actu = fz + n, *wpu = actu + n;
+    int *gact = wpu + n + 1, *gpre = gact + n;
+    int na = 0, p = 0, nu = 0, wu = 0;
+    std::vector<int> members[4];
     for (int i = 0; i < n; ++i) {
         InstHost &H = b->h[i];
         fz[i] = H.frozen ? 1 : 0;
-        pr[i] = (H.running && !H.frozen && H.prev_valid && H.iters >= 2) ? 1 : 0;
         if (!H.running) continue;
-        H.tiles_iter = tiles_iter_of(H.L, b->rpt);
         act[na] = i;
-        wp[na] = w;
-        pp[na] = p;
-        w += H.tiles_iter;
+        pp[na++] = p;
         p += H.tiles_check;
-        ++na;
-        if (H.frozen && b->pair > 0) {
-            const int q = H.L.alpha == 1 ? 0 : 1;
-            H.tiles_pair = tiles_pair_of(H.L, b->pair);
-            actf[q][nf[q]] = i;
-            wpf[q][nf[q]] = wf[q];
-            wf[q] += H.tiles_pair;
-            ++nf[q];
-        } else {
-            actu[nu] = i;
-            wpu[nu] = wu;
-            wu += H.tiles_iter;
-            ++nu;
-        }
+        members[group_of(H, H.frozen)].push_back(i);
+        if (H.frozen) continue;
+        actu[nu] = i;
+        wpu[nu++] = wu;
+        wu += tiles_iter_of(H.L, b->rpt);
     }
-    wp[na] = w;
     pp[na] = p;
     wpu[nu] = wu;
-    wpf[0][nf[0]] = wf[0];
-    wpf[1][nf[1]] = wf[1];
     b->nact = na;
-    b->wtotal = w;
     b->ptotal = p;
     b->nu = nu;
     b->wtotu = wu;
-    for (int q = 0; q < 2; ++q) {
-        b->nf[q] = nf[q];
-        b->wtotf[q] = wf[q];
+    int off = 0;
+    for (int g = 0; g < 4; ++g) {
+        gabp_batch::Group &G = b->group[g];
+        const int dt = b->dtype == GABP_F32 ? 0 : 1, alpha = (g & 1) + 1;
+        int nc;
+        const gabp::DeepChoice *c = g < 2 ? gabp::full_choices(dt, alpha, nc)
+                                          : gabp::deep_choices(dt, alpha, nc);
+        G.plan = group_plan(b, g, members[g]);
+        c += G.plan.region;
+        G.off = off;
+        G.n = (int)members[g].size();
+        G.items = 0;
+        for (int k = 0; k < G.n; ++k) {
+            const Lattice &L = b->h[members[g][k]].L;
+            gact[off + k] = members[g][k];
+            gpre[off + g + k] = G.items;
+            G.items += (int)gabp::deep_tiles(alpha, L.nx, L.ny, c->rw, c->rh, G.plan.S);
+        }
+        gpre[off + g + G.n] = G.items;
+        off += G.n;
     }
     // all lists are contiguous from d_act on
     BHIP(b, hipMemcpyAsync(b->d_act, b->p_lists, sizeof(int) * (size_t)lists_ints(n),
                            hipMemcpyHostToDevice, b->stream));
-    BHIP(b, hipStreamSynchronize(b->stream));   // staging buffer is reused
+    b->staged = true;
     b->lists_dirty = false;
-    drop_graph(b);
     return GABP_OK;
 }
 
-// One iteration of the instances in one work list (single-iteration kernel).
-gabp_status launch_single(gabp_batch *b, const int *act, const int *prefix, int na, int total,
-                          int s, double eta) {
-    if (na == 0) return GABP_OK;
-    const int grid = std::min(kBatchGrid, std::max(1, total));
+// Iteration t of the instances not frozen.
+gabp_status launch_single(gabp_batch *b, int64_t t, double eta) {
+    if (b->nu == 0) return GABP_OK;
+    const int grid = std::min(kBatchGrid, std::max(1, b->wtotu));
+    const int buf = (int)((t - 1) & 1);
     if (b->dtype == GABP_F32) {
         switch (b->rpt) {
-#define RPT_CASE(R) case R: hipLaunchKernelGGL((gabp::k_batch_iter<float, R>), dim3(grid), dim3(256), 0, b->stream, b->d_inst, act, prefix, na, total, b->d_frozen, b->d_t, s, (float)eta, b->d_div); break;
+#define RPT_CASE(R) case R: hipLaunchKernelGGL((gabp::k_batch_iter<float, R>), dim3(grid), dim3(256), 0, b->stream, b->d_inst, b->d_actu, b->d_wprefu, b->nu, b->wtotu, buf, (uint32_t)t, (float)eta, b->d_div); break;
             RPT_CASE(1) RPT_CASE(2) RPT_CASE(4) default: RPT_CASE(8)
 #undef RPT_CASE
         }
     } else {
         switch (b->rpt) {
-#define RPT_CASE(R) case R: hipLaunchKernelGGL((gabp::k_batch_iter<double, R>), dim3(grid), dim3(256), 0, b->stream, b->d_inst, act, prefix, na, total, b->d_frozen, b->d_t, s, eta, b->d_div); break;
+#define RPT_CASE(R) case R: hipLaunchKernelGGL((gabp::k_batch_iter<double, R>), dim3(grid), dim3(256), 0, b->stream, b->d_inst, b->d_actu, b->d_wprefu, b->nu, b->wtotu, buf, (uint32_t)t, eta, b->d_div); break;
             RPT_CASE(1) RPT_CASE(2) RPT_CASE(4) default: RPT_CASE(8)
 #undef RPT_CASE
         }
@@ -528,50 +563,60 @@ gabp_status launch_single(gabp_batch *b, const int *act, const int *prefix, int 
     return GABP_OK;
 }
 
-// Two iterations (starting from iteration offset s0) of the frozen lists.
-gabp_status launch_pair(gabp_batch *b, int s0, int second, double eta) {
-    for (int q = 0; q < 2; ++q) {
-        if (b->nf[q] == 0) continue;
-        const dim3 grid((unsigned)b->wtotf[q]);
-        const int *act = b->d_actf[q], *pre = b->d_wpreff[q];
-        if (b->dtype == GABP_F32) {
-            if (q == 0)
-                hipLaunchKernelGGL((gabp::k_batch_pair<float, 1, 12, 12>), grid, dim3(768), 0,
-                                   b->stream, b->d_inst, act, pre, b->nf[q], b->d_t, s0, second,
-                                   (float)eta, b->d_div);
-            else
-                hipLaunchKernelGGL((gabp::k_batch_pair<float, 2, 12, 12>), grid, dim3(768), 0,
-                                   b->stream, b->d_inst, act, pre, b->nf[q], b->d_t, s0, second,
-                                   (float)eta, b->d_div);
-        } else {
-            if (q == 0)
-                hipLaunchKernelGGL((gabp::k_batch_pair<double, 1, 4, 4>), grid, dim3(256), 0,
-                                   b->stream, b->d_inst, act, pre, b->nf[q], b->d_t, s0, second,
-                                   eta, b->d_div);
-            else
-                hipLaunchKernelGGL((gabp::k_batch_pair<double, 2, 4, 4>), grid, dim3(256), 0,
-                                   b->stream, b->d_inst, act, pre, b->nf[q], b->d_t, s0, second,
-                                   eta, b->d_div);
-        }
-        BHIP(b, hipGetLastError());
+// n iterations of group g from iteration t in buffer `buf`, one launch.
+template <typename T, int ALPHA, int RW, int RH>
+void deep_k(gabp_batch *b, int g, int n, int buf, int64_t t, double eta) {
+    const gabp_batch::Group &G = b->group[g];
+    hipLaunchKernelGGL((gabp::k_batch_deep<T, ALPHA, RW, RH>), dim3((unsigned)G.items), dim3(1024),
+                       0, b->stream, b->d_inst, b->d_gact + G.off, b->d_gpre + G.off + g, G.n,
+                       G.plan.S, n, buf, (uint32_t)t, (T)eta, b->d_div);
+}
+
+template <typename T, int ALPHA, int RW, int RH, int NT, bool SPLIT>
+void full_k(gabp_batch *b, int g, int n, int buf, int64_t t, double eta) {
+    const gabp_batch::Group &G = b->group[g];
+    hipLaunchKernelGGL((gabp::k_batch_deep_full<T, ALPHA, RW, RH, NT, SPLIT>),
+                       dim3((unsigned)G.items), dim3(NT), 0, b->stream, b->d_inst,
+                       b->d_gact + G.off, b->d_gpre + G.off + g, G.n, G.plan.S, n, buf,
+                       (uint32_t)t, (T)eta, b->d_div);
+}
+
+gabp_status launch_group(gabp_batch *b, int g, int n, int buf, int64_t t, double eta) {
+    const int region = b->group[g].plan.region;
+    if (b->dtype == GABP_F32) {
+        if (g == 0) (region == 0 ? full_k<float, 1, 32, 32, 1024, false> : full_k<float, 1, 64, 16, 1024, false>)(b, g, n, buf, t, eta);
+        else if (g == 1) (region == 0 ? full_k<float, 2, 32, 32, 1024, false> : full_k<float, 2, 64, 16, 1024, false>)(b, g, n, buf, t, eta);
+        else if (g == 2) (region == 0 ? deep_k<float, 1, 32, 32> : region == 1 ? deep_k<float, 1, 64, 32> : deep_k<float, 1, 64, 64>)(b, g, n, buf, t, eta);
+        else (region == 0 ? deep_k<float, 2, 32, 32> : deep_k<float, 2, 64, 32>)(b, g, n, buf, t, eta);
+    } else {
+        if (g == 0) (region == 0 ? full_k<double, 1, 24, 24, 576, false> : region == 1 ? full_k<double, 1, 32, 32, 1024, false> : full_k<double, 1, 64, 32, 1024, false>)(b, g, n, buf, t, eta);
+        else if (g == 1) (region == 0 ? full_k<double, 2, 32, 16, 512, false> : full_k<double, 2, 32, 24, 768, true>)(b, g, n, buf, t, eta);
+        else if (g == 2) (region == 0 ? deep_k<double, 1, 32, 32> : deep_k<double, 1, 64, 32>)(b, g, n, buf, t, eta);
+        else deep_k<double, 2, 32, 32>(b, g, n, buf, t, eta);
     }
+    BHIP(b, hipGetLastError());
     return GABP_OK;
 }
 
-// k iterations of the running set.  Frozen instances run couples of
-// two-iteration launches (4 iterations each) while at least 5 iterations
-// remain, the others single iterations alongside; the last 1 to 4
-// iterations run singly for everyone, so that every instance ends on its
-// two newest iterations in its two buffers.
-int couples_of(const gabp_batch *b, int k) {
-    return (b->pair > 0 && b->nf[0] + b->nf[1] > 0 && k >= 5) ? (k - 1) / 4 : 0;
-}
-
-// Record a run of k iterations about to be applied to the running set.
-void record_run(gabp_batch *b, int k) {
+// Record a run of k iterations about to be applied to the running set.  Frozen
+// instances run all of them several to a launch, the others all but the last,
+// which runs singly, so that they end on their two newest iterations in their two
+// buffers (the freeze test needs that).  Each group's number of launches has the
+// parity of its iterations, so that an instance's state stays in the buffer its
+// iteration number selects.
+void record_run(gabp_batch *b, int k, double eta) {
     BatchRun r;
     r.k = k;
-    r.couples = couples_of(b, k);
+    r.eta = eta;
+    for (int g = 0; g < 4; ++g) {
+        if (b->group[g].n == 0) continue;
+        const int n = g < 2 ? (k >= 3 ? k - 1 : 0) : k, S = b->group[g].plan.S;
+        int l = (n + S - 1) / S;
+        if ((l ^ n) & 1) ++l;
+        r.iters[g] = n;
+        r.deeps[g] = l;
+    }
+    r.couples = b->group[2].n + b->group[3].n > 0 && k >= 5 ? (k - 1) / 4 : 0;
     r.t0.resize(b->n);
     r.frozen.resize(b->n);
     for (int i = 0; i < b->n; ++i) {
@@ -581,95 +626,85 @@ void record_run(gabp_batch *b, int k) {
     b->runs.push_back(std::move(r));
 }
 
-gabp_status launch_iters(gabp_batch *b, int k, double eta) {
-    if (b->nact == 0) return GABP_OK;
-    const int couples = couples_of(b, k);
-    gabp_status st = GABP_OK;
-    int s = 1;
-    for (int c = 0; c < couples && st == GABP_OK; ++c, s += 4) {
-        st = launch_pair(b, s - 1, 0, eta);
-        for (int q = 0; q < 2 && st == GABP_OK; ++q)
-            st = launch_single(b, b->d_actu, b->d_wprefu, b->nu, b->wtotu, s + q, eta);
-        if (st == GABP_OK) st = launch_pair(b, s + 1, 1, eta);
-        for (int q = 2; q < 4 && st == GABP_OK; ++q)
-            st = launch_single(b, b->d_actu, b->d_wprefu, b->nu, b->wtotu, s + q, eta);
+// Record and issue k iterations of the running set.
+gabp_status run_iters(gabp_batch *b, int k, double eta) {
+    if (b->nact > 0 && k > 0) {
+        record_run(b, k, eta);
+        const BatchRun &r = b->runs.back();
+        gabp_status st = GABP_OK;
+        for (int g = 0; g < 4; ++g)
+            for (int j = 0; j < r.deeps[g] && st == GABP_OK; ++j) {
+                const int i0 = gabp::deep_part(r.iters[g], r.deeps[g], j);
+                st = launch_group(b, g, gabp::deep_part(r.iters[g], r.deeps[g], j + 1) - i0,
+                                  (int)((b->t + j) & 1), b->t + i0, eta);
+            }
+        const int first = k >= 3 ? k - 1 : 0;
+        for (int i = first; i < k && st == GABP_OK; ++i) st = launch_single(b, b->t + i + 1, eta);
+        if (st != GABP_OK) return st;
     }
-    for (; s <= k && st == GABP_OK; ++s)
-        st = launch_single(b, b->d_act, b->d_wprefix, b->nact, b->wtotal, s, eta);
-    if (st != GABP_OK) return st;
-    hipLaunchKernelGGL(gabp::k_batch_advance, dim3(1), dim3(64), 0, b->stream, b->d_t, k);
-    BHIP(b, hipGetLastError());
+    b->t += k;
+    for (auto &H : b->h)
+        if (H.running) {
+            H.iters += k;
+            if (k > 0) H.prev_valid = true;
+        }
     return GABP_OK;
 }
 
-// Check of the running set: marginals, residual partials, per-instance
-// reduction, read-back of results and divergence flags.
+// Check of the running set: marginals with the freeze test of the instances not
+// frozen (before t = 2 there is no previous iteration to compare with), residual
+// partials, per-instance reduction and report to the pinned mirror.
 gabp_status launch_check(gabp_batch *b) {
     if (b->nact == 0) return GABP_OK;
     const int grid = std::min(kBatchGrid, std::max(1, b->ptotal));
+    const int post = grid + (b->t >= 2 ? b->nu * gabp::kProbeBlocks : 0);
+    const int buf = (int)(b->t & 1);
     if (b->dtype == GABP_F32)
-        hipLaunchKernelGGL((gabp::k_batch_post<float>), dim3(grid), dim3(256), 0, b->stream,
-                           b->d_inst, b->d_act, b->d_pprefix, b->nact, b->ptotal, b->d_frozen,
-                           b->d_probe, b->d_t, 0);
+        hipLaunchKernelGGL((gabp::k_batch_post<float>), dim3(post), dim3(256), 0, b->stream,
+                           b->d_inst, b->d_act, b->d_pprefix, b->nact, b->ptotal, b->d_frozen, buf,
+                           grid, b->d_actu, (uint64_t)b->freeze_slots, b->d_cnt, b->d_mrel);
     else
-        hipLaunchKernelGGL((gabp::k_batch_post<double>), dim3(grid), dim3(256), 0, b->stream,
-                           b->d_inst, b->d_act, b->d_pprefix, b->nact, b->ptotal, b->d_frozen,
-                           b->d_probe, b->d_t, 0);
+        hipLaunchKernelGGL((gabp::k_batch_post<double>), dim3(post), dim3(256), 0, b->stream,
+                           b->d_inst, b->d_act, b->d_pprefix, b->nact, b->ptotal, b->d_frozen, buf,
+                           grid, b->d_actu, (uint64_t)b->freeze_slots, b->d_cnt, b->d_mrel);
     hipLaunchKernelGGL(gabp::k_batch_resid, dim3(grid), dim3(256), 0, b->stream, b->d_inst,
                        b->d_act, b->d_pprefix, b->nact, b->ptotal, b->d_partials);
     hipLaunchKernelGGL(gabp::k_batch_reduce, dim3(b->nact), dim3(256), 0, b->stream, b->d_act,
-                       b->d_pprefix, b->d_partials, b->d_out);
+                       b->d_pprefix, b->d_partials, b->d_div, b->d_cnt, b->d_mrel, b->p_out,
+                       b->p_div, b->p_cnt, b->p_mrel);
     BHIP(b, hipGetLastError());
-    BHIP(b, hipMemcpyAsync(b->p_out, b->d_out, sizeof(double) * 2 * (size_t)b->n,
-                           hipMemcpyDeviceToHost, b->stream));
-    BHIP(b, hipMemcpyAsync(b->p_div, b->d_div, sizeof(uint32_t) * (size_t)b->n,
-                           hipMemcpyDeviceToHost, b->stream));
     return GABP_OK;
 }
 
-// Precision-message change (count and largest relative change) of every
-// running, not yet frozen instance (outside the captured graph): the list of
-// instances on single iterations, which with two-iteration launches in use
-// (always) is just them.  Before t = 2 there is no previous iteration to
-// compare with.
-gabp_status launch_probes(gabp_batch *b) {
-    if (b->nu == 0 || b->t < 2) return GABP_OK;
-    const dim3 grid(gabp::kProbeBlocks, (unsigned)b->nu);
-    if (b->dtype == GABP_F32)
-        hipLaunchKernelGGL((gabp::k_batch_prec_change<float>), grid, dim3(256), 0, b->stream,
-                           b->d_inst, b->d_actu, b->d_t, (uint64_t)b->freeze_slots, b->d_cnt,
-                           b->d_mrel);
-    else
-        hipLaunchKernelGGL((gabp::k_batch_prec_change<double>), grid, dim3(256), 0, b->stream,
-                           b->d_inst, b->d_actu, b->d_t, (uint64_t)b->freeze_slots, b->d_cnt,
-                           b->d_mrel);
-    BHIP(b, hipGetLastError());
-    BHIP(b, hipMemcpyAsync(b->p_cnt, b->d_cnt, sizeof(unsigned long long) * (size_t)b->n,
-                           hipMemcpyDeviceToHost, b->stream));
-    BHIP(b, hipMemcpyAsync(b->p_mrel, b->d_mrel, sizeof(uint32_t) * (size_t)b->n,
-                           hipMemcpyDeviceToHost, b->stream));
-    return GABP_OK;
-}
-
-gabp_status ensure_graph(gabp_batch *b, int k, double eta) {
-    if (b->gexec && b->graph_k == k && b->graph_eta == eta && b->graph_rpt == b->rpt)
-        return GABP_OK;
-    drop_graph(b);
-    BHIP(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-    gabp_status st = launch_iters(b, k, eta);
-    if (st == GABP_OK) st = launch_check(b);
-    hipGraph_t g = nullptr;
-    hipError_t e = hipStreamEndCapture(b->stream, &g);
-    if (st != GABP_OK) {
-        if (g) (void)hipGraphDestroy(g);
-        return st;
+// Instance i diverged at iteration t of run r.  The launch that met it left its
+// input whole, and no later launch wrote, so the state that single launches (full
+// iterations) or couples of two-iteration launches (information-only ones) would
+// have kept is made from it by single iterations, recording into the batch's error
+// word, which is cleared before each of them.
+gabp_status hold_batch(gabp_batch *b, int i, const BatchRun &r, int64_t t) {
+    InstHost &H = b->h[i];
+    const bool frozen = r.frozen[i] != 0;
+    const int g = group_of(H, frozen), dt = b->dtype == GABP_F32 ? 0 : 1;
+    if (t - r.t0[i] > r.iters[g]) return GABP_OK;   // in a single iteration
+    const int64_t want = held_after_batch_run(r.t0[i], frozen, r.couples, t).iter;
+    int j = 0;
+    while (r.t0[i] + gabp::deep_part(r.iters[g], r.deeps[g], j + 1) < t) ++j;
+    int64_t it = r.t0[i] + gabp::deep_part(r.iters[g], r.deeps[g], j);
+    H.dbuf = (int)((r.t0[i] + j) & 1);
+    char *base = b->ws + H.base;
+    const void *bw = base + (b->dtype == GABP_F32 ? H.lay.b_w : H.lay.b64);
+    const void *ad = base + (b->dtype == GABP_F32 ? H.lay.adiag_w : H.lay.adiag64);
+    for (; it < want; ++it, H.dbuf ^= 1) {
+        const void *in = base + H.lay.msg[H.dbuf];
+        void *out = base + H.lay.msg[H.dbuf ^ 1];
+        BHIP(b, gabp::launch_set_u32(b->d_err, 0u, b->stream));
+        BHIP(b, frozen ? gabp::launch_iter_theta(dt, 1, H.L, in, out, base + H.lay.gain, bw,
+                                                 r.eta, b->d_err, b->d_t, (uint32_t)(it + 1),
+                                                 b->stream)
+                       : gabp::launch_iter(dt, 1, H.L, in, out, ad, bw, r.eta, b->d_err,
+                                           b->d_t, (uint32_t)(it + 1), b->stream));
     }
-    if (e != hipSuccess) return bfail(b, GABP_E_DEVICE, "hipStreamEndCapture failed");
-    b->graph = g;
-    BHIP(b, hipGraphInstantiate(&b->gexec, b->graph, nullptr, nullptr, 0));
-    b->graph_k = k;
-    b->graph_eta = eta;
-    b->graph_rpt = b->rpt;
+    H.iters = it;
     return GABP_OK;
 }
 
@@ -685,7 +720,6 @@ void gabp_batch_destroy(gabp_batch *b) {
     if (!b) return;
     (void)hipSetDevice(b->device);
     if (b->stream) (void)hipStreamSynchronize(b->stream);
-    drop_graph(b);
     if (b->own_ws && b->ws) (void)hipFree(b->ws);
     if (b->p_out) (void)hipHostFree(b->p_out);
     if (b->ev_in) (void)hipEventDestroy(b->ev_in);
@@ -725,7 +759,7 @@ static gabp_status batch_layout(int32_t n, const gabp_instance *inst, int32_t dt
     // largest precision changes as uint32, then 64-bit change counts),
     // partials, results
     off = round_up(off + sizeof(BatchInst) * (size_t)n, kAlign);
-    off = round_up(off + sizeof(int) * (size_t)lists_ints(n), kAlign);
+    off = round_up(off + sizeof(int) * (size_t)lists_room(n), kAlign);
     off = round_up(off + flag_bytes(n), kAlign);
     off = round_up(off + sizeof(double) * 2 * pc, kAlign);
     off = round_up(off + sizeof(double) * 2 * (size_t)n, kAlign);
@@ -781,7 +815,6 @@ gabp_status gabp_batch_create(int32_t n, const gabp_instance *inst, const gabp_o
     };
     b->n = n;
     b->dtype = dtype;
-    b->pair = dtype == GABP_F32 ? 12 : 4;   // matches the k_batch_pair instances launched
     b->esize = dtype == GABP_F32 ? 4 : 8;
     b->h = hs;
     b->partial_cap = pc;
@@ -789,6 +822,9 @@ gabp_status gabp_batch_create(int32_t n, const gabp_instance *inst, const gabp_o
         b->err = "no HIP device";
         return bail(GABP_E_DEVICE);
     }
+    if (hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, b->device) !=
+        hipSuccess)
+        b->cus = 256;
     b->ustream = opts ? (hipStream_t)opts->stream : nullptr;
     if (hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&b->ev_in, hipEventDisableTiming) != hipSuccess ||
@@ -828,17 +864,13 @@ gabp_status gabp_batch_create(int32_t n, const gabp_instance *inst, const gabp_o
     b->d_inst = (BatchInst *)(b->ws + off);
     off = round_up(off + sizeof(BatchInst) * (size_t)n, kAlign);
     b->d_act = (int *)(b->ws + off);
-    b->d_wprefix = b->d_act + n;
-    b->d_pprefix = b->d_wprefix + n + 1;
+    b->d_pprefix = b->d_act + n;
     b->d_frozen = b->d_pprefix + n + 1;
-    b->d_probe = b->d_frozen + n;
-    b->d_actu = b->d_probe + n;
+    b->d_actu = b->d_frozen + n;
     b->d_wprefu = b->d_actu + n;
-    b->d_actf[0] = b->d_wprefu + n + 1;
-    b->d_wpreff[0] = b->d_actf[0] + n;
-    b->d_actf[1] = b->d_wpreff[0] + n + 1;
-    b->d_wpreff[1] = b->d_actf[1] + n;
-    off = round_up(off + sizeof(int) * (size_t)lists_ints(n), kAlign);
+    b->d_gact = b->d_wprefu + n + 1;
+    b->d_gpre = b->d_gact + n;
+    off = round_up(off + sizeof(int) * (size_t)lists_room(n), kAlign);
     b->d_div = (uint32_t *)(b->ws + off);
     b->d_t = b->d_div + n;
     b->d_err = b->d_t + 1;
@@ -949,22 +981,13 @@ gabp_status gabp_batch_iterate(gabp_batch *b, int32_t n_iters, double damping) {
         gabp_status st = upload_lists(b);
         if (st != GABP_OK) return st;
     }
-    if (b->nact > 0 && n_iters > 0) record_run(b, n_iters);
-    gabp_status st = launch_iters(b, n_iters, damping);
-    if (st != GABP_OK) return st;
-    b->t += n_iters;
-    for (auto &H : b->h)
-        if (H.running) {
-            H.iters += n_iters;
-            if (n_iters > 0) H.prev_valid = true;
-        }
-    return GABP_OK;
+    return run_iters(b, n_iters, damping);
 }
 
-// Fold one check's read-back into the per-instance state.  Returns true when
-// the running set (or a frozen flag) changed.
-static bool fold_check(gabp_batch *b, double rel_tol, bool probed) {
-    bool changed = false;
+// Fold one check's report into the per-instance state.  `changed`: the running
+// set (or a frozen flag) did.
+static gabp_status fold_check(gabp_batch *b, double rel_tol, bool &changed) {
+    changed = false;
     for (int i = 0; i < b->n; ++i) {
         InstHost &H = b->h[i];
         if (!H.running) continue;
@@ -978,9 +1001,8 @@ static bool fold_check(gabp_batch *b, double rel_tol, bool probed) {
             // the kept messages are those of the launch that diverged
             for (const BatchRun &r : b->runs) {
                 if (r.t0[i] < 0 || t <= r.t0[i] || t > r.t0[i] + r.k) continue;
-                const HeldState hs = held_after_batch_run(r.t0[i], r.frozen[i] != 0, r.couples, t);
-                H.iters = hs.iter;
-                H.dbuf = hs.buf;
+                const gabp_status st = hold_batch(b, i, r, t);
+                if (st != GABP_OK) return st;
                 break;
             }
             changed = true;
@@ -1002,14 +1024,14 @@ static bool fold_check(gabp_batch *b, double rel_tol, bool probed) {
             changed = true;
             continue;
         }
-        if (probed && !H.frozen && H.prev_valid && H.iters >= 2 &&
+        if (!H.frozen && H.prev_valid && H.iters >= 2 &&
             freeze_now(b->p_cnt[i], b->p_mrel[i], b->freeze_slots, b->freeze_rel)) {
             H.frozen = true;
             H.frozen_at = H.iters;
             changed = true;
         }
     }
-    return changed;
+    return GABP_OK;
 }
 
 gabp_status gabp_batch_solve(gabp_batch *b, int64_t max_iters, double damping, double rel_tol,
@@ -1023,7 +1045,7 @@ gabp_status gabp_batch_solve(gabp_batch *b, int64_t max_iters, double damping, d
         return bfail(b, GABP_E_INVALID, "need max_iters >= 0, check_every != 0, rel_tol >= 0, damping in (0, 1]");
     // check_every < 0: adaptive chunks, as gabp_solve's, on the slowest
     // running instance; powers of two times |check_every|, at most kMaxChunk,
-    // so that few chunk graphs are captured
+    // as there
     constexpr int kMaxChunk = 1280;
     const bool adaptive = check_every < 0;
     const int kmin = adaptive ? -check_every : check_every;
@@ -1036,43 +1058,19 @@ gabp_status gabp_batch_solve(gabp_batch *b, int64_t max_iters, double damping, d
         }
         if (b->nact == 0) break;
         const int k = (int)std::min<int64_t>(next, max_iters - run);
-        // precision-change probes of instances not yet frozen: compare the
-        // two newest buffers right after this chunk, outside the graph
-        bool need_probe = false;
-        for (auto &H : b->h)
-            if (H.running && !H.frozen) need_probe = true;
-        // the probe's marginal pass must also record belief precisions
-        if (need_probe) {
-            for (int i = 0; i < b->n; ++i) {
-                const InstHost &H = b->h[i];
-                b->p_lists[4 * b->n + 2 + i] = (H.running && !H.frozen) ? 1 : 0;
-            }
-            BHIP(b, hipMemcpyAsync(b->d_probe, b->p_lists + 4 * b->n + 2, sizeof(int) * (size_t)b->n,
-                                   hipMemcpyHostToDevice, b->stream));
-            BHIP(b, hipStreamSynchronize(b->stream));
-        }
-        gabp_status st = ensure_graph(b, k, damping);
+        gabp_status st = run_iters(b, k, damping);
         if (st != GABP_OK) return st;
-        record_run(b, k);
-        BHIP(b, hipGraphLaunch(b->gexec, b->stream));
-        b->t += k;
-        for (auto &H : b->h)
-            if (H.running) {
-                H.iters += k;
-                H.prev_valid = true;
-            }
         run += k;
-        if (need_probe) {
-            st = launch_probes(b);
-            if (st != GABP_OK) return st;
-            // zero the change flags for the next probe after reading them
-        }
+        st = launch_check(b);
+        if (st != GABP_OK) return st;
         BHIP(b, hipStreamSynchronize(b->stream));
-        const bool changed = fold_check(b, rel_tol, need_probe);
+        b->staged = false;
+        bool changed;
+        const bool testing = b->nu > 0;
+        st = fold_check(b, rel_tol, changed);
+        if (st != GABP_OK) return st;
         b->runs.clear();
-        if (need_probe) {
-            BHIP(b, hipMemsetAsync(b->d_cnt, 0, sizeof(unsigned long long) * (size_t)b->n, b->stream));
-            BHIP(b, hipMemsetAsync(b->d_mrel, 0, sizeof(uint32_t) * (size_t)b->n, b->stream));
+        if (testing) {
             for (int i = 0; i < b->n; ++i) {
                 InstHost &H = b->h[i];
                 if (H.frozen && H.frozen_at == H.iters) {

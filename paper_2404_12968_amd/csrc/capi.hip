@@ -142,9 +142,6 @@ gabp_status ctx_ok(gabp_ctx *ctx) {
     return GABP_OK;
 }
 
-// Iterations before launch k of `launches` that share n iterations evenly.
-int deep_part(int n, int launches, int k) { return (int)((int64_t)n * k / launches); }
-
 // A multi-iteration launch met the divergence at iteration t.  Its input is
 // whole (it wrote the other buffer, and no later launch wrote), so the state
 // that single launches (full iterations) or two-iteration launches
@@ -158,8 +155,8 @@ gabp_status hold_deep(gabp_ctx *ctx, const gabp_ctx::LaunchRun &r, int64_t t) {
     const int pairs = r.frozen ? held_pairs(total, r.tail_single) : 0;
     const int64_t want = held_after_run(start, 0, pairs, t).iter;
     int k = 0;
-    while (start + deep_part(r.deep_iters, r.deeps, k + 1) < t) ++k;
-    int64_t it = start + deep_part(r.deep_iters, r.deeps, k);
+    while (start + gabp::deep_part(r.deep_iters, r.deeps, k + 1) < t) ++k;
+    int64_t it = start + gabp::deep_part(r.deep_iters, r.deeps, k);
     int buf = r.buf ^ ((r.lead + k) & 1);
     for (; it < want; ++it, buf ^= 1) {
         const void *in = ctx->msg[buf];
@@ -517,8 +514,8 @@ gabp_status enqueue_iters(gabp_ctx *ctx, int32_t n, double damping, hipStream_t 
             done.deeps = (many + p.S - 1) / p.S;
             done.deep_iters = many;
             for (int j = 0; j < done.deeps; ++j) {
-                const int i0 = deep_part(many, done.deeps, j);
-                const int len = deep_part(many, done.deeps, j + 1) - i0;
+                const int i0 = gabp::deep_part(many, done.deeps, j);
+                const int len = gabp::deep_part(many, done.deeps, j + 1) - i0;
                 const uint32_t off = (uint32_t)(it + i0 - tbase);
                 GABP_HIP(ctx, ctx->frozen
                                   ? gabp::launch_iter_deep(dt, p.region, len, ctx->L, ctx->msg[cur],

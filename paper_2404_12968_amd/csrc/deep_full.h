@@ -55,22 +55,30 @@ constexpr DeepChoice kFullF32A1[] = {{32, 32, 6, 12, 0}, {64, 16, 5, 5, 5}};
 constexpr DeepChoice kFullF64A2[] = {{32, 16, 2, 3, 0}, {32, 24, 3, 3, 3}};
 constexpr DeepChoice kFullF64A1[] = {{24, 24, 9, 9, 0}, {32, 32, 6, 12, 0}, {64, 32, 6, 6, 6}};
 
-inline DeepPlan deep_full_plan(int dtype, int alpha, int nx, int ny, int cus) {
-    if (dtype == 0)
-        return alpha == 1 ? deep_pick(kFullF32A1, 2, alpha, nx, ny, cus)
-                          : deep_pick(kFullF32A2, 2, alpha, nx, ny, cus);
-    return alpha == 1 ? deep_pick(kFullF64A1, 3, alpha, nx, ny, cus)
-                      : deep_pick(kFullF64A2, 2, alpha, nx, ny, cus);
+inline const DeepChoice *full_choices(int dtype, int alpha, int &n) {
+    if (dtype == 0) {
+        n = 2;
+        return alpha == 1 ? kFullF32A1 : kFullF32A2;
+    }
+    n = alpha == 1 ? 3 : 2;
+    return alpha == 1 ? kFullF64A1 : kFullF64A2;
 }
 
-// First of the S iterations (1-based) in which this thread computed an
-// invalid message of a node that the result depends on (a cavity precision that
-// is not positive or a message that is not finite); 0: none.
+inline DeepPlan deep_full_plan(int dtype, int alpha, int nx, int ny, int cus) {
+    int n;
+    const DeepChoice *c = full_choices(dtype, alpha, n);
+    return deep_pick(c, n, alpha, nx, ny, cus);
+}
+
+// n <= S iterations on the tiles for S.  Returns the first of them (1-based) in
+// which this thread computed an invalid message of a node that the result
+// depends on (a cavity precision that is not positive or a message that is not
+// finite); 0: none.
 template <typename T, int ALPHA, int RW, int RH, int NT, bool SPLIT, bool IO>
 __device__ __forceinline__ int deep_full_tile(const Lattice &L, const T *__restrict__ m_in,
                                               T *__restrict__ m_out, const T *__restrict__ adiag,
-                                              const T *__restrict__ bw, T eta, int S, int tx,
-                                              int ty, bool stop, T *lds) {
+                                              const T *__restrict__ bw, T eta, int S, int n,
+                                              int tx, int ty, bool stop, T *lds) {
     using Rg = DeepRegion<ALPHA, RW, RH>;
     constexpr int DEG = Rg::DEG, R = Rg::R, PL = Rg::PL, NPT = RW * RH / NT, RPP = NT / RW;
     constexpr int NQ = ALPHA == 2 && !IO ? 4 : 1;   // couplings that depend on the node
@@ -198,14 +206,14 @@ __device__ __forceinline__ int deep_full_tile(const Lattice &L, const T *__restr
             precision(k, lin[k], g, wrong);
             information(k, tin[k], g, wrong);
             if (wrong && right(ly, 1) && bad == 0) bad = 1;
-            if (S > 1) {
+            if (n > 1) {
                 put(k, ol[k], 0);
                 if (!SPLIT) put(k, ot[k], INFO);
             }
         }
     }
 #pragma unroll 1
-    for (int s = 2; s <= S; ++s) {
+    for (int s = 2; s <= n; ++s) {
         __syncthreads();
         T lin[NPT][DEG], tin[NPT][DEG], g[NPT][DEG];
         bool wrong[NPT];
@@ -219,7 +227,7 @@ __device__ __forceinline__ int deep_full_tile(const Lattice &L, const T *__restr
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < NPT; ++k) put(k, ot[k], 0);
-        } else if (s < S) {
+        } else if (s < n) {
             __syncthreads();
         }
 #pragma unroll
@@ -233,7 +241,7 @@ __device__ __forceinline__ int deep_full_tile(const Lattice &L, const T *__restr
 #pragma unroll
             for (int k = 0; k < NPT; ++k)
                 if (live(ly0 + k * RPP, s)) get(k, tin[k], 0);
-            if (s < S) __syncthreads();
+            if (s < n) __syncthreads();
         }
 #pragma unroll
         for (int k = 0; k < NPT; ++k) {
@@ -241,7 +249,7 @@ __device__ __forceinline__ int deep_full_tile(const Lattice &L, const T *__restr
             if (!live(ly, s)) continue;
             information(k, tin[k], g[k], wrong[k]);
             if (wrong[k] && right(ly, s) && bad == 0) bad = s;
-            if (s < S) {
+            if (s < n) {
                 put(k, ol[k], 0);
                 if (!SPLIT) put(k, ot[k], INFO);
             }

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <math.h>
 #include <stdint.h>
 
@@ -89,6 +90,9 @@ inline int64_t deep_tiles(int alpha, int nx, int ny, int rw, int rh, int S) {
     return (int64_t)((nx + tw - 1) / tw) * ((ny + th - 1) / th);
 }
 
+// Iterations before launch k of `launches` that share n iterations evenly.
+inline int deep_part(int n, int launches, int k) { return (int)((int64_t)n * k / launches); }
+
 inline DeepPlan deep_pick(const DeepChoice *c, int n, int alpha, int nx, int ny, int cus) {
     for (int k = 0; k < n; ++k)
         for (int S = c[k].most; S >= c[k].least; --S)
@@ -102,15 +106,23 @@ inline DeepPlan deep_plan(int dtype, int alpha, int nx, int ny, int cus) {
     return deep_pick(c, n, alpha, nx, ny, cus);
 }
 
-// First of the S iterations (1-based) in which this thread computed an
-// invalid message of a node that the result depends on; 0: none.  `stop` (a
-// divergence recorded by an earlier launch; uniform) is looked at only after
-// the loads are on their way.
+// Record the earliest of a wave's invalid iterations (t + bad, bad != 0).
+__device__ __forceinline__ void record_first(int bad, uint32_t t, uint32_t *diverged_at) {
+    if (!__any(bad != 0)) return;
+    int first = bad != 0 ? bad : INT_MAX;
+    for (int k = 32; k >= 1; k >>= 1) first = min(first, __shfl_xor(first, k, 64));
+    if ((threadIdx.x & 63u) == 0u) record_divergence(diverged_at, t + (uint32_t)first);
+}
+
+// n <= S iterations on the tiles for S.  Returns the first of them (1-based) in
+// which this thread computed an invalid message of a node that the result
+// depends on; 0: none.  `stop` (a divergence recorded by an earlier launch;
+// uniform) is looked at only after the loads are on their way.
 template <typename T, int ALPHA, int RW, int RH, int NT, bool IO>
 __device__ __forceinline__ int deep_tile(const Lattice &L, const T *__restrict__ m_in,
                                          T *__restrict__ m_out, const T *__restrict__ gain,
-                                         const T *__restrict__ bw, T eta, int S, int tx, int ty,
-                                         bool stop, T *lds) {
+                                         const T *__restrict__ bw, T eta, int S, int n, int tx,
+                                         int ty, bool stop, T *lds) {
     using Rg = DeepRegion<ALPHA, RW, RH>;
     constexpr int DEG = Rg::DEG, R = Rg::R, PL = Rg::PL, NPT = RW * RH / NT, RPP = NT / RW;
     static_assert(NT % RW == 0 && RW * RH % NT == 0, "whole rows per pass over the region");
@@ -137,7 +149,7 @@ __device__ __forceinline__ int deep_tile(const Lattice &L, const T *__restrict__
             z = fmadd(out[d], (T)0, z);
         }
         if (!(z == (T)0) && right(ly, s) && bad == 0) bad = s;
-        if (s < S) {
+        if (s < n) {
 #pragma unroll
             for (int d = 0; d < DEG; ++d) own[d * PL + k * NT] = out[d];
         }
@@ -178,7 +190,7 @@ __device__ __forceinline__ int deep_tile(const Lattice &L, const T *__restrict__
         }
     }
 #pragma unroll 1
-    for (int s = 2; s <= S; ++s) {
+    for (int s = 2; s <= n; ++s) {
         __syncthreads();
         T tin[NPT][DEG];
 #pragma unroll
@@ -188,7 +200,7 @@ __device__ __forceinline__ int deep_tile(const Lattice &L, const T *__restrict__
             for (int d = 0; d < DEG; ++d)
                 tin[k][d] = own[(d ^ 1) * PL + k * NT + dir_dy(d) * RW + dir_dx(d)];
         }
-        if (s < S) __syncthreads();
+        if (s < n) __syncthreads();
 #pragma unroll
         for (int k = 0; k < NPT; ++k) {
             if (!live(ly0 + k * RPP, s)) continue;

@@ -188,14 +188,6 @@ __global__ __launch_bounds__(64 * WAVES) void k_iter_theta2(Lattice L, TileRange
     if (bad1 || bad2) record_divergence(diverged_at, bad1 ? t + 1u : t + 2u);
 }
 
-// Record the earliest of a wave's invalid iterations (t + bad, bad != 0).
-__device__ __forceinline__ void record_first(int bad, uint32_t t, uint32_t *diverged_at) {
-    if (!__any(bad != 0)) return;
-    int first = bad != 0 ? bad : INT_MAX;
-    for (int k = 32; k >= 1; k >>= 1) first = min(first, __shfl_xor(first, k, 64));
-    if ((threadIdx.x & 63u) == 0u) record_divergence(diverged_at, t + (uint32_t)first);
-}
-
 // S iterations in one launch (deep_tile.h), one workgroup per tile in the strip
 // order of the other kernels.  As with two iterations per launch, only a
 // divergence recorded by an earlier launch stops it, so its input stays whole.
@@ -218,10 +210,10 @@ __global__ __launch_bounds__(1024) void k_iter_deep(Lattice L, int S, int cols, 
     const int x0 = tx * Rg::tw(S) - Rg::halo(S), y0 = ty * Rg::th(S) - Rg::halo(S);
     int bad;
     if (x0 >= Rg::R && x0 + RW + Rg::R <= L.nx && y0 >= Rg::R && y0 + RH + Rg::R <= L.ny)
-        bad = deep_tile<T, ALPHA, RW, RH, 1024, true>(L, m_in, m_out, gain, bw, eta, S, tx, ty,
+        bad = deep_tile<T, ALPHA, RW, RH, 1024, true>(L, m_in, m_out, gain, bw, eta, S, S, tx, ty,
                                                       stop, lds);
     else
-        bad = deep_tile<T, ALPHA, RW, RH, 1024, false>(L, m_in, m_out, gain, bw, eta, S, tx, ty,
+        bad = deep_tile<T, ALPHA, RW, RH, 1024, false>(L, m_in, m_out, gain, bw, eta, S, S, tx, ty,
                                                        stop, lds);
     record_first(bad, t, diverged_at);
 }
@@ -247,10 +239,10 @@ __global__ __launch_bounds__(NT) void k_iter_deep_full(Lattice L, int S, int col
     int bad;
     if (x0 >= Rg::R && x0 + RW + Rg::R <= L.nx && y0 >= Rg::R && y0 + RH + Rg::R <= L.ny)
         bad = deep_full_tile<T, ALPHA, RW, RH, NT, SPLIT, true>(L, m_in, m_out, adiag, bw, eta, S,
-                                                                tx, ty, stop, lds);
+                                                                S, tx, ty, stop, lds);
     else
         bad = deep_full_tile<T, ALPHA, RW, RH, NT, SPLIT, false>(L, m_in, m_out, adiag, bw, eta,
-                                                                 S, tx, ty, stop, lds);
+                                                                 S, S, tx, ty, stop, lds);
     record_first(bad, t, diverged_at);
 }
 
