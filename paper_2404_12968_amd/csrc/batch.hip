@@ -898,7 +898,8 @@ gabp_status gabp_batch_create(int32_t n, const gabp_instance *inst, const gabp_o
         b->err = "hipMemsetAsync failed";
         return bail(GABP_E_DEVICE);
     }
-    // instance records and per-instance set-up
+    // instance records and per-instance set-up; an instance whose cells repeat out
+    // of order raises its word of d_div and is set up again
     std::vector<BatchInst> rec((size_t)n);
     for (int i = 0; i < n; ++i) {
         InstHost &H = b->h[i];
@@ -914,6 +915,11 @@ gabp_status gabp_batch_create(int32_t n, const gabp_instance *inst, const gabp_o
         R.bel64 = (double *)(base + H.lay.bel64);
         R.adiag_w = dtype == GABP_F32 ? (const void *)(base + H.lay.adiag_w) : (const void *)R.adiag64;
         R.b_w = dtype == GABP_F32 ? (const void *)(base + H.lay.b_w) : (const void *)R.b64;
+    }
+    auto setup = [&](int i, uint32_t *repeated) -> gabp_status {
+        InstHost &H = b->h[i];
+        char *base = b->ws + H.base;
+        BatchInst &R = rec[(size_t)i];
         const gabp_obs &o = inst[i].obs;
         const gabp_noise &nz = inst[i].noise;
         int64_t *tc = nullptr;
@@ -933,7 +939,7 @@ gabp_status gabp_batch_create(int32_t n, const gabp_instance *inst, const gabp_o
                 (void)hipFree(ty);
                 (void)hipFree(tv);
                 b->err = "staging observations failed";
-                return bail(GABP_E_NOMEM);
+                return GABP_E_NOMEM;
             }
             dc = tc;
             dy = ty;
@@ -943,7 +949,7 @@ gabp_status gabp_batch_create(int32_t n, const gabp_instance *inst, const gabp_o
                                           nz.var ? 0.0 : nz.sigma * nz.sigma, R.adiag64, R.b64,
                                           nullptr, dtype == GABP_F32 ? base + H.lay.adiag_w : nullptr,
                                           dtype == GABP_F32 ? base + H.lay.b_w : nullptr, b->d_err,
-                                          b->stream);
+                                          repeated, b->stream);
         if (tc || ty || tv) {
             (void)hipStreamSynchronize(b->stream);
             (void)hipFree(tc);
@@ -952,14 +958,35 @@ gabp_status gabp_batch_create(int32_t n, const gabp_instance *inst, const gabp_o
         }
         if (e != hipSuccess) {
             b->err = std::string("setup failed: ") + hipGetErrorString(e);
-            return bail(GABP_E_DEVICE);
+            return GABP_E_DEVICE;
         }
+        return GABP_OK;
+    };
+    for (int i = 0; i < n; ++i) {
+        const gabp_status s2 = setup(i, b->d_div + i);
+        if (s2 != GABP_OK) return bail(s2);
     }
     if (hipMemcpyAsync(b->d_inst, rec.data(), sizeof(BatchInst) * (size_t)n, hipMemcpyHostToDevice,
+                       b->stream) != hipSuccess ||
+        hipMemcpyAsync(b->p_div, b->d_div, sizeof(uint32_t) * (size_t)n, hipMemcpyDeviceToHost,
                        b->stream) != hipSuccess ||
         hipMemcpyAsync(b->p_t, b->d_err, sizeof(uint32_t), hipMemcpyDeviceToHost, b->stream) != hipSuccess ||
         hipStreamSynchronize(b->stream) != hipSuccess) {
         b->err = "uploading the instance table failed";
+        return bail(GABP_E_DEVICE);
+    }
+    bool again = false;
+    for (int i = 0; i < n; ++i) {
+        if (b->p_div[i] == 0u) continue;
+        again = true;
+        const gabp_status s2 = setup(i, nullptr);
+        if (s2 != GABP_OK) return bail(s2);
+    }
+    if (again &&
+        (hipMemsetAsync(b->d_div, 0, sizeof(uint32_t) * (size_t)n, b->stream) != hipSuccess ||
+         hipMemcpyAsync(b->p_t, b->d_err, sizeof(uint32_t), hipMemcpyDeviceToHost, b->stream) != hipSuccess ||
+         hipStreamSynchronize(b->stream) != hipSuccess)) {
+        b->err = "setting an instance up again failed";
         return bail(GABP_E_DEVICE);
     }
     if (b->p_t[0] != 0u) {

@@ -64,7 +64,7 @@ struct gabp_ctx {
     void *adiag_w = nullptr, *b_w = nullptr;
     double *partials = nullptr, *red = nullptr;
     uint32_t *flags = nullptr;     // [0] diverged-at iteration, [1] input error, [2] workgroups
-                                   // of the residual done,
+                                   // of the residual done (at set-up: repeated cells),
                                    // [3] iteration counter of the launches, [4, 5] precision
                                    // messages changed by the last iteration (64-bit) and
                                    // [6] their largest relative change (float bits)
@@ -429,14 +429,21 @@ gabp_status gabp_create(const gabp_grid *grid, const gabp_stencil *stencil, cons
         }
     }
     const double s2 = noise->var ? 0.0 : noise->sigma * noise->sigma;
-    hipError_t e = gabp::launch_setup(dtype == GABP_F32 ? 0 : 1, ctx->L, nobs, d_cell, d_y, d_var,
-                                      s2, ctx->adiag64, ctx->b64, opts ? opts->prior_mean : nullptr,
-                                      dtype == GABP_F32 ? ctx->adiag_w : nullptr,
-                                      dtype == GABP_F32 ? ctx->b_w : nullptr, ctx->flags + 1,
-                                      ctx->stream);
-    hipError_t e2 = hipMemcpyAsync(ctx->host->flags, ctx->flags, 4 * sizeof(uint32_t),
-                                   hipMemcpyDeviceToHost, ctx->stream);
-    hipError_t e3 = hipStreamSynchronize(ctx->stream);
+    // flags[2] tells when a cell's observations did not follow one another
+    hipError_t e, e2, e3;
+    for (bool direct : {true, false}) {
+        e = gabp::launch_setup(dtype == GABP_F32 ? 0 : 1, ctx->L, nobs, d_cell, d_y, d_var, s2,
+                               ctx->adiag64, ctx->b64, opts ? opts->prior_mean : nullptr,
+                               dtype == GABP_F32 ? ctx->adiag_w : nullptr,
+                               dtype == GABP_F32 ? ctx->b_w : nullptr, ctx->flags + 1,
+                               direct ? ctx->flags + 2 : nullptr, ctx->stream);
+        e2 = hipMemcpyAsync(ctx->host->flags, ctx->flags, 4 * sizeof(uint32_t),
+                            hipMemcpyDeviceToHost, ctx->stream);
+        if (!direct && e == hipSuccess) e = gabp::launch_set_u32(ctx->flags + 2, 0u, ctx->stream);
+        e3 = hipStreamSynchronize(ctx->stream);
+        if (e != hipSuccess || e2 != hipSuccess || e3 != hipSuccess || ctx->host->flags[2] == 0u)
+            break;
+    }
     (void)hipFree(tmp_cell);
     (void)hipFree(tmp_y);
     (void)hipFree(tmp_var);

@@ -569,10 +569,16 @@ hipError_t launch_abs_change(int dtype, const void *a, const void *b, int64_t n,
 hipError_t launch_setup(int dtype, const Lattice &L, int64_t nobs, const int64_t *cell,
                         const double *y, const double *var, double sigma2, double *adiag64,
                         double *b64, const double *prior_mean, void *adiag_w, void *b_w,
-                        uint32_t *err_flag, hipStream_t s) {
+                        uint32_t *err_flag, uint32_t *repeated, hipStream_t s) {
+    if (!repeated) {
+        const size_t bytes = (size_t)L.pitch * (size_t)L.ny * sizeof(double);
+        const hipError_t e = hipMemsetAsync(
+            adiag64, 0, (size_t)((char *)b64 - (char *)adiag64) + bytes, s);
+        if (e != hipSuccess) return e;
+    }
     if (nobs > 0) {
         const hipError_t e = launch_obs_fold(nobs, cell, y, var, sigma2, (int64_t)L.nx * L.ny, L.nx,
-                                             L.pitch, adiag64, b64, err_flag, s);
+                                             L.pitch, adiag64, b64, err_flag, repeated, s);
         if (e != hipSuccess) return e;
     }
     dim3 grid(tiles_of(L)), block(256);

@@ -587,28 +587,40 @@ gabp_status gabp_st_create(const gabp_st_model *model, const gabp_obs *obs,
         dv = tv;
     }
     const double s2 = noise->var ? 0.0 : noise->sigma * noise->sigma;
-    hipError_t e = gabp::launch_obs_fold(nobs, dc, dy, dv, s2,
-                                         (int64_t)G.nx * G.ny * G.nt, G.nx, G.pitch, ctx->adiag64,
-                                         ctx->b64, ctx->flags + 1, ctx->stream);
+    // flags[7] tells when a cell's observations did not follow one another
+    hipError_t e = hipSuccess;
+    for (bool direct : {true, false}) {
+        if (!direct) {
+            // b64 follows adiag64
+            e = hipMemsetAsync(ctx->adiag64, 0, l.mu64 - l.adiag64, ctx->stream);
+            if (e == hipSuccess)
+                e = hipMemsetAsync(ctx->flags + 7, 0, sizeof(uint32_t), ctx->stream);
+        }
+        if (e == hipSuccess)
+            e = gabp::launch_obs_fold(nobs, dc, dy, dv, s2, (int64_t)G.nx * G.ny * G.nt, G.nx,
+                                      G.pitch, ctx->adiag64, ctx->b64, ctx->flags + 1,
+                                      direct ? ctx->flags + 7 : nullptr, ctx->stream);
+        if (e == hipSuccess) {
+            if (esize == 4)
+                hipLaunchKernelGGL((gabp::st::k_node_init<float>), dim3(node_blocks(G)), dim3(256),
+                                   0, ctx->stream, G, ctx->adiag64, ctx->b64, prior_mean,
+                                   (float *)ctx->aw, (float *)ctx->bw, ctx->flags + 1);
+            else
+                hipLaunchKernelGGL((gabp::st::k_node_init<double>), dim3(node_blocks(G)), dim3(256),
+                                   0, ctx->stream, G, ctx->adiag64, ctx->b64, prior_mean,
+                                   (double *)ctx->aw, (double *)ctx->bw, ctx->flags + 1);
+            e = hipGetLastError();
+        }
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(ctx->host_flags, ctx->flags, 8 * sizeof(uint32_t),
+                               hipMemcpyDeviceToHost, ctx->stream);
+        const hipError_t es = hipStreamSynchronize(ctx->stream);
+        if (e == hipSuccess) e = es;
+        if (e != hipSuccess || ctx->host_flags[7] == 0u) break;
+    }
     (void)hipFree(tc);
     (void)hipFree(ty);
     (void)hipFree(tv);
-    if (e == hipSuccess) {
-        if (esize == 4)
-            hipLaunchKernelGGL((gabp::st::k_node_init<float>), dim3(node_blocks(G)), dim3(256), 0,
-                               ctx->stream, G, ctx->adiag64, ctx->b64, prior_mean, (float *)ctx->aw, (float *)ctx->bw,
-                               ctx->flags + 1);
-        else
-            hipLaunchKernelGGL((gabp::st::k_node_init<double>), dim3(node_blocks(G)), dim3(256), 0,
-                               ctx->stream, G, ctx->adiag64, ctx->b64, prior_mean, (double *)ctx->aw, (double *)ctx->bw,
-                               ctx->flags + 1);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(ctx->host_flags, ctx->flags, 8 * sizeof(uint32_t),
-                           hipMemcpyDeviceToHost, ctx->stream);
-    const hipError_t es = hipStreamSynchronize(ctx->stream);
-    if (e == hipSuccess) e = es;
     if (e != hipSuccess) {
         ctx->err = std::string("set-up failed: ") + hipGetErrorString(e);
         return bail(GABP_E_DEVICE);
