@@ -72,10 +72,36 @@ __global__ __launch_bounds__(256) void k_node_init(Grid G, double *__restrict__ 
     bw[i] = (T)b;
 }
 
+// Node k of the dense order (x fastest, then y, then t) with its plane index; its
+// neighbours' plane indices (its own where there is none).
+struct NodeAt {
+    int x, y, t;
+    uint32_t i;
+};
+__device__ __forceinline__ NodeAt node_at(const Grid &G, uint32_t k) {
+    NodeAt n;
+    const uint32_t row = k / (uint32_t)G.nx, t = row / (uint32_t)G.ny;
+    n.x = (int)(k - row * (uint32_t)G.nx);
+    n.y = (int)(row - t * (uint32_t)G.ny);
+    n.t = (int)t;
+    n.i = t * (uint32_t)G.slice + (uint32_t)(n.y * G.pitch + n.x);
+    return n;
+}
+__device__ __forceinline__ bool nbr_at(const Grid &G, const NodeAt &n, int d, uint32_t &j, int &xn,
+                                       int &yn) {
+    int tn;
+    const bool ok = nbr(G, n.x, n.y, n.t, d, xn, yn, tn);
+    j = ok ? (uint32_t)tn * (uint32_t)G.slice + (uint32_t)(yn * G.pitch + xn) : n.i;
+    return ok;
+}
+
 // --------------------------------------------------------------------------
 // Marginals (Compute Marginal) in FP64: Lam = A_ii + c sum Lam_{k->i},
 // th = b_i + c sum th_{k->i}, mu = th / Lam, var = 1 / Lam.  Writes the
-// pitched mean plane read by the residual and, when given, dense outputs.
+// pitched mean plane read by the residual and, when given, dense outputs.  Bound
+// by reading the messages: all 76 loads of a node are issued before the first use
+// (one direction after the other: 512^2 x 64 FP32 1500 -> 1033 us, 5.0 TB/s;
+// 100 x 75 x 12 35 -> 10 us).
 // --------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(256) void k_post(Grid G, const T *__restrict__ m,
@@ -87,28 +113,38 @@ __global__ __launch_bounds__(256) void k_post(Grid G, const T *__restrict__ m,
     const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t nodes = (int64_t)G.nx * G.ny * G.nt;
     if (k >= nodes) return;
-    const int x = (int)(k % G.nx);
-    const int y = (int)((k / G.nx) % G.ny);
-    const int t = (int)(k / ((int64_t)G.nx * G.ny));
-    const int64_t i = (int64_t)t * G.slice + (int64_t)y * G.pitch + x;
-    double sl = 0.0, st = 0.0;
+    const NodeAt n = node_at(G, (uint32_t)k);
+    T lin[kDeg], tin[kDeg];
+    bool ok[kDeg];
+#pragma unroll
     for (int d = 0; d < kDeg; ++d) {
-        int xn, yn, tn;
-        if (!nbr(G, x, y, t, d, xn, yn, tn)) continue;
-        const int64_t j = (int64_t)tn * G.slice + (int64_t)yn * G.pitch + xn;
-        sl += (double)(m + (size_t)(d ^ 1) * G.plane)[j];
-        st += (double)(m + (size_t)(kDeg + (d ^ 1)) * G.plane)[j];
+        uint32_t j;
+        int xn, yn;
+        ok[d] = nbr_at(G, n, d, j, xn, yn);
+        lin[d] = (m + (size_t)(d ^ 1) * G.plane)[j];
+        tin[d] = (m + (size_t)(kDeg + (d ^ 1)) * G.plane)[j];
     }
-    const double bl = adiag64[i] + G.c * sl;
-    const double bt = b64[i] + G.c * st;
+    const double a = adiag64[n.i], b = b64[n.i];
+    double sl = 0.0, st = 0.0;
+#pragma unroll
+    for (int d = 0; d < kDeg; ++d) {
+        sl += ok[d] ? (double)lin[d] : 0.0;
+        st += ok[d] ? (double)tin[d] : 0.0;
+    }
+    const double bl = a + G.c * sl;
+    const double bt = b + G.c * st;
     const double mu = bt / bl;
-    mu_plane[i] = mu;
+    mu_plane[n.i] = mu;
     if (mean) mean[k] = mu;
     if (var) var[k] = 1.0 / bl;
 }
 
 // FP64 residual partials: workgroup g sums (A mu - b)_i^2 and b_i^2 over the
-// nodes g*256 + l + k*256*gridDim (fixed order), wave64 butterfly then LDS.
+// nodes g*256 + l + k*256*gridDim (fixed order), wave64 butterfly then LDS.  The
+// means come from the caches but for the first touch; a node's 38 loads are
+// issued together, the relation of every direction is known at compile time
+// (decided for each of them as it ran: 512^2 x 64 1600 -> 650 us, 100 x 75 x 12
+// 30 -> 9.8 us).
 __global__ __launch_bounds__(256) void k_resid(Grid G, const double *__restrict__ mu,
                                                const double *__restrict__ adiag64,
                                                const double *__restrict__ b64,
@@ -118,23 +154,32 @@ __global__ __launch_bounds__(256) void k_resid(Grid G, const double *__restrict_
     double rr = 0.0, bb = 0.0;
     for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < nodes;
          k += (int64_t)gridDim.x * 256) {
-        const int x = (int)(k % G.nx);
-        const int y = (int)((k / G.nx) % G.ny);
-        const int t = (int)(k / ((int64_t)G.nx * G.ny));
-        const int64_t i = (int64_t)t * G.slice + (int64_t)y * G.pitch + x;
-        const int kind = slice_kind(G, t);
-        const double gi = (double)(axis_g(x, G.nx, G.bcx) + axis_g(y, G.ny, G.bcy));
-        double r = adiag64[i] * mu[i];
+        const NodeAt n = node_at(G, (uint32_t)k);
+        const double *blk = G.blk[slice_kind(G, n.t)];
+        const double gi = (double)(axis_g(n.x, G.nx, G.bcx) + axis_g(n.y, G.ny, G.bcy));
+        double v[kDeg];
+#pragma unroll
         for (int d = 0; d < kDeg; ++d) {
-            int xn, yn, tn;
-            if (!nbr(G, x, y, t, d, xn, yn, tn)) continue;
-            const int64_t j = (int64_t)tn * G.slice + (int64_t)yn * G.pitch + xn;
-            const double gj = (double)(axis_g(xn, G.nx, G.bcx) + axis_g(yn, G.ny, G.bcy));
-            r += coef<double>(d < 12 ? G.blk[kind] : G.blk[3], scls(d), gi, gj) * mu[j];
+            uint32_t j;
+            int xn, yn;
+            nbr_at(G, n, d, j, xn, yn);
+            v[d] = mu[j];
         }
-        r -= b64[i];
+        const double b = b64[n.i];
+        double r = adiag64[n.i] * mu[n.i];
+#pragma unroll
+        for (int d = 0; d < kDeg; ++d) {
+            uint32_t j;
+            int xn, yn;
+            const bool ok = nbr_at(G, n, d, j, xn, yn);
+            const double gj = scls(d) != 1 ? 0.0
+                                           : (double)(axis_g(xn, G.nx, G.bcx) +
+                                                      axis_g(yn, G.ny, G.bcy));
+            r += ok ? coef<double>(d < 12 ? blk : G.blk[3], scls(d), gi, gj) * v[d] : 0.0;
+        }
+        r -= b;
         rr += r * r;
-        bb += b64[i] * b64[i];
+        bb += b * b;
     }
     rr = wave_sum(rr);
     bb = wave_sum(bb);
