@@ -671,8 +671,43 @@ __global__ __launch_bounds__(256) void k_warm_loss(const float *__restrict__ pre
 
 // Input features of a lattice problem, NHWC BF16 [ny][nx][16]: channel 0 the
 // observation mask, 1 the mean observed value (0 where unobserved), 2 the
-// log prior scale kappa (shifted), the rest zero.  cnt/sum are FP32
-// scratch planes of nx*ny, zeroed by the caller.
+// log prior scale kappa (shifted), the rest zero.  cnt/sum are FP32 scratch
+// planes of nx*ny.  Bound by writing the features, 32 bytes a cell in two 16-byte
+// stores: every cell's are written as unobserved, together with zeros into the
+// scratch of the observed cells, then the observations are added up there and
+// those cells' two channels written over.  Clearing the scratch and reading it
+// back for every cell, with 2-byte stores, took 27 us on 1024^2 cells with 6 %
+// observed, this 20.  ALIGNED: x is 16-byte aligned.
+template <bool ALIGNED>
+__global__ __launch_bounds__(256) void k_feat_fill(long N, float kfeat, __bf16 *__restrict__ x,
+                                                   long n, const int64_t *__restrict__ cell,
+                                                   float *__restrict__ cnt,
+                                                   float *__restrict__ sum) {
+    const long p = (long)blockIdx.x * 256 + threadIdx.x;
+    if (p < n) {
+        const int64_t c = cell[p];
+        if (c >= 0 && c < N) {
+            cnt[c] = 0.0f;
+            sum[c] = 0.0f;
+        }
+    }
+    if (p >= N) return;
+    typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+    bf16x8 a = {}, b = {};
+    a[2] = (__bf16)kfeat;
+    __bf16 *o = x + p * 16;
+    if (ALIGNED) {
+        ((bf16x8 *)o)[0] = a;
+        ((bf16x8 *)o)[1] = b;
+    } else {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            o[k] = a[k];
+            o[8 + k] = b[k];
+        }
+    }
+}
+
 __global__ __launch_bounds__(256) void k_feat_scatter(long n, const int64_t *__restrict__ cell,
                                                       const double *__restrict__ yv, long N,
                                                       float *__restrict__ cnt,
@@ -687,23 +722,16 @@ __global__ __launch_bounds__(256) void k_feat_scatter(long n, const int64_t *__r
 
 // p[0 .. n) = 0 (a kernel, not a memset, so that callers may capture it in
 // a graph)
-__global__ __launch_bounds__(256) void k_zero_f32(float *__restrict__ p, long n) {
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = 0.0f;
-}
-
-__global__ __launch_bounds__(256) void k_feat_build(long N, const float *__restrict__ cnt,
-                                                    const float *__restrict__ sum, float kfeat,
-                                                    __bf16 *__restrict__ x) {
-    const long p = (long)blockIdx.x * 256 + threadIdx.x;
-    if (p >= N) return;
-    const float c = cnt[p];
-    __bf16 *o = x + p * 16;
-    o[0] = (__bf16)(c > 0.0f ? 1.0f : 0.0f);
-    o[1] = (__bf16)(c > 0.0f ? sum[p] / c : 0.0f);
-    o[2] = (__bf16)kfeat;
-#pragma unroll
-    for (int k = 3; k < 16; ++k) o[k] = (__bf16)0.0f;
+__global__ __launch_bounds__(256) void k_feat_observed(long n, const int64_t *__restrict__ cell,
+                                                       long N, const float *__restrict__ cnt,
+                                                       const float *__restrict__ sum,
+                                                       __bf16 *__restrict__ x) {
+    const long k = (long)blockIdx.x * 256 + threadIdx.x;
+    if (k >= n) return;
+    const int64_t c = cell[k];
+    if (c < 0 || c >= N) return;
+    x[c * 16] = (__bf16)1.0f;
+    x[c * 16 + 1] = (__bf16)(sum[c] / cnt[c]);
 }
 
 // Warm start of the messages from a prediction (mean mu^ and log(-Lam^) per
@@ -849,14 +877,23 @@ hipError_t scratch_address(float **out) {
 // (2 N floats, cleared here by a kernel).
 hipError_t features_into(int64_t nobs, const int64_t *cell, const double *y, long N,
                          double kappa, float *scr, void *x_bf16, hipStream_t s) {
-    hipLaunchKernelGGL(gabp::k_zero_f32, dim3((unsigned)((2 * N + 255) / 256)), dim3(256), 0, s,
-                       scr, 2 * N);
-    if (nobs > 0)
-        hipLaunchKernelGGL(gabp::k_feat_scatter, dim3((unsigned)((nobs + 255) / 256)), dim3(256), 0, s,
-                           (long)nobs, cell, y, N, scr, scr + N);
     const float kf = (float)(std::log(kappa) + 2.5);
-    hipLaunchKernelGGL(gabp::k_feat_build, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, N,
-                       (const float *)scr, (const float *)(scr + N), kf, (__bf16 *)x_bf16);
+    const dim3 cells((unsigned)((std::max(N, (long)nobs) + 255) / 256));
+    const dim3 obs((unsigned)((nobs + 255) / 256));
+    float *cnt = scr, *sum = scr + N;
+    __bf16 *x = (__bf16 *)x_bf16;
+    if ((uintptr_t)x_bf16 % 16 == 0)
+        hipLaunchKernelGGL(gabp::k_feat_fill<true>, cells, dim3(256), 0, s, N, kf, x, (long)nobs,
+                           cell, cnt, sum);
+    else
+        hipLaunchKernelGGL(gabp::k_feat_fill<false>, cells, dim3(256), 0, s, N, kf, x, (long)nobs,
+                           cell, cnt, sum);
+    if (nobs > 0) {
+        hipLaunchKernelGGL(gabp::k_feat_scatter, obs, dim3(256), 0, s, (long)nobs, cell, y, N, cnt,
+                           sum);
+        hipLaunchKernelGGL(gabp::k_feat_observed, obs, dim3(256), 0, s, (long)nobs, cell, N,
+                           (const float *)cnt, (const float *)sum, x);
+    }
     return hipGetLastError();
 }
 
