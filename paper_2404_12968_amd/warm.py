@@ -73,6 +73,15 @@ class WarmNet:
                 pred = yf
         return acts, pred
 
+    def _infer(self, x: torch.Tensor) -> torch.Tensor:
+        """pred of ``forward`` alone (the last layer writes no BF16 output)."""
+        pred = None
+        for l in range(len(DILATIONS)):
+            last = l == len(DILATIONS) - 1
+            x, pred = G.gabp_conv3x3_fwd(x, self.wb[l], self.b[l], COUT[l], DILATIONS[l],
+                                         bool(RELU[l]), want_bf16=not last, want_f32=last)
+        return pred
+
     # -- training ----------------------------------------------------------
     def backward(self, acts, grad):
         """Gradients (dw, db) of every layer from the loss gradient (FP32)."""
@@ -332,8 +341,7 @@ def train(net: WarmNet, ts: TrainingSet, steps: int, batch: int = 8, crop: int =
 def predict(net: WarmNet, prob: I.Problem, device="cuda") -> torch.Tensor:
     """Prediction [ny, nx, 16] FP32 for one problem."""
     x = G.gabp_warm_features(prob.cells, prob.y, prob.nx, prob.ny, prob.kappa, device=device)
-    _, pred = net.forward(x.unsqueeze(0).contiguous())
-    return pred[0].contiguous()
+    return net._infer(x.unsqueeze(0).contiguous())[0].contiguous()
 
 
 def warm_solve(net: WarmNet, prob: I.Problem, max_iters: int = 300000, probe: int = 100,
