@@ -485,6 +485,17 @@ gabp_status gabp_adam_step(float *w, const float *g, float *m, float *v, void *w
                            double lr, double beta1, double beta2, double eps, int32_t step,
                            void *stream);
 
+/* gabp_adam_step on n_tensors of them with one set of parameters, 16 to a launch. */
+typedef struct {
+    float *w;
+    const float *g;
+    float *m, *v;
+    void *w_bf16;
+    int64_t n;
+} gabp_adam_tensor;
+gabp_status gabp_adam_steps(int32_t n_tensors, const gabp_adam_tensor *t, double lr, double beta1,
+                            double beta2, double eps, int32_t step, void *stream);
+
 /* Warm-start loss on P pixels: mean of (pred[.,0] - mu_t)^2 plus lam_weight
  * times the mean over existing edges (valid[d][p] > 0) of
  * (pred[.,1+d] - lam_t[d][p])^2, d < ndir.  Writes the gradient grad

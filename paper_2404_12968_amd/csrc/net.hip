@@ -604,21 +604,27 @@ __global__ __launch_bounds__(32 * kSumRuns) void k_sum_partials(const float *__r
 }
 
 // Adam step on FP32 master weights (bias-corrected moments); refreshes the
-// BF16 copy used by the matrix cores.
-__global__ __launch_bounds__(256) void k_adam(float *__restrict__ w, const float *__restrict__ g,
-                                              float *__restrict__ m, float *__restrict__ v,
-                                              __bf16 *__restrict__ wb, long n, float lr, float b1,
-                                              float b2, float eps, float c1, float c2) {
+// BF16 copy used by the matrix cores.  A tensor has 32 to 9216 elements, so a launch
+// takes its 3 us whatever it does: workgroup row blockIdx.y takes one of up to 16
+// tensors (a network's twelve, one launch each: 57 us of a training step, XXX now).
+constexpr int kAdamTensors = 16;
+struct AdamList {
+    gabp_adam_tensor t[kAdamTensors];
+};
+
+__global__ __launch_bounds__(256) void k_adam(AdamList list, float lr, float b1, float b2,
+                                              float eps, float c1, float c2) {
+    const gabp_adam_tensor &t = list.t[blockIdx.y];
     const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float wi = w[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-    w[i] = wi;
-    if (wb) wb[i] = (__bf16)wi;
+    if (i >= t.n) return;
+    const float gi = t.g[i];
+    const float mi = b1 * t.m[i] + (1.0f - b1) * gi;
+    const float vi = b2 * t.v[i] + (1.0f - b2) * gi * gi;
+    t.m[i] = mi;
+    t.v[i] = vi;
+    const float wi = t.w[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    t.w[i] = wi;
+    if (t.w_bf16) ((__bf16 *)t.w_bf16)[i] = (__bf16)wi;
 }
 
 // Loss and output gradient.  pred[p][16]: channel 0 the mean, channels 1..12
@@ -1056,17 +1062,35 @@ gabp_status gabp_conv3x3_bwd(const void *x, const void *y, const float *dy, int3
     return GABP_OK;
 }
 
+gabp_status gabp_adam_steps(int32_t n_tensors, const gabp_adam_tensor *t, double lr, double beta1,
+                            double beta2, double eps, int32_t step, void *stream) {
+    if (n_tensors < 0 || (n_tensors > 0 && !t) || step < 1)
+        return nfail(GABP_E_INVALID, "adam_steps: bad arguments");
+    for (int k = 0; k < n_tensors; ++k)
+        if (!t[k].w || !t[k].g || !t[k].m || !t[k].v || t[k].n < 0)
+            return nfail(GABP_E_INVALID, "adam_step: bad arguments");
+    const float c1 = (float)(1.0 - std::pow(beta1, step)), c2 = (float)(1.0 - std::pow(beta2, step));
+    for (int k = 0; k < n_tensors; k += gabp::kAdamTensors) {
+        gabp::AdamList list{};
+        const int n = std::min(gabp::kAdamTensors, n_tensors - k);
+        int64_t most = 0;
+        for (int q = 0; q < n; ++q) {
+            list.t[q] = t[k + q];
+            most = std::max(most, t[k + q].n);
+        }
+        hipLaunchKernelGGL(gabp::k_adam, dim3((unsigned)((most + 255) / 256), (unsigned)n), dim3(256),
+                           0, (hipStream_t)stream, list, (float)lr, (float)beta1, (float)beta2,
+                           (float)eps, c1, c2);
+        NHIP(hipGetLastError());
+    }
+    return GABP_OK;
+}
+
 gabp_status gabp_adam_step(float *w, const float *g, float *m, float *v, void *w_bf16, int64_t n,
                            double lr, double beta1, double beta2, double eps, int32_t step,
                            void *stream) {
-    if (!w || !g || !m || !v || n < 0 || step < 1)
-        return nfail(GABP_E_INVALID, "adam_step: bad arguments");
-    const float c1 = (float)(1.0 - std::pow(beta1, step)), c2 = (float)(1.0 - std::pow(beta2, step));
-    hipLaunchKernelGGL(gabp::k_adam, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                       (hipStream_t)stream, w, g, m, v, (__bf16 *)w_bf16, (long)n, (float)lr,
-                       (float)beta1, (float)beta2, (float)eps, c1, c2);
-    NHIP(hipGetLastError());
-    return GABP_OK;
+    const gabp_adam_tensor t{w, g, m, v, w_bf16, n};
+    return gabp_adam_steps(1, &t, lr, beta1, beta2, eps, step, stream);
 }
 
 gabp_status gabp_warm_loss(const float *pred, const float *mu_t, const float *lam_t,

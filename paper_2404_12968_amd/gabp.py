@@ -122,6 +122,8 @@ _SIGS = {
                           _P, _P, _P, _P, ctypes.c_size_t, _P], ctypes.c_int),
     "gabp_adam_step": ([_P, _P, _P, _P, _P, ctypes.c_int64, ctypes.c_double, ctypes.c_double,
                         ctypes.c_double, ctypes.c_double, ctypes.c_int32, _P], ctypes.c_int),
+    "gabp_adam_steps": ([ctypes.c_int32, _P, ctypes.c_double, ctypes.c_double, ctypes.c_double,
+                         ctypes.c_double, ctypes.c_int32, _P], ctypes.c_int),
     "gabp_warm_loss": ([_P, _P, _P, _P, ctypes.c_int64, ctypes.c_int32, ctypes.c_double, _P, _P,
                         _P, _P], ctypes.c_int),
     "gabp_warm_features_noalloc": ([ctypes.c_int64, _P, _P, ctypes.c_int64, ctypes.c_int64,
@@ -581,6 +583,19 @@ def gabp_adam_step(w, g, m, v, w_bf16, lr, beta1, beta2, eps, step, stream=None)
     _ncheck(_lib.gabp_adam_step(_ptr(w), _ptr(g), _ptr(m), _ptr(v), _ptr(w_bf16), int(w.numel()),
                                 float(lr), float(beta1), float(beta2), float(eps), int(step),
                                 _stream_handle(stream)))
+
+
+class gabp_adam_tensor(ctypes.Structure):
+    _fields_ = [("w", _P), ("g", _P), ("m", _P), ("v", _P), ("w_bf16", _P), ("n", ctypes.c_int64)]
+
+
+def gabp_adam_steps(tensors, lr, beta1, beta2, eps, step, stream=None) -> None:
+    """gabp_adam_step on a list of (w, g, m, v, w_bf16 or None)."""
+    t = (gabp_adam_tensor * len(tensors))(*[
+        gabp_adam_tensor(_ptr(w), _ptr(g), _ptr(m), _ptr(v), _ptr(wb), int(w.numel()))
+        for w, g, m, v, wb in tensors])
+    _ncheck(_lib.gabp_adam_steps(len(tensors), t, float(lr), float(beta1), float(beta2),
+                                 float(eps), int(step), _stream_handle(stream)))
 
 
 def gabp_warm_loss(pred, mu_t, lam_t, valid, ndir, lam_weight, stream=None):

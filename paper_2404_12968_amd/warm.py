@@ -98,11 +98,9 @@ class WarmNet:
     def adam(self, dws, dbs, lr, beta1=0.9, beta2=0.999, eps=1e-8):
         self.step += 1
         L = len(DILATIONS)
-        for l in range(L):
-            G.gabp_adam_step(self.w[l], dws[l], self.m[l], self.v[l], self.wb[l], lr, beta1, beta2,
-                             eps, self.step)
-            G.gabp_adam_step(self.b[l], dbs[l], self.m[L + l], self.v[L + l], None, lr, beta1,
-                             beta2, eps, self.step)
+        G.gabp_adam_steps([(self.w[l], dws[l], self.m[l], self.v[l], self.wb[l]) for l in range(L)] +
+                          [(self.b[l], dbs[l], self.m[L + l], self.v[L + l], None) for l in range(L)],
+                          lr, beta1, beta2, eps, self.step)
 
     # -- persistence -------------------------------------------------------
     def save(self, path: str, meta: Optional[Dict] = None) -> None:
