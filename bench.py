@@ -1,9 +1,8 @@
 """Benchmark of the lattice GaBP hot path on one MI355X.
 
 One step = one check interval of the solver (`gabp_solve` with a 10-iteration
-chunk): 10 flooding iterations (once the precision messages froze, five
-two-iteration launches replayed from a recorded graph), then the FP64
-posterior mean, the FP64 residual reduction and its read-back (the unit of
+chunk): 10 flooding iterations (once the precision messages froze, two launches
+of five on this lattice), then the FP64 posterior mean, the FP64 residual reduction and its read-back (the unit of
 work the convergence driver repeats).  Default workload: the 8192 x 4096 global-scale lattice (periodic
 in x, zero-flux in y, 13-point prior, kappa 0.02, 60 satellite-like tracks,
 ~5 % coverage, FP32 messages, FP64 residual).
@@ -30,8 +29,7 @@ HBM_PEAK_GBS = 8000.0
 METRIC = "edge-message updates/s + HBM GB/s; time to 1e-6 rel. residual, warm vs cold"
 ITERS_PER_STEP = 10
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "k_iter_global8192_traffic.md")
-PHASE_KERNEL = {"full": "k_iter_direct", "theta": "k_iter_theta", "theta2": "k_iter_theta2",
-                "theta2w": "k_iter_theta2w"}
+PHASE_KERNEL = {"full": "k_iter_deep_full", "theta": "k_iter_deep"}
 
 
 def edge_count(nx, ny, alpha, bcx, bcy):
@@ -48,7 +46,8 @@ def edge_count(nx, ny, alpha, bcx, bcy):
     return total
 
 
-ITER_SOURCES = ("iter.hip", "iter_node.h", "pair_tile.h", "walk_strip.h", "numerics.h", "lattice.h")
+ITER_SOURCES = ("iter.hip", "iter_node.h", "deep_tile.h", "deep_full.h", "pair_tile.h",
+                "walk_strip.h", "numerics.h", "lattice.h")
 ST_SOURCES = ("st_iter.h", "numerics.h", "lattice.h")
 ST_TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "spacetime512x512x64_traffic.md")
 
@@ -80,14 +79,13 @@ def _summary_value(path, digest, key):
     return float(t.group(1))
 
 
-def measured_traffic(phase, rpt, workload="global8192"):
-    """HBM bytes per launch of the timed kernel (its tile shape) from the
-    committed PMC summary of the 8192 x 4096 workload, if that was taken on
+def measured_traffic(phase, iters_per_launch, workload="global8192"):
+    """HBM bytes per launch of the timed kernel (so many iterations each) from
+    the committed PMC summary of the 8192 x 4096 workload, if that was taken on
     the current kernel source."""
     if workload != "global8192":
         return None
-    shape = {"theta2": f"pair{rpt}", "theta2w": f"walk{-rpt}"}.get(phase, f"rpt{rpt}")
-    key = f"{PHASE_KERNEL[phase]}_{shape}_traffic_bytes_per_launch"
+    key = f"{PHASE_KERNEL[phase]}_s{iters_per_launch:g}_traffic_bytes_per_launch"
     return _summary_value(TRAFFIC_SUMMARY, kernel_source_digest(), key)
 
 
@@ -933,8 +931,8 @@ def main(argv=None):
     stream = ctx.stream
 
     def step(ev0=None, ev1=None):
-        # one check interval of the solver: ITERS_PER_STEP iterations (a
-        # recorded chunk graph), FP64 marginals and residual, read-back
+        # one check interval of the solver: ITERS_PER_STEP iterations, FP64
+        # marginals and residual, read-back
         if ev0 is not None:
             ev0.record(stream)
         _, _, rel = G.gabp_solve(ctx, ITERS_PER_STEP, prob.damping, 0.0, ITERS_PER_STEP)
@@ -955,30 +953,6 @@ def main(argv=None):
         it_ms = sum(a.elapsed_time(b) for a, b in evs) / (nsteps * ITERS_PER_STEP)
         return wall, it_ms, r
 
-    kernels = {}
-    # phase 1: full iteration kernel.  Freezing is only detected by residual
-    # checks, so iterations without them stay on the full kernel.
-    rpt_full = G.gabp_autotune(ctx, 3, prob.damping)
-    torch.cuda.synchronize()
-    evf = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))
-           for _ in range(3)]
-    for a, b in evf:
-        a.record(stream)
-        G.gabp_iterate(ctx, ITERS_PER_STEP, prob.damping)
-        b.record(stream)
-    torch.cuda.synchronize()
-    ms = sum(a.elapsed_time(b) for a, b in evf) / (3 * ITERS_PER_STEP)
-    kernels["full"] = {"iter_ms": ms, "algorithmic_bytes": alg_full,
-                       "gbps": alg_full / (ms * 1e-3) / 1e9, "rows_per_thread": rpt_full}
-    step()
-    # run on until the precision messages freeze (bounded)
-    while G.gabp_precision_frozen(ctx) < 0 and G.gabp_iteration_count(ctx)[0] < 2000:
-        step()
-    frozen_at = G.gabp_precision_frozen(ctx)
-    phase = "theta" if frozen_at >= 0 else "full"
-    rpt = G.gabp_autotune(ctx, 3, prob.damping) if phase == "theta" else rpt_full
-    pair = G.gabp_get_tile(ctx)[1] if phase == "theta" else 0
-
     def event_ms(fn, reps):
         torch.cuda.synchronize()
         ev = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))
@@ -990,14 +964,59 @@ def main(argv=None):
         torch.cuda.synchronize()
         return sum(a.elapsed_time(b_) for a, b_ in ev) / reps
 
+    def launch_cost():
+        """(ms, iterations) of a launch of several iterations: two calls that
+        differ in 60 iterations, both ending on one single iteration."""
+        t, n = [], []
+        for its in (61, 121):
+            before = G.gabp_launch_counts(ctx)["pair_tiles"]
+            t.append(event_ms(lambda: G.gabp_iterate(ctx, its, prob.damping), 3))
+            n.append((G.gabp_launch_counts(ctx)["pair_tiles"] - before) / 3)
+        return (t[1] - t[0]) / (n[1] - n[0]), 60 / (n[1] - n[0])
+
+    def several(alg):
+        """Figures of the several-iteration launches: each must read its inputs
+        and write its outputs once, the bytes of one single iteration."""
+        ms, its = launch_cost()
+        return {"launch_ms": ms, "iters_per_launch": its, "iter_ms": ms / its,
+                "algorithmic_bytes": alg, "gbps": alg / (ms * 1e-3) / 1e9,
+                "single_pass_equivalent_gbps": its * alg / (ms * 1e-3) / 1e9}
+
+    kernels = {}
+    # phase 1: full iterations, as the solver launches them.  Freezing is only
+    # detected by residual checks, so iterations without them stay full.
+    G.gabp_iterate(ctx, ITERS_PER_STEP, prob.damping)
+    kernels["full"] = several(alg_full)
+    step()
+    # run on until the precision messages freeze (bounded)
+    while G.gabp_precision_frozen(ctx) < 0 and G.gabp_iteration_count(ctx)[0] < 2000:
+        step()
+    frozen_at = G.gabp_precision_frozen(ctx)
+    phase = "theta" if frozen_at >= 0 else "full"
     if phase == "theta":
-        # single-iteration information kernel, then the two-iteration kernel:
-        # a call of 2m+1 iterations is m pair launches and one single launch
+        kernels["theta"] = several(alg_theta)
+    for _ in range(args.warmup):
+        step()
+    wall, iter_ms, rel = timed(args.steps)
+    total_iters = args.steps * ITERS_PER_STEP
+    value = E * total_iters / wall
+    before_timing = G.gabp_iteration_count(ctx)[0] - total_iters
+    kname = PHASE_KERNEL[phase]
+    launch_ms, its_launch = kernels[phase]["launch_ms"], kernels[phase]["iters_per_launch"]
+    alg_launch = kernels[phase]["algorithmic_bytes"]
+    traffic = measured_traffic(phase, its_launch, prob.name)
+    achieved = alg_launch / (launch_ms * 1e-3) / 1e9
+
+    if phase == "theta":
+        # the other launch shapes, on the same context after the timed steps:
+        # one iteration per launch, then two on tiles of a height or by the
+        # column-strip walker in bands (negative); a call of 2m+1 iterations is
+        # m launches of two and a single one
+        rpt = G.gabp_autotune(ctx, 3, prob.damping)
         G.gabp_set_tile(ctx, rpt, 0)
         ms1 = event_ms(lambda: G.gabp_iterate(ctx, ITERS_PER_STEP, prob.damping), 3) / ITERS_PER_STEP
-        kernels["theta"] = {"iter_ms": ms1, "algorithmic_bytes": alg_theta,
-                            "gbps": alg_theta / (ms1 * 1e-3) / 1e9, "rows_per_thread": rpt}
-        # tile heights, then the column-strip walker's bands (negative)
+        kernels["theta_single"] = {"iter_ms": ms1, "algorithmic_bytes": alg_theta,
+                                   "gbps": alg_theta / (ms1 * 1e-3) / 1e9, "rows_per_thread": rpt}
         for p2 in ((4, 8, 12, 16, 32, -2, -4, -8) if prob.dtype == "f32" else (4, -2)):
             G.gabp_set_tile(ctx, rpt, p2)
             m = 10
@@ -1009,33 +1028,6 @@ def main(argv=None):
                 "gbps": alg_theta / (ms2 * 1e-3) / 1e9,
                 "single_pass_equivalent_gbps": 2 * alg_theta / (ms2 * 1e-3) / 1e9,
                 "pair_rows": p2}
-        G.gabp_set_tile(ctx, rpt, pair)
-    for _ in range(args.warmup):
-        step()
-    wall, iter_ms, rel = timed(args.steps)
-    if phase == "full":
-        kernels["full_timed"] = {"iter_ms": iter_ms}
-    total_iters = args.steps * ITERS_PER_STEP
-    value = E * total_iters / wall
-    if phase == "theta" and pair != 0:
-        # two iterations per launch with the intermediate one kept on chip:
-        # the launch must read its inputs and write its outputs once, the
-        # bytes of one single-iteration pass
-        kname = "k_iter_theta2" if pair > 0 else "k_iter_theta2w"
-        launch_ms = kernels[f"theta_pair{pair}" if pair > 0 else f"theta_walk{-pair}"]["launch_ms"]
-        alg_launch = alg_theta
-        traffic = measured_traffic("theta2" if pair > 0 else "theta2w", pair, prob.name)
-    elif phase == "theta":
-        kname = "k_iter_theta"
-        launch_ms = kernels["theta"]["iter_ms"]
-        alg_launch = alg_theta
-        traffic = measured_traffic("theta", rpt, prob.name)
-    else:
-        kname = "k_iter_direct"
-        launch_ms = kernels["full"]["iter_ms"]
-        alg_launch = alg_full
-        traffic = measured_traffic("full", rpt, prob.name)
-    achieved = alg_launch / (launch_ms * 1e-3) / 1e9
 
     out = {
         "metric": METRIC,
@@ -1060,17 +1052,15 @@ def main(argv=None):
         "step_ms_per_iteration": iter_ms,
         "rel_residual_after": rel,
         "timed_phase": {"kernel": kname, "precision_frozen_at_iteration": frozen_at,
-                        "rows_per_thread": rpt, "pair_rows": pair,
-                        "iterations_before_timing": G.gabp_iteration_count(ctx)[0] - total_iters},
+                        "iterations_per_launch": its_launch,
+                        "iterations_before_timing": before_timing},
         "kernels": kernels,
         "roofline": {"bound": "hbm", "kernel": kname, "achieved": achieved,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "measured_copy_ceiling": copy_ceiling_gbps(torch, dev),
                      "launch_ms": launch_ms, "algorithmic_bytes_per_launch": alg_launch,
-                     "iterations_per_launch": 2 if kname.startswith("k_iter_theta2") else 1,
-                     "single_pass_equivalent_gbps": (
-                         (2 if kname.startswith("k_iter_theta2") else 1) * alg_launch
-                         / (launch_ms * 1e-3) / 1e9),
+                     "iterations_per_launch": its_launch,
+                     "single_pass_equivalent_gbps": kernels[phase]["single_pass_equivalent_gbps"],
                      "traffic": traffic},
     }
     del ctx

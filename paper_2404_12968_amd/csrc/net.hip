@@ -606,7 +606,7 @@ __global__ __launch_bounds__(32 * kSumRuns) void k_sum_partials(const float *__r
 // Adam step on FP32 master weights (bias-corrected moments); refreshes the
 // BF16 copy used by the matrix cores.  A tensor has 32 to 9216 elements, so a launch
 // takes its 3 us whatever it does: workgroup row blockIdx.y takes one of up to 16
-// tensors (a network's twelve, one launch each: 57 us of a training step, XXX now).
+// tensors (a network's twelve, one launch each: 57 us of a training step, 5 now).
 constexpr int kAdamTensors = 16;
 struct AdamList {
     gabp_adam_tensor t[kAdamTensors];
