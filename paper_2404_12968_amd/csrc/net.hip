@@ -351,18 +351,24 @@ __global__ __launch_bounds__(256, kRowsWaves) void k_conv_rows(
 // runs of chunks) is fixed.
 //
 // Bound by HBM on large inputs (dY, y and x read, dZ written): 8 x 256 x 256 pixels
-// of a 32 -> 32 layer take 44 us, 3.8 TB/s (34 us at the copy rate; transposed
-// copies of dZ and x, then products and four sums, took 204).  Bound by the
-// latency of a chunk's 16 units on small ones: 36 us for 2 x 61 x 93 pixels
-// (544 with a per-pixel path for widths that are no multiple of 8).  The
-// barrier between the dZ wave and the others waits for LDS only, so that
-// loads stay in flight across it.
+// of a 32 -> 32 layer take 41 us, 4.0 TB/s (34 us at the copy rate; transposed
+// copies of dZ and x, then products and four sums, took 204), of a 32 -> 16 layer 27
+// (40).  On small ones by the instructions of a chunk's 16 units, each wave alone on
+// its SIMD: 20 us for 2 x 61 x 93 pixels, 36 with a loaded pixel's bounds worked out
+// in 64 bits for each load, divisions for its column and row in each unit and the
+// fragments' rows selected in every unit (544 with a per-pixel path for widths that
+// are no multiple of 8).  The barrier between the dZ wave and the others waits for LDS
+// only, so that loads stay in flight across it.
 // --------------------------------------------------------------------------
 constexpr int kUnit = 64;       // pixels per unit
 constexpr int kChunk = 1024;    // pixels per workgroup and partial sum
 constexpr int kSumRuns = 16;    // runs of chunks that k_sum_partials forms first
-constexpr int kSpan = 192;      // staged pixels per tap row: 64 + 2 dil where that is at
-                                // most 128, else 64 for each of the three taps
+
+// Staged pixels per tap row, a template argument of k_wgrad so that its loads are
+// straight-line code (with their number a variable the loads were waited for one
+// by one): 64 + 2 dil in a row where that is at most 128, else 64 for each of the
+// three taps.
+inline int wgrad_span(int dil) { return dil <= 16 ? 96 : dil <= 32 ? 128 : 192; }
 
 // Eight pixels of 32 channels, transposed: lane l gets pixels 8 (l / 32) + j
 // (j < 8) of channel l % 32 from LDS rows of 64 bytes per pixel.  `at` and `at4`
@@ -404,7 +410,7 @@ __device__ __forceinline__ void flip_weight(const __bf16 *__restrict__ w, int ci
     wt[idx] = v;
 }
 
-template <int CIN, int COUT>
+template <int CIN, int COUT, int SPAN>
 __global__ __launch_bounds__(256) void k_wgrad(
     const float *__restrict__ dy, const __bf16 *__restrict__ y, int relu,
     const __bf16 *__restrict__ x, int H, int W, int dilx, int dily, int P, int nchunks,
@@ -412,7 +418,7 @@ __global__ __launch_bounds__(256) void k_wgrad(
     const __bf16 *__restrict__ w, __bf16 *__restrict__ wt) {
     constexpr int NN = 9 * CIN;
     // three waves' staged pixels, each followed by a pixel of zeros; dZ, twice
-    constexpr int XB = (kSpan + 1) * 64, ZB = kUnit * 64;
+    constexpr int XB = (SPAN + 1) * 64, ZB = kUnit * 64;
     __shared__ __align__(16) char lds[3 * XB + 2 * ZB];
     if ((int)blockIdx.x >= nchunks) {
         flip_weight(w, CIN, COUT, ((int)blockIdx.x - nchunks) * 256 + (int)threadIdx.x, wt);
@@ -434,31 +440,44 @@ __global__ __launch_bounds__(256) void k_wgrad(
         constexpr int LPP = COUT / 8, PPL = 64 / LPP, NC = kUnit / PPL;   // lanes per pixel, pixels per load
         float f[NC][8];
         bf16x8 yv[NC];
+        // this lane's first element of the chunk's first unit
+        const size_t e0 = (size_t)(c0 + lane / LPP) * COUT + (lane % LPP) * 8;
         auto load_dy = [&](int i) {
+            const size_t e = e0 + (size_t)(i * kUnit) * COUT;
+            if ((i + 1) * kUnit <= c1 - c0) {      // a whole unit (uniform)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) __builtin_memcpy(f[c], dy + e + c * PPL * COUT, 32);
+                if (!relu) return;
+#pragma unroll
+                for (int c = 0; c < NC; ++c) __builtin_memcpy(&yv[c], y + e + c * PPL * COUT, 16);
+                return;
+            }
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
-                const int p = c0 + i * kUnit + c * PPL + lane / LPP;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) f[c][j] = 0.0f;
                 yv[c] = zero_bf16x8();
-                if (p < c1) {
-                    const size_t e = (size_t)p * COUT + (lane % LPP) * 8;
-                    __builtin_memcpy(f[c], dy + e, 32);
-                    if (relu) __builtin_memcpy(&yv[c], y + e, 16);
+                if (i * kUnit + c * PPL + lane / LPP < c1 - c0) {
+                    __builtin_memcpy(f[c], dy + e + c * PPL * COUT, 32);
+                    if (relu) __builtin_memcpy(&yv[c], y + e + c * PPL * COUT, 16);
                 }
             }
         };
         load_dy(0);
         for (int i = 0; i < nu; ++i) {
             bf16x8 z[NC];
+            if (relu) {
 #pragma unroll
-            for (int c = 0; c < NC; ++c)
+                for (int c = 0; c < NC; ++c)
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    float v = f[c][j];
-                    if (relu && !((float)yv[c][j] > 0.0f)) v = 0.0f;
-                    z[c][j] = (__bf16)v;
-                }
+                    for (int j = 0; j < 8; ++j)
+                        z[c][j] = (__bf16)((float)yv[c][j] > 0.0f ? f[c][j] : 0.0f);
+            } else {
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) z[c][j] = (__bf16)f[c][j];
+            }
             if (i + 1 < nu) load_dy(i + 1);
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
@@ -478,47 +497,67 @@ __global__ __launch_bounds__(256) void k_wgrad(
     float bsum = 0.0f;
     char *xs = lds + wave * XB;
     const int oy = (wave - 1) * dily;
-    const bool span = dilx <= 32;              // one staged run serves the three column shifts
+    constexpr bool span = SPAN <= 128;         // one staged run serves the three column shifts
     const int pitch = span ? dilx : kUnit;     // staged pixels between two column shifts
-    const int nstage = span ? kUnit + 2 * dilx : 3 * kUnit;
-    constexpr int LPP = CIN / 8, PPL = 64 / LPP, NS = kSpan / PPL;
+    constexpr int LPP = CIN / 8, PPL = 64 / LPP, NS = SPAN / PPL;
     bf16x8 st[NS];
     // loads of unit i: staged pixel p is pixel (unit's first) + oy W - dil + p, or
-    // + oy W + (c - 1) dil + p % 64 for the run c = p / 64 of a column shift
-    // (pixels outside the batch are not read)
+    // + oy W + (c - 1) dil + p % 64 for the run c = p / 64 of a column shift.  A
+    // run's loads go through a buffer that starts at the chunk's first pixel of it (or
+    // the batch's) and ends with the batch: a pixel past the end reads zeros, and
+    // so does one before the start, at an offset that wraps.
+    struct Run {
+        __amdgpu_buffer_rsrc_t pixels;
+        int off;
+    } run[3];
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        constexpr long kReach = kChunk + 2 * kUnit;   // staged pixels of a run, and past them
+        const long q = (long)c0 + (long)oy * W + (long)(t - 1) * dilx, qb = max(q, 0L);
+        const bool none = q <= -kReach;
+        run[t].pixels = buf_of(x + min(qb, (long)P) * CIN,
+                               none ? 0 : (int)min(max((long)P - qb, 0L), kReach) * CIN * 2);
+        run[t].off = (none ? 0 : (int)(q - qb) * CIN * 2) + lane * 16;
+    }
     auto load_unit = [&](int i) {
-        const long base = (long)c0 + i * kUnit + (long)oy * W;
+        const int u = i * kUnit * CIN * 2;
 #pragma unroll
         for (int c = 0; c < NS; ++c) {
-            if (c * PPL >= nstage) continue;   // uniform
-            const long q = base + (span ? (long)c * PPL - dilx
-                                        : (long)(c * PPL / kUnit - 1) * dilx + c * PPL % kUnit);
-            const int first = (int)min(max(-q, 0L), 64L), last = (int)min(max((long)P - q, 0L), 64L);
-            const int p = lane / LPP;
-            const bool ok = p >= first && p < last && c * PPL + p < nstage;
-            st[c] = load_bf16x8(buf_of(x + q * CIN, 1024), ok ? lane * 16 : kOut);
+            const Run &r = run[span ? 0 : c * PPL / kUnit];
+            st[c] = load_bf16x8(r.pixels,
+                                r.off + u + (span ? c * PPL : c * PPL % kUnit) * CIN * 2);
         }
     };
     const int lo = tr_lane_offset(lane);
     const int lp = lo >> 6;                    // this lane's pixel of a fragment's first read
+    const char *xt[3];                         // of the three column shifts
+#pragma unroll
+    for (int c = 0; c < 3; ++c) xt[c] = xs + lo + c * pitch * 64;
+    // this lane's pixel of the unit: column and image row, carried from unit to unit
+    const unsigned w64 = (unsigned)kUnit / (unsigned)W, wrest = (unsigned)kUnit % (unsigned)W;
+    const unsigned hstep = w64 % (unsigned)H;
+    const unsigned p0 = (unsigned)c0 + (unsigned)lane;
+    unsigned px = p0 % (unsigned)W, py = p0 / (unsigned)W % (unsigned)H;
     load_unit(0);
     for (int i = 0; i < nu; ++i) {
         wave_lds_order();                      // the reads of the unit before are done
 #pragma unroll
-        for (int c = 0; c < NS; ++c) {
-            if (c * PPL >= nstage) continue;
+        for (int c = 0; c < NS; ++c)
             *(bf16x8 *)(xs + (c * PPL + lane / LPP) * 64 + (lane % LPP) * 16) = st[c];
-        }
         if (i + 1 < nu) load_unit(i + 1);
         // which taps of the unit's pixels stay in the image
-        const unsigned p = (unsigned)(c0 + i * kUnit + lane);
-        const unsigned row = p / (unsigned)W;
-        const unsigned px = p - row * (unsigned)W;
-        const bool row_in = p < (unsigned)P && (row % (unsigned)H) + (unsigned)oy < (unsigned)H;
+        const bool row_in = p0 + (unsigned)(i * kUnit) < (unsigned)P && py + (unsigned)oy < (unsigned)H;
         uint64_t in[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c)
             in[c] = __ballot(row_in && px + (unsigned)((c - 1) * dilx) < (unsigned)W);
+        px += wrest;
+        py += hstep;
+        if (px >= (unsigned)W) {
+            px -= (unsigned)W;
+            ++py;
+        }
+        if (py >= (unsigned)H) py -= (unsigned)H;
         lds_barrier();                         // the unit's dZ is there
         bf16x8 af[4];
 #pragma unroll
@@ -530,35 +569,33 @@ __global__ __launch_bounds__(256) void k_wgrad(
                 for (int j = 0; j < 8; ++j) bsum += (float)af[k][j];
             }
         }
-        // LDS rows of the taps' fragments, selected apart from the products so
-        // that reads and products of the whole unit are one block
-        int o[3][4][2];
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
+        // reads and products of the whole unit as one block, the LDS rows of its
+        // fragments constants but for the units with a tap outside the image
+        auto products = [&](auto row) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                o[c][k][0] = lo + (c * pitch + k * 16) * 64;
-                o[c][k][1] = o[c][k][0] + 4 * 64;
+                bf16x8 bf[3];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) bf[c] = tr_frag(row(c, k, 0), row(c, k, 1));
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[k], bf[c], acc[c], 0, 0, 0);
             }
-        if ((in[0] & in[1] & in[2]) != ~0ull) {   // uniform
-            const int zero = kSpan * 64 + (lo & 63);
+        };
+        if ((in[0] & in[1] & in[2]) == ~0ull) {   // uniform
+            products([&](int c, int k, int q) { return xt[c] + (k * 16 + q * 4) * 64; });
+        } else {
+            const char *zero = xs + SPAN * 64 + (lo & 63);
+            const char *o[3][4][2];
 #pragma unroll
             for (int c = 0; c < 3; ++c)
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const uint32_t m = (uint32_t)(in[c] >> (32 * (k / 2))) >> (16 * (k % 2));
-                    if (!((m >> lp) & 1u)) o[c][k][0] = zero;
-                    if (!((m >> (lp + 4)) & 1u)) o[c][k][1] = zero;
+                    o[c][k][0] = (m >> lp) & 1u ? xt[c] + k * 16 * 64 : zero;
+                    o[c][k][1] = (m >> (lp + 4)) & 1u ? xt[c] + (k * 16 + 4) * 64 : zero;
                 }
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            bf16x8 bf[3];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) bf[c] = tr_frag(xs + o[c][k][0], xs + o[c][k][1]);
-#pragma unroll
-            for (int c = 0; c < 3; ++c)
-                acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[k], bf[c], acc[c], 0, 0, 0);
+            products([&](int c, int k, int q) { return o[c][k][q]; });
         }
     }
     // D[co][ci] with co = 8 i + 4 h + j in accumulator 4 i + j, ci = lane % 32
@@ -985,14 +1022,22 @@ hipError_t wgrad_dispatch(const float *dy, const void *y, int relu, const void *
     dim3 grid((unsigned)(nchunks + nflip)), block(256);
     const __bf16 *yy = (const __bf16 *)y, *xx = (const __bf16 *)x, *ww = (const __bf16 *)w;
     __bf16 *z = (__bf16 *)dz, *t = (__bf16 *)wt;
-    if (cin == 16 && cout == 16)
-        hipLaunchKernelGGL((gabp::k_wgrad<16, 16>), grid, block, 0, s, dy, yy, relu, xx, H, W, dx, dyl, P, nchunks, z, part, dbpart, ww, t);
-    else if (cin == 16)
-        hipLaunchKernelGGL((gabp::k_wgrad<16, 32>), grid, block, 0, s, dy, yy, relu, xx, H, W, dx, dyl, P, nchunks, z, part, dbpart, ww, t);
-    else if (cout == 16)
-        hipLaunchKernelGGL((gabp::k_wgrad<32, 16>), grid, block, 0, s, dy, yy, relu, xx, H, W, dx, dyl, P, nchunks, z, part, dbpart, ww, t);
-    else
-        hipLaunchKernelGGL((gabp::k_wgrad<32, 32>), grid, block, 0, s, dy, yy, relu, xx, H, W, dx, dyl, P, nchunks, z, part, dbpart, ww, t);
+#define WGRAD(CI, CO, SP)                                                                          \
+    hipLaunchKernelGGL((gabp::k_wgrad<CI, CO, SP>), grid, block, 0, s, dy, yy, relu, xx, H, W, dx, \
+                       dyl, P, nchunks, z, part, dbpart, ww, t)
+#define WGRAD_SPAN(CI, CO)                                                                         \
+    do {                                                                                           \
+        if (span == 96) WGRAD(CI, CO, 96);                                                         \
+        else if (span == 128) WGRAD(CI, CO, 128);                                                  \
+        else WGRAD(CI, CO, 192);                                                                   \
+    } while (0)
+    const int span = gabp::wgrad_span(dx);
+    if (cin == 16 && cout == 16) WGRAD_SPAN(16, 16);
+    else if (cin == 16) WGRAD_SPAN(16, 32);
+    else if (cout == 16) WGRAD_SPAN(32, 16);
+    else WGRAD_SPAN(32, 32);
+#undef WGRAD_SPAN
+#undef WGRAD
     return hipGetLastError();
 }
 
