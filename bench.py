@@ -488,8 +488,8 @@ def bench_multigrid(G, prob, ref=None):
 
 def bench_batch(G, I, torch, dev, args):
     """The 256-instance uneven batch: every instance solved to 1e-6 by the
-    batched path (persistent work-list launches, per-instance retirement,
-    captured chunk graphs)."""
+    batched path (work-list launches of several iterations per group,
+    per-instance retirement)."""
     import numpy as np
     probs = I.batch256()
     Es = np.array([edge_count(p.nx, p.ny, p.alpha, p.bc_x, p.bc_y) for p in probs], dtype=np.int64)
