@@ -155,7 +155,7 @@ def _crop(I, prob, w, h):
 
 
 def cpu_baseline(prob, seconds=10.0, gpu_iters=None):
-    """The FP64 oracle, as it is, on the GPU machine's host cores (rank 0, one
+    """The FP64 oracle, as it is, on the host's cores (rank 0, one
     GPU).  Headline: per-iteration throughput on a 2048 x 2048 crop of the
     workload (same prior, coverage pattern and noise) with all host threads;
     beside it the same on one thread, the 64 x 64 parity workload solved to
