@@ -407,6 +407,7 @@ void block_coefficients(const gabp_st_model &m, double blk[4][3], double lsq[3])
 }  // namespace
 
 struct gabp_st_ctx {
+    int cus = 256;                 // compute units of the device
     int device = 0;
     hipStream_t stream = nullptr;
     Grid G{};
@@ -474,32 +475,40 @@ gabp_status st_sync(gabp_st_ctx *ctx) {
     return GABP_OK;
 }
 
-template <typename T, int MODE, int SL>
+template <typename T, int MODE, int SL, bool AHEAD>
 void launch_mode(const Grid &G, const void *in, void *out, void *gain, const void *aw,
                  const void *bw, T eta, uint32_t *flags, uint32_t it, hipStream_t s) {
     const unsigned n = (unsigned)(G.tiles_x * G.tiles_y * ((G.nt + SL - 1) / SL));
-    hipLaunchKernelGGL((gabp::st::k_iter<T, MODE, SL>), dim3(n), dim3(256 * SL), 0, s, G,
+    hipLaunchKernelGGL((gabp::st::k_iter<T, MODE, SL, AHEAD>), dim3(n), dim3(256 * SL), 0, s, G,
                        (const T *)in, (T *)out, (T *)gain, (const T *)aw, (const T *)bw, eta,
                        flags, it);
 }
 
 // mode's kernel; the information-only one covers theta_slices slices per
-// workgroup (1, 2 or 4), the others one
+// workgroup (1, 2 or 4), the others one.  Loads ahead: the full iteration in FP32
+// (k_iter), the information-only one where that leaves it as many waves as
+// there are, between one and two per SIMD (a wave to 64 nodes of a row): 100 x 75 x 12
+// 12.5 -> 11.7 us, but 30 x 20 x 6 4.8 -> 6.0 and 512 x 256 x 8 90 -> 98.
 template <typename T>
-void launch_any(int mode, int theta_slices, const Grid &G, const void *in, void *out, void *gain,
-                const void *aw, const void *bw, T eta, uint32_t *flags, uint32_t it,
+void launch_any(int mode, int theta_slices, int cus, const Grid &G, const void *in, void *out,
+                void *gain, const void *aw, const void *bw, T eta, uint32_t *flags, uint32_t it,
                 hipStream_t s) {
     using namespace gabp::st;
+    constexpr bool F = sizeof(T) == 4;
+    const int64_t waves = (int64_t)G.tiles_x * G.ny * G.nt;
+    const bool ahead = F && waves > (int64_t)4 * cus && waves <= (int64_t)8 * cus;
     if (mode == MODE_FULL)
-        launch_mode<T, MODE_FULL, 1>(G, in, out, gain, aw, bw, eta, flags, it, s);
+        launch_mode<T, MODE_FULL, 1, F>(G, in, out, gain, aw, bw, eta, flags, it, s);
     else if (mode == MODE_GAIN)
-        launch_mode<T, MODE_GAIN, 1>(G, in, out, gain, aw, bw, eta, flags, it, s);
+        launch_mode<T, MODE_GAIN, 1, false>(G, in, out, gain, aw, bw, eta, flags, it, s);
     else if (theta_slices == 4)
-        launch_mode<T, MODE_THETA, 4>(G, in, out, gain, aw, bw, eta, flags, it, s);
+        launch_mode<T, MODE_THETA, 4, false>(G, in, out, gain, aw, bw, eta, flags, it, s);
     else if (theta_slices == 2)
-        launch_mode<T, MODE_THETA, 2>(G, in, out, gain, aw, bw, eta, flags, it, s);
+        launch_mode<T, MODE_THETA, 2, false>(G, in, out, gain, aw, bw, eta, flags, it, s);
+    else if (ahead)
+        launch_mode<T, MODE_THETA, 1, F>(G, in, out, gain, aw, bw, eta, flags, it, s);
     else
-        launch_mode<T, MODE_THETA, 1>(G, in, out, gain, aw, bw, eta, flags, it, s);
+        launch_mode<T, MODE_THETA, 1, false>(G, in, out, gain, aw, bw, eta, flags, it, s);
 }
 
 unsigned node_blocks(const Grid &G) {
@@ -556,6 +565,9 @@ gabp_status gabp_st_create(const gabp_st_model *model, const gabp_obs *obs,
         ctx->err = "hipGetDevice failed";
         return bail(GABP_E_DEVICE);
     }
+    if (hipDeviceGetAttribute(&ctx->cus, hipDeviceAttributeMultiprocessorCount, ctx->device) !=
+        hipSuccess)
+        ctx->cus = 256;
     ctx->stream = (hipStream_t)stream;
     ctx->dtype = dtype;
     const size_t esize = dtype == GABP_F32 ? 4 : 8;
@@ -694,11 +706,11 @@ gabp_status gabp_st_iterate(gabp_st_ctx *ctx, int32_t n_iters, double damping) {
         const uint32_t it = (uint32_t)(ctx->iter + 1);
         void *in = ctx->msg[ctx->cur], *out = ctx->msg[ctx->cur ^ 1];
         if (ctx->dtype == GABP_F32)
-            launch_any<float>(mode, ctx->theta_slices, G, in, out, ctx->gain, ctx->aw, ctx->bw,
-                              (float)damping, ctx->flags, it, ctx->stream);
+            launch_any<float>(mode, ctx->theta_slices, ctx->cus, G, in, out, ctx->gain, ctx->aw,
+                              ctx->bw, (float)damping, ctx->flags, it, ctx->stream);
         else
-            launch_any<double>(mode, ctx->theta_slices, G, in, out, ctx->gain, ctx->aw, ctx->bw,
-                               damping, ctx->flags, it, ctx->stream);
+            launch_any<double>(mode, ctx->theta_slices, ctx->cus, G, in, out, ctx->gain, ctx->aw,
+                               ctx->bw, damping, ctx->flags, it, ctx->stream);
         ST_HIP(ctx, hipGetLastError());
         ctx->cur ^= 1;
         ctx->iter += 1;
@@ -771,10 +783,10 @@ gabp_status gabp_st_residual(gabp_st_ctx *ctx, double *rel_residual, double *abs
                                    ctx->freeze_rel)) {
             // gains from the current precisions; both buffers keep them
             if (ctx->dtype == GABP_F32)
-                launch_any<float>(gabp::st::MODE_GAIN, 1, G, ctx->msg[ctx->cur], nullptr,
+                launch_any<float>(gabp::st::MODE_GAIN, 1, ctx->cus, G, ctx->msg[ctx->cur], nullptr,
                                   ctx->gain, ctx->aw, ctx->bw, 0.0f, ctx->flags, 0u, ctx->stream);
             else
-                launch_any<double>(gabp::st::MODE_GAIN, 1, G, ctx->msg[ctx->cur], nullptr,
+                launch_any<double>(gabp::st::MODE_GAIN, 1, ctx->cus, G, ctx->msg[ctx->cur], nullptr,
                                    ctx->gain, ctx->aw, ctx->bw, 0.0, ctx->flags, 0u, ctx->stream);
             ST_HIP(ctx, hipGetLastError());
             const size_t esize = ctx->dtype == GABP_F32 ? 4 : 8;

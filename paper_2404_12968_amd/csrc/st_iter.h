@@ -258,15 +258,33 @@ struct Edges {
     }
 };
 
+// A node's previous outgoing messages, with AHEAD loaded beside the incoming ones
+// (MODE_THETA: the gains in place of the precision messages).
+template <typename T, int MODE, bool AHEAD>
+struct Own {
+    T l[AHEAD ? kDeg : 1], t[AHEAD ? kDeg : 1];
+    __device__ __forceinline__ void load(const T *__restrict__ m_in, const T *__restrict__ gain,
+                                         int64_t plane, uint32_t rc, uint32_t xb) {
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int d = 0; d < kDeg; ++d) {
+                const size_t at = (size_t)d * plane + rc, at2 = (size_t)(kDeg + d) * plane + rc;
+                l[d] = *behind((MODE == MODE_THETA ? gain : m_in) + at, xb);
+                t[d] = *behind(m_in + at2, xb);
+            }
+        }
+    }
+};
+
 // New messages of a node from its gathered incoming ones and its beliefs (bl
 // unused in MODE_THETA, bt and tin in MODE_GAIN).  The planes' addresses are
 // made again (`plane` is a copy the compiler cannot tell from another value)
 // rather than kept from the gather: 76 pairs of scalar registers spill.
-template <typename T, int MODE, bool INNER>
+template <typename T, int MODE, bool INNER, bool AHEAD>
 __device__ __forceinline__ void st_out(const Edges<T, INNER> &E, int64_t plane, uint32_t rc, uint32_t xb,
                                        const T *__restrict__ m_in, T *__restrict__ m_out,
                                        T *__restrict__ gain, T eta, const T *lin, const T *tin,
-                                       T bl, T bt, bool &bad) {
+                                       T bl, T bt, const Own<T, MODE, AHEAD> &own, bool &bad) {
     const T keep = (T)1 - eta;
     T z = (T)0;   // MODE_THETA: stays zero exactly when every new message is finite
 #pragma unroll
@@ -278,8 +296,10 @@ __device__ __forceinline__ void st_out(const Edges<T, INNER> &E, int64_t plane, 
             const T lc = bl - lin[d];
             const T tc = bt - tin[d];
             const T g = edge_gain(q, lc);
-            T dl = fmadd(eta, g * q, keep * *behind(m_in + at, xb));
-            T dt = fmadd(eta, g * tc, keep * *behind(m_in + at2, xb));
+            const T ol = AHEAD ? own.l[AHEAD ? d : 0] : *behind(m_in + at, xb);
+            const T ot = AHEAD ? own.t[AHEAD ? d : 0] : *behind(m_in + at2, xb);
+            T dl = fmadd(eta, g * q, keep * ol);
+            T dt = fmadd(eta, g * tc, keep * ot);
             bad |= ok && (!(lc > (T)0) || !isfinite(dl) || !isfinite(dt));
             dl = ok ? dl : (T)0;
             dt = ok ? dt : (T)0;
@@ -290,8 +310,9 @@ __device__ __forceinline__ void st_out(const Edges<T, INNER> &E, int64_t plane, 
             *behind(gain + at, xb) = ok ? g : (T)0;
         } else {
             // edges that do not exist: gain and previous message are zero
-            const T g = __builtin_nontemporal_load(behind(gain + at, xb));
-            const T dt = fmadd(eta, g * (bt - tin[d]), keep * *behind(m_in + at2, xb));
+            const T g = AHEAD ? own.l[AHEAD ? d : 0] : __builtin_nontemporal_load(behind(gain + at, xb));
+            const T ot = AHEAD ? own.t[AHEAD ? d : 0] : *behind(m_in + at2, xb);
+            const T dt = fmadd(eta, g * (bt - tin[d]), keep * ot);
             z = fmadd(dt, (T)0, z);
             __builtin_nontemporal_store(dt, behind(m_out + at2, xb));
         }
@@ -333,19 +354,23 @@ __device__ __forceinline__ void wg_tile(int b, int tiles_x, int tiles_y, int nt,
 }
 
 // One launch of a mode over the grid, SL slices per workgroup.  Bound by memory
-// on large grids: 512 x 512 x 64 in FP32, 2.38 ms per full iteration (10.3 GB read and
-// written once at least: 4.3 TB/s; 2.64 ms when boundary tiles took a masked
+// on large grids: 512 x 512 x 64 in FP32, 2.21 ms per full iteration (10.3 GB read and
+// written once at least: 4.6 TB/s; 2.64 ms when boundary tiles took a masked
 // path in a second launch) and 1.42 ms per information-only one (7.6 GB, 5.4 TB/s,
-// above what a device copy streams).  Small ones wait for loads and, in the
-// full iteration, instruction issue: 100 x 75 x 12 takes 25 us (35) and 12.5 us
-// (13.7).  112 VGPRs in FP32 (four waves per SIMD; at five it spills) and 64.
+// above what a device copy streams).  AHEAD: a node's previous messages (and
+// gains) are loaded beside the incoming ones, every load before the first use, at
+// the price of registers.  The full iteration has it in FP32: 183 VGPRs, two waves per
+// SIMD, against 112 and four, yet 25 -> 18 us on 100 x 75 x 12, 675 -> 567 on 256 x
+// 256 x 64, 2380 -> 2208 on 512 x 512 x 64; held to three waves it spills (670 and
+// 2675).
 // diverged_at[0]
 // records the first iteration whose launch met an invalid value; launches of
 // later iterations return at once (the launch of the iteration that met it
 // completes, so its output buffer holds that iteration).  MODE_GAIN passes
 // it = 0.
-template <typename T, int MODE, int SL>
-__global__ __launch_bounds__(256 * SL, sizeof(T) == 8 ? 2 : MODE == MODE_THETA ? 8 : 4) void k_iter(
+template <typename T, int MODE, int SL, bool AHEAD>
+__global__ __launch_bounds__(256 * SL,
+                             sizeof(T) == 8 || AHEAD ? 2 : MODE == MODE_THETA ? 8 : 4) void k_iter(
     Grid G, const T *__restrict__ m_in, T *__restrict__ m_out, T *__restrict__ gain,
     const T *__restrict__ aw, const T *__restrict__ bw, T eta, uint32_t *__restrict__ diverged_at,
     uint32_t it) {
@@ -376,19 +401,23 @@ __global__ __launch_bounds__(256 * SL, sizeof(T) == 8 ? 2 : MODE == MODE_THETA ?
         if (MODE != MODE_THETA) lin[d] = R.in(m_in + (size_t)(d ^ 1) * G.plane, d);
         if (MODE != MODE_GAIN) tin[d] = R.in(m_in + (size_t)(kDeg + (d ^ 1)) * G.plane, d);
     }
+    Own<T, MODE, AHEAD> own;
+    own.load(m_in, gain, G.plane, rc, xb);
+    const T a = *behind(aw + rc, xb), b = *behind(bw + rc, xb);
+    if (AHEAD) __builtin_amdgcn_sched_barrier(0);   // every load is on its way
     if (MODE == MODE_FULL) __builtin_amdgcn_s_setprio(0);
-    if (MODE != MODE_THETA) bl = belief(*behind(aw + rc, xb), lin, c);
-    if (MODE != MODE_GAIN) bt = belief(*behind(bw + rc, xb), tin, c);
+    if (MODE != MODE_THETA) bl = belief(a, lin, c);
+    if (MODE != MODE_GAIN) bt = belief(b, tin, c);
     uint32_t pl = (uint32_t)G.plane;      // below 2^31 + 512
     asm volatile("" : "+s"(pl));
     const int64_t plane = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)pl);
     bool bad = false;
     if (MODE == MODE_THETA || inner)
-        st_out<T, MODE, true>(Edges<T, true>(G, R, pq_same, pq_cross, x, y, t), plane, rc, xb, m_in,
-                              m_out, gain, eta, lin, tin, bl, bt, bad);
+        st_out<T, MODE, true, AHEAD>(Edges<T, true>(G, R, pq_same, pq_cross, x, y, t), plane, rc, xb, m_in,
+                              m_out, gain, eta, lin, tin, bl, bt, own, bad);
     else
-        st_out<T, MODE, false>(Edges<T, false>(G, R, pq_same, pq_cross, x, y, t), plane, rc, xb, m_in,
-                               m_out, gain, eta, lin, tin, bl, bt, bad);
+        st_out<T, MODE, false, AHEAD>(Edges<T, false>(G, R, pq_same, pq_cross, x, y, t), plane, rc, xb, m_in,
+                               m_out, gain, eta, lin, tin, bl, bt, own, bad);
     if (MODE != MODE_GAIN && bad) atomicCAS(diverged_at, 0u, it);
 }
 
