@@ -77,7 +77,8 @@ __global__ __launch_bounds__(256) void k_batch_iter(const BatchInst *__restrict_
     for (int w = (int)blockIdx.x * per; w < w1; ++w) {
         const int a = __builtin_amdgcn_readfirstlane(find_item(prefix, nact, w));
         const int I = __builtin_amdgcn_readfirstlane(act[a]);
-        if (diverged_at[I] != 0u) continue;
+        const uint32_t seen = diverged_at[I];
+        if (seen != 0u && seen < t) continue;   // of an earlier iteration: this one is written whole
         const BatchInst &B = inst[I];
         const Lattice L = B.L;
         const int tile = w - prefix[a];

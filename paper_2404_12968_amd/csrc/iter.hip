@@ -36,7 +36,9 @@ namespace gabp {
 
 // One workgroup = 256 threads on a 64 x (4*RPT) tile: lane -> column, wave ->
 // row, each thread walks RPT rows 4 apart.  The tile shape is a tuning knob
-// (gabp_autotune); results do not depend on it.
+// (gabp_autotune); results do not depend on it.  Only a divergence recorded by an
+// earlier iteration stops a launch: the one that diverges is written whole,
+// whichever of its workgroups meets the invalid value first.
 template <typename T, int ALPHA, int RPT>
 __global__ __launch_bounds__(256) void k_iter_direct(Lattice L, const T *__restrict__ m_in,
                                                      T *__restrict__ m_out,
@@ -44,8 +46,9 @@ __global__ __launch_bounds__(256) void k_iter_direct(Lattice L, const T *__restr
                                                      const T *__restrict__ bw, T eta,
                                                      uint32_t *__restrict__ diverged_at,
                                                      const uint32_t *__restrict__ t_base, uint32_t t_off) {
-    if (*diverged_at != 0u) return;
     const uint32_t t = *t_base + t_off;   // this iteration's number
+    const uint32_t seen = *diverged_at;
+    if (seen != 0u && seen < t) return;   // uniform across the workgroup
     constexpr int TH = 4 * RPT;
     int tx, ty;
     strip_order(xcd_remap((int)blockIdx.x, (int)gridDim.x), L.tiles_x, (L.ny + TH - 1) / TH, tx,
@@ -117,8 +120,9 @@ __global__ __launch_bounds__(256) void k_iter_theta(Lattice L, const T *__restri
                                                     const T *__restrict__ bw, T eta,
                                                     uint32_t *__restrict__ diverged_at,
                                                     const uint32_t *__restrict__ t_base, uint32_t t_off) {
-    if (*diverged_at != 0u) return;
     const uint32_t t = *t_base + t_off;   // this iteration's number
+    const uint32_t seen = *diverged_at;
+    if (seen != 0u && seen < t) return;   // uniform across the workgroup
     constexpr int TH = 4 * RPT;
     int tx, ty;
     strip_order(xcd_remap((int)blockIdx.x, (int)gridDim.x), L.tiles_x, (L.ny + TH - 1) / TH, tx,
