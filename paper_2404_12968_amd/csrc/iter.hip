@@ -265,8 +265,9 @@ __global__ __launch_bounds__(64 * RB) void k_iter_theta2w(Lattice L, const T *__
     constexpr int DEG = ALPHA == 1 ? 4 : 12;
     constexpr int R = ALPHA == 1 ? 1 : 2;
     __shared__ T lds[WalkRing<RB>::kRows * DEG * (64 + 2 * R)];
-    if (*diverged_at != 0u) return;               // uniform across the workgroup
     const uint32_t t = *t_base + t_off;           // the iteration the launch starts from
+    const uint32_t seen = *diverged_at;
+    if (seen != 0u && seen <= t) return;          // uniform across the workgroup
     const int g = xcd_remap((int)blockIdx.x, (int)gridDim.x);
     const int seg = g / L.tiles_x, strip = g - seg * L.tiles_x;
     const int Y0 = seg * seglen;

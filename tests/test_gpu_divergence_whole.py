@@ -70,7 +70,7 @@ def test_information_only_iterations(G, alpha):
     at = set()
     for s in SCALES:
         out = []
-        for tile in (None, (1, 4), (4, 0)):
+        for tile in (None, (1, 4), (1, -2), (4, 0)):
             c = _frozen(G, _problem(alpha, s), tile)
             if c is None:
                 break
@@ -83,10 +83,11 @@ def test_information_only_iterations(G, alpha):
             kept = G.gabp_get_messages(c)
             assert _whole(kept, G.gabp_get_messages(r), alpha, it), (s, tile, it)
             out.append((it, kept))
-        if len(out) == 3:
+        if len(out) == 4:
             at.add(out[0][0])
             # as two-iteration launches keep it
-            assert out[0][0] == out[1][0] and all(map(_same, out[0][1], out[1][1])), s
+            for other in out[1:3]:
+                assert out[0][0] == other[0] and all(map(_same, out[0][1], other[1])), s
     assert len(at) >= 2
 
 
