@@ -139,7 +139,11 @@ __device__ __forceinline__ int deep_tile(const Lattice &L, const T *__restrict__
         return live(ly, s) && lx >= R * (s - 1) && lx < RW - R * (s - 1);
     };
     // a thread's new messages: kept, and in LDS for the next iteration.  The
-    // products with zero add up to zero exactly when every message is finite.
+    // products with zero add up to zero exactly when every message is finite.  An
+    // edge that does not exist adds an invalid value only where an infinite belief
+    // makes the node's other messages invalid too, or there is no other: a grid of
+    // one node has no messages, and nothing to report.
+    const bool edges = IO || L.nx > 1 || L.ny > 1;
     auto finish = [&](int k, int s, const T *out) {
         const int ly = ly0 + k * RPP;
         T z = 0;
@@ -148,7 +152,7 @@ __device__ __forceinline__ int deep_tile(const Lattice &L, const T *__restrict__
             ot[k][d] = out[d];
             z = fmadd(out[d], (T)0, z);
         }
-        if (!(z == (T)0) && right(ly, s) && bad == 0) bad = s;
+        if (!(z == (T)0) && edges && right(ly, s) && bad == 0) bad = s;
         if (s < n) {
 #pragma unroll
             for (int d = 0; d < DEG; ++d) own[d * PL + k * NT] = out[d];

@@ -701,7 +701,10 @@ gabp_status gabp_st_iterate(gabp_st_ctx *ctx, int32_t n_iters, double damping) {
     if (ctx->iter + n_iters >= (int64_t)UINT32_MAX)
         return st_fail(ctx, GABP_E_INVALID, "iteration count would exceed 2^32 - 1");
     const Grid &G = ctx->G;
-    const int mode = ctx->frozen ? gabp::st::MODE_THETA : gabp::st::MODE_FULL;
+    // a grid of one node has no messages: only the full iteration masks the edges
+    // that an infinite belief would make invalid (elsewhere its others are, too)
+    const bool edges = G.nx > 1 || G.ny > 1 || G.nt > 1;
+    const int mode = ctx->frozen && edges ? gabp::st::MODE_THETA : gabp::st::MODE_FULL;
     for (int32_t k = 0; k < n_iters; ++k) {
         const uint32_t it = (uint32_t)(ctx->iter + 1);
         void *in = ctx->msg[ctx->cur], *out = ctx->msg[ctx->cur ^ 1];
