@@ -498,7 +498,8 @@ namespace {
 // on, whose change the first iterations record) as information-only: all but the
 // last, which runs singly, so that the two buffers end on m^{t-1} and m^t (the
 // message-change statistic and the freeze probe need that); frozen contexts
-// need that with tail_single only, else they run all so.  With a tile set by
+// need that with tail_single or an odd n (as two-iteration launches leave it),
+// else they run all so.  With a tile set by
 // gabp_set_tile, full iterations run singly and frozen contexts two per launch;
 // with tail_single the last one or two singly, else while two remain.
 // Touches no context state; reports the launches.
@@ -513,7 +514,7 @@ gabp_status enqueue_iters(gabp_ctx *ctx, int32_t n, double damping, hipStream_t 
     while (k < n) {
         const void *src = ctx->msg[cur];
         void *dst = ctx->msg[cur ^ 1];
-        const int32_t many = n - k - (tail_single || !ctx->frozen ? 1 : 0);
+        const int32_t many = n - k - (tail_single || !ctx->frozen || n % 2 != 0 ? 1 : 0);
         if (ctx->deep && it >= 2 && many >= 2 && done.deeps == 0) {
             const gabp::DeepPlan &p = ctx->frozen ? ctx->plan : ctx->plan_full;
             done.lead = done.singles;

@@ -1,0 +1,40 @@
+"""Which launches a context takes, and what its two message buffers then hold."""
+import pytest
+
+from paper_2404_12968_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def G():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2404_12968_amd import gabp
+    return gabp
+
+
+def _frozen(G, dtype, alpha, tile):
+    prob = I.small_lattice(130, 90, alpha, bc_x=I.BC_PERIODIC, kappa=0.12, frac=0.1, sigma=0.05,
+                           seed=5, dtype=dtype)
+    c = G.gabp_create_problem(prob)
+    if tile is not None:
+        G.gabp_set_tile(c, *tile)
+    G.gabp_set_freeze_tolerance(c, 10**9, 1e9)
+    G.gabp_iterate(c, 6, 0.5)
+    G.gabp_residual(c)
+    assert G.gabp_precision_frozen(c) == 6
+    return c
+
+
+@pytest.mark.parametrize("dtype,alpha", [("f32", 2), ("f32", 1), ("f64", 2), ("f64", 1)])
+def test_a_chunk_of_odd_length_ends_on_consecutive_iterations(G, dtype, alpha):
+    """gabp_message_change after a solve whose last chunk was odd."""
+    a, b = _frozen(G, dtype, alpha, None), _frozen(G, dtype, alpha, (1, 0))
+    for most, check in ((25, 10), (7, 7), (3, 10), (1, 10)):
+        ra, rb = (G.gabp_solve(c, most, 0.5, 0.0, check) for c in (a, b))
+        assert ra == rb
+        assert G.gabp_message_change(a) == G.gabp_message_change(b), most
+        for x, y in zip(G.gabp_get_messages(a), G.gabp_get_messages(b)):
+            assert torch.equal(x, y)
