@@ -225,11 +225,15 @@ gabp_status gabp_set_messages(gabp_ctx *ctx, const void *prec, const void *info)
 /* Autotuner: after one untimed iteration, run `trials` iterations with each
  * tile shape of the active iteration kernel (rows per thread 1, 2, 4, 8),
  * twice over, time them with HIP events on the context's stream, and keep
- * the fastest for this context and for later contexts of the same prior
- * order, dtype and size class in this process.  Once the precision messages
- * have frozen, the two-iteration tile kernel (tile heights 4, 8, 12, 16 and
- * 32 in FP32, 4 in FP64; see gabp_set_tile) is timed against the best of those,
- * twice over, and the fastest kept (the column-strip walker is not timed).
+ * the fastest for the single iterations of this context and of later contexts
+ * of the same prior order, dtype and size class in this process.  Once the
+ * precision messages have frozen, the two-iteration tile kernel (tile heights 4,
+ * 8, 12, 16 and 32 in FP32, 4 in FP64; see gabp_set_tile) is timed against the
+ * best of those, twice over (the column-strip walker is not timed), and the
+ * fastest kept for gabp_get_tile.  The context then takes its default launches
+ * of several iterations, which are faster than any of these shapes, also where
+ * gabp_set_tile had been called; pass what gabp_get_tile reports to gabp_set_tile
+ * to run the shape itself.
  * Every shape computes bitwise-identical messages, so these are ordinary
  * iterations: the counter advances by 1 + 8 * trials, plus 10 * trials (FP32)
  * or 2 * trials (FP64) when frozen.  *chosen (may be NULL) receives the rows
@@ -269,8 +273,11 @@ gabp_status gabp_set_graph(gabp_ctx *ctx, int32_t enable);
  * and -8 for FP32 only): persistent workgroups walk 64-column strips
  * downwards in bands of -pair_rows rows, keeping iteration t+1 of the rows
  * the next band needs in LDS; 0 = always one iteration per launch.
- * Default: rows 4, pair 8 (FP32) or 4 (FP64), or what the autotuner chose
- * for this problem class.  INVALID for other values. */
+ * INVALID for other values.  Slower than the default launches on every lattice
+ * measured; gabp_autotune returns a context to them.
+ * gabp_get_tile reports the shape set, else the one the autotuner found for this
+ * problem class, else rows 4, pair 8 (FP32) or 4 (FP64): what two-iteration
+ * launches would take, not what a context on its default launches runs. */
 gabp_status gabp_set_tile(gabp_ctx *ctx, int32_t rows_per_thread, int32_t pair_rows);
 gabp_status gabp_get_tile(const gabp_ctx *ctx, int32_t *rows_per_thread, int32_t *pair_rows);
 

@@ -933,8 +933,11 @@ gabp_status gabp_autotune(gabp_ctx *ctx, int32_t trials, double damping, int32_t
     const bool saved_deep = ctx->deep, saved_set = ctx->rpt_set;
     ctx->deep = false;             // the timed calls run the shapes they set
     ctx->rpt_set = true;
+    // the launches of several iterations are faster than every shape timed here
+    // (tables in deep_tile.h and deep_full.h): a tuned context takes them, with the
+    // row count found for its single iterations, also where a tile was set
     auto finish = [&](gabp_status s1) {
-        ctx->deep = saved_deep;
+        ctx->deep = s1 == GABP_OK || saved_deep;
         if (s1 != GABP_OK) ctx->rpt_set = saved_set;
         (void)hipEventDestroy(ev[0]);
         (void)hipEventDestroy(ev[1]);

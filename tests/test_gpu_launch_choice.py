@@ -38,3 +38,18 @@ def test_a_chunk_of_odd_length_ends_on_consecutive_iterations(G, dtype, alpha):
         assert G.gabp_message_change(a) == G.gabp_message_change(b), most
         for x, y in zip(G.gabp_get_messages(a), G.gabp_get_messages(b)):
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("dtype,alpha", [("f32", 2), ("f64", 1)])
+def test_the_autotuner_gives_a_context_its_default_launches(G, dtype, alpha):
+    """They are faster than every tile shape, so a set tile ends there."""
+    a, b = _frozen(G, dtype, alpha, (4, 4)), _frozen(G, dtype, alpha, None)
+    G.gabp_autotune(a, 1, 0.5)
+    t, _ = G.gabp_iteration_count(a)
+    G.gabp_iterate(b, t - 6, 0.5)
+    for c in (a, b):
+        before = G.gabp_launch_counts(c)["pair_tiles"]
+        G.gabp_iterate(c, 61, 0.5)
+        assert G.gabp_launch_counts(c)["pair_tiles"] - before < 25   # 30 of two iterations
+    for x, y in zip(G.gabp_get_messages(a), G.gabp_get_messages(b)):
+        assert torch.equal(x, y)
