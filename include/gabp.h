@@ -420,8 +420,10 @@ gabp_status gabp_batch_solve(gabp_batch *b, int64_t max_iters, double damping, d
 gabp_status gabp_batch_posterior(gabp_batch *b, int32_t i, double *mean, double *var);
 gabp_status gabp_batch_get_messages(gabp_batch *b, int32_t i, void *prec, void *info);
 
-/* Tile-shape autotuner of the batched iteration, as gabp_autotune (advances
- * every running instance by 1 + 8 * trials iterations). */
+/* Autotuner of the rows per thread (1, 2, 4, 8) that single iterations of
+ * instances not frozen take, timed on trials such iterations each, twice over
+ * (advances every running instance by 1 + 8 * trials iterations).  With no such
+ * instance the choice stays. */
 gabp_status gabp_batch_autotune(gabp_batch *b, int32_t trials, double damping, int32_t *chosen);
 
 /* gabp_warm_init for instance i of a batch (its current messages; the

@@ -1251,14 +1251,17 @@ gabp_status gabp_batch_autotune(gabp_batch *b, int32_t trials, double damping, i
     for (int pass = 0; pass < 2 && st == GABP_OK; ++pass)
         for (int r : gabp::kRptChoices) {
             b->rpt = r;
-            b->lists_dirty = true;   // work-item counts depend on the tile shape
+            st = upload_lists(b);    // work-item counts depend on the tile shape
+            if (st != GABP_OK) break;
             if (hipEventRecord(e0, b->stream) != hipSuccess) { st = GABP_E_DEVICE; break; }
-            st = gabp_batch_iterate(b, trials, damping);
+            // one at a time: only single iterations of instances not frozen have
+            // rows per thread
+            for (int k = 0; k < trials && st == GABP_OK; ++k) st = run_iters(b, 1, damping);
             if (st != GABP_OK) break;
             float ms = 0.f;
             if (hipEventRecord(e1, b->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
                 hipEventElapsedTime(&ms, e0, e1) != hipSuccess) { st = GABP_E_DEVICE; break; }
-            if (ms < best) {
+            if (b->nu > 0 && ms < best) {
                 best = ms;
                 best_r = r;
             }

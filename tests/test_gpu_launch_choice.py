@@ -53,3 +53,22 @@ def test_the_autotuner_gives_a_context_its_default_launches(G, dtype, alpha):
         assert G.gabp_launch_counts(c)["pair_tiles"] - before < 25   # 30 of two iterations
     for x, y in zip(G.gabp_get_messages(a), G.gabp_get_messages(b)):
         assert torch.equal(x, y)
+
+
+def test_the_batch_autotuner_chooses_among_what_it_times(G):
+    """Rows per thread belong to the single iterations of instances not frozen:
+    with none, the default of one row stays, and the iterations are the same."""
+    probs = [I.small_lattice(nx, ny, a, kappa=0.15, frac=0.1, sigma=0.05, seed=nx, dtype="f32")
+             for nx, ny, a in ((140, 90, 2), (60, 75, 1), (200, 33, 2))]
+    a, b = G.gabp_batch_create(probs), G.gabp_batch_create(probs)
+    for x in (a, b):
+        G.gabp_batch_set_freeze_tolerance(x, 10**9, 1e9)
+        G.gabp_batch_solve(x, 6, 0.5, 0.0, 6)
+        assert all(G.gabp_batch_info(x, i) == (6, 6, True) for i in range(3))
+    for trials in (3, 5, 4):
+        assert G.gabp_batch_autotune(a, trials, 0.5) == 1
+        G.gabp_batch_iterate(b, 1 + 8 * trials, 0.5)
+        for i in range(3):
+            assert G.gabp_batch_info(a, i) == G.gabp_batch_info(b, i)
+            for x, y in zip(G.gabp_batch_get_messages(a, i), G.gabp_batch_get_messages(b, i)):
+                assert torch.equal(x, y)
