@@ -339,7 +339,11 @@ def train(net: WarmNet, ts: TrainingSet, steps: int, batch: int = 8, crop: int =
 def predict(net: WarmNet, prob: I.Problem, device="cuda") -> torch.Tensor:
     """Prediction [ny, nx, 16] FP32 for one problem."""
     x = G.gabp_warm_features(prob.cells, prob.y, prob.nx, prob.ny, prob.kappa, device=device)
-    return net._infer(x.unsqueeze(0).contiguous())[0].contiguous()
+    x = x.unsqueeze(0).contiguous()
+    if getattr(net.forward, "__func__", None) is WarmNet.forward:
+        return net._infer(x)[0].contiguous()
+    _, pred = net.forward(x)                  # a network of the caller's
+    return pred[0].contiguous()
 
 
 def warm_solve(net: WarmNet, prob: I.Problem, max_iters: int = 300000, probe: int = 100,
