@@ -900,7 +900,9 @@ gabp_status gabp_batch_create(int32_t n, const gabp_instance *inst, const gabp_o
         return bail(GABP_E_DEVICE);
     }
     // instance records and per-instance set-up; an instance whose cells repeat out
-    // of order raises its word of d_div and is set up again
+    // of order raises its word of d_div and is set up again: where its observations
+    // are staged here, at once (the staging waits for the stream in any case), else
+    // when the words are looked at together
     std::vector<BatchInst> rec((size_t)n);
     for (int i = 0; i < n; ++i) {
         InstHost &H = b->h[i];
@@ -946,11 +948,24 @@ gabp_status gabp_batch_create(int32_t n, const gabp_instance *inst, const gabp_o
             dy = ty;
             dv = tv;
         }
-        hipError_t e = gabp::launch_setup(dtype == GABP_F32 ? 0 : 1, H.L, o.n, dc, dy, dv,
-                                          nz.var ? 0.0 : nz.sigma * nz.sigma, R.adiag64, R.b64,
-                                          nullptr, dtype == GABP_F32 ? base + H.lay.adiag_w : nullptr,
-                                          dtype == GABP_F32 ? base + H.lay.b_w : nullptr, b->d_err,
-                                          repeated, b->stream);
+        auto terms = [&](uint32_t *rep) {
+            return gabp::launch_setup(dtype == GABP_F32 ? 0 : 1, H.L, o.n, dc, dy, dv,
+                                      nz.var ? 0.0 : nz.sigma * nz.sigma, R.adiag64, R.b64, nullptr,
+                                      dtype == GABP_F32 ? base + H.lay.adiag_w : nullptr,
+                                      dtype == GABP_F32 ? base + H.lay.b_w : nullptr, b->d_err, rep,
+                                      R.mu64, H.lay.check_room(), b->stream);
+        };
+        hipError_t e = terms(repeated);
+        if (e == hipSuccess && tc && repeated) {
+            e = hipMemcpyAsync(b->p_div + i, repeated, sizeof(uint32_t), hipMemcpyDeviceToHost,
+                               b->stream);
+            const hipError_t es = hipStreamSynchronize(b->stream);
+            if (e == hipSuccess) e = es;
+            if (e == hipSuccess && b->p_div[i] != 0u) {
+                e = terms(nullptr);
+                if (e == hipSuccess) e = gabp::launch_set_u32(repeated, 0u, b->stream);
+            }
+        }
         if (tc || ty || tv) {
             (void)hipStreamSynchronize(b->stream);
             (void)hipFree(tc);

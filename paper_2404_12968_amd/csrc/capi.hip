@@ -436,7 +436,8 @@ gabp_status gabp_create(const gabp_grid *grid, const gabp_stencil *stencil, cons
                                ctx->adiag64, ctx->b64, opts ? opts->prior_mean : nullptr,
                                dtype == GABP_F32 ? ctx->adiag_w : nullptr,
                                dtype == GABP_F32 ? ctx->b_w : nullptr, ctx->flags + 1,
-                               direct ? ctx->flags + 2 : nullptr, ctx->stream);
+                               direct ? ctx->flags + 2 : nullptr, ctx->mu64, lay.check_room(),
+                               ctx->stream);
         e2 = hipMemcpyAsync(ctx->host->flags, ctx->flags, 4 * sizeof(uint32_t),
                             hipMemcpyDeviceToHost, ctx->stream);
         if (!direct && e == hipSuccess) e = gabp::launch_set_u32(ctx->flags + 2, 0u, ctx->stream);

@@ -30,6 +30,8 @@ struct Layout {
     size_t gain = 0;
     size_t adiag64 = 0, b64 = 0, mu64 = 0, bel64 = 0, adiag_w = 0, b_w = 0;
     size_t partials = 0, red = 0, flags = 0, total = 0;
+    // the mean and belief planes, which only checks write: room for set-up
+    size_t check_room() const { return 2 * (bel64 - mu64); }
 };
 
 // Freeze decision from one precision-change probe: `changed` messages

@@ -81,21 +81,23 @@ hipError_t launch_abs_change(int dtype, const void *a, const void *b, int64_t n,
 // p[i] += sum 1/s_k^2 and h[i] += sum y_k/s_k^2 over the observations of
 // cell c, i = (c / nx) * pitch + c % nx, summed in input order; p and h are zero
 // before.  With `repeated` (zero before) one launch, which raises it if a cell's
-// observations do not follow one another: p and h are then worthless.  Without,
-// any order; synchronises the stream (temporary sort buffers are freed before it
-// returns).
+// observations do not follow one another: p and h are then worthless at the
+// observed cells.  Without, after such a call, from any order: sorts in `room` (zero
+// before and after, 256-byte aligned, room_bytes), or, where that is too small, in
+// temporary memory, which it waits for.
 hipError_t launch_obs_fold(int64_t n, const int64_t *cell, const double *y, const double *var,
                            double sigma2, int64_t ncells, int32_t nx, int32_t pitch,
                            double *p_plane, double *h_plane, uint32_t *err_flag,
-                           uint32_t *repeated, hipStream_t s);
+                           uint32_t *repeated, void *room, size_t room_bytes,
+                           hipStream_t s);
 // Node terms on zeroed planes: launch_obs_fold with `repeated`, then A_ii, b_i and
-// their copies in message precision.  repeated == NULL: after a call that raised
-// it, the same from any order (the planes are cleared first, in one operation:
-// b64 follows adiag64 in every layout).
+// their copies in message precision, unless it was raised.  repeated == NULL: after a
+// call that raised it, the same from any order, with room as there.
 hipError_t launch_setup(int dtype, const Lattice &L, int64_t nobs, const int64_t *cell,
                         const double *y, const double *var, double sigma2, double *adiag64,
                         double *b64, const double *prior_mean, void *adiag_w, void *b_w,
-                        uint32_t *err_flag, uint32_t *repeated, hipStream_t s);
+                        uint32_t *err_flag, uint32_t *repeated, void *room, size_t room_bytes,
+                           hipStream_t s);
 // Multigrid: bilinear upsampling of a coarse mean into a prediction.
 hipError_t launch_upscale_prec(int dtype, const Lattice &Lc, const void *m, float scale,
                                float *pred, int nxf, int nyf, hipStream_t s);

@@ -296,7 +296,9 @@ __global__ __launch_bounds__(256) void k_node_init(Lattice L, double *__restrict
                                                    double *__restrict__ b64,
                                                    const double *__restrict__ prior_mean,
                                                    T *__restrict__ adiag_w, T *__restrict__ b_w,
-                                                   uint32_t *__restrict__ err_flag) {
+                                                   uint32_t *__restrict__ err_flag,
+                                                   const uint32_t *__restrict__ repeated) {
+    if (repeated && *repeated != 0u) return;      // the fold is made again (obs.hip)
     const int tile = (int)blockIdx.x;
     const int x = (tile % L.tiles_x) * 64 + (int)(threadIdx.x & 63u);
     const int y = (tile / L.tiles_x) * 4 + (int)(threadIdx.x >> 6);
@@ -569,25 +571,22 @@ hipError_t launch_abs_change(int dtype, const void *a, const void *b, int64_t n,
 hipError_t launch_setup(int dtype, const Lattice &L, int64_t nobs, const int64_t *cell,
                         const double *y, const double *var, double sigma2, double *adiag64,
                         double *b64, const double *prior_mean, void *adiag_w, void *b_w,
-                        uint32_t *err_flag, uint32_t *repeated, hipStream_t s) {
-    if (!repeated) {
-        const size_t bytes = (size_t)L.pitch * (size_t)L.ny * sizeof(double);
-        const hipError_t e = hipMemsetAsync(
-            adiag64, 0, (size_t)((char *)b64 - (char *)adiag64) + bytes, s);
-        if (e != hipSuccess) return e;
-    }
+                        uint32_t *err_flag, uint32_t *repeated, void *room,
+                        size_t room_bytes, hipStream_t s) {
     if (nobs > 0) {
         const hipError_t e = launch_obs_fold(nobs, cell, y, var, sigma2, (int64_t)L.nx * L.ny, L.nx,
-                                             L.pitch, adiag64, b64, err_flag, repeated, s);
+                                             L.pitch, adiag64, b64, err_flag, repeated, room, room_bytes,
+                                             s);
         if (e != hipSuccess) return e;
     }
     dim3 grid(tiles_of(L)), block(256);
     if (dtype == 0)
         hipLaunchKernelGGL((k_node_init<float>), grid, block, 0, s, L, adiag64, b64, prior_mean,
-                           (float *)adiag_w, (float *)b_w, err_flag);
+                           (float *)adiag_w, (float *)b_w, err_flag, (const uint32_t *)repeated);
     else
         hipLaunchKernelGGL((k_node_init<double>), grid, block, 0, s, L, adiag64, b64, prior_mean,
-                           (double *)nullptr, (double *)nullptr, err_flag);
+                           (double *)nullptr, (double *)nullptr, err_flag,
+                           (const uint32_t *)repeated);
     return hipGetLastError();
 }
 

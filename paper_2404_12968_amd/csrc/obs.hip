@@ -13,10 +13,14 @@
 // A run that meets a cell already taken raises a flag, which the caller looks at
 // when it next waits; only then are the observations brought into their cells'
 // order by a stable radix sort over the bits that a cell number has, and folded
-// anew.  The sort, its four allocations and its wait were a third of a set-up:
-// 64^2 with 5 % observed 97 -> 67 us, 2048^2 460 -> 290, a batch of 24 2.4 -> 1.0
-// ms.  Repeated cells out of order take both passes, the second with one allocation
-// and fewer sorted bits: 99 -> 107, 256^2 147 -> 150, 2048^2 528 -> 548 us.
+// anew.  Set-up without a sort and with one before every fold: 64^2 with 5 %
+// observed 64 and 94 us, 2048^2 283 and 440, a batch of 24 0.37 and 1.4 ms.
+// Cells repeated out of order (10 %) take both passes.  The first does little then:
+// its workgroups, and the node terms after it, end once the flag is up.  The sort
+// takes its memory from planes that only checks write, and takes the fewer bits; what
+// is left is one wait more: 64^2 93 us (94 with the sort first), 256^2 162 (142),
+// 1024^2 238 (219), 2048^2 498 (500), a batch of 24 on the device 1.15 ms (1.74).
+// Allocating costs more: 1 us up to some hundred KB, 100 us with its release from 2 MB.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -31,9 +35,21 @@ namespace gabp {
 
 namespace {
 
-__global__ __launch_bounds__(256) void k_obs_index(int64_t n, int32_t *__restrict__ idx) {
+// Positions before the sort, and the observed cells' terms back to zero after a
+// pass that found repeated ones.
+__global__ __launch_bounds__(256) void k_obs_index(int64_t n, const int64_t *__restrict__ cell,
+                                                   int64_t ncells, int32_t nx, int32_t pitch,
+                                                   int32_t *__restrict__ idx,
+                                                   double *__restrict__ p_plane,
+                                                   double *__restrict__ h_plane) {
     const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (k < n) idx[k] = (int32_t)k;
+    if (k >= n) return;
+    idx[k] = (int32_t)k;
+    const int64_t c = cell[k];
+    if (c < 0 || c >= ncells) return;
+    const int64_t i = (c / nx) * (int64_t)pitch + c % nx;
+    p_plane[i] = 0.0;
+    h_plane[i] = 0.0;
 }
 
 // Thread per position s; the first of each run of equal cells sums the run.  With
@@ -55,6 +71,10 @@ __global__ __launch_bounds__(256) void k_obs_fold(int64_t n, const int64_t *__re
                                                   uint32_t *__restrict__ repeated) {
     const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (s >= n) return;
+    // nothing that follows is used once it is raised
+    if (repeated &&
+        __hip_atomic_load(repeated, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)
+        return;
     const int64_t c = cell_s[s];
     if (s > 0 && cell_s[s - 1] == c) return;
     if (c < 0 || c >= ncells) {
@@ -89,7 +109,7 @@ __global__ __launch_bounds__(256) void k_obs_fold(int64_t n, const int64_t *__re
 hipError_t launch_obs_fold(int64_t n, const int64_t *cell, const double *y, const double *var,
                            double sigma2, int64_t ncells, int32_t nx, int32_t pitch,
                            double *p_plane, double *h_plane, uint32_t *err_flag,
-                           uint32_t *repeated, hipStream_t s) {
+                           uint32_t *repeated, void *room, size_t room_bytes, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     if (n > INT32_MAX) return hipErrorInvalidValue;
     const unsigned nb = (unsigned)((n + 255) / 256);
@@ -99,10 +119,9 @@ hipError_t launch_obs_fold(int64_t n, const int64_t *cell, const double *y, cons
                            h_plane, err_flag, repeated);
         return hipGetLastError();
     }
-    // one allocation: sorted cells, positions before and after, the sort's own
+    // sorted cells, positions before and after, the sort's own
     int64_t *cell_s = nullptr;
     int32_t *idx = nullptr, *idx_s = nullptr;
-    char *mem = nullptr;
     size_t tmp_bytes = 0;
     int bits = 1;                   // of a cell inside the grid; others are refused
     while (bits < 63 && (ncells - 1) >> bits != 0) ++bits;
@@ -110,7 +129,13 @@ hipError_t launch_obs_fold(int64_t n, const int64_t *cell, const double *y, cons
                                                       idx_s, (int)n, 0, bits, s);
     const size_t cells_b = ((size_t)n * sizeof(int64_t) + 255) / 256 * 256;
     const size_t idx_b = ((size_t)n * sizeof(int32_t) + 255) / 256 * 256;
-    if (e == hipSuccess) e = hipMalloc((void **)&mem, cells_b + 2 * idx_b + tmp_bytes + 256);
+    const size_t bytes = cells_b + 2 * idx_b + tmp_bytes + 256;
+    const bool own = bytes > room_bytes;
+    char *mem = (char *)room;
+    if (e == hipSuccess && own) {
+        mem = nullptr;
+        e = hipMalloc((void **)&mem, bytes);
+    }
     void *tmp = nullptr;
     if (e == hipSuccess) {
         cell_s = (int64_t *)mem;
@@ -119,7 +144,8 @@ hipError_t launch_obs_fold(int64_t n, const int64_t *cell, const double *y, cons
         tmp = mem + cells_b + 2 * idx_b;
     }
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_obs_index, dim3(nb), dim3(256), 0, s, n, idx);
+        hipLaunchKernelGGL(k_obs_index, dim3(nb), dim3(256), 0, s, n, cell, ncells, nx, pitch, idx,
+                           p_plane, h_plane);
         e = hipGetLastError();
     }
     if (e == hipSuccess)
@@ -130,6 +156,10 @@ hipError_t launch_obs_fold(int64_t n, const int64_t *cell, const double *y, cons
                            (const int32_t *)idx_s, y, var, sigma2, ncells, nx, pitch, p_plane,
                            h_plane, err_flag, (uint32_t *)nullptr);
         e = hipGetLastError();
+    }
+    if (!own) {
+        if (e == hipSuccess) e = hipMemsetAsync(room, 0, bytes, s);
+        return e;
     }
     const hipError_t es = hipStreamSynchronize(s);
     if (e == hipSuccess) e = es;

@@ -42,7 +42,9 @@ __global__ __launch_bounds__(256) void k_node_init(Grid G, double *__restrict__ 
                                                    double *__restrict__ b64,
                                                    const double *__restrict__ pm,
                                                    T *__restrict__ aw, T *__restrict__ bw,
-                                                   uint32_t *__restrict__ err_flag) {
+                                                   uint32_t *__restrict__ err_flag,
+                                                   const uint32_t *__restrict__ repeated) {
+    if (repeated && *repeated != 0u) return;      // the fold is made again (obs.hip)
     const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t nodes = (int64_t)G.nx * G.ny * G.nt;
     if (k >= nodes) return;
@@ -647,25 +649,23 @@ gabp_status gabp_st_create(const gabp_st_model *model, const gabp_obs *obs,
     // flags[7] tells when a cell's observations did not follow one another
     hipError_t e = hipSuccess;
     for (bool direct : {true, false}) {
-        if (!direct) {
-            // b64 follows adiag64
-            e = hipMemsetAsync(ctx->adiag64, 0, l.mu64 - l.adiag64, ctx->stream);
-            if (e == hipSuccess)
-                e = hipMemsetAsync(ctx->flags + 7, 0, sizeof(uint32_t), ctx->stream);
-        }
+        uint32_t *repeated = direct ? ctx->flags + 7 : nullptr;
+        if (!direct) e = hipMemsetAsync(ctx->flags + 7, 0, sizeof(uint32_t), ctx->stream);
         if (e == hipSuccess)
             e = gabp::launch_obs_fold(nobs, dc, dy, dv, s2, (int64_t)G.nx * G.ny * G.nt, G.nx,
-                                      G.pitch, ctx->adiag64, ctx->b64, ctx->flags + 1,
-                                      direct ? ctx->flags + 7 : nullptr, ctx->stream);
+                                      G.pitch, ctx->adiag64, ctx->b64, ctx->flags + 1, repeated,
+                                      ctx->mu64, (size_t)l.node_elems * sizeof(double), ctx->stream);
         if (e == hipSuccess) {
             if (esize == 4)
                 hipLaunchKernelGGL((gabp::st::k_node_init<float>), dim3(node_blocks(G)), dim3(256),
                                    0, ctx->stream, G, ctx->adiag64, ctx->b64, prior_mean,
-                                   (float *)ctx->aw, (float *)ctx->bw, ctx->flags + 1);
+                                   (float *)ctx->aw, (float *)ctx->bw, ctx->flags + 1,
+                                   (const uint32_t *)repeated);
             else
                 hipLaunchKernelGGL((gabp::st::k_node_init<double>), dim3(node_blocks(G)), dim3(256),
                                    0, ctx->stream, G, ctx->adiag64, ctx->b64, prior_mean,
-                                   (double *)ctx->aw, (double *)ctx->bw, ctx->flags + 1);
+                                   (double *)ctx->aw, (double *)ctx->bw, ctx->flags + 1,
+                                   (const uint32_t *)repeated);
             e = hipGetLastError();
         }
         if (e == hipSuccess)
