@@ -49,6 +49,13 @@ constexpr int deep_full_lds() {
 //                  1024^2 84 -> 74, 2048^2 336 -> 284
 //   FP64 5-point   64^2 3.7 -> 1.3, 256^2 4.2 -> 1.8, 512^2 8.9 -> 3.8,
 //                  1024^2 33 -> 14, 2048^2 118 -> 49
+// The 24 x 24 region is for FP64 with 5 points up to 128^2, where one tile per CU
+// leaves an iteration to the CU's FP64 rate and barriers: 9 waves to a workgroup
+// instead of 16.  Against the 32 x 32 one, calls of 10, 50 and 200 iterations: 24^2 1.50,
+// 1.35, 1.28 (1.81, 1.56, 1.42), 64^2 1.50, 1.37, 1.30 (1.86, 1.60, 1.44), 90 x 61 1.51,
+// 1.40, 1.30 (1.88, 1.62, 1.46), 128^2 1.55, 1.40, 1.32 (1.83, 1.61, 1.47).  Nine
+// iterations at most keep one tile per CU up to that size; eight of them (136^2) take
+// 2.03 in calls of 10 and 1.39 in calls of 200, against 1.94 and 1.48.
 // --------------------------------------------------------------------------
 constexpr DeepChoice kFullF32A2[] = {{32, 32, 3, 5, 0}, {64, 16, 3, 3, 3}};
 constexpr DeepChoice kFullF32A1[] = {{32, 32, 6, 12, 0}, {64, 16, 5, 5, 5}};

@@ -488,9 +488,13 @@ void launch_mode(const Grid &G, const void *in, void *out, void *gain, const voi
 
 // mode's kernel; the information-only one covers theta_slices slices per
 // workgroup (1, 2 or 4), the others one.  Loads ahead: the full iteration in FP32
-// (k_iter), the information-only one where that leaves it as many waves as
-// there are, between one and two per SIMD (a wave to 64 nodes of a row): 100 x 75 x 12
-// 12.5 -> 11.7 us, but 30 x 20 x 6 4.8 -> 6.0 and 512 x 256 x 8 90 -> 98.
+// (k_iter), the information-only one between one and two waves per SIMD (a wave to 64
+// nodes of a row), where its registers take no wave away and a wave's loads are not
+// hidden by others.  Microseconds without and with, by waves on 1024 SIMDs: 1100 9.8
+// and 8.9, 1280 10.4 and 9.5, 1350 11.7 and 11.4, 1800 12.5 and 11.7, 2040 12.6 and
+// 12.6, 2048 13.2 and 13.0.  Outside: 120 4.8 and 6.0, 256 5.6 and 6.4 (the kernel
+// starts 1 us later), 500 to 1000 1 to 5 % less; 2560 17.3 and 15.7, 3072 18.8 and
+// 18.6, 4000 23.7 and 24.3, 16384 90 and 97 (fewer waves at a time).
 template <typename T>
 void launch_any(int mode, int theta_slices, int cus, const Grid &G, const void *in, void *out,
                 void *gain, const void *aw, const void *bw, T eta, uint32_t *flags, uint32_t it,
