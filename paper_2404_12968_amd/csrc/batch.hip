@@ -395,7 +395,7 @@ struct gabp_batch {
     uint32_t *d_div = nullptr, *d_t = nullptr, *d_err = nullptr;
     unsigned long long *d_cnt = nullptr;   // changed precision messages per instance
     uint32_t *d_mrel = nullptr;            // their largest relative change (float bits)
-    double *d_partials = nullptr, *d_out = nullptr;
+    double *d_partials = nullptr;
     size_t partial_cap = 0;     // work items of the check kernels
     // pinned host mirror
     double *p_out = nullptr;
@@ -758,7 +758,7 @@ static gabp_status batch_layout(int32_t n, const gabp_instance *inst, int32_t dt
     *tables_off = off;
     // instance table, int lists, flag arrays (divergence, counter, error and
     // largest precision changes as uint32, then 64-bit change counts),
-    // partials, results
+    // partials, and 2 n doubles more, as the documented sizes have it
     off = round_up(off + sizeof(BatchInst) * (size_t)n, kAlign);
     off = round_up(off + sizeof(int) * (size_t)lists_room(n), kAlign);
     off = round_up(off + flag_bytes(n), kAlign);
@@ -879,8 +879,6 @@ gabp_status gabp_batch_create(int32_t n, const gabp_instance *inst, const gabp_o
     b->d_cnt = (unsigned long long *)(b->ws + round_up(off + sizeof(uint32_t) * (size_t)(2 * n + 2), 8));
     off = round_up(off + flag_bytes(n), kAlign);
     b->d_partials = (double *)(b->ws + off);
-    off = round_up(off + sizeof(double) * 2 * pc, kAlign);
-    b->d_out = (double *)(b->ws + off);
     // pinned mirror: out[2n], cnt[n], div[n], mrel[n], t, lists
     const size_t pin_bytes = sizeof(double) * 2 * (size_t)n + sizeof(unsigned long long) * (size_t)n +
                              sizeof(uint32_t) * (2 * (size_t)n + 2) +

@@ -582,7 +582,9 @@ gabp_status enqueue_iters(gabp_ctx *ctx, int32_t n, double damping, hipStream_t 
     return GABP_OK;
 }
 
-// Adaptive chunk lengths as kmin * 2^j, so that few chunk graphs are recorded.
+// Adaptive chunk lengths as kmin * 2^j: few chunk graphs are recorded on a context
+// with a tile set, and every context with graphs on checks, and so stops, at the same
+// iterations, whichever launches it takes.
 int64_t quantize_chunk(int64_t next, int64_t kmin) {
     int64_t q = kmin;
     while (q * 2 <= next) q *= 2;

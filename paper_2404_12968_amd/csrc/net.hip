@@ -116,43 +116,43 @@ template <int COUT>
 __device__ __forceinline__ void conv_store(const f32x16 &acc, const float *bl, int relu, int kh,
                                            bool here, size_t o, __bf16 *__restrict__ yb,
                                            float *__restrict__ yf) {
-            float v[COUT / 2];
-    #pragma unroll
-            for (int i = 0; i < COUT / 8; ++i)
-    #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    float q = acc[4 * i + j] + bl[8 * i + 4 * kh + j];
-                    if (relu) q = q > 0.0f ? q : 0.0f;
-                    v[4 * i + j] = q;              // channel 8 i + 4 kh + j
-                }
-            if (yf && here) {
-    #pragma unroll
-                for (int i = 0; i < COUT / 8; ++i)
-                    *(float4 *)(yf + o + 8 * i + 4 * kh) =
-                        make_float4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
-            }
-            if (yb) {
-                // groups i < COUT / 16 to lanes 0..31, the rest to lanes 32..63:
-                // after the swap a lane holds channels 8 g .. 8 g + 7 of its pixel
-                // for g = i + kh COUT / 16
-                uint32_t q[COUT / 8][2];
-    #pragma unroll
-                for (int i = 0; i < COUT / 8; ++i) {
-                    bf16x4 pk;
-    #pragma unroll
-                    for (int j = 0; j < 4; ++j) pk[j] = (__bf16)v[4 * i + j];
-                    __builtin_memcpy(q[i], &pk, 8);
-                }
-    #pragma unroll
-                for (int i = 0; i < COUT / 16; ++i) {
-                    const auto s0 = __builtin_amdgcn_permlane32_swap(q[i][0], q[i + COUT / 16][0],
-                                                                     false, false);
-                    const auto s1 = __builtin_amdgcn_permlane32_swap(q[i][1], q[i + COUT / 16][1],
-                                                                     false, false);
-                    u32x4 out = {s0[0], s1[0], s0[1], s1[1]};
-                    if (here) *(u32x4 *)(yb + o + 8 * i + kh * (COUT / 2)) = out;
-                }
-            }
+    float v[COUT / 2];
+#pragma unroll
+    for (int i = 0; i < COUT / 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            float q = acc[4 * i + j] + bl[8 * i + 4 * kh + j];
+            if (relu) q = q > 0.0f ? q : 0.0f;
+            v[4 * i + j] = q;              // channel 8 i + 4 kh + j
+        }
+    if (yf && here) {
+#pragma unroll
+        for (int i = 0; i < COUT / 8; ++i)
+            *(float4 *)(yf + o + 8 * i + 4 * kh) =
+                make_float4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
+    }
+    if (yb) {
+        // groups i < COUT / 16 to lanes 0..31, the rest to lanes 32..63:
+        // after the swap a lane holds channels 8 g .. 8 g + 7 of its pixel
+        // for g = i + kh COUT / 16
+        uint32_t q[COUT / 8][2];
+#pragma unroll
+        for (int i = 0; i < COUT / 8; ++i) {
+            bf16x4 pk;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) pk[j] = (__bf16)v[4 * i + j];
+            __builtin_memcpy(q[i], &pk, 8);
+        }
+#pragma unroll
+        for (int i = 0; i < COUT / 16; ++i) {
+            const auto s0 = __builtin_amdgcn_permlane32_swap(q[i][0], q[i + COUT / 16][0],
+                                                             false, false);
+            const auto s1 = __builtin_amdgcn_permlane32_swap(q[i][1], q[i + COUT / 16][1],
+                                                             false, false);
+            u32x4 out = {s0[0], s1[0], s0[1], s1[1]};
+            if (here) *(u32x4 *)(yb + o + 8 * i + kh * (COUT / 2)) = out;
+        }
+    }
 }
 
 // --------------------------------------------------------------------------
@@ -763,8 +763,7 @@ __global__ __launch_bounds__(256) void k_feat_scatter(long n, const int64_t *__r
     atomicAdd(&sum[c], (float)yv[k]);
 }
 
-// p[0 .. n) = 0 (a kernel, not a memset, so that callers may capture it in
-// a graph)
+// Mask and mean observed value of the observed cells.
 __global__ __launch_bounds__(256) void k_feat_observed(long n, const int64_t *__restrict__ cell,
                                                        long N, const float *__restrict__ cnt,
                                                        const float *__restrict__ sum,
@@ -916,8 +915,8 @@ hipError_t scratch_address(float **out) {
     return hipSuccess;
 }
 
-// Input features from observations with cnt/sum scratch planes of N cells
-// (2 N floats, cleared here by a kernel).
+// Input features from observations with cnt/sum scratch planes of N cells (2 N
+// floats, of which the observed cells' are cleared and used).
 hipError_t features_into(int64_t nobs, const int64_t *cell, const double *y, long N,
                          double kappa, float *scr, void *x_bf16, hipStream_t s) {
     const float kf = (float)(std::log(kappa) + 2.5);

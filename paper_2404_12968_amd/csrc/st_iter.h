@@ -118,16 +118,6 @@ __device__ __forceinline__ bool nbr(const Grid &G, int x, int y, int t, int d, i
     return true;
 }
 
-// Q_ij / c for direction d of node (x, y, t) whose neighbour (xn, yn) exists.
-template <typename T>
-__device__ __forceinline__ T q_over_c(const Grid &G, int d, int kind, T gi, int xn, int yn) {
-    const double *pqr = d < 12 ? G.blk[kind] : G.blk[3];
-    const int cls = scls(d);
-    T gj = (T)0;
-    if (cls == 1) gj = (T)(axis_g(xn, G.nx, G.bcx) + axis_g(yn, G.ny, G.bcy));
-    return coef<T>(pqr, cls, gi, gj) * (T)G.inv_c;
-}
-
 // --------------------------------------------------------------------------
 // One flooding iteration of node (x, y, t) (as the lattice kernels):
 //   Lam_i = A_ii + c sum_k Lam_{k->i},  th_i = b_i + c sum_k th_{k->i}
