@@ -82,27 +82,15 @@ __global__ __launch_bounds__(256) void k_post(Lattice L, int ntiles, FreezeTest 
 // node's arithmetic (resid_accum) and the order of the sums (tile by tile)
 // are those of resid_node, so the r^2 and b^2 partials (wave64 butterfly,
 // then LDS across the four waves, into partials[g]) are deterministic and do
-// not depend on the staging.  The workgroup that finishes last adds the partials
-// up, in the order of k_reduce, and reports to the host's pinned mirror: the sums,
-// and the context's flag words, whose freeze-test words it clears for the next
-// check.  A check of a small lattice was seven operations (clear, freeze test,
-// marginals, residual, reduction, two copies), 19 us of device time on 64 x 64
-// nodes and a gap after each; it is two launches of 10 us together.
+// not depend on the staging.  k_resid_report adds them up and reports.
 // --------------------------------------------------------------------------
 constexpr int kResidUnroll = 4;
-
-__device__ __forceinline__ double load_shared(const double *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 template <int ALPHA>
 __global__ __launch_bounds__(256) void k_resid(Lattice L, const double *__restrict__ mu,
                                                const double *__restrict__ adiag64,
                                                const double *__restrict__ b64,
-                                               double *__restrict__ partials, int ntiles,
-                                               uint32_t *__restrict__ flags,
-                                               double *__restrict__ h_red,
-                                               uint32_t *__restrict__ h_flags) {
+                                               double *__restrict__ partials, int ntiles) {
     constexpr int DEG = ALPHA == 1 ? 4 : 12;
     constexpr int R = ALPHA == 1 ? 1 : 2;
     constexpr int WX = 64 + 2 * R, WY = 4 + 2 * R, WN = WX * WY;
@@ -211,23 +199,33 @@ __global__ __launch_bounds__(256) void k_resid(Lattice L, const double *__restri
         sh[1][w] = bb;
     }
     __syncthreads();
-    __shared__ bool last;
     if (threadIdx.x == 0) {
         partials[2 * g] = (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]);
         partials[2 * g + 1] = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
-        // releases this workgroup's partials, acquires everyone's before it
-        last = __hip_atomic_fetch_add(flags + 2, 1u, __ATOMIC_ACQ_REL,
-                                      __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)nb - 1u;
     }
-    __syncthreads();
-    if (!last) return;
-    rr = bb = 0.0;
+}
+
+// The residual's partials added up in the order of k_reduce and reported to the
+// host's pinned mirror: the sums, and the context's flag words, whose freeze-test
+// words it clears for the next check.  A check was seven operations (clear, freeze
+// test, marginals, residual, reduction, two copies) and is three launches: with the
+// wait for it, frozen, 64^2 24 -> 20.6 us, 512^2 29.7 -> 26.3, 2048 x 1024 62 -> 58.9.
+// The last workgroup of k_resid to finish, which an atomic counter tells, could report:
+// 20.4 us on 64^2, but every workgroup writes its L2 back before it counts itself
+// (38.8 on 512^2, 79 on 2048 x 1024).
+__global__ __launch_bounds__(256) void k_resid_report(const double *__restrict__ partials, int nb,
+                                                      uint32_t *__restrict__ flags,
+                                                      double *__restrict__ h_red,
+                                                      uint32_t *__restrict__ h_flags) {
+    __shared__ double sh[2][4];
+    double rr = 0.0, bb = 0.0;
     for (int k = (int)threadIdx.x; k < nb; k += 256) {
-        rr += load_shared(partials + 2 * k);
-        bb += load_shared(partials + 2 * k + 1);
+        rr += partials[2 * k];
+        bb += partials[2 * k + 1];
     }
     rr = wave_sum(rr);
     bb = wave_sum(bb);
+    const int w = (int)(threadIdx.x >> 6);
     if ((threadIdx.x & 63u) == 0u) {
         sh[0][w] = rr;
         sh[1][w] = bb;
@@ -237,7 +235,6 @@ __global__ __launch_bounds__(256) void k_resid(Lattice L, const double *__restri
         h_red[0] = (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]);
         h_red[1] = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
         for (int k = 0; k < 8; ++k) h_flags[k] = flags[k];
-        flags[2] = 0;
         flags[4] = flags[5] = flags[6] = 0;
     }
 }
@@ -547,10 +544,12 @@ hipError_t launch_resid(const Lattice &L, const double *mu, const double *adiag6
     if (resident > 0 && resident < nb) nb = resident;
     if (L.alpha == 1)
         hipLaunchKernelGGL((k_resid<1>), dim3(nb), dim3(256), 0, s, L, mu, adiag64, b64, partials,
-                           nt, flags, h_red, h_flags);
+                           nt);
     else
         hipLaunchKernelGGL((k_resid<2>), dim3(nb), dim3(256), 0, s, L, mu, adiag64, b64, partials,
-                           nt, flags, h_red, h_flags);
+                           nt);
+    hipLaunchKernelGGL(k_resid_report, dim3(1), dim3(256), 0, s, (const double *)partials, nb,
+                       flags, h_red, h_flags);
     return hipGetLastError();
 }
 
