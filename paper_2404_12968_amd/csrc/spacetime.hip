@@ -282,31 +282,28 @@ __global__ __launch_bounds__(256) void k_upsample(const double *__restrict__ coa
 // Warm start from a predicted mean mu (dense FP64 [nt][ny][nx]): precision
 // messages zero, information messages th_{i->j} = -(Q_ij/c) mu_i, so the
 // beliefs start at mu + (b - A mu) / diag(A) (the fixed point when mu is the
-// posterior mean).  The entries Q_ij/c are those the iteration uses.
+// posterior mean).  The entries Q_ij/c are those the iteration uses.  Unrolled, so that
+// a direction's relation is known at compile time.
 template <typename T>
 __global__ __launch_bounds__(256) void k_warm_init(Grid G, const double *__restrict__ mu,
                                                    T *__restrict__ m) {
     const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (k >= (int64_t)G.nx * G.ny * G.nt) return;
-    const int x = (int)(k % G.nx);
-    const int y = (int)((k / G.nx) % G.ny);
-    const int t = (int)(k / ((int64_t)G.nx * G.ny));
-    const uint32_t i = (uint32_t)t * (uint32_t)G.slice + (uint32_t)(y * G.pitch + x);
-    const int kind = slice_kind(G, t);
+    const NodeAt n = node_at(G, (uint32_t)k);
+    const int kind = slice_kind(G, n.t);
     const T pq_same[3] = {(T)G.blk[kind][0], (T)G.blk[kind][1], (T)G.blk[kind][2]};
     const T pq_cross[3] = {(T)G.blk[3][0], (T)G.blk[3][1], (T)G.blk[3][2]};
-    const T gi = (T)(axis_g(x, G.nx, G.bcx) + axis_g(y, G.ny, G.bcy));
+    const T gi = (T)(axis_g(n.x, G.nx, G.bcx) + axis_g(n.y, G.ny, G.bcy));
     const T mi = (T)mu[k];
+#pragma unroll
     for (int d = 0; d < kDeg; ++d) {
-        int xn, yn, tn;
-        const bool ok = nbr(G, x, y, t, d, xn, yn, tn);
-        T th = (T)0;
-        if (ok) {
-            const T gj = (T)(axis_g(xn, G.nx, G.bcx) + axis_g(yn, G.ny, G.bcy));
-            th = -(q_dir<T>(G, d, gi, gj, pq_same, pq_cross) * mi);
-        }
-        (m + (size_t)d * G.plane)[i] = (T)0;
-        (m + (size_t)(kDeg + d) * G.plane)[i] = th;
+        uint32_t j;
+        int xn, yn;
+        const bool ok = nbr_at(G, n, d, j, xn, yn);
+        const T gj = scls(d) != 1 ? (T)0 : (T)(axis_g(xn, G.nx, G.bcx) + axis_g(yn, G.ny, G.bcy));
+        const T th = -(q_dir<T>(G, d, gi, gj, pq_same, pq_cross) * mi);
+        (m + (size_t)d * G.plane)[n.i] = (T)0;
+        (m + (size_t)(kDeg + d) * G.plane)[n.i] = ok ? th : (T)0;
     }
 }
 
