@@ -474,7 +474,7 @@ gabp_status st_sync(gabp_st_ctx *ctx) {
     return GABP_OK;
 }
 
-template <typename T, int MODE, int SL, bool AHEAD>
+template <typename T, int MODE, int SL, int AHEAD>
 void launch_mode(const Grid &G, const void *in, void *out, void *gain, const void *aw,
                  const void *bw, T eta, uint32_t *flags, uint32_t it, hipStream_t s) {
     const unsigned n = (unsigned)(G.tiles_x * G.tiles_y * ((G.nt + SL - 1) / SL));
@@ -484,8 +484,8 @@ void launch_mode(const Grid &G, const void *in, void *out, void *gain, const voi
 }
 
 // mode's kernel; the information-only one covers theta_slices slices per
-// workgroup (1, 2 or 4), the others one.  Loads ahead: the full iteration in FP32
-// (k_iter), the information-only one between one and two waves per SIMD (a wave to 64
+// workgroup (1, 2 or 4), the others one.  Loads ahead: the full iteration
+// (k_iter), in FP32 the information-only one between one and two waves per SIMD (a wave to 64
 // nodes of a row), where its registers take no wave away and a wave's loads are not
 // hidden by others.  Microseconds without and with, by waves on 1024 SIMDs: 1100 9.8
 // and 8.9, 1280 10.4 and 9.5, 1350 11.7 and 11.4, 1800 12.5 and 11.7, 2040 12.6 and
@@ -501,17 +501,17 @@ void launch_any(int mode, int theta_slices, int cus, const Grid &G, const void *
     const int64_t waves = (int64_t)G.tiles_x * G.ny * G.nt;
     const bool ahead = F && waves > (int64_t)4 * cus && waves <= (int64_t)8 * cus;
     if (mode == MODE_FULL)
-        launch_mode<T, MODE_FULL, 1, F>(G, in, out, gain, aw, bw, eta, flags, it, s);
+        launch_mode<T, MODE_FULL, 1, F ? kDeg : 6>(G, in, out, gain, aw, bw, eta, flags, it, s);
     else if (mode == MODE_GAIN)
-        launch_mode<T, MODE_GAIN, 1, false>(G, in, out, gain, aw, bw, eta, flags, it, s);
+        launch_mode<T, MODE_GAIN, 1, 0>(G, in, out, gain, aw, bw, eta, flags, it, s);
     else if (theta_slices == 4)
-        launch_mode<T, MODE_THETA, 4, false>(G, in, out, gain, aw, bw, eta, flags, it, s);
+        launch_mode<T, MODE_THETA, 4, 0>(G, in, out, gain, aw, bw, eta, flags, it, s);
     else if (theta_slices == 2)
-        launch_mode<T, MODE_THETA, 2, false>(G, in, out, gain, aw, bw, eta, flags, it, s);
+        launch_mode<T, MODE_THETA, 2, 0>(G, in, out, gain, aw, bw, eta, flags, it, s);
     else if (ahead)
-        launch_mode<T, MODE_THETA, 1, F>(G, in, out, gain, aw, bw, eta, flags, it, s);
+        launch_mode<T, MODE_THETA, 1, F ? kDeg : 0>(G, in, out, gain, aw, bw, eta, flags, it, s);
     else
-        launch_mode<T, MODE_THETA, 1, false>(G, in, out, gain, aw, bw, eta, flags, it, s);
+        launch_mode<T, MODE_THETA, 1, 0>(G, in, out, gain, aw, bw, eta, flags, it, s);
 }
 
 unsigned node_blocks(const Grid &G) {

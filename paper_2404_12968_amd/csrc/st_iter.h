@@ -248,20 +248,19 @@ struct Edges {
     }
 };
 
-// A node's previous outgoing messages, with AHEAD loaded beside the incoming ones
-// (MODE_THETA: the gains in place of the precision messages).
-template <typename T, int MODE, bool AHEAD>
+// A node's previous outgoing messages (MODE_THETA: the gains in place of the precision
+// messages).  Those of the first AHEAD directions are loaded beside the incoming
+// messages, direction d's of the others when direction d - AHEAD is computed.
+template <typename T, int MODE, int AHEAD>
 struct Own {
-    T l[AHEAD ? kDeg : 1], t[AHEAD ? kDeg : 1];
-    __device__ __forceinline__ void load(const T *__restrict__ m_in, const T *__restrict__ gain,
-                                         int64_t plane, uint32_t rc, uint32_t xb) {
-        if constexpr (AHEAD) {
-#pragma unroll
-            for (int d = 0; d < kDeg; ++d) {
-                const size_t at = (size_t)d * plane + rc, at2 = (size_t)(kDeg + d) * plane + rc;
-                l[d] = *behind((MODE == MODE_THETA ? gain : m_in) + at, xb);
-                t[d] = *behind(m_in + at2, xb);
-            }
+    T l[AHEAD > 0 ? kDeg : 1], t[AHEAD > 0 ? kDeg : 1];
+    __device__ __forceinline__ void load(int d, const T *__restrict__ m_in,
+                                         const T *__restrict__ gain, int64_t plane, uint32_t rc,
+                                         uint32_t xb) {
+        if constexpr (AHEAD > 0) {
+            const size_t at = (size_t)d * plane + rc, at2 = (size_t)(kDeg + d) * plane + rc;
+            l[d] = *behind((MODE == MODE_THETA ? gain : m_in) + at, xb);
+            t[d] = *behind(m_in + at2, xb);
         }
     }
 };
@@ -270,15 +269,19 @@ struct Own {
 // unused in MODE_THETA, bt and tin in MODE_GAIN).  The planes' addresses are
 // made again (`plane` is a copy the compiler cannot tell from another value)
 // rather than kept from the gather: 76 pairs of scalar registers spill.
-template <typename T, int MODE, bool INNER, bool AHEAD>
+template <typename T, int MODE, bool INNER, int AHEAD>
 __device__ __forceinline__ void st_out(const Edges<T, INNER> &E, int64_t plane, uint32_t rc, uint32_t xb,
                                        const T *__restrict__ m_in, T *__restrict__ m_out,
                                        T *__restrict__ gain, T eta, const T *lin, const T *tin,
-                                       T bl, T bt, const Own<T, MODE, AHEAD> &own, bool &bad) {
+                                       T bl, T bt, Own<T, MODE, AHEAD> &own, bool &bad) {
     const T keep = (T)1 - eta;
     T z = (T)0;   // MODE_THETA: stays zero exactly when every new message is finite
 #pragma unroll
     for (int d = 0; d < kDeg; ++d) {
+        if (AHEAD > 0 && d + AHEAD < kDeg) {
+            own.load(d + AHEAD, m_in, gain, plane, rc, xb);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         const bool ok = E.ok(d);
         const size_t at = (size_t)d * plane + rc, at2 = (size_t)(kDeg + d) * plane + rc;
         if constexpr (MODE == MODE_FULL) {
@@ -286,8 +289,8 @@ __device__ __forceinline__ void st_out(const Edges<T, INNER> &E, int64_t plane, 
             const T lc = bl - lin[d];
             const T tc = bt - tin[d];
             const T g = edge_gain(q, lc);
-            const T ol = AHEAD ? own.l[AHEAD ? d : 0] : *behind(m_in + at, xb);
-            const T ot = AHEAD ? own.t[AHEAD ? d : 0] : *behind(m_in + at2, xb);
+            const T ol = AHEAD > 0 ? own.l[AHEAD > 0 ? d : 0] : *behind(m_in + at, xb);
+            const T ot = AHEAD > 0 ? own.t[AHEAD > 0 ? d : 0] : *behind(m_in + at2, xb);
             T dl = fmadd(eta, g * q, keep * ol);
             T dt = fmadd(eta, g * tc, keep * ot);
             bad |= ok && (!(lc > (T)0) || !isfinite(dl) || !isfinite(dt));
@@ -300,8 +303,8 @@ __device__ __forceinline__ void st_out(const Edges<T, INNER> &E, int64_t plane, 
             *behind(gain + at, xb) = ok ? g : (T)0;
         } else {
             // edges that do not exist: gain and previous message are zero
-            const T g = AHEAD ? own.l[AHEAD ? d : 0] : __builtin_nontemporal_load(behind(gain + at, xb));
-            const T ot = AHEAD ? own.t[AHEAD ? d : 0] : *behind(m_in + at2, xb);
+            const T g = AHEAD > 0 ? own.l[AHEAD > 0 ? d : 0] : __builtin_nontemporal_load(behind(gain + at, xb));
+            const T ot = AHEAD > 0 ? own.t[AHEAD > 0 ? d : 0] : *behind(m_in + at2, xb);
             const T dt = fmadd(eta, g * (bt - tin[d]), keep * ot);
             z = fmadd(dt, (T)0, z);
             __builtin_nontemporal_store(dt, behind(m_out + at2, xb));
@@ -348,19 +351,22 @@ __device__ __forceinline__ void wg_tile(int b, int tiles_x, int tiles_y, int nt,
 // written once at least: 4.6 TB/s; 2.64 ms when boundary tiles took a masked
 // path in a second launch) and 1.42 ms per information-only one (7.6 GB, 5.4 TB/s,
 // above what a device copy streams).  AHEAD: a node's previous messages (and
-// gains) are loaded beside the incoming ones, every load before the first use, at
-// the price of registers.  The full iteration has it in FP32: 183 VGPRs, two waves per
-// SIMD, against 112 and four, yet 25 -> 18 us on 100 x 75 x 12, 675 -> 567 on 256 x
-// 256 x 64, 2380 -> 2208 on 512 x 512 x 64; held to three waves it spills (670 and
-// 2675).
+// gains) are loaded beside the incoming ones, of so many directions (Own), every load
+// before the first use, at the price of registers.  The full iteration has it in FP32
+// for all 38: 183 VGPRs, two waves per SIMD, against 112 and four, yet 25 -> 18 us on
+// 100 x 75 x 12, 675 -> 567 on 256 x 256 x 64, 2380 -> 2208 on 512 x 512 x 64; held to
+// three waves it spills (670 and 2675).  In FP64 for six at a time, as many as fit into
+// the 256 VGPRs of two waves (248; 204 with none, 36 spilled with 12): 100 x 75 x 12
+// 37.3 -> 30.0, 256 x 256 x 16 419 -> 297, 128 x 128 x 64 417 -> 280, periodic 130 x
+// 130 x 10 67 -> 60.5.
 // diverged_at[0]
 // records the first iteration whose launch met an invalid value; launches of
 // later iterations return at once (the launch of the iteration that met it
 // completes, so its output buffer holds that iteration).  MODE_GAIN passes
 // it = 0.
-template <typename T, int MODE, int SL, bool AHEAD>
+template <typename T, int MODE, int SL, int AHEAD>
 __global__ __launch_bounds__(256 * SL,
-                             sizeof(T) == 8 || AHEAD ? 2 : MODE == MODE_THETA ? 8 : 4) void k_iter(
+                             sizeof(T) == 8 || AHEAD > 0 ? 2 : MODE == MODE_THETA ? 8 : 4) void k_iter(
     Grid G, const T *__restrict__ m_in, T *__restrict__ m_out, T *__restrict__ gain,
     const T *__restrict__ aw, const T *__restrict__ bw, T eta, uint32_t *__restrict__ diverged_at,
     uint32_t it) {
@@ -392,9 +398,10 @@ __global__ __launch_bounds__(256 * SL,
         if (MODE != MODE_GAIN) tin[d] = R.in(m_in + (size_t)(kDeg + (d ^ 1)) * G.plane, d);
     }
     Own<T, MODE, AHEAD> own;
-    own.load(m_in, gain, G.plane, rc, xb);
+#pragma unroll
+    for (int d = 0; d < AHEAD; ++d) own.load(d, m_in, gain, G.plane, rc, xb);
     const T a = *behind(aw + rc, xb), b = *behind(bw + rc, xb);
-    if (AHEAD) __builtin_amdgcn_sched_barrier(0);   // every load is on its way
+    if (AHEAD > 0) __builtin_amdgcn_sched_barrier(0);   // every load is on its way
     if (MODE == MODE_FULL) __builtin_amdgcn_s_setprio(0);
     if (MODE != MODE_THETA) bl = belief(a, lin, c);
     if (MODE != MODE_GAIN) bt = belief(b, tin, c);
