@@ -60,52 +60,71 @@ __device__ __forceinline__ int find_item(const int *__restrict__ prefix, int n, 
     return lo;
 }
 
-// One full iteration of every instance of a list, from its buffer `buf` to the
-// other, iteration number t.  Work item w maps to
-// instance act[a] and tile w - prefix[a] of that instance (64 x 4*RPT nodes);
-// each workgroup of the persistent grid takes one contiguous range of items,
-// so neighbouring tiles share a CU and its XCD's L2.
-template <typename T, int RPT>
+// One iteration (number t) of every instance of a list, from its buffer `buf` to the
+// other: full, or, FROZEN, information-only.  Workgroup g after the XCD remap takes
+// work item prefix[0] + g, tile item - prefix[a] of instance act[a] (64 x 4*RPT nodes,
+// a row of threads to every fourth row) in the strip order of the lone context's
+// kernels, so that each XCD takes a contiguous range of tiles and the rows a tile
+// shares with its neighbours are in its L2.
+// ALPHA: the instances' prior order, 0 for either.
+// The rows are a loop the compiler cannot see through, also where there is one: the
+// loads of every prior order, inside and at the boundary, brought in front of their
+// branches took 231 registers in FP32 and 256 in FP64 (now 131 and 211, for one order
+// of 13 points 128 and 204).  One iteration of 1024^2 alone, call and waits included,
+// FP32 73 -> 68 us, FP64 132 -> 105; of 2048 x 1024 with 13 and with 5 points 153 -> 140
+// and 321 -> 265 (two launches); information-only 76 -> 52, 110 -> 74, 165 -> 104 and
+// 270 -> 195, where a tile of several iterations had taken one.
+template <typename T, int RPT, int ALPHA, bool FROZEN>
 __global__ __launch_bounds__(256) void k_batch_iter(const BatchInst *__restrict__ inst,
                                                     const int *__restrict__ act,
                                                     const int *__restrict__ prefix, int nact,
-                                                    int total, int buf, uint32_t t, T eta,
+                                                    int buf, uint32_t t, T eta,
                                                     uint32_t *__restrict__ diverged_at) {
     constexpr int TH = 4 * RPT;
-    const int per = (total + (int)gridDim.x - 1) / (int)gridDim.x;
-    const int w1 = min(total, ((int)blockIdx.x + 1) * per);
-    for (int w = (int)blockIdx.x * per; w < w1; ++w) {
-        const int a = __builtin_amdgcn_readfirstlane(find_item(prefix, nact, w));
-        const int I = __builtin_amdgcn_readfirstlane(act[a]);
-        const uint32_t seen = diverged_at[I];
-        if (seen != 0u && seen < t) continue;   // of an earlier iteration: this one is written whole
-        const BatchInst &B = inst[I];
-        const Lattice L = B.L;
-        const int tile = w - prefix[a];
-        const int tx = tile % L.tiles_x, ty = tile / L.tiles_x;
-        const int x = tx * 64 + (int)(threadIdx.x & 63u);
-        const int y0 = ty * TH + (int)(threadIdx.x >> 6);
-        const bool interior = tx * 64 >= 2 && tx * 64 + 66 <= L.nx && ty * TH >= 2 &&
-                              ty * TH + TH + 2 <= L.ny;
-        const T *m_in = (const T *)B.msg[buf];
-        T *m_out = (T *)B.msg[buf ^ 1];
-        bool bad = false;
-        if (x < L.nx) {
+    const int w = prefix[0] + xcd_remap((int)blockIdx.x, (int)gridDim.x);
+    const int a = __builtin_amdgcn_readfirstlane(find_item(prefix, nact, w));
+    const int I = __builtin_amdgcn_readfirstlane(act[a]);
+    const uint32_t seen = diverged_at[I];
+    if (seen != 0u && seen < t) return;   // of an earlier iteration: this one is written whole
+    const BatchInst &B = inst[I];
+    const Lattice L = B.L;
+    int tx, ty;
+    strip_order(w - prefix[a], L.tiles_x, (L.ny + TH - 1) / TH, tx, ty);
+    const int x = tx * 64 + (int)(threadIdx.x & 63u);
+    const int y0 = ty * TH + (int)(threadIdx.x >> 6);
+    const bool interior = tx * 64 >= 2 && tx * 64 + 66 <= L.nx && ty * TH >= 2 &&
+                          ty * TH + TH + 2 <= L.ny;
+    const T *m_in = (const T *)B.msg[buf], *bw = (const T *)B.b_w;
+    const T *co = (const T *)(FROZEN ? B.gain : B.adiag_w);
+    T *m_out = (T *)B.msg[buf ^ 1];
+    bool bad = false;
+    int rows = RPT;
+    asm volatile("" : "+s"(rows));
+    if (x < L.nx) {
 #pragma unroll 1
-            for (int k = 0; k < RPT; ++k) {
-                const int y = y0 + 4 * k;
-                if (y >= L.ny) break;
-                if (L.alpha == 1) {
-                    if (interior) iter_node<T, 1, true>(L, m_in, m_out, (const T *)B.adiag_w, (const T *)B.b_w, eta, bad, x, y);
-                    else iter_node<T, 1, false>(L, m_in, m_out, (const T *)B.adiag_w, (const T *)B.b_w, eta, bad, x, y);
+        for (int k = 0; k < rows; ++k) {
+            const int y = y0 + 4 * k;
+            if (y >= L.ny) break;
+            if constexpr (FROZEN) {
+                if (ALPHA == 1 || (ALPHA == 0 && L.alpha == 1)) {
+                    if (interior) iter_theta_node<T, 1, true>(L, m_in, m_out, co, bw, eta, bad, x, y);
+                    else iter_theta_node<T, 1, false>(L, m_in, m_out, co, bw, eta, bad, x, y);
                 } else {
-                    if (interior) iter_node<T, 2, true>(L, m_in, m_out, (const T *)B.adiag_w, (const T *)B.b_w, eta, bad, x, y);
-                    else iter_node<T, 2, false>(L, m_in, m_out, (const T *)B.adiag_w, (const T *)B.b_w, eta, bad, x, y);
+                    if (interior) iter_theta_node<T, 2, true>(L, m_in, m_out, co, bw, eta, bad, x, y);
+                    else iter_theta_node<T, 2, false>(L, m_in, m_out, co, bw, eta, bad, x, y);
+                }
+            } else {
+                if (ALPHA == 1 || (ALPHA == 0 && L.alpha == 1)) {
+                    if (interior) iter_node<T, 1, true>(L, m_in, m_out, co, bw, eta, bad, x, y);
+                    else iter_node<T, 1, false>(L, m_in, m_out, co, bw, eta, bad, x, y);
+                } else {
+                    if (interior) iter_node<T, 2, true>(L, m_in, m_out, co, bw, eta, bad, x, y);
+                    else iter_node<T, 2, false>(L, m_in, m_out, co, bw, eta, bad, x, y);
                 }
             }
         }
-        if (bad) diverged_at[I] = t;
     }
+    if (bad) diverged_at[I] = t;
 }
 
 // Work item of a multi-iteration launch: the tile (tx, ty) of instance I, on the
@@ -390,8 +409,8 @@ struct gabp_batch {
     // device arrays (inside the workspace)
     BatchInst *d_inst = nullptr;
     int *d_act = nullptr, *d_pprefix = nullptr, *d_frozen = nullptr;
-    int *d_actu = nullptr, *d_wprefu = nullptr;   // running, precision not frozen (1 iteration)
-    int *d_gact = nullptr, *d_gpre = nullptr;     // running, by group (several iterations)
+    int *d_gact = nullptr;      // running, by group, those not frozen first
+    int *d_gpre = nullptr, *d_spre = nullptr;   // their items of several and of one iteration
     uint32_t *d_div = nullptr, *d_t = nullptr, *d_err = nullptr;
     unsigned long long *d_cnt = nullptr;   // changed precision messages per instance
     uint32_t *d_mrel = nullptr;            // their largest relative change (float bits)
@@ -401,8 +420,8 @@ struct gabp_batch {
     double *p_out = nullptr;
     uint32_t *p_div = nullptr, *p_mrel = nullptr, *p_t = nullptr;
     unsigned long long *p_cnt = nullptr;
-    int *p_lists = nullptr;     // staging of the lists
-    bool staged = false;        // ... which a copy still reads
+    int *p_lists = nullptr;     // kStages stagings of the lists,
+    int staged = 0;             // of which copies may still read so many
     // rows per thread of the one-iteration kernel: the last iteration before a
     // check, of instances not frozen; one hides its loads best
     int rpt = 1;
@@ -411,10 +430,12 @@ struct gabp_batch {
     double freeze_rel = 0.0;
     int64_t t = 0;              // iterations applied to the running set
     // current work lists
-    int nact = 0, ptotal = 0, nu = 0, wtotu = 0;
+    int nact = 0, ptotal = 0, nu = 0;
     struct Group {
-        int off = 0, n = 0, items = 0;   // in d_gact; d_gpre from off + its index
+        int off = 0, n = 0;              // in d_gact and d_spre; in d_gpre from off + its index
+        int items = 0, singles = 0;
         gabp::DeepPlan plan{0, 1};
+        int S = 1;                       // iterations that its tiles are for, at most plan.S
     } group[4];
     bool lists_dirty = true;
     std::vector<BatchRun> runs;   // runs since the last check read-back
@@ -458,9 +479,10 @@ int tiles_iter_of(const Lattice &L, int rpt) {
     return L.tiles_x * ((L.ny + 4 * rpt - 1) / (4 * rpt));
 }
 
-// lists staging / device layout: act[n] pprefix[n+1] frozen[n] actu[n]
-// wprefu[n+1] gact[n] gpre[n+4]
-constexpr int lists_ints(int n) { return 7 * n + 6; }
+// lists staging / device layout: act[n] pprefix[n+1] frozen[n] gact[n] gpre[n+4]
+// spre[n+1]
+constexpr int lists_ints(int n) { return 6 * n + 6; }
+constexpr int kStages = 4;
 // the workspace's share, as the documented sizes have it
 constexpr int lists_room(int n) { return 11 * n + 5; }
 static_assert(lists_ints(1) <= lists_room(1), "lists fit their room from n = 1 on");
@@ -484,15 +506,52 @@ gabp::DeepPlan group_plan(const gabp_batch *b, int g, const std::vector<int> &me
     return {n - 1, c[n - 1].bulk};
 }
 
-// Rebuild the work lists of the running instances (host staging, then one
-// copy into the device arrays).
-gabp_status upload_lists(gabp_batch *b) {
+// A run of k iterations of a group: the first `iters` in `launches` launches of several
+// iterations, the others singly.  Instances not frozen run at least the last one
+// singly, so that they end on their two newest iterations in their two buffers (the
+// freeze test needs that).  The launches have the parity of their iterations, so that
+// an instance's state stays in the buffer its iteration number selects: one iteration
+// more runs singly where that makes it so.  Launches of one iteration are left to
+// the single kernel, whose tiles have no region around them; and four full iterations
+// are three and a single one where they would be two and two: those read and write a
+// region twice for what one iteration costs alone (1024^2 FP64, five iterations a call
+// 459 -> 414 us; two of two took as long as four single ones).
+struct Split {
+    int iters = 0, launches = 0;
+    // iterations that the tiles are for, the longest launch's: tiles for more have a
+    // larger halo than it needs (four frozen iterations of 1024^2 FP32 in two launches
+    // 144 -> 107 us, of 700 x 600 with 5 points in one 61 -> 60)
+    int tile() const { return launches > 0 ? (iters + launches - 1) / launches : 1; }
+};
+Split split_run(int g, int k, int S) {
+    int n = g < 2 ? k - 1 : k;
+    if (n < 3) return {};
+    auto launches = [&]() { return (n + S - 1) / S; };
+    n -= (launches() ^ n) & 1;
+    const int l = launches() + ((launches() ^ n) & 1);
+    if (g < 2 && n == 4 && l == 2 && S >= 3) return {3, 1};
+    return l < n ? Split{n, l} : Split{};
+}
+
+// Work lists of the running instances for a run of k iterations, if they are not
+// up to date (host staging, then one copy into the device arrays).
+gabp_status upload_lists(gabp_batch *b, int k) {
+    bool same = !b->lists_dirty;
+    for (int g = 0; g < 4; ++g) {
+        const gabp_batch::Group &G = b->group[g];
+        const Split q = split_run(g, k, G.plan.S);
+        same = same && (G.n == 0 || q.launches == 0 || G.S == q.tile());
+    }
+    if (same) return GABP_OK;
     const int n = b->n;
-    if (b->staged) BHIP(b, hipStreamSynchronize(b->stream));
-    b->staged = false;
-    int *act = b->p_lists, *pp = act + n, *fz = pp + n + 1, *actu = fz + n, *wpu = actu + n;
-    int *gact = wpu + n + 1, *gpre = gact + n;
-    int na = 0, p = 0, nu = 0, wu = 0;
+    if (b->staged == kStages) {
+        BHIP(b, hipStreamSynchronize(b->stream));
+        b->staged = 0;
+    }
+    int *act = b->p_lists + (size_t)b->staged * lists_ints(n), *pp = act + n, *fz = pp + n + 1;
+    int *gact = fz + n, *gpre = gact + n, *spre = gpre + n + 4;
+    const int *lists = act;
+    int na = 0, p = 0;
     std::vector<int> members[4];
     for (int i = 0; i < n; ++i) {
         InstHost &H = b->h[i];
@@ -502,63 +561,75 @@ gabp_status upload_lists(gabp_batch *b) {
         pp[na++] = p;
         p += H.tiles_check;
         members[group_of(H, H.frozen)].push_back(i);
-        if (H.frozen) continue;
-        actu[nu] = i;
-        wpu[nu++] = wu;
-        wu += tiles_iter_of(H.L, b->rpt);
     }
     pp[na] = p;
-    wpu[nu] = wu;
     b->nact = na;
     b->ptotal = p;
-    b->nu = nu;
-    b->wtotu = wu;
-    int off = 0;
+    b->nu = (int)(members[0].size() + members[1].size());
+    int off = 0, singles = 0;
     for (int g = 0; g < 4; ++g) {
         gabp_batch::Group &G = b->group[g];
         const int dt = b->dtype == GABP_F32 ? 0 : 1, alpha = (g & 1) + 1;
         int nc;
         const gabp::DeepChoice *c = g < 2 ? gabp::full_choices(dt, alpha, nc)
                                           : gabp::deep_choices(dt, alpha, nc);
-        G.plan = group_plan(b, g, members[g]);
+        if (b->lists_dirty) G.plan = group_plan(b, g, members[g]);
+        G.S = split_run(g, k, G.plan.S).tile();
         c += G.plan.region;
         G.off = off;
         G.n = (int)members[g].size();
+        const int s0 = singles;
         G.items = 0;
-        for (int k = 0; k < G.n; ++k) {
-            const Lattice &L = b->h[members[g][k]].L;
-            gact[off + k] = members[g][k];
-            gpre[off + g + k] = G.items;
-            G.items += (int)gabp::deep_tiles(alpha, L.nx, L.ny, c->rw, c->rh, G.plan.S);
+        for (int q = 0; q < G.n; ++q) {
+            const Lattice &L = b->h[members[g][q]].L;
+            gact[off + q] = members[g][q];
+            gpre[off + g + q] = G.items;
+            G.items += (int)gabp::deep_tiles(alpha, L.nx, L.ny, c->rw, c->rh, G.S);
+            spre[off + q] = singles;
+            singles += tiles_iter_of(L, g < 2 ? b->rpt : 1);
         }
         gpre[off + g + G.n] = G.items;
+        G.singles = singles - s0;
         off += G.n;
     }
+    spre[off] = singles;
     // all lists are contiguous from d_act on
-    BHIP(b, hipMemcpyAsync(b->d_act, b->p_lists, sizeof(int) * (size_t)lists_ints(n),
+    BHIP(b, hipMemcpyAsync(b->d_act, lists, sizeof(int) * (size_t)lists_ints(n),
                            hipMemcpyHostToDevice, b->stream));
-    b->staged = true;
+    ++b->staged;
     b->lists_dirty = false;
     return GABP_OK;
 }
 
-// Iteration t of the instances not frozen.
-gabp_status launch_single(gabp_batch *b, int64_t t, double eta) {
-    if (b->nu == 0) return GABP_OK;
-    const int grid = std::min(kBatchGrid, std::max(1, b->wtotu));
-    const int buf = (int)((t - 1) & 1);
-    if (b->dtype == GABP_F32) {
-        switch (b->rpt) {
-#define RPT_CASE(R) case R: hipLaunchKernelGGL((gabp::k_batch_iter<float, R>), dim3(grid), dim3(256), 0, b->stream, b->d_inst, b->d_actu, b->d_wprefu, b->nu, b->wtotu, buf, (uint32_t)t, (float)eta, b->d_div); break;
-            RPT_CASE(1) RPT_CASE(2) RPT_CASE(4) default: RPT_CASE(8)
-#undef RPT_CASE
-        }
+// Iteration t of groups g0 to g1 (both not frozen or both frozen), one launch.
+template <typename T, int ALPHA>
+void single_k(gabp_batch *b, int g0, int g1, int64_t t, double eta) {
+    const gabp_batch::Group &G0 = b->group[g0], &G1 = b->group[g1];
+    const int n = g0 == g1 ? G0.n : G0.n + G1.n;
+    const unsigned items = (unsigned)(g0 == g1 ? G0.singles : G0.singles + G1.singles);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(items), dim3(256), 0, b->stream, b->d_inst,
+                           b->d_gact + G0.off, b->d_spre + G0.off, n, (int)((t - 1) & 1),
+                           (uint32_t)t, (T)eta, b->d_div);
+    };
+    if (g0 >= 2) go(gabp::k_batch_iter<T, 1, ALPHA, true>);
+    else if (b->rpt == 1) go(gabp::k_batch_iter<T, 1, ALPHA, false>);
+    else if (b->rpt == 2) go(gabp::k_batch_iter<T, 2, ALPHA, false>);
+    else if (b->rpt == 4) go(gabp::k_batch_iter<T, 4, ALPHA, false>);
+    else go(gabp::k_batch_iter<T, 8, ALPHA, false>);
+}
+
+// Iteration t of group g (5-point) and the one after it (13-point), as far as they are
+// named: in one launch while its workgroups run at once (nine instances up to 150 x 120
+// FP32 29 us, 35 in two), then each in one, with the registers of its own order only
+// (2048 x 1024 of both orders 174 us in one, 141 in two).
+gabp_status launch_single(gabp_batch *b, int g, bool five, bool thirteen, int64_t t, double eta) {
+    const bool f32 = b->dtype == GABP_F32;
+    if (five && thirteen && b->group[g].singles + b->group[g + 1].singles <= 4 * b->cus) {
+        (f32 ? single_k<float, 0> : single_k<double, 0>)(b, g, g + 1, t, eta);
     } else {
-        switch (b->rpt) {
-#define RPT_CASE(R) case R: hipLaunchKernelGGL((gabp::k_batch_iter<double, R>), dim3(grid), dim3(256), 0, b->stream, b->d_inst, b->d_actu, b->d_wprefu, b->nu, b->wtotu, buf, (uint32_t)t, eta, b->d_div); break;
-            RPT_CASE(1) RPT_CASE(2) RPT_CASE(4) default: RPT_CASE(8)
-#undef RPT_CASE
-        }
+        if (five) (f32 ? single_k<float, 1> : single_k<double, 1>)(b, g, g, t, eta);
+        if (thirteen) (f32 ? single_k<float, 2> : single_k<double, 2>)(b, g + 1, g + 1, t, eta);
     }
     BHIP(b, hipGetLastError());
     return GABP_OK;
@@ -570,7 +641,7 @@ void deep_k(gabp_batch *b, int g, int n, int buf, int64_t t, double eta) {
     const gabp_batch::Group &G = b->group[g];
     hipLaunchKernelGGL((gabp::k_batch_deep<T, ALPHA, RW, RH>), dim3((unsigned)G.items), dim3(1024),
                        0, b->stream, b->d_inst, b->d_gact + G.off, b->d_gpre + G.off + g, G.n,
-                       G.plan.S, n, buf, (uint32_t)t, (T)eta, b->d_div);
+                       G.S, n, buf, (uint32_t)t, (T)eta, b->d_div);
 }
 
 template <typename T, int ALPHA, int RW, int RH, int NT, bool SPLIT>
@@ -578,7 +649,7 @@ void full_k(gabp_batch *b, int g, int n, int buf, int64_t t, double eta) {
     const gabp_batch::Group &G = b->group[g];
     hipLaunchKernelGGL((gabp::k_batch_deep_full<T, ALPHA, RW, RH, NT, SPLIT>),
                        dim3((unsigned)G.items), dim3(NT), 0, b->stream, b->d_inst,
-                       b->d_gact + G.off, b->d_gpre + G.off + g, G.n, G.plan.S, n, buf,
+                       b->d_gact + G.off, b->d_gpre + G.off + g, G.n, G.S, n, buf,
                        (uint32_t)t, (T)eta, b->d_div);
 }
 
@@ -599,23 +670,16 @@ gabp_status launch_group(gabp_batch *b, int g, int n, int buf, int64_t t, double
     return GABP_OK;
 }
 
-// Record a run of k iterations about to be applied to the running set.  Frozen
-// instances run all of them several to a launch, the others all but the last,
-// which runs singly, so that they end on their two newest iterations in their two
-// buffers (the freeze test needs that).  Each group's number of launches has the
-// parity of its iterations, so that an instance's state stays in the buffer its
-// iteration number selects.
+// Record a run of k iterations about to be applied to the running set.
 void record_run(gabp_batch *b, int k, double eta) {
     BatchRun r;
     r.k = k;
     r.eta = eta;
     for (int g = 0; g < 4; ++g) {
         if (b->group[g].n == 0) continue;
-        const int n = g < 2 ? (k >= 3 ? k - 1 : 0) : k, S = b->group[g].plan.S;
-        int l = (n + S - 1) / S;
-        if ((l ^ n) & 1) ++l;
-        r.iters[g] = n;
-        r.deeps[g] = l;
+        const Split q = split_run(g, k, b->group[g].plan.S);
+        r.iters[g] = q.iters;
+        r.deeps[g] = q.launches;
     }
     r.couples = b->group[2].n + b->group[3].n > 0 && k >= 5 ? (k - 1) / 4 : 0;
     r.t0.resize(b->n);
@@ -627,20 +691,25 @@ void record_run(gabp_batch *b, int k, double eta) {
     b->runs.push_back(std::move(r));
 }
 
-// Record and issue k iterations of the running set.
+// Record and issue k iterations of the running set (on lists for them).
 gabp_status run_iters(gabp_batch *b, int k, double eta) {
+    gabp_status st = upload_lists(b, k);
+    if (st != GABP_OK) return st;
     if (b->nact > 0 && k > 0) {
         record_run(b, k, eta);
         const BatchRun &r = b->runs.back();
-        gabp_status st = GABP_OK;
         for (int g = 0; g < 4; ++g)
             for (int j = 0; j < r.deeps[g] && st == GABP_OK; ++j) {
                 const int i0 = gabp::deep_part(r.iters[g], r.deeps[g], j);
                 st = launch_group(b, g, gabp::deep_part(r.iters[g], r.deeps[g], j + 1) - i0,
                                   (int)((b->t + j) & 1), b->t + i0, eta);
             }
-        const int first = k >= 3 ? k - 1 : 0;
-        for (int i = first; i < k && st == GABP_OK; ++i) st = launch_single(b, b->t + i + 1, eta);
+        for (int g : {0, 2}) {     // both prior orders, from where both go on singly
+            const int i0 = b->group[g].n > 0 ? r.iters[g] : k;
+            const int i1 = b->group[g + 1].n > 0 ? r.iters[g + 1] : k;
+            for (int i = std::min(i0, i1); i < k && st == GABP_OK; ++i)
+                st = launch_single(b, g, i >= i0, i >= i1, b->t + i + 1, eta);
+        }
         if (st != GABP_OK) return st;
     }
     b->t += k;
@@ -663,11 +732,11 @@ gabp_status launch_check(gabp_batch *b) {
     if (b->dtype == GABP_F32)
         hipLaunchKernelGGL((gabp::k_batch_post<float>), dim3(post), dim3(256), 0, b->stream,
                            b->d_inst, b->d_act, b->d_pprefix, b->nact, b->ptotal, b->d_frozen, buf,
-                           grid, b->d_actu, (uint64_t)b->freeze_slots, b->d_cnt, b->d_mrel);
+                           grid, b->d_gact, (uint64_t)b->freeze_slots, b->d_cnt, b->d_mrel);
     else
         hipLaunchKernelGGL((gabp::k_batch_post<double>), dim3(post), dim3(256), 0, b->stream,
                            b->d_inst, b->d_act, b->d_pprefix, b->nact, b->ptotal, b->d_frozen, buf,
-                           grid, b->d_actu, (uint64_t)b->freeze_slots, b->d_cnt, b->d_mrel);
+                           grid, b->d_gact, (uint64_t)b->freeze_slots, b->d_cnt, b->d_mrel);
     hipLaunchKernelGGL(gabp::k_batch_resid, dim3(grid), dim3(256), 0, b->stream, b->d_inst,
                        b->d_act, b->d_pprefix, b->nact, b->ptotal, b->d_partials);
     hipLaunchKernelGGL(gabp::k_batch_reduce, dim3(b->nact), dim3(256), 0, b->stream, b->d_act,
@@ -867,10 +936,9 @@ gabp_status gabp_batch_create(int32_t n, const gabp_instance *inst, const gabp_o
     b->d_act = (int *)(b->ws + off);
     b->d_pprefix = b->d_act + n;
     b->d_frozen = b->d_pprefix + n + 1;
-    b->d_actu = b->d_frozen + n;
-    b->d_wprefu = b->d_actu + n;
-    b->d_gact = b->d_wprefu + n + 1;
+    b->d_gact = b->d_frozen + n;
     b->d_gpre = b->d_gact + n;
+    b->d_spre = b->d_gpre + n + 4;
     off = round_up(off + sizeof(int) * (size_t)lists_room(n), kAlign);
     b->d_div = (uint32_t *)(b->ws + off);
     b->d_t = b->d_div + n;
@@ -882,7 +950,7 @@ gabp_status gabp_batch_create(int32_t n, const gabp_instance *inst, const gabp_o
     // pinned mirror: out[2n], cnt[n], div[n], mrel[n], t, lists
     const size_t pin_bytes = sizeof(double) * 2 * (size_t)n + sizeof(unsigned long long) * (size_t)n +
                              sizeof(uint32_t) * (2 * (size_t)n + 2) +
-                             sizeof(int) * (size_t)lists_ints(n) + 64;
+                             sizeof(int) * (size_t)lists_ints(n) * kStages + 64;
     if (hipHostMalloc((void **)&b->p_out, pin_bytes, hipHostMallocDefault) != hipSuccess) {
         b->p_out = nullptr;
         b->err = "pinned host allocation failed";
@@ -1007,7 +1075,7 @@ gabp_status gabp_batch_create(int32_t n, const gabp_instance *inst, const gabp_o
         b->err = "invalid observation (cell out of range, non-finite value or non-positive variance)";
         return bail(GABP_E_INVALID);
     }
-    if (upload_lists(b) != GABP_OK) return bail(GABP_E_DEVICE);
+    if (upload_lists(b, 0) != GABP_OK) return bail(GABP_E_DEVICE);
     *out = b;
     return GABP_OK;   // create synchronised the internal stream
 }
@@ -1018,10 +1086,6 @@ gabp_status gabp_batch_iterate(gabp_batch *b, int32_t n_iters, double damping) {
     if (!join.ok) return bfail(b, GABP_E_DEVICE, "stream ordering failed");
     if (n_iters < 0 || !(damping > 0.0) || !(damping <= 1.0))
         return bfail(b, GABP_E_INVALID, "need n_iters >= 0 and damping in (0, 1]");
-    if (b->lists_dirty) {
-        gabp_status st = upload_lists(b);
-        if (st != GABP_OK) return st;
-    }
     return run_iters(b, n_iters, damping);
 }
 
@@ -1093,19 +1157,17 @@ gabp_status gabp_batch_solve(gabp_batch *b, int64_t max_iters, double damping, d
     int next = kmin;
     int64_t run = 0;
     while (run < max_iters) {
-        if (b->lists_dirty) {
-            gabp_status st = upload_lists(b);
-            if (st != GABP_OK) return st;
-        }
-        if (b->nact == 0) break;
         const int k = (int)std::min<int64_t>(next, max_iters - run);
-        gabp_status st = run_iters(b, k, damping);
+        gabp_status st = upload_lists(b, k);
+        if (st != GABP_OK) return st;
+        if (b->nact == 0) break;
+        st = run_iters(b, k, damping);
         if (st != GABP_OK) return st;
         run += k;
         st = launch_check(b);
         if (st != GABP_OK) return st;
         BHIP(b, hipStreamSynchronize(b->stream));
-        b->staged = false;
+        b->staged = 0;
         bool changed;
         const bool testing = b->nu > 0;
         st = fold_check(b, rel_tol, changed);
@@ -1264,7 +1326,8 @@ gabp_status gabp_batch_autotune(gabp_batch *b, int32_t trials, double damping, i
     for (int pass = 0; pass < 2 && st == GABP_OK; ++pass)
         for (int r : gabp::kRptChoices) {
             b->rpt = r;
-            st = upload_lists(b);    // work-item counts depend on the tile shape
+            b->lists_dirty = true;   // work-item counts depend on the tile shape
+            st = upload_lists(b, 1);
             if (st != GABP_OK) break;
             if (hipEventRecord(e0, b->stream) != hipSuccess) { st = GABP_E_DEVICE; break; }
             // one at a time: only single iterations of instances not frozen have
