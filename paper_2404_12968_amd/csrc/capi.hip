@@ -243,6 +243,23 @@ void drop_chunks(gabp_ctx *ctx) {
     ctx->chunks.clear();
 }
 
+// Tile height of two-iteration launches where none is set.
+int default_pair(int dtype) { return dtype == GABP_F32 ? 8 : 4; }
+
+// Whether `many` information-only iterations of a context without a tile set go in
+// launches of two on their own tiles: where no launch of several would have more,
+// from 2^19 nodes on.  A region for several iterations has more idle waves than
+// tiles for two, and small lattices like its one workgroup per CU.  Two and one iteration
+// by region and by tiles: FP64 5-point 256^2 9.7 and 10.2 us, 800^2 30.3 and 30.5, 2048 x
+// 1024 93 and 90, 4096 x 2048 345 and 313; FP32 13-point 256^2 12.3 and 16.5, 1024^2 67 and
+// 67, 4096 x 2048 557 and 491; FP64 13-point two of two and one, 512^2 62 and 65, 800^2 129
+// and 127, 4096 x 2048 1712 and 1522.
+bool takes_pairs(const gabp_ctx *ctx, int32_t many) {
+    if (!ctx->frozen || many < 2 || (int64_t)ctx->L.nx * ctx->L.ny < (1 << 19)) return false;
+    const int launches = (many + ctx->plan.S - 1) / ctx->plan.S;
+    return (many + launches - 1) / launches <= 2;
+}
+
 // Autotuner results (rows per thread, pair tile height), process-wide,
 // keyed by (alpha, dtype, size class).
 std::mutex g_tune_mu;
@@ -472,7 +489,7 @@ gabp_status gabp_create(const gabp_grid *grid, const gabp_stencil *stencil, cons
             ctx->rpt_set = true;
             ctx->pair = it->second.second;
         } else {
-            ctx->pair = dtype == GABP_F32 ? 8 : 4;
+            ctx->pair = default_pair(dtype);
         }
     }
     *out = ctx;
@@ -499,7 +516,8 @@ namespace {
 // last, which runs singly, so that the two buffers end on m^{t-1} and m^t (the
 // message-change statistic and the freeze probe need that); frozen contexts
 // need that with tail_single or an odd n (as two-iteration launches leave it),
-// else they run all so.  With a tile set by
+// else they run all so.  Frozen launches of two may be the two-iteration kernel's
+// (takes_pairs).  With a tile set by
 // gabp_set_tile, full iterations run singly and frozen contexts two per launch;
 // with tail_single the last one or two singly, else while two remain.
 // Touches no context state; reports the launches.
@@ -515,8 +533,9 @@ gabp_status enqueue_iters(gabp_ctx *ctx, int32_t n, double damping, hipStream_t 
         const void *src = ctx->msg[cur];
         void *dst = ctx->msg[cur ^ 1];
         const int32_t many = n - k - (tail_single || !ctx->frozen || n % 2 != 0 ? 1 : 0);
-        if (ctx->deep && it >= 2 && many >= 2 && done.deeps == 0) {
-            const gabp::DeepPlan &p = ctx->frozen ? ctx->plan : ctx->plan_full;
+        const gabp::DeepPlan &p = ctx->frozen ? ctx->plan : ctx->plan_full;
+        const bool pairs = ctx->deep ? takes_pairs(ctx, many) : ctx->frozen && ctx->pair != 0;
+        if (ctx->deep && !pairs && it >= 2 && many >= 2 && done.deeps == 0) {
             done.lead = done.singles;
             done.singles = 0;
             done.deeps = (many + p.S - 1) / p.S;
@@ -541,8 +560,12 @@ gabp_status enqueue_iters(gabp_ctx *ctx, int32_t n, double damping, hipStream_t 
             done.last_single = false;
             continue;
         }
-        if (ctx->frozen && !ctx->deep && ctx->pair != 0 && it >= 2 && n - k >= min_left) {
-            if (ctx->pair < 0)
+        if (pairs && it >= 2 && n - k >= min_left) {
+            if (ctx->deep)
+                GABP_HIP(ctx, gabp::launch_iter_theta2(dt, default_pair(ctx->dtype), ctx->L, src, dst,
+                                                       ctx->gain, ctx->b_w, damping, ctx->flags,
+                                                       ctx->flags + 3, (uint32_t)(it - tbase), s));
+            else if (ctx->pair < 0)
                 GABP_HIP(ctx, gabp::launch_iter_theta2w(dt, -ctx->pair, ctx->L, src, dst,
                                                         ctx->gain, ctx->b_w, damping, ctx->flags,
                                                         ctx->flags + 3, (uint32_t)(it - tbase), s));
@@ -597,7 +620,7 @@ void advance_state(gabp_ctx *ctx, int32_t n, double damping, bool tail_single, c
     ctx->runs.push_back({ctx->iter, ctx->cur, d.lead, d.deeps, d.deep_iters, d.pairs, d.singles,
                          ctx->frozen, tail_single, damping});
     ctx->launches[ctx->frozen ? 1 : 0] += d.lead + d.singles;
-    ctx->launches[ctx->pair >= 0 ? 2 : 3] += d.pairs;
+    ctx->launches[ctx->deep || ctx->pair >= 0 ? 2 : 3] += d.pairs;
     ctx->launches[2] += d.deeps;
     ctx->iter += n;
     ctx->cur ^= (d.lead + d.deeps + d.pairs + d.singles) & 1;

@@ -18,7 +18,7 @@ def G():
 
 
 @pytest.mark.parametrize("dtype,alpha", [("f32", 2), ("f32", 1), ("f64", 2), ("f64", 1)])
-@pytest.mark.parametrize("nx,ny", [(150, 140), (700, 610)])
+@pytest.mark.parametrize("nx,ny", [(150, 140), (700, 610), (760, 700)])   # 2^19 nodes from the last on
 def test_spacing_and_stream(G, dtype, alpha, nx, ny):
     prob = I.small_lattice(nx, ny, alpha, bc_x=I.BC_PERIODIC, kappa=0.31, tau=2.3, frac=0.1,
                            sigma=0.05, seed=nx, hx=0.7, hy=1.3, dtype=dtype)
@@ -45,8 +45,10 @@ def test_spacing_and_stream(G, dtype, alpha, nx, ny):
     same()
     assert G.gabp_residual(a) == G.gabp_residual(b)
     assert G.gabp_precision_frozen(a) == G.gabp_precision_frozen(b) == 24
-    for c in (a, b):
-        G.gabp_iterate(c, 33, 0.5)
-    same()
-    assert G.gabp_solve(a, 20, 0.5, 0.0, 10) == G.gabp_solve(b, 20, 0.5, 0.0, 10)
-    same()
+    for n in (33, 3, 5, 4, 2):
+        for c in (a, b):
+            G.gabp_iterate(c, n, 0.5)
+        same()
+    for most, check in ((20, 10), (9, 3), (8, 2), (9, 5)):
+        assert G.gabp_solve(a, most, 0.5, 0.0, check) == G.gabp_solve(b, most, 0.5, 0.0, check)
+        same()
