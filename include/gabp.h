@@ -516,7 +516,7 @@ gabp_status gabp_warm_loss(const float *pred, const float *mu_t, const float *la
 
 /* Network input features [ny][nx][16] BF16 from observations (device arrays):
  * channel 0 mask, 1 mean observed value, 2 log(kappa) + 2.5, others 0.
- * scratch: 2*nx*ny FP32; counts and sums, of the observed cells only, after. */
+ * scratch: 2*nx*ny FP32, of which the observed cells' values are set, or all. */
 gabp_status gabp_warm_features(int64_t nobs, const int64_t *cell, const double *y, int64_t nx,
                                int64_t ny, double kappa, float *scratch, void *x_bf16,
                                void *stream);
@@ -526,7 +526,7 @@ gabp_status gabp_warm_features(int64_t nobs, const int64_t *cell, const double *
  * forbid allocation): the two scratch planes live in a static device array
  * of 2 x 2^21 FP32 values (16 MiB per GPU, held until the process ends), so
  * nx * ny may be at most 2^21 (INVALID beyond).  The call allocates nothing;
- * a kernel clears the observed cells' scratch on every call.  Every call on one GPU
+ * a kernel clears the scratch it uses on every call.  Every call on one GPU
  * shares that GPU's array: calls that overlap on one GPU (different streams
  * or threads without ordering) race.  Same arguments and results otherwise. */
 gabp_status gabp_warm_features_noalloc(int64_t nobs, const int64_t *cell, const double *y,

@@ -718,9 +718,33 @@ __global__ __launch_bounds__(256) void k_warm_loss(const float *__restrict__ pre
 // planes of nx*ny.  Bound by writing the features, 32 bytes a cell in two 16-byte
 // stores: every cell's are written as unobserved, together with zeros into the
 // scratch of the observed cells, then the observations are added up there and
-// those cells' two channels written over.  Clearing the scratch and reading it
-// back for every cell, with 2-byte stores, took 27 us on 1024^2 cells with 6 %
-// observed, this 20.  ALIGNED: x is 16-byte aligned.
+// those cells' two channels written over.  From one observation in 12 cells on the
+// whole scratch is cleared and every cell's features are built from it instead:
+// observations in no order reach the scratch and the features a cell at a time, each
+// for a line of its own.  First way, second and the second with 2-byte stores, us:
+// 1024^2 with 1 % observed 17.3, 17.9 and 24, 6 % in no order 21.7, 21.6 and 28 and by
+// cell 18.4, 19.4 and 26, 15 % 39, 31 and 38 and by cell 22.0, 22.3 and 28, every cell 175,
+// 115 and 122 and by cell 29, 23 and 30; 2048 x 1500 with 1 % 26, 32 and 53, every cell 514,
+// 322 and 342.  ALIGNED: x is 16-byte aligned.
+template <bool ALIGNED>
+__device__ __forceinline__ void feat_store(__bf16 *__restrict__ o, float mask, float mean,
+                                           float kfeat) {
+    bf16x8 a = {}, b = {};
+    a[0] = (__bf16)mask;
+    a[1] = (__bf16)mean;
+    a[2] = (__bf16)kfeat;
+    if (ALIGNED) {
+        ((bf16x8 *)o)[0] = a;
+        ((bf16x8 *)o)[1] = b;
+    } else {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            o[k] = a[k];
+            o[8 + k] = b[k];
+        }
+    }
+}
+
 template <bool ALIGNED>
 __global__ __launch_bounds__(256) void k_feat_fill(long N, float kfeat, __bf16 *__restrict__ x,
                                                    long n, const int64_t *__restrict__ cell,
@@ -734,21 +758,23 @@ __global__ __launch_bounds__(256) void k_feat_fill(long N, float kfeat, __bf16 *
             sum[c] = 0.0f;
         }
     }
+    if (p < N) feat_store<ALIGNED>(x + p * 16, 0.0f, 0.0f, kfeat);
+}
+
+// p[0 .. n) = 0 (a kernel, not a memset, so that callers may capture it in a graph)
+__global__ __launch_bounds__(256) void k_feat_zero(long n, float *__restrict__ p) {
+    const long i = (long)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) p[i] = 0.0f;
+}
+
+template <bool ALIGNED>
+__global__ __launch_bounds__(256) void k_feat_build(long N, const float *__restrict__ cnt,
+                                                    const float *__restrict__ sum, float kfeat,
+                                                    __bf16 *__restrict__ x) {
+    const long p = (long)blockIdx.x * 256 + threadIdx.x;
     if (p >= N) return;
-    typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-    bf16x8 a = {}, b = {};
-    a[2] = (__bf16)kfeat;
-    __bf16 *o = x + p * 16;
-    if (ALIGNED) {
-        ((bf16x8 *)o)[0] = a;
-        ((bf16x8 *)o)[1] = b;
-    } else {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            o[k] = a[k];
-            o[8 + k] = b[k];
-        }
-    }
+    const float c = cnt[p];
+    feat_store<ALIGNED>(x + p * 16, c > 0.0f ? 1.0f : 0.0f, c > 0.0f ? sum[p] / c : 0.0f, kfeat);
 }
 
 __global__ __launch_bounds__(256) void k_feat_scatter(long n, const int64_t *__restrict__ cell,
@@ -916,26 +942,34 @@ hipError_t scratch_address(float **out) {
 }
 
 // Input features from observations with cnt/sum scratch planes of N cells (2 N
-// floats, of which the observed cells' are cleared and used).
+// floats, of which at least the observed cells' are cleared and used).
 hipError_t features_into(int64_t nobs, const int64_t *cell, const double *y, long N,
                          double kappa, float *scr, void *x_bf16, hipStream_t s) {
     const float kf = (float)(std::log(kappa) + 2.5);
-    const dim3 cells((unsigned)((std::max(N, (long)nobs) + 255) / 256));
-    const dim3 obs((unsigned)((nobs + 255) / 256));
+    const bool aligned = (uintptr_t)x_bf16 % 16 == 0, dense = nobs > N / 12;
+    auto blocks = [](long n) { return dim3((unsigned)((n + 255) / 256)); };
+    const dim3 obs = blocks((long)nobs), block(256);
     float *cnt = scr, *sum = scr + N;
     __bf16 *x = (__bf16 *)x_bf16;
-    if ((uintptr_t)x_bf16 % 16 == 0)
-        hipLaunchKernelGGL(gabp::k_feat_fill<true>, cells, dim3(256), 0, s, N, kf, x, (long)nobs,
-                           cell, cnt, sum);
+    if (dense)
+        hipLaunchKernelGGL(gabp::k_feat_zero, blocks(2 * N), block, 0, s, 2 * N, scr);
+    else if (aligned)
+        hipLaunchKernelGGL(gabp::k_feat_fill<true>, blocks(std::max(N, (long)nobs)), block, 0, s, N,
+                           kf, x, (long)nobs, cell, cnt, sum);
     else
-        hipLaunchKernelGGL(gabp::k_feat_fill<false>, cells, dim3(256), 0, s, N, kf, x, (long)nobs,
-                           cell, cnt, sum);
-    if (nobs > 0) {
-        hipLaunchKernelGGL(gabp::k_feat_scatter, obs, dim3(256), 0, s, (long)nobs, cell, y, N, cnt,
-                           sum);
-        hipLaunchKernelGGL(gabp::k_feat_observed, obs, dim3(256), 0, s, (long)nobs, cell, N,
+        hipLaunchKernelGGL(gabp::k_feat_fill<false>, blocks(std::max(N, (long)nobs)), block, 0, s, N,
+                           kf, x, (long)nobs, cell, cnt, sum);
+    if (nobs > 0)
+        hipLaunchKernelGGL(gabp::k_feat_scatter, obs, block, 0, s, (long)nobs, cell, y, N, cnt, sum);
+    if (dense && aligned)
+        hipLaunchKernelGGL(gabp::k_feat_build<true>, blocks(N), block, 0, s, N, (const float *)cnt,
+                           (const float *)sum, kf, x);
+    else if (dense)
+        hipLaunchKernelGGL(gabp::k_feat_build<false>, blocks(N), block, 0, s, N, (const float *)cnt,
+                           (const float *)sum, kf, x);
+    else if (nobs > 0)
+        hipLaunchKernelGGL(gabp::k_feat_observed, obs, block, 0, s, (long)nobs, cell, N,
                            (const float *)cnt, (const float *)sum, x);
-    }
     return hipGetLastError();
 }
 
