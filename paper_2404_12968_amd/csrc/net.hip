@@ -15,7 +15,6 @@
 // and D[8 i + 4 (l / 32) + j][l % 32] in accumulator 4 i + j.
 #include <hip/hip_runtime.h>
 
-#include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <mutex>
@@ -988,18 +987,12 @@ bool chan_ok(int c) { return c == 16 || c == 32; }
             return nfail(GABP_E_DEVICE, std::string(#call) + ": " + hipGetErrorString(e_)); \
     } while (0)
 
-// Compute units of the current device, asked for once per device: the runtime takes
-// 0.6 us to tell, a seventh of what a convolution's launch costs the host.
 int cu_count() {
-    static std::atomic<int> known[kMaxDevices];
     int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 256;
-    cus = known[dev].load(std::memory_order_relaxed);
-    if (cus > 0) return cus;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         cus <= 0)
         return 256;
-    known[dev].store(cus, std::memory_order_relaxed);
     return cus;
 }
 
