@@ -63,8 +63,9 @@ struct gabp_ctx {
     double *bel64 = nullptr;       // FP64 belief precisions once frozen
     void *adiag_w = nullptr, *b_w = nullptr;
     double *partials = nullptr, *red = nullptr;
-    uint32_t *flags = nullptr;     // [0] diverged-at iteration, [1] input error, [2] repeated
-                                   // cells (at set-up), [3] iteration counter of the launches, [4, 5] precision
+    uint32_t *flags = nullptr;     // [0] diverged-at iteration, [1] input error, [2] workgroups
+                                   // of the residual done (at set-up: repeated cells),
+                                   // [3] iteration counter of the launches, [4, 5] precision
                                    // messages changed by the last iteration (64-bit) and
                                    // [6] their largest relative change (float bits)
     HostMirror *host = nullptr;    // pinned

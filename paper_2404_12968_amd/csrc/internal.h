@@ -70,7 +70,8 @@ hipError_t launch_post_probe(int dtype, const Lattice &L, const void *m, const v
                              uint64_t limit, uint32_t *flags, const double *adiag64,
                              const double *b64, double *mu_plane, double *bel_out, hipStream_t s);
 // FP64 residual sums |r|^2, |b|^2 into the host's pinned h_red[0, 1], and the
-// eight flag words into its h_flags; clears flags[4..6].
+// eight flag words into its h_flags; clears flags[4..6].  flags[2] counts the
+// workgroups done and is zero before and after.
 hipError_t launch_resid(const Lattice &L, const double *mu, const double *adiag64,
                         const double *b64, double *partials, int npart, uint32_t *flags,
                         double *h_red, uint32_t *h_flags, hipStream_t s);

@@ -82,15 +82,62 @@ __global__ __launch_bounds__(256) void k_post(Lattice L, int ntiles, FreezeTest 
 // node's arithmetic (resid_accum) and the order of the sums (tile by tile)
 // are those of resid_node, so the r^2 and b^2 partials (wave64 butterfly,
 // then LDS across the four waves, into partials[g]) are deterministic and do
-// not depend on the staging.  k_resid_report adds them up and reports.
+// not depend on the staging.  The partials are added up in the order of k_reduce and
+// reported to the host's pinned mirror together with the context's flag words, whose
+// freeze-test words are cleared for the next check (resid_report): by the workgroup
+// that ends last, which an atomic counter (flags[2]) tells, or by a launch of its own.
+// A check was seven operations (clear, freeze test, marginals, residual, reduction,
+// two copies) and is two or three launches.  The counter saves a launch but every
+// workgroup writes its L2 back before it counts itself: with the wait for it, a check
+// by the counter and by the launch takes 20.2 and 20.4 us with 16 workgroups (64^2),
+// 20.4 and 20.6 with 32, 20.9 and 20.6 with 48, 42 and 26 with 1024 (512^2), 83 and
+// 58 with 2048.  So up to kResidCounted workgroups count.
 // --------------------------------------------------------------------------
 constexpr int kResidUnroll = 4;
+constexpr int kResidCounted = 32;
 
-template <int ALPHA>
+__device__ __forceinline__ void resid_report(const double *__restrict__ partials, int nb,
+                                             uint32_t *__restrict__ flags,
+                                             double *__restrict__ h_red,
+                                             uint32_t *__restrict__ h_flags, double (&sh)[2][4]) {
+    double rr = 0.0, bb = 0.0;
+    for (int k = (int)threadIdx.x; k < nb; k += 256) {
+        rr += __hip_atomic_load(partials + 2 * k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bb += __hip_atomic_load(partials + 2 * k + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    rr = wave_sum(rr);
+    bb = wave_sum(bb);
+    const int w = (int)(threadIdx.x >> 6);
+    if ((threadIdx.x & 63u) == 0u) {
+        sh[0][w] = rr;
+        sh[1][w] = bb;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        h_red[0] = (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]);
+        h_red[1] = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
+        flags[2] = 0;
+        for (int k = 0; k < 8; ++k) h_flags[k] = flags[k];
+        flags[4] = flags[5] = flags[6] = 0;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_resid_report(const double *__restrict__ partials, int nb,
+                                                      uint32_t *__restrict__ flags,
+                                                      double *__restrict__ h_red,
+                                                      uint32_t *__restrict__ h_flags) {
+    __shared__ double sh[2][4];
+    resid_report(partials, nb, flags, h_red, h_flags, sh);
+}
+
+template <int ALPHA, bool COUNTED>
 __global__ __launch_bounds__(256) void k_resid(Lattice L, const double *__restrict__ mu,
                                                const double *__restrict__ adiag64,
                                                const double *__restrict__ b64,
-                                               double *__restrict__ partials, int ntiles) {
+                                               double *__restrict__ partials, int ntiles,
+                                               uint32_t *__restrict__ flags,
+                                               double *__restrict__ h_red,
+                                               uint32_t *__restrict__ h_flags) {
     constexpr int DEG = ALPHA == 1 ? 4 : 12;
     constexpr int R = ALPHA == 1 ? 1 : 2;
     constexpr int WX = 64 + 2 * R, WY = 4 + 2 * R, WN = WX * WY;
@@ -199,44 +246,18 @@ __global__ __launch_bounds__(256) void k_resid(Lattice L, const double *__restri
         sh[1][w] = bb;
     }
     __syncthreads();
+    __shared__ bool last;
     if (threadIdx.x == 0) {
         partials[2 * g] = (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]);
         partials[2 * g + 1] = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
+        // releases this workgroup's partials, acquires everyone's before it
+        if (COUNTED)
+            last = __hip_atomic_fetch_add(flags + 2, 1u, __ATOMIC_ACQ_REL,
+                                          __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)nb - 1u;
     }
-}
-
-// The residual's partials added up in the order of k_reduce and reported to the
-// host's pinned mirror: the sums, and the context's flag words, whose freeze-test
-// words it clears for the next check.  A check was seven operations (clear, freeze
-// test, marginals, residual, reduction, two copies) and is three launches: with the
-// wait for it, frozen, 64^2 24 -> 20.6 us, 512^2 29.7 -> 26.3, 2048 x 1024 62 -> 58.9.
-// The last workgroup of k_resid to finish, which an atomic counter tells, could report:
-// 20.4 us on 64^2, but every workgroup writes its L2 back before it counts itself
-// (38.8 on 512^2, 79 on 2048 x 1024).
-__global__ __launch_bounds__(256) void k_resid_report(const double *__restrict__ partials, int nb,
-                                                      uint32_t *__restrict__ flags,
-                                                      double *__restrict__ h_red,
-                                                      uint32_t *__restrict__ h_flags) {
-    __shared__ double sh[2][4];
-    double rr = 0.0, bb = 0.0;
-    for (int k = (int)threadIdx.x; k < nb; k += 256) {
-        rr += partials[2 * k];
-        bb += partials[2 * k + 1];
-    }
-    rr = wave_sum(rr);
-    bb = wave_sum(bb);
-    const int w = (int)(threadIdx.x >> 6);
-    if ((threadIdx.x & 63u) == 0u) {
-        sh[0][w] = rr;
-        sh[1][w] = bb;
-    }
+    if (!COUNTED) return;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        h_red[0] = (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]);
-        h_red[1] = (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]);
-        for (int k = 0; k < 8; ++k) h_flags[k] = flags[k];
-        flags[4] = flags[5] = flags[6] = 0;
-    }
+    if (last) resid_report(partials, nb, flags, h_red, h_flags, sh);
 }
 
 // Sum of |a - b| over a flat range of message slots (the paper's early-stop
@@ -526,8 +547,8 @@ static int resident_resid_blocks(int alpha) {
     if (v > 0) return v;
     int per_cu = 0, cus = 0;
     const hipError_t e1 =
-        alpha == 1 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_resid<1>, 256, 0)
-                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_resid<2>, 256, 0);
+        alpha == 1 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_resid<1, false>, 256, 0)
+                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_resid<2, false>, 256, 0);
     const hipError_t e2 = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e1 != hipSuccess || e2 != hipSuccess || per_cu <= 0 || cus <= 0) return 0;
     v = per_cu * cus;
@@ -542,14 +563,14 @@ hipError_t launch_resid(const Lattice &L, const double *mu, const double *adiag6
     int nb = nt < npart ? nt : npart;
     const int resident = resident_resid_blocks(L.alpha);
     if (resident > 0 && resident < nb) nb = resident;
-    if (L.alpha == 1)
-        hipLaunchKernelGGL((k_resid<1>), dim3(nb), dim3(256), 0, s, L, mu, adiag64, b64, partials,
-                           nt);
-    else
-        hipLaunchKernelGGL((k_resid<2>), dim3(nb), dim3(256), 0, s, L, mu, adiag64, b64, partials,
-                           nt);
-    hipLaunchKernelGGL(k_resid_report, dim3(1), dim3(256), 0, s, (const double *)partials, nb,
-                       flags, h_red, h_flags);
+    const bool counted = nb <= kResidCounted;
+    auto *k = L.alpha == 1 ? (counted ? k_resid<1, true> : k_resid<1, false>)
+                           : (counted ? k_resid<2, true> : k_resid<2, false>);
+    hipLaunchKernelGGL(k, dim3(nb), dim3(256), 0, s, L, mu, adiag64, b64, partials, nt, flags,
+                       h_red, h_flags);
+    if (!counted)
+        hipLaunchKernelGGL(k_resid_report, dim3(1), dim3(256), 0, s, (const double *)partials, nb,
+                           flags, h_red, h_flags);
     return hipGetLastError();
 }
 
