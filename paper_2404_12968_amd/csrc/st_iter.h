@@ -359,10 +359,9 @@ __device__ __forceinline__ void wg_tile(int b, int tiles_x, int tiles_y, int nt,
 // the 256 VGPRs of two waves (248; 204 with none, 36 spilled with 12): 100 x 75 x 12
 // 37.3 -> 30.0, 256 x 256 x 16 419 -> 297, 128 x 128 x 64 417 -> 280, periodic 130 x
 // 130 x 10 67 -> 60.5.
-// diverged_at[0]
-// records the first iteration whose launch met an invalid value; launches of
-// later iterations return at once (the launch of the iteration that met it
-// completes, so its output buffer holds that iteration).  MODE_GAIN passes
+// diverged_at[0] records the first iteration whose launch met an invalid value;
+// launches of later iterations return at once (the launch of the iteration that met
+// it completes, so its output buffer holds that iteration).  MODE_GAIN passes
 // it = 0.
 template <typename T, int MODE, int SL, int AHEAD>
 __global__ __launch_bounds__(256 * SL,
